@@ -23,7 +23,7 @@ HOST_TUS = ("rocket_api.hip",)
 
 
 def sources():
-    names = ("sampler.cpp", "rocket_internal.hpp", "rocket_device.hpp", "rocket_forward_impl.hpp") + KERNEL_TUS + HOST_TUS
+    names = ("sampler.cpp", "rocket_internal.hpp", "rocket_device.hpp", "rocket_forward_impl.hpp", "rocket_limbs.hpp") + KERNEL_TUS + HOST_TUS
     return [os.path.join(CSRC, f) for f in names] + [os.path.join(ROOT, "include", "rocket.h")]
 
 

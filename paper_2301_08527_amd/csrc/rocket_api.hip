@@ -39,6 +39,12 @@ int rk_fail(int code, const std::string &msg)
             return rk_fail(ROCKET_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
+RkLaunchers &rk_launchers()
+{
+    static RkLaunchers table;
+    return table;
+}
+
 // ------------------------------------------------------------------ host plan
 
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
@@ -799,11 +805,19 @@ static void minirocket_plan(rocket_kernels &h)
             }
         } else {
             const int64_t rows_total = (n + d - 1) / d;
-            const int64_t blocks = (d + 255) / 256;
-            const int64_t width = round_up((d + blocks - 1) / blocks, 64);
-            const int64_t rows_max = kMrTileFloats / width - (kMrLen - 1);
-            const int64_t row_tiles = (rows_total + rows_max - 1) / rows_max;
-            const int64_t each = (rows_total + row_tiles - 1) / row_tiles;
+            // block width of 64 to 256 columns: the one that stages and computes least.  A narrow block has room
+            // for many rows beside the eight of the halo, a wide one leaves fewer columns of the last block idle; a
+            // position computed costs about as much as eight samples staged, a work item as much as 1,900 (instructions
+            // counted).
+            int64_t width = 64, each = 1;
+            int64_t least = INT64_MAX;
+            for (int64_t w = 64; w <= 256; w += 64) {
+                const int64_t rows_max = kMrTileFloats / w - (kMrLen - 1);
+                const int64_t row_tiles = (rows_total + rows_max - 1) / rows_max;
+                const int64_t blocks = (d + w - 1) / w;
+                const int64_t cost = blocks * (w * (rows_total * 9 + row_tiles * (kMrLen - 1)) + row_tiles * 1900);
+                if (cost <= least) { least = cost; width = w; each = (rows_total + row_tiles - 1) / row_tiles; }
+            }
             for (int64_t r0 = 0; r0 < rows_total; r0 += each)
                 for (int64_t c0 = 0; c0 < d; c0 += width) {
                     if (r0 * d + c0 >= n) continue;   // the output ends before this block begins
@@ -963,17 +977,26 @@ static int minirocket_transform_impl(const char *fn, rocket_kernels *h, const vo
     float *xpad = static_cast<float *>(ws);
     int32_t *counts = reinterpret_cast<int32_t *>(base + padded_batch_bytes(h, B));
     void *stats = base + padded_batch_bytes(h, B) + minirocket_counts_bytes(h, B);
-    const int padded = is_u8 ? rk_launch_pad_u8(h, static_cast<const uint8_t *>(x_dev), B, xpad, stats, stream)
-                             : rk_launch_pad(h, static_cast<const float *>(x_dev), B, xpad, stream);
-    if (padded != ROCKET_OK || rk_launch_minirocket_clear(h, B, counts, stream) != ROCKET_OK)
-        return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
+    // raw bytes are normalised into the padded copy; floats are read where they are
+    const float *x = static_cast<const float *>(x_dev);
+    int64_t row_stride = h->L;
+    if (is_u8) {
+        if (rk_launch_pad_u8(h, static_cast<const uint8_t *>(x_dev), B, xpad, stats, stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
+        x = xpad + h->lead;
+        row_stride = h->row_len;
+    }
+    // one work item per group (short series): its workgroup writes the features itself
+    const bool direct = rk_launchers().minirocket_one_pass(h);
+    if (!direct && rk_launch_minirocket_clear(h, B, counts, stream) != ROCKET_OK)
+        return rk_fail(ROCKET_EHIP, "launch of the clearing kernel failed");
     rc = profile_mark(h, stream, true);
     if (rc != ROCKET_OK) return rc;
-    if (rk_launch_minirocket_forward(h, xpad, B, counts, stream) != ROCKET_OK)
+    if (rk_launchers().minirocket_forward(h, x, row_stride, B, counts, direct ? out_dev : nullptr, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the group kernel failed");
     rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;
-    if (rk_launch_minirocket_features(h, counts, B, out_dev, stream) != ROCKET_OK)
+    if (!direct && rk_launch_minirocket_features(h, counts, B, out_dev, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the feature kernel failed");
     return ROCKET_OK;
 }

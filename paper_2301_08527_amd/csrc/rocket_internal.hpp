@@ -29,7 +29,7 @@ constexpr int64_t kTilePositions = RK_TILE_POSITIONS;   // smallest time tile of
 constexpr int kMrSet = 84;
 constexpr int kMrLen = 9;
 #ifndef RK_MR_TILE
-#define RK_MR_TILE 6144
+#define RK_MR_TILE 4864
 #endif
 #ifndef RK_MR_LINEAR_MAXD
 #define RK_MR_LINEAR_MAXD 256
@@ -128,10 +128,19 @@ int rk_launch_minirocket_outputs(const rocket_kernels *h, const float *xpad, con
 int rk_launch_minirocket_select(const rocket_kernels *h, const int32_t *rank_dev, int32_t k0, int32_t count,
                                 int64_t stride, const float *ybuf, void *stream);
 // rocket_minirocket_forward.hip: the PPV features of a MINIROCKET-style handle, group by group: clears the
-// B x K counters, adds every work item's positive counts to them, turns them into features
+// B x K counters; turns them into features (the kernel that counts is in the table below)
 int rk_launch_minirocket_clear(const rocket_kernels *h, int32_t B, int32_t *counts, void *stream);
-int rk_launch_minirocket_forward(const rocket_kernels *h, const float *xpad, int32_t B, int32_t *counts, void *stream);
 int rk_launch_minirocket_features(const rocket_kernels *h, const int32_t *counts, int32_t B, float *out, void *stream);
+// Launchers that the kernels' translation units enter here when the library is loaded, so that the host code links
+// without them.
+struct RkLaunchers {
+    // rocket_minirocket_forward.hip.  x: rows of L samples that start row_stride floats apart.  Adds every work item's
+    // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
+    int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
+                              void *stream) = nullptr;
+    bool (*minirocket_one_pass)(const rocket_kernels *h) = nullptr;
+};
+RkLaunchers &rk_launchers();      // rocket_api.hip
 // rocket_api.hip: offsets, job plan, padded row geometry; returns ROCKET_OK or an error
 int rk_finish_handle(rocket_kernels &h);
 

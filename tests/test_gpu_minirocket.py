@@ -251,3 +251,20 @@ def test_group_kernel_from_bytes():
     check_forward(oracle.znormalize_u8(raw), kr, out.cpu().numpy(), 2)
     with pytest.raises(rocket.RocketError):
         rocket.rocket_minirocket_transform_u8(h, _gpu(raw.astype(np.float32)))
+
+
+@pytest.mark.parametrize("B,C,L,groups", [
+    (3, 1, 9, 2), (2, 1, 63, 3), (1, 1, 129, 5),      # one channel, shorter and longer than a chunk of 64 positions
+    (2, 1, 3217, 5), (2, 1, 3249, 5),                 # either side of the largest series that is staged whole
+    (5, 2, 2431, 9), (9, 12, 4871, 4), (8, 3, 20011, 6),   # tiles of one group, several to a workgroup, ragged ends
+])
+def test_matrix_core_group_kernel_at_its_edges(B, C, L, groups):
+    rng = np.random.default_rng(L)
+    x = rng.standard_normal((B, C, L)).astype(np.float32)
+    h = rocket.rocket_minirocket_kernels(L, groups, C, L)
+    bias = rng.standard_normal(h.K).astype(np.float32)
+    rocket.rocket_kernels_set_params(h, bias=bias)
+    kr = dict(oracle.minirocket_kernels(L, groups, C, L), bias=bias)
+    print("minirocket edges", B, C, L, groups, flush=True)
+    out = rocket.rocket_minirocket_transform(h, _gpu(x)).cpu().numpy()
+    check_forward(x, kr, out, 2)
