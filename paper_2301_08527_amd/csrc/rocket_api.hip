@@ -49,6 +49,93 @@ RkLaunchers &rk_launchers()
 
 static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
+// Which taps the four lane groups read together.  Instruction e of a set reads, 16 samples to a lane group, one tap in each
+// of the four groups; two taps whose samples lie k * 64 words apart, give or take 15, meet in LDS banks (the same
+// words do not).  Of four ways to spread the taps over the four instructions, the one where the fewest meet; a group without
+// a tap repeats another's addresses, which costs nothing.  (A search over all ways cost more on the host than it gave.)
+static void spread_taps(int32_t d, int32_t len, int8_t (&tap)[16], int8_t (&read)[16])
+{
+    static const int8_t ways[4][4][4] = {
+        {{0, 1, 2, -1}, {3, 4, 5, -1}, {6, 7, 8, -1}, {9, 10, -1, -1}},
+        {{0, 2, 4, -1}, {1, 3, 5, -1}, {6, 8, 10, -1}, {7, 9, -1, -1}},
+        {{0, 3, 6, 9}, {1, 4, 7, 10}, {2, 5, 8, -1}, {-1, -1, -1, -1}},
+        {{0, 4, 8, -1}, {1, 5, 9, -1}, {2, 6, 10, -1}, {3, 7, -1, -1}},
+    };
+    bool meet[11] = {};
+    for (int32_t k = 0; k < len; ++k) {
+        const int64_t delta = static_cast<int64_t>(k) * d, r = delta % 64;
+        meet[k] = delta >= 49 && (r < 16 || r > 48);
+    }
+    int best = 0, least = INT32_MAX;
+    for (int w = 0; w < 4; ++w) {
+        int cost = 0;
+        for (int e = 0; e < 4; ++e)
+            for (int i = 0; i < 4; ++i)
+                for (int j = i + 1; j < 4; ++j)
+                    if (const int a = ways[w][e][i], b = ways[w][e][j]; a >= 0 && b >= 0 && b < len && meet[b - a]) ++cost;
+        if (cost < least) { least = cost; best = w; }
+    }
+    for (int e = 0; e < 4; ++e)
+        for (int g = 0; g < 4; ++g) {
+            const int8_t t = ways[best][e][g] < len ? ways[best][e][g] : static_cast<int8_t>(-1);
+            tap[4 * g + e] = t;
+            read[4 * g + e] = t >= 0 ? t : ways[best][e][0] >= 0 && ways[best][e][0] < len ? ways[best][e][0] : static_cast<int8_t>(0);
+        }
+}
+
+// Sets of the series kernel (rocket_forward_series.hip): kernels of equal dilation, 16 to a set, equal padding and length
+// side by side so that most positions of a set exist for all of its kernels.
+static void plan_sets(rocket_kernels &h)
+{
+    h.sets.clear(); h.set_rows.clear(); h.thin.clear();
+    h.thick_sets = 0; h.thin_steps = 0;
+    if (h.C != 1 || h.L > 65000) return;
+    std::vector<int64_t> keyed(h.K);      // dilation, padded or not, length, kernel
+    for (int32_t k = 0; k < h.K; ++k)
+        keyed[k] = (static_cast<int64_t>(h.dilation[k]) * 32 + (h.padding[k] > 0 ? 16 : 0) + h.length[k]) << 31 | k;
+    std::sort(keyed.begin(), keyed.end());
+    std::vector<int32_t> order(h.K);
+    for (int32_t k = 0; k < h.K; ++k) order[k] = static_cast<int32_t>(keyed[k] & INT32_MAX);
+    std::vector<std::pair<int32_t, int32_t>> spans;      // [begin, end) in `order`; thick sets first
+    for (int32_t i = 0, end; i < h.K; i = end) {
+        end = i;
+        while (end < h.K && end < i + 16 && h.dilation[order[end]] == h.dilation[order[i]]) ++end;
+        spans.push_back({i, end});
+    }
+    std::stable_partition(spans.begin(), spans.end(), [](const std::pair<int32_t, int32_t> &s) { return s.second - s.first >= 4; });
+    int32_t first = 0, reach = 0;        // smallest position, one past the last sample read
+    for (const auto &span : spans) {
+        RkSet s{};
+        s.dil = h.dilation[order[span.first]];
+        s.lo = INT32_MAX; s.hi = INT32_MIN; s.in_lo = INT32_MIN; s.in_hi = INT32_MAX;
+        s.regs = (span.second - span.first + 3) / 4;
+        h.set_rows.resize(h.set_rows.size() + 16, -1);
+        int32_t *rows = h.set_rows.data() + h.set_rows.size() - 16;
+        for (int32_t q = 0; q < span.second - span.first; ++q) {
+            const int32_t k = order[span.first + q], lo = -h.padding[k], hi = h.L + h.padding[k] - (h.length[k] - 1) * s.dil;
+            s.len = std::max(s.len, h.length[k]);
+            s.lo = std::min(s.lo, lo); s.hi = std::max(s.hi, hi);
+            s.in_lo = std::max(s.in_lo, lo); s.in_hi = std::min(s.in_hi, hi);
+            rows[4 * (q % 4) + q / 4] = k;
+        }
+        spread_taps(s.dil, s.len, s.tap, s.read);
+        s.lo = -((-s.lo + 15) / 16 * 16);      // every lane then meets the same positions of a kernel in any set
+        const int64_t last = s.lo + round_up(s.hi - s.lo, 32) + static_cast<int64_t>(s.len - 1) * s.dil;
+        reach = static_cast<int32_t>(std::max<int64_t>(reach, last));
+        first = std::min(first, s.lo);
+        h.sets.push_back(s);
+        if (span.second - span.first >= 4) { ++h.thick_sets; continue; }
+        h.thin.insert(h.thin.end(), order.begin() + span.first, order.begin() + span.second);
+        h.thin_steps += (s.hi - s.lo + 15) / 16;
+    }
+    h.set_origin = static_cast<int32_t>(round_up(-first, 4));
+    h.set_plane = static_cast<int32_t>(round_up(reach + h.set_origin, 4));
+    if (8LL * h.set_plane > kSeriesLdsBytes) {
+        h.sets.clear(); h.set_rows.clear(); h.thin.clear();
+        h.thick_sets = 0; h.thin_steps = 0;
+    }
+}
+
 int rk_finish_handle(rocket_kernels &h)
 {
     const int32_t K = h.K;
@@ -76,6 +163,9 @@ int rk_finish_handle(rocket_kernels &h)
     }
     if (h.w_off[K] > INT32_MAX || h.ch_off[K] > INT32_MAX)
         return rk_fail(ROCKET_EINVAL, "too many weights for 32-bit offsets");
+    plan_sets(h);
+    std::vector<char> is_thin(K, 0);
+    for (int32_t k : h.thin) is_thin[k] = 1;
     // Jobs of the forward and the backward pass.  A kernel's rows are cut into tiles of at least kTilePositions output
     // positions (whole LDS chunks or whole 32-row bands); jobs are ordered by the time
     // window they start in, so the workgroups that run together read one stretch of the
@@ -86,7 +176,6 @@ int rk_finish_handle(rocket_kernels &h)
         std::vector<Key> keys;
         h.jobs.clear();
         h.kjob_off.assign(K + 1, 0);
-        std::vector<std::vector<int32_t>> per_kernel(K);
         for (int32_t k = 0; k < K; ++k) {
             const int64_t d = h.dilation[k];
             const int64_t n = static_cast<int64_t>(h.L) + 2LL * h.padding[k] - static_cast<int64_t>(h.length[k] - 1) * d;
@@ -95,7 +184,6 @@ int rk_finish_handle(rocket_kernels &h)
             auto add = [&](int64_t r0, int64_t r1, int flags, int64_t window) {
                 RkJob j;
                 j.kernel = k; j.row0 = static_cast<int32_t>(r0); j.row1 = static_cast<int32_t>(r1); j.flags = flags;
-                per_kernel[k].push_back(static_cast<int32_t>(h.jobs.size()));
                 h.jobs.push_back(j);
                 const double pos = static_cast<double>((r1 - r0) * d + ((flags & 1) ? tail : 0));
                 keys.push_back({window, pos * per_pos});
@@ -130,12 +218,15 @@ int rk_finish_handle(rocket_kernels &h)
                     add(r0, r1, (t == tiles - 1) ? 1 : 0, (r0 * d) / kTilePositions);
                 }
             }
+            h.kjob_off[k + 1] = static_cast<int32_t>(std::min<size_t>(h.jobs.size(), INT32_MAX));
         }
         const size_t J = h.jobs.size();
         if (J > static_cast<size_t>(INT32_MAX)) return rk_fail(ROCKET_EINVAL, "too many forward jobs");
         std::vector<int32_t> perm(J);
         for (size_t i = 0; i < J; ++i) perm[i] = static_cast<int32_t>(i);
         std::stable_sort(perm.begin(), perm.end(), [&](int32_t a, int32_t b) {
+            const char ta = is_thin[h.jobs[a].kernel], tb = is_thin[h.jobs[b].kernel];
+            if (ta != tb) return ta > tb;
             if (keys[a].window != keys[b].window) return keys[a].window < keys[b].window;
             return keys[a].cost > keys[b].cost;
         });
@@ -143,11 +234,9 @@ int rk_finish_handle(rocket_kernels &h)
         std::vector<int32_t> where(J);
         for (size_t i = 0; i < J; ++i) { sorted[i] = h.jobs[perm[i]]; where[perm[i]] = static_cast<int32_t>(i); }
         h.jobs.swap(sorted);
-        h.kjob_idx.clear();
-        for (int32_t k = 0; k < K; ++k) {
-            for (int32_t j : per_kernel[k]) h.kjob_idx.push_back(where[j]);
-            h.kjob_off[k + 1] = static_cast<int32_t>(h.kjob_idx.size());
-        }
+        h.thin_jobs = 0;
+        while (h.thin_jobs < static_cast<int32_t>(J) && is_thin[h.jobs[h.thin_jobs].kernel]) ++h.thin_jobs;
+        h.kjob_idx.swap(where);         // jobs were made kernel after kernel
         // backward pass: words of partial results per job (its kernel's gradient sums, the sum of
         // q, the largest output and its position, one spare)
         h.bjob_off.assign(J + 1, 0);
@@ -445,10 +534,13 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
     const size_t job_b = round_up(static_cast<int64_t>(h->jobs.size()) * sizeof(RkJob), 256);
     const size_t koff_b = round_up(static_cast<int64_t>(K + 1) * 4, 256);
     const size_t kidx_b = round_up(static_cast<int64_t>(h->kjob_idx.size()) * 4, 256);
+    const size_t set_b = round_up(static_cast<int64_t>(h->sets.size()) * sizeof(RkSet), 256);
+    const size_t row_b = round_up(static_cast<int64_t>(h->set_rows.size()) * 4, 256);
+    const size_t thin_b = round_up(static_cast<int64_t>(h->thin.size()) * 4, 256);
     if (h->d_blob && h->device != cur)
         return rk_fail(ROCKET_EINVAL, "handle was first used on another device");
     if (!h->d_blob) {
-        h->blob_bytes = rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b;
+        h->blob_bytes = rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b + thin_b;
         RK_HIP(hipMalloc(&h->d_blob, h->blob_bytes));
         h->device = cur;
         char *base = static_cast<char *>(h->d_blob);
@@ -459,6 +551,9 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         h->d_jobs = reinterpret_cast<const RkJob *>(base + rec_b + boff_b + ch_b + w_b);
         h->d_kjob_off = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b);
         h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b);
+        h->d_sets = reinterpret_cast<const RkSet *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b);
+        h->d_set_rows = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b);
+        h->d_thin = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b);
         h->params_dirty = true;
     }
     if (h->params_dirty) {
@@ -479,6 +574,11 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         RK_HIP(hipMemcpyAsync(const_cast<RkJob *>(h->d_jobs), h->jobs.data(), h->jobs.size() * sizeof(RkJob), hipMemcpyHostToDevice, stream));
         RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_kjob_off), h->kjob_off.data(), (K + 1) * 4, hipMemcpyHostToDevice, stream));
         RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_kjob_idx), h->kjob_idx.data(), h->kjob_idx.size() * 4, hipMemcpyHostToDevice, stream));
+        if (!h->sets.empty()) {
+            RK_HIP(hipMemcpyAsync(const_cast<RkSet *>(h->d_sets), h->sets.data(), h->sets.size() * sizeof(RkSet), hipMemcpyHostToDevice, stream));
+            RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_set_rows), h->set_rows.data(), h->set_rows.size() * 4, hipMemcpyHostToDevice, stream));
+            if (!h->thin.empty()) RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_thin), h->thin.data(), h->thin.size() * 4, hipMemcpyHostToDevice, stream));
+        }
         RK_HIP(hipStreamSynchronize(stream));
         h->params_dirty = false;
     }
@@ -487,6 +587,7 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront forward kernel
+constexpr int64_t kThinSteps = 500000;    // 50 clk x 500,000 tiles over 1,024 SIMDs: some 10 us
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
 // ------------------------------------------------------------------ launches
@@ -543,11 +644,26 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
         if (rc != ROCKET_OK) return rc;
     }
     float *xpad = static_cast<float *>(ws);
-    rc = pad_batch(h, x_dev, is_u8, B, ws, 0, stream);
-    if (rc != ROCKET_OK) return rc;
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
+    // Short univariate series: sets of kernels of one dilation, straight from the samples (raw bytes are normalised into
+    // the padded copy).  Its edges rest on lambda > 0.
+    const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
+    // The thin sets take some 50 clk of a SIMD more per 16-position tile than the job kernels; those need three launches.
+    const bool split = series && h->thin_jobs > 0 && h->thin_steps * B > kThinSteps;
+    if (is_u8 || split || !series) {
+        rc = pad_batch(h, x_dev, is_u8, B, ws, 0, stream);
+        if (rc != ROCKET_OK) return rc;
+    }
     if (!resident_only) rc = profile_mark(h, stream, true);
     if (rc != ROCKET_OK) return rc;
+    if (series) {
+        const float *x = is_u8 ? xpad + h->lead : static_cast<const float *>(x_dev);
+        if (!(split && h->thick_sets == 0) &&
+            rk_launchers().forward_series(h, x, is_u8 ? h->row_len : h->L, B, mask, nl, ns, split, out_dev, stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the series kernel failed");
+        if (!split) return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
+    }
+    h->thin_only = split;
     // series of at most kShortSeries samples: one wavefront per (series, kernel) instead of four
     float *partials = reinterpret_cast<float *>(static_cast<char *>(ws) + padded_batch_bytes(h, B));
     const int launched = h->L <= kShortSeries ? rk_launch_forward_short(h, xpad, B, mask, nl, ns, partials, stream)

@@ -62,6 +62,19 @@ struct RkJob {
     int32_t flags;   // bit 0: also owns the partial last row; bit 1: covers the whole kernel
 };
 
+// Up to 16 kernels of one dilation for rk_forward_series (64 bytes).  Positions are u = t - padding.
+constexpr int kSeriesLdsBytes = 159744;  // LDS of a CU that its workgroups may fill
+struct RkSet {
+    int32_t dil;
+    int32_t len;               // longest kernel
+    int32_t lo, hi;            // positions that any kernel has, lo rounded down to a multiple of 16
+    int32_t in_lo, in_hi;      // positions that all kernels have
+    int32_t regs;              // result registers in use: ceil(kernels / 4)
+    int32_t reserved;
+    int8_t tap[16];            // word 4 g + e of lane group g belongs to this tap ...
+    int8_t read[16];           // ... or, where that is -1, reads this tap's samples against zero weights
+};
+
 struct rocket_kernels {
     int32_t K = 0, C = 0, L = 0;
     std::vector<int32_t> length, dilation, padding, n_ch, channels;
@@ -83,6 +96,19 @@ struct rocket_kernels {
     double outputs = 0.0;    // sum_k n_k
     int32_t max_terms = 0;   // largest n_ch * length of any kernel
 
+    // one channel and short series: sets of kernels of one dilation (empty: rk_forward_series does not apply), the kernels
+    // in their 16 rows (-1: none), words of an LDS plane and the index of sample 0 in it
+    std::vector<RkSet> sets;
+    std::vector<int32_t> set_rows;
+    int32_t set_plane = 0, set_origin = 0;
+    // Sets of fewer than four kernels come last, after thick_sets others: their kernels (`thin`) are cheaper one by one
+    // in the job kernels where there is much of them.  Their jobs are the first thin_jobs of the list, and thin_steps is
+    // the number of 16-position tiles of those sets.
+    int32_t thick_sets = 0, thin_jobs = 0;
+    int64_t thin_steps = 0;
+    std::vector<int32_t> thin;
+    bool thin_only = false;    // the forward launchers take the thin kernels only (set for the call)
+
     // device mirror (allocated on first use on `device`)
     int device = -1;
     void *d_blob = nullptr;
@@ -95,6 +121,9 @@ struct rocket_kernels {
     const int32_t *d_kjob_off = nullptr;
     const int32_t *d_kjob_idx = nullptr;
     const int32_t *d_bjob_off = nullptr;
+    const RkSet *d_sets = nullptr;
+    const int32_t *d_set_rows = nullptr;
+    const int32_t *d_thin = nullptr;
     const int32_t *d_channels = nullptr;
     float *d_weights = nullptr;
 
@@ -134,6 +163,10 @@ int rk_launch_minirocket_features(const rocket_kernels *h, const int32_t *counts
 // Launchers that the kernels' translation units enter here when the library is loaded, so that the host code links
 // without them.
 struct RkLaunchers {
+    // rocket_forward_series.hip: the transform of a handle's sets (thick_only: without the thin ones; nl < 0 where the
+    // mask has softPPV).  x as below.
+    int (*forward_series)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, uint32_t mask, float nl, float ns,
+                          bool thick_only, float *out, void *stream) = nullptr;
     // rocket_minirocket_forward.hip.  x: rows of L samples that start row_stride floats apart.  Adds every work item's
     // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
