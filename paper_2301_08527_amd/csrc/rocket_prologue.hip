@@ -6,8 +6,8 @@
 // makes anyway reads the bytes and writes (x - mean) / std: the batch is read as 1 byte per
 // sample instead of 4, and no extra pass over it is needed beyond the row statistics.
 //
-//   rk_row_stats_u8 : one workgroup per (series, channel) row; exact 64-bit integer sums of
-//                     x and x^2, then mean and population standard deviation in fp64
+//   rk_row_stats_u8 : one workgroup per (series, channel) row; exact integer sums of x and x^2,
+//                     then mean and population standard deviation in fp64
 //   rk_pad_rows_u8  : the padding copy with the normalisation folded in; fp64 subtract and
 //                     divide, rounded once to fp32.  A row with zero variance becomes zeros.
 #include <hip/hip_runtime.h>
@@ -24,29 +24,57 @@ __device__ __forceinline__ unsigned long long rk_wave_sum_u64(unsigned long long
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void rk_row_stats_u8(const uint8_t *__restrict__ x, int L, int nrows,
-                                                       double2 *__restrict__ stats)
+// Sums of 16 samples by the byte instructions: exact.
+__device__ __forceinline__ void rk_add_word(uint32_t v, uint32_t &s, uint32_t &s2)
 {
-    __shared__ unsigned long long part[2][4];
+    s = __builtin_amdgcn_sad_u8(v, 0u, s);
+    s2 = __builtin_amdgcn_udot4(v, v, s2, false);
+}
+
+// A few rows (one reading) leave most of the chip idle, so a row is a matter of latency: 16 samples per lane and load from the
+// row's first 16-byte boundary on, NT lanes.  20 rows of 50,000 samples, byte by byte with 256 lanes 52 us, now 5.7 us.
+template <int NT>
+__global__ __launch_bounds__(NT) void rk_row_stats_u8(const uint8_t *__restrict__ x, int L, int nrows, double2 *__restrict__ stats)
+{
+    __shared__ unsigned long long part[2][NT / 64];
+    const int t = static_cast<int>(threadIdx.x);
     for (int row = blockIdx.x; row < nrows; row += gridDim.x) {
         const uint8_t *src = x + static_cast<size_t>(row) * L;
+        const int head = min(L, static_cast<int>(-reinterpret_cast<uintptr_t>(src) & 15));
+        const int pieces = (L - head) / 16, rest = head + 16 * pieces;   // rest .. L - 1: fewer than 16
+        const uint4 *wide = reinterpret_cast<const uint4 *>(src + head);
         unsigned long long s = 0, s2 = 0;
-        for (int i = threadIdx.x; i < L; i += 256) {
-            const unsigned v = src[i];
+#pragma unroll 4
+        for (int i = t; i < pieces; i += NT) {
+            const uint4 v = wide[i];
+            uint32_t p = 0, p2 = 0;
+            rk_add_word(v.x, p, p2);
+            rk_add_word(v.y, p, p2);
+            rk_add_word(v.z, p, p2);
+            rk_add_word(v.w, p, p2);
+            s += p;
+            s2 += p2;
+        }
+        if (t < head || (t >= 32 && t - 32 < L - rest)) {
+            const uint32_t v = src[t < head ? t : rest + t - 32];
             s += v;
             s2 += v * v;
         }
         s = rk_wave_sum_u64(s);
         s2 = rk_wave_sum_u64(s2);
-        const int wave = threadIdx.x >> 6;
-        if ((threadIdx.x & 63) == 0) {
+        const int wave = t >> 6;
+        if ((t & 63) == 0) {
             part[0][wave] = s;
             part[1][wave] = s2;
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            const unsigned long long ts = part[0][0] + part[0][1] + part[0][2] + part[0][3];
-            const unsigned long long ts2 = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+        if (t == 0) {
+            unsigned long long ts = 0, ts2 = 0;
+#pragma unroll
+            for (int w = 0; w < NT / 64; ++w) {
+                ts += part[0][w];
+                ts2 += part[1][w];
+            }
             const double mean = static_cast<double>(ts) / L;
             const double var = (static_cast<double>(ts2) - static_cast<double>(ts) * mean) / L;
             // ts2 == ts*mean exactly when all samples are equal; guard tiny negative rounding too
@@ -56,29 +84,44 @@ __global__ __launch_bounds__(256) void rk_row_stats_u8(const uint8_t *__restrict
     }
 }
 
-// Rows of row_len floats: `lead` zeros, the L normalised samples, zeros to the end; row number
-// nrows (one past the last) is written as zeros only.
+// Rows of row_len floats: `lead` zeros, the L normalised samples, zeros to the end; row number nrows (one past the last) is
+// written as zeros only.  A row has 256 different samples at most: each lane normalises one value (fp64 subtract and divide)
+// into an LDS table, and the kPadRounds x 1,024 columns of a workgroup are looked up there.
+constexpr int kPadRounds = 4;
 __global__ __launch_bounds__(256) void rk_pad_rows_u8(const uint8_t *__restrict__ x,
                                                       const double2 *__restrict__ stats,
                                                       float *__restrict__ xpad, int L, int lead, int row_len,
                                                       int nrows)
 {
-    const int col = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (col >= row_len) return;
+    struct __attribute__((packed)) Word { uint32_t v; };   // rows of x start at any byte
+    __shared__ float table[256];
+    const int t = static_cast<int>(threadIdx.x);
     for (int row = blockIdx.y; row <= nrows; row += gridDim.y) {
         const uint8_t *src = x + static_cast<size_t>(row) * L;
         const double2 ms = row < nrows ? stats[row] : make_double2(0.0, 0.0);
         const bool live = ms.y > 0.0;
-        const double sd = live ? ms.y : 1.0;
-        float v[4];
+        table[t] = live ? static_cast<float>((static_cast<double>(t) - ms.x) / ms.y) : 0.f;
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int s = col + q - lead;
-            float z = 0.f;
-            if (live && s >= 0 && s < L) z = static_cast<float>((static_cast<double>(src[s]) - ms.x) / sd);
-            v[q] = z;
+        for (int round = 0; round < kPadRounds; ++round) {
+            const uint32_t at = ((blockIdx.x * kPadRounds + round) * 256u + static_cast<uint32_t>(t)) * 4u;
+            if (at >= static_cast<uint32_t>(row_len)) break;
+            const int col = static_cast<int>(at), s = col - lead;
+            float v[4] = {0.f, 0.f, 0.f, 0.f};
+            if (row < nrows) {
+                if (s >= 0 && s <= L - 4) {
+                    const uint32_t word = reinterpret_cast<const Word *>(src + s)->v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = table[(word >> (8 * q)) & 255u];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (s + q >= 0 && s + q < L) v[q] = table[src[s + q]];
+                }
+            }
+            *reinterpret_cast<float4 *>(xpad + static_cast<size_t>(row) * row_len + col) = make_float4(v[0], v[1], v[2], v[3]);
         }
-        *reinterpret_cast<float4 *>(xpad + static_cast<size_t>(row) * row_len + col) = make_float4(v[0], v[1], v[2], v[3]);
+        __syncthreads();   // the table is done with
     }
 }
 
@@ -88,10 +131,12 @@ int rk_launch_pad_u8(const rocket_kernels *h, const uint8_t *x, int32_t B, float
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     double2 *stats = static_cast<double2 *>(stats_ptr);
     const int nrows = B * h->C;
-    hipLaunchKernelGGL(rk_row_stats_u8, dim3(static_cast<unsigned>(nrows < 65536 ? nrows : 65536)), dim3(256), 0,
-                       stream, x, h->L, nrows, stats);
+    // 1,024 lanes where a row gives each of them samples
+    const dim3 rows(static_cast<unsigned>(nrows < 65536 ? nrows : 65536));
+    if (h->L >= 16384) hipLaunchKernelGGL(rk_row_stats_u8<1024>, rows, dim3(1024), 0, stream, x, h->L, nrows, stats);
+    else hipLaunchKernelGGL(rk_row_stats_u8<256>, rows, dim3(256), 0, stream, x, h->L, nrows, stats);
     if (hipGetLastError() != hipSuccess) return ROCKET_EHIP;
-    dim3 grid(static_cast<unsigned>((h->row_len / 4 + 255) / 256), static_cast<unsigned>(nrows < 32768 ? nrows + 1 : 32768));
+    dim3 grid(static_cast<unsigned>((h->row_len + 1024 * kPadRounds - 1) / (1024 * kPadRounds)), static_cast<unsigned>(nrows < 32768 ? nrows + 1 : 32768));
     hipLaunchKernelGGL(rk_pad_rows_u8, grid, dim3(256), 0, stream, x, stats, xpad, h->L, h->lead,
                        static_cast<int>(h->row_len), nrows);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;

@@ -42,6 +42,19 @@ def test_small_ragged_with_dead_and_saturated_channels():
     check_forward(z, kr, out, 7)
 
 
+@pytest.mark.parametrize("L", [11, 15, 16, 17, 63, 1021, 1025, 4093, 4097, 16383, 16384, 16389])
+def test_rows_at_every_alignment(L):
+    """15 rows whose first bytes fall on different boundaries, series shorter than the widest load, and lengths around the
+    columns of a workgroup (4,096) and the change of its width (16,384); every row has its own mean and spread"""
+    rng = np.random.default_rng(L)
+    B, C = 3, 5
+    x = np.clip(rng.normal(128, rng.uniform(4, 60, size=(B, C, 1)), size=(B, C, L)).round(), 0, 255).astype(np.uint8)
+    h = rocket.rocket_make_kernels(78, 60, C, L)
+    kr = rocket.rocket_kernels_view_get(h)
+    print("u8 alignment", L, flush=True)
+    check_forward(oracle.znormalize_u8(x), kr, _run_u8(h, x, 7), 7)
+
+
 def test_matches_float_entry_point_on_normalised_input():
     """same kernels, the oracle's normalised fp32 batch through rocket_transform"""
     import torch
