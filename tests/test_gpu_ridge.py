@@ -43,6 +43,33 @@ def test_small_systems(n, p, alpha):
     _check(X, y, alpha)
 
 
+@pytest.mark.parametrize("n", [31, 32, 33, 511, 512, 513, 1024, 1025, 1056, 1567, 1568, 1569])
+def test_systems_around_the_fused_panels(n):
+    """examples around a panel (32), around what the back substitution keeps in registers (512 and 1,024) and around the
+    48 tiles of 32 rows from which a panel and its update are two launches (1,568 + the target's row = 32 + 48 x 32 + 1)"""
+    print("ridge panels", n, flush=True)
+    rng = np.random.default_rng(n)
+    X = (rng.standard_normal((n, 37)) * rng.uniform(0.2, 3.0, 37) + rng.uniform(-2, 2, 37)).astype(np.float32)
+    y = (X[:, :4].sum(axis=1) * 0.25 + 1.0 + 0.05 * rng.standard_normal(n)).astype(np.float32)
+    _check(X, y, 0.7)
+
+
+@pytest.mark.parametrize("p", [1, 3, 4, 1027, 2047, 2048, 2049, 4097, 8195])
+def test_predict_row_widths(p):
+    """feature counts around a lane's four columns and the change of the workgroup's width at 2,048; rows of odd length start
+    at every multiple of 4 bytes.  fp64 sums in another order: (p + 2) roundings of the sum of magnitudes bound the error."""
+    import torch
+    rng = np.random.default_rng(p)
+    X = rng.standard_normal((5, p)).astype(np.float32)
+    w, b = rng.standard_normal(p), 0.3
+    print("predict", p, flush=True)
+    pred = rocket.rocket_ridge_predict(torch.from_numpy(X).cuda(), torch.from_numpy(w).cuda(),
+                                       torch.tensor([b], dtype=torch.float64, device="cuda"))
+    torch.cuda.synchronize()
+    X = X.astype(np.float64)
+    assert np.all(np.abs(pred.cpu().numpy() - (X @ w + b)) <= 2 * (p + 2) * 2.0 ** -53 * (np.abs(X) @ np.abs(w) + b))
+
+
 def test_paper_sized_fit_on_transform_features():
     """677 training examples x 20,000 features, the paper's sizes (sections 3.3 and 4):
     features of a short synthetic workload, max + PPV planes of K = 10,000 kernels"""
