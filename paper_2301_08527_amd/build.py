@@ -16,14 +16,14 @@ LIB = os.environ.get("ROCKET_LIB_OUT", LIB)
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-KERNEL_TUS = ("rocket_forward.hip", "rocket_forward_short.hip", "rocket_forward_series.hip", "rocket_backward.hip", "rocket_ridge.hip",
+KERNEL_TUS = ("rocket_forward.hip", "rocket_forward_short.hip", "rocket_forward_series.hip", "rocket_backward.hip", "rocket_backward_short.hip", "rocket_ridge.hip",
               "rocket_prologue.hip", "rocket_train.hip", "rocket_calibrate.hip", "rocket_minirocket.hip",
               "rocket_minirocket_forward.hip")   # translation units that hold device code
 HOST_TUS = ("rocket_api.hip",)
 
 
 def sources():
-    names = ("sampler.cpp", "rocket_internal.hpp", "rocket_device.hpp", "rocket_forward_impl.hpp", "rocket_limbs.hpp") + KERNEL_TUS + HOST_TUS
+    names = ("sampler.cpp", "rocket_internal.hpp", "rocket_device.hpp", "rocket_forward_impl.hpp", "rocket_backward_impl.hpp", "rocket_limbs.hpp") + KERNEL_TUS + HOST_TUS
     return [os.path.join(CSRC, f) for f in names] + [os.path.join(ROOT, "include", "rocket.h")]
 
 

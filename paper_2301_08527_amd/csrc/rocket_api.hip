@@ -587,6 +587,8 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront forward kernel
+constexpr int kOneWaveSeries = 1024;     // some 64 strips of 16 or more rows: one for each lane of a wavefront
+constexpr int64_t kManyJobs = 8192;      // eight wavefronts to each of 1,024 SIMDs
 constexpr int64_t kThinSteps = 500000;    // 50 clk x 500,000 tiles over 1,024 SIMDs: some 10 us
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
@@ -779,7 +781,13 @@ static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, b
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
     rc = profile_mark(h, stream, true);
     if (rc != ROCKET_OK) return rc;
-    if (rk_launch_backward(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
+    // Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
+    // 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 428 us against 169 with 64 lanes).  Longer ones take longer on one
+    // wavefront, which only pays where others fill the chip: 4 x 4 x 8,000, 200 kernels, 800 jobs: 41 us against 81;
+    // 8 x 1 x 4,000, 2,400 jobs: 31 against 33; 16 x 4 x 6,000, 16,000 jobs: 251 against 246; 60 x 3 x 8,192, 120,000
+    // jobs: 1779 against 1421.
+    const bool narrow = h->L <= kShortSeries && (h->L <= kOneWaveSeries || static_cast<int64_t>(B) * h->jobs.size() >= kManyJobs);
+    if ((narrow ? rk_launch_backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
     rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;

@@ -219,6 +219,9 @@ int rk_launch_finalize(const rocket_kernels *h, const float *partials, int32_t B
                        void *stream);
 int rk_launch_backward(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F,
                        int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, void *stream);
+// the same with one wavefront to a workgroup
+int rk_launch_backward_short(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F,
+                             int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, void *stream);
 // sums the job partials of every kernel over the jobs and the batch, adds the max plane's
 // sub-gradient at the first arg-max, writes grad_w and grad_b
 int rk_launch_reduce_jobs(const rocket_kernels *h, const float *partial, const float *xpad, int32_t B,
