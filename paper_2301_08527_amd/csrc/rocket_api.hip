@@ -649,7 +649,14 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
     // Short univariate series: sets of kernels of one dilation, straight from the samples (raw bytes are normalised into
     // the padded copy).  Its edges rest on lambda > 0.
-    const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
+    // A set walks over all of a series on one wavefront, whether it holds sixteen kernels or one.  The job kernels are faster
+    // where a series is long and the chip not full of sets, and where most sets hold one or two kernels (series
+    // against job kernels, max and PPV: 4 x 8,000, 2,000 kernels 153 and 56 us; 64 x 4,000, 500 kernels 87 and 79;
+    // 16 x 2,000, 500 kernels 25 and 23; 64 x 1,000, 200 kernels with softPPV 26 and 22; but 64 x 2,000, 2,000 kernels 112 and 150;
+    // 64 x 1,000, 500 kernels 31 and 37; 4 x 1,000, 200 kernels, launches only, 11 and 17).
+    const int64_t pairs = static_cast<int64_t>(B) * h->K;
+    const bool thin_or_long = h->L <= kOneWaveSeries ? 3LL * h->K < h->L && pairs > 4096 : h->K < h->L || pairs < 100000;
+    const bool series = !h->sets.empty() && !thin_or_long && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
     // The thin sets take some 50 clk of a SIMD more per 16-position tile than the job kernels; those need three launches.
     const bool split = series && h->thin_jobs > 0 && h->thin_steps * B > kThinSteps;
     if (is_u8 || split || !series) {
@@ -1111,7 +1118,7 @@ static int minirocket_transform_impl(const char *fn, rocket_kernels *h, const vo
         row_stride = h->row_len;
     }
     // one work item per group (short series): its workgroup writes the features itself
-    const bool direct = rk_launchers().minirocket_one_pass(h);
+    const bool direct = rk_launchers().minirocket_one_pass(h, B);
     if (!direct && rk_launch_minirocket_clear(h, B, counts, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the clearing kernel failed");
     rc = profile_mark(h, stream, true);

@@ -171,7 +171,7 @@ struct RkLaunchers {
     // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
                               void *stream) = nullptr;
-    bool (*minirocket_one_pass)(const rocket_kernels *h) = nullptr;
+    bool (*minirocket_one_pass)(const rocket_kernels *h, int32_t B) = nullptr;
 };
 RkLaunchers &rk_launchers();      // rocket_api.hip
 // rocket_api.hip: offsets, job plan, padded row geometry; returns ROCKET_OK or an error

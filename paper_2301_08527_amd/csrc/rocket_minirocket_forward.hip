@@ -497,22 +497,25 @@ int rk_launch_minirocket_clear(const rocket_kernels *h, int32_t B, int32_t *coun
 }
 
 // Whether rk_mr_forward_series applies: one channel, and the padded series' planes leave a CU room for four workgroups.
-static int mr_series_plane(const rocket_kernels *h)
+// A wavefront walks over the whole output of its group, so longer series are for batches that fill the chip with groups
+// (this kernel against the tiles of rk_mr_forward: 4 x 4,000 samples, 12 groups 47 and 21 us; 64 x 2,000, 40 groups 46 and 40).
+static int mr_series_plane(const rocket_kernels *h, int32_t B)
 {
+    if (h->L > 1024 && static_cast<int64_t>(B) * h->mr_groups < 8192) return 0;
     const int64_t plane = (static_cast<int64_t>(h->L) + 2LL * h->pad_max + kMrChunk + 63) / 64 * 64 + 32;
     return h->C == 1 && plane * 6 <= 39000 ? static_cast<int>(plane) : 0;
 }
 
-static bool minirocket_one_pass(const rocket_kernels *h)
+static bool minirocket_one_pass(const rocket_kernels *h, int32_t B)
 {
-    return mr_series_plane(h) != 0 || h->mr_jobs.size() == static_cast<size_t>(h->mr_groups);
+    return mr_series_plane(h, B) != 0 || h->mr_jobs.size() == static_cast<size_t>(h->mr_groups);
 }
 
 static int launch_minirocket_forward(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts,
                                      float *out, void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    if (const int plane = mr_series_plane(h); plane != 0) {
+    if (const int plane = mr_series_plane(h, B); plane != 0) {
         const int blocks = (h->mr_groups + 3) / 4;
         hipLaunchKernelGGL(rk_mr_forward_series, dim3(static_cast<unsigned>(static_cast<int64_t>(B) * blocks)), dim3(256),
                            static_cast<unsigned>((3 * plane + 2 * kMrChunk) * 2), stream, x, static_cast<size_t>(row_stride), h->L, h->d_rec,

@@ -286,3 +286,23 @@ def test_exact_ties_send_the_max_gradient_to_the_first_position():
     # all quantities are small integers (the soft plane's upstream gradient is zero): exact equality
     assert np.array_equal(gw.cpu().numpy().astype(np.float64), gw_ref)
     assert np.array_equal(gb.cpu().numpy().astype(np.float64), gb_ref)
+
+
+@pytest.mark.parametrize("C,L", [(1, 1025), (3, 3001), (2, 8192)])
+def test_one_wavefront_per_kernel_equals_four(C, L):
+    # 9,000 jobs go one to a wavefront, the 4,500 of half a batch one to a workgroup of four; gradients add up over the batch
+    import torch
+    K, B = 900, 10
+    h = rocket.rocket_make_kernels(L, K, C, L)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn((B, C, L), generator=g, device="cuda")
+    gout = torch.randn((B, 2 * K), generator=g, device="cuda")
+    print("one wavefront per kernel", C, L, flush=True)
+    whole = rocket.rocket_soft_ppv_backward(h, x, 5, gout, 10.0, -3.0, True)
+    parts = [rocket.rocket_soft_ppv_backward(h, x[i:i + 5].contiguous(), 5, gout[i:i + 5].contiguous(), 10.0, -3.0, True)
+             for i in (0, 5)]
+    for a, b, c in zip(whole, *parts):
+        a, want = a.double(), b.double() + c.double()
+        # fp32 sums of the same terms in another order: 2^-24 sqrt(80,000 terms) of sums around their rms, tenfold
+        assert float((a - want).norm()) <= 1e-5 * float(want.norm())
+        assert float((a - want).abs().max()) <= 1e-4 * float(want.abs().max())

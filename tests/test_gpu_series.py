@@ -35,6 +35,8 @@ def test_every_mask_on_small_series(B, L, K, mask):
 @pytest.mark.parametrize("B,L,K,mask", [
     (3, 2400, 600, 7), (2, 4900, 300, 3),       # four, two and one workgroup to a CU
     (2, 9700, 100, 7), (2, 10400, 100, 7),      # either side of the longest series that LDS holds
+    (11, 9700, 9700, 3), (10, 10400, 10400, 2),     # the same, with enough kernels for the sets to be taken
+    (40, 3000, 3000, 3), (25, 4900, 4900, 7),
     (40, 1500, 3000, 3),                        # several sets to a wavefront
     (64, 3000, 300, 7), (40, 8000, 200, 2),     # few kernels to a dilation: those go through the job kernels
 ])
