@@ -794,7 +794,7 @@ static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, b
     // 8 x 1 x 4,000, 2,400 jobs: 31 against 33; 16 x 4 x 6,000, 16,000 jobs: 251 against 246; 60 x 3 x 8,192, 120,000
     // jobs: 1779 against 1421.
     const bool narrow = h->L <= kShortSeries && (h->L <= kOneWaveSeries || static_cast<int64_t>(B) * h->jobs.size() >= kManyJobs);
-    if ((narrow ? rk_launch_backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
+    if ((narrow ? rk_launchers().backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
     rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;

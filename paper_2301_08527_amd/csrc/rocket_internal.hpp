@@ -172,6 +172,9 @@ struct RkLaunchers {
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
                               void *stream) = nullptr;
     bool (*minirocket_one_pass)(const rocket_kernels *h, int32_t B) = nullptr;
+    // rk_launch_backward with one wavefront to a workgroup
+    int (*backward_short)(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F, int plane_soft,
+                          int plane_max, float lambda, float nl, float ns, float *partial, void *stream) = nullptr;
 };
 RkLaunchers &rk_launchers();      // rocket_api.hip
 // rocket_api.hip: offsets, job plan, padded row geometry; returns ROCKET_OK or an error
@@ -219,9 +222,6 @@ int rk_launch_finalize(const rocket_kernels *h, const float *partials, int32_t B
                        void *stream);
 int rk_launch_backward(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F,
                        int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, void *stream);
-// the same with one wavefront to a workgroup
-int rk_launch_backward_short(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F,
-                             int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, void *stream);
 // sums the job partials of every kernel over the jobs and the batch, adds the max plane's
 // sub-gradient at the first arg-max, writes grad_w and grad_b
 int rk_launch_reduce_jobs(const rocket_kernels *h, const float *partial, const float *xpad, int32_t B,
