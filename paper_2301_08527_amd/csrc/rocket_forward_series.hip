@@ -258,7 +258,7 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
         for (int u = tid * 4; u < plane; u += waves * 256) {
             float v[4];
             const int i = u - origin;
-            if (static_cast<unsigned>(i) <= static_cast<unsigned>(L - 4)) {
+            if (i >= 0 && i <= L - 4) {      // signed: a series may be shorter than four samples
                 const f4u q = *reinterpret_cast<const f4u *>(row + i);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = q[e];

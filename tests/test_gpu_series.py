@@ -51,3 +51,27 @@ def test_slope_of_any_sign(lam):
 
 def test_raw_bytes():
     _run(5, 701, 333, 7, u8=True)
+
+
+def _imported(rng, L, lengths, dilations, padded=True):
+    """(handle, oracle arrays) of one-channel kernels of given lengths and dilations"""
+    K = len(lengths)
+    length, dilation = np.asarray(lengths, np.int32), np.asarray(dilations, np.int32)
+    kr = dict(K=K, C=1, L=L, length=length, dilation=dilation,
+              padding=((length - 1) // 2 * dilation if padded else np.zeros(K)).astype(np.int32),
+              bias=rng.uniform(-1, 1, K).astype(np.float32), n_ch=np.ones(K, np.int32), channels=np.zeros(K, np.int32),
+              ch_off=np.arange(K + 1, dtype=np.int64), w_off=np.concatenate([[0], np.cumsum(length)]).astype(np.int64),
+              weights=rng.standard_normal(int(length.sum())).astype(np.float32))
+    h = rocket.rocket_kernels_import(K, 1, L, length, dilation, kr["padding"], kr["bias"], kr["n_ch"], kr["channels"], kr["weights"])
+    return h, kr
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5])
+def test_series_shorter_than_a_vector_load(L):
+    import torch
+    rng = np.random.default_rng(L)
+    h, kr = _imported(rng, L, [7, 9, 11] * 7, [1, 1, 2, 1, 3, 1, 1] * 3)
+    x = rng.standard_normal((5, 1, L)).astype(np.float32)
+    print("short series", L, flush=True)
+    out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 7).cpu().numpy()
+    check_forward(x, kr, out, 7)
