@@ -89,7 +89,11 @@ static void plan_sets(rocket_kernels &h)
 {
     h.sets.clear(); h.set_rows.clear(); h.thin.clear();
     h.thick_sets = 0; h.thin_steps = 0;
-    if (h.C != 1 || h.L > 65000) return;
+    if (h.C != 1) return;
+    // A plane holds the zeros before the series and the series.  (Checked first: an imported kernel may be padded to 2^31.)
+    int64_t words = h.L;
+    for (int32_t k = 0; k < h.K; ++k) words = std::max<int64_t>(words, static_cast<int64_t>(h.padding[k]) + h.L);
+    if (8 * words > kSeriesLdsBytes) return;
     std::vector<int64_t> keyed(h.K);      // dilation, padded or not, length, kernel
     for (int32_t k = 0; k < h.K; ++k)
         keyed[k] = (static_cast<int64_t>(h.dilation[k]) * 32 + (h.padding[k] > 0 ? 16 : 0) + h.length[k]) << 31 | k;
@@ -561,7 +565,7 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         for (int32_t k = 0; k < K; ++k) {
             RkKernelRec &r = rec[k];
             r.len = h->length[k]; r.dil = h->dilation[k]; r.pad = h->padding[k];
-            r.nout = h->L + 2 * h->padding[k] - (h->length[k] - 1) * h->dilation[k];
+            r.nout = static_cast<int32_t>(h->L + 2LL * h->padding[k] - static_cast<int64_t>(h->length[k] - 1) * h->dilation[k]);
             r.bias = h->bias[k]; r.nch = h->n_ch[k];
             r.ch_off = static_cast<int32_t>(h->ch_off[k]);
             r.w_off = static_cast<int32_t>(h->w_off[k]);

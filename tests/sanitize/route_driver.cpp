@@ -1,0 +1,96 @@
+// Drives the host side of the compute entry points under AddressSanitizer and UndefinedBehaviorSanitizer without a GPU:
+// the HIP calls of rocket_api.hip are replaced by host memory and the kernel launchers by stubs that record which of them
+// a call reached.  Linked like host_driver.cpp.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+#include "rocket_internal.hpp"
+
+static int g_copies = 0, g_mallocs = 0;
+static std::string g_route;
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { ++g_mallocs; *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { ++g_copies; std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+}
+
+#define RECORD(name) { g_route += name " "; return ROCKET_OK; }
+int rk_launch_pad(const rocket_kernels *, const float *, int32_t, float *, void *) RECORD("pad")
+int rk_launch_mse_grad(const double *, const float *, const double *, int32_t, int32_t, float *, double *, void *) RECORD("mse")
+int rk_launch_sgd_update(const rocket_kernels *, const float *, const float *, float, int, void *) RECORD("sgd")
+int rk_launch_pad_u8(const rocket_kernels *, const uint8_t *, int32_t, float *, void *, void *) RECORD("pad_u8")
+int rk_launch_forward(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("forward")
+int rk_launch_forward_short(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("short")
+int rk_launch_finalize(const rocket_kernels *, const float *, int32_t, uint32_t, float *, void *) RECORD("finalize")
+int rk_launch_backward(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
+                       float *, void *) RECORD("backward")
+int rk_launch_reduce_jobs(const rocket_kernels *, const float *, const float *, int32_t, const float *, int, int, float *,
+                          float *, void *) RECORD("reduce")
+int rk_launch_minirocket_outputs(const rocket_kernels *, const float *, const int32_t *, int32_t, int32_t, int64_t, float *,
+                                 void *) RECORD("mr_outputs")
+int rk_launch_minirocket_select(const rocket_kernels *, const int32_t *, int32_t, int32_t, int64_t, const float *, void *)
+    RECORD("mr_select")
+int rk_launch_minirocket_clear(const rocket_kernels *, int32_t, int32_t *, void *) RECORD("mr_clear")
+int rk_launch_minirocket_features(const rocket_kernels *, const int32_t *, int32_t, float *, void *) RECORD("mr_features")
+extern "C" int rocket_ridge_predict(const float *, int32_t, int32_t, const double *, const double *, double *, void *)
+    RECORD("ridge_predict")
+
+static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, bool, float *, void *) RECORD("series")
+static int backward_short_stub(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
+                               float *, void *) RECORD("backward_short")
+[[maybe_unused]] static const bool kEntered = (rk_launchers().forward_series = series_stub,
+                                               rk_launchers().backward_short = backward_short_stub, true);
+
+#define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s (route: %s)\n", __LINE__, #cond, g_route.c_str()); return 1; } } while (0)
+
+// The launches of one rocket_transform call.  The stubs touch no sample, so x and the workspace are addresses only.
+static std::string transform_route(rocket_kernels *h, int32_t B, uint32_t mask, float lambda = 10.f)
+{
+    g_route.clear();
+    alignas(256) static char there[256];
+    const int rc = rocket_transform(h, reinterpret_cast<const float *>(there), B, mask, lambda, -3.f,
+                                    reinterpret_cast<float *>(there), there, static_cast<size_t>(1) << 50, nullptr);
+    return rc == ROCKET_OK ? g_route : std::string("error ") + rocket_last_error();
+}
+
+// One-channel kernels of one length, padded, with the given dilations.
+static rocket_kernels *padded_kernels(int32_t L, const std::vector<int32_t> &dilation)
+{
+    const int32_t K = static_cast<int32_t>(dilation.size());
+    std::vector<int32_t> length(K, 11), padding(K), n_ch(K, 1), channels(K, 0);
+    std::vector<float> bias(K, 0.5f), weights(11 * static_cast<size_t>(K), 0.25f);
+    for (int32_t k = 0; k < K; ++k) padding[k] = 5 * dilation[k];
+    rocket_kernels *h = nullptr;
+    rocket_kernels_import(K, 1, L, length.data(), dilation.data(), padding.data(), bias.data(), n_ch.data(), channels.data(),
+                          weights.data(), &h);
+    return h;
+}
+
+// Padded kernels may be wider than their series: an imported dilation has no upper limit but its padding's 32 bits.
+static int wide_kernels()
+{
+    rocket_kernels *h = padded_kernels(100, {1, 7, 300000000, 400000000});
+    CHECK(h != nullptr);
+    CHECK(transform_route(h, 2, 7) == "pad short finalize ");      // too wide for the LDS planes of the series kernel
+    rocket_free_kernels(h);
+    return 0;
+}
+
+int main()
+{
+    if (wide_kernels()) return 1;
+    std::puts("route driver: ok");
+    return 0;
+}
