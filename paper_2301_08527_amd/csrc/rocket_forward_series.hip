@@ -32,7 +32,12 @@
 namespace {
 
 constexpr int kSerStep = 32;               // positions of a step: two matrix instructions wide
-constexpr int kSerTaps = 11;
+constexpr int kSerMost = 32;               // most series of a workgroup
+
+// Samples and weights that go through the split: with these limits the smallest product of parts is 2^-120.  A series with another
+// sample, or a kernel with another weight, is computed by plain multiply-adds (ser_plain).
+__device__ __forceinline__ bool ser_samples_split(const RkSpan &x) { return x.within<-64, 60>(); }
+__device__ __forceinline__ bool ser_weights_split(const RkSpan &w) { return w.within<-32, 60>(); }
 
 // min / sum over each row of 16 lanes (all 16 lanes end up with the result)
 template <class F>
@@ -68,7 +73,8 @@ __device__ __forceinline__ int ser_byte(const int8_t (&table)[16], int g, int e)
 }
 
 // Weight operands of a set: lane (row m = lane % 16, g = lane / 16) holds words 4 g .. 4 g + 3 of its row's kernel.
-__device__ __forceinline__ void ser_weights(SerState &st, const RkSet &set, const int32_t *__restrict__ rows, const RkKernelRec *__restrict__ recs,
+// Returns the rows (bit m) whose weights the split does not carry.
+__device__ __forceinline__ uint32_t ser_weights(SerState &st, const RkSet &set, const int32_t *__restrict__ rows, const RkKernelRec *__restrict__ recs,
                                             const float *__restrict__ weights, int lane)
 {
     const int m = lane & 15, g = lane >> 4;
@@ -78,10 +84,12 @@ __device__ __forceinline__ void ser_weights(SerState &st, const RkSet &set, cons
     if (k >= 0) { len = recs[k].len; w += recs[k].w_off; }
     auto weight = [&](int j) { return j >= 0 && j < len ? 0.f - w[j] : 0.f; };
     uint32_t r[3][4];
+    RkSpan span;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         uint32_t l[3];
         const float v = weight(ser_byte(set.tap, g, e));
+        span.add(v);
         rk_split2(v, v, l);
         r[0][e] = l[0];
         r[1][e] = l[1];
@@ -95,6 +103,8 @@ __device__ __forceinline__ void ser_weights(SerState &st, const RkSet &set, cons
         st.C[v] = 0.f; st.lo[v] = 0; st.n[v] = 0;
         if (kk >= 0) { st.C[v] = 0.f - recs[kk].bias; st.lo[v] = -recs[kk].pad; st.n[v] = recs[kk].nout; }
     }
+    const uint64_t lanes = __ballot(!ser_weights_split(span));
+    return static_cast<uint32_t>(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu;
 }
 
 // A word of LDS at a byte address.  A relaxed atomic load, so that the reads of two neighbouring matrix operands are
@@ -210,9 +220,9 @@ __device__ __forceinline__ void ser_run(SerState &st, const RkSet &set, const ui
     ser_steps<MASK, NV, true>(st, at, step, planes, u0, end, sl, ns, lane);
 }
 
-// Features of the rows in registers v < NV of series b.
+// Features of the rows in registers v < NV, those in `skip` excepted.
 template <int MASK, int NV>
-__device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restrict__ rows, int K, float *__restrict__ out, int lane)
+__device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restrict__ rows, uint32_t skip, int K, float *__restrict__ out, int lane)
 {
     const int m = lane & 15, g = lane >> 4;
     float low = 0.f, soft = 0.f;
@@ -228,12 +238,42 @@ __device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restric
         }
         n = m == v ? st.n[v] : n;
     });
-    const int k = m < NV ? rows[4 * g + m] : -1;
+    const int k = m < NV && (skip >> (4 * g + m) & 1u) == 0u ? rows[4 * g + m] : -1;
     if (k < 0) return;
     float *o = out + k;
     if constexpr ((MASK & ROCKET_F_MAX) != 0) { *o = 0.f - low; o += K; }
     if constexpr ((MASK & ROCKET_F_PPV) != 0) { *o = static_cast<float>(static_cast<double>(count) / static_cast<double>(n)); o += K; }
     if constexpr ((MASK & ROCKET_F_SOFTPPV) != 0) *o = soft / static_cast<float>(n);
+}
+
+// Kernel k over one series, by multiply-adds and pooling as in the job kernels: for the few numbers that the split does not carry.
+template <int MASK>
+__device__ __forceinline__ void ser_plain(int k, const RkKernelRec *__restrict__ recs, const float *__restrict__ weights,
+                                          const float *__restrict__ row, int L, float sl, float ns, int K, float *__restrict__ out, int lane)
+{
+    const RkKernelRec rec = recs[k];
+    const float *w = weights + rec.w_off;
+    const float nl = 0.f - sl, shifted = fmaf(rec.bias, nl, ns);
+    PoolState st = {-INFINITY, 0.f, 0};
+    for (int t = lane; t < rec.nout; t += 64) {
+        float z[1] = {0.f};
+        for (int j = 0; j < rec.len; ++j) {
+            const int64_t i = static_cast<int64_t>(t) - rec.pad + static_cast<int64_t>(j) * rec.dil;
+            const float v = i >= 0 && i < L ? row[i] : 0.f;
+            z[0] = j == 0 ? w[0] * v : fmaf(w[j], v, z[0]);
+        }
+        rk_pool<1>(z, MASK, -rec.bias, nl, shifted, st);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        st.vmax = fmaxf(st.vmax, __shfl_xor(st.vmax, off));
+        st.ssum += __shfl_xor(st.ssum, off);
+    }
+    if (lane != 0) return;       // the first lane has a position in every round and so all counts
+    float *o = out + k;
+    if constexpr ((MASK & ROCKET_F_MAX) != 0) { *o = st.vmax + rec.bias; o += K; }
+    if constexpr ((MASK & ROCKET_F_PPV) != 0) { *o = static_cast<float>(static_cast<double>(st.cnt) / static_cast<double>(rec.nout)); o += K; }
+    if constexpr ((MASK & ROCKET_F_SOFTPPV) != 0) *o = st.ssum / static_cast<float>(rec.nout);
 }
 
 }  // namespace
@@ -248,13 +288,16 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
                        int K, float *__restrict__ out)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t planes[];    // per series two planes of `plane` words
+    __shared__ uint32_t wave_odd[16];
     const int waves = static_cast<int>(blockDim.x) / 64;
     const int tid = static_cast<int>(threadIdx.x);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int sb = static_cast<int>(blockIdx.x) / blocks, block = static_cast<int>(blockIdx.x) - sb * blocks;
     const int b0 = sb * some, nb = min(some, B - b0);
+    uint32_t odd = 0u;       // bit s: series b0 + s has a sample that the split does not carry
     for (int s = 0; s < nb; ++s) {
         const float *row = x + static_cast<size_t>(b0 + s) * row_stride;
+        RkSpan span;
         for (int u = tid * 4; u < plane; u += waves * 256) {
             float v[4];
             const int i = u - origin;
@@ -270,29 +313,41 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 float rest;
+                span.add(v[e]);
                 p[e] = rk_split_pair(v[e], rest);
                 q[e] = (p[e] & 0xFFFFu) | rk_pack_bf16(rest, rest) << 16;
             }
             *reinterpret_cast<rk_u32x4 *>(planes + static_cast<size_t>(s) * 2 * plane + u) = p;
             *reinterpret_cast<rk_u32x4 *>(planes + static_cast<size_t>(s) * 2 * plane + plane + u) = q;
         }
+        if (__ballot(!ser_samples_split(span)) != 0u) odd |= 1u << s;
     }
+    if (lane == 0) wave_odd[wave] = odd;
     __syncthreads();
+    for (int w = 0; w < waves; ++w) odd |= wave_odd[w];
+    odd = __builtin_amdgcn_readfirstlane(odd);
     asm volatile("" : "+v"(sl), "+v"(ns));
     const int last = min(nsets, (block + 1) * per);
     for (int i = block * per + wave; i < last; i += waves) {
         const RkSet set = sets[i];
         const int32_t *rows = set_rows + 16 * i;
         SerState st;
-        ser_weights(st, set, rows, recs, weights, lane);
+        const uint32_t odd_rows = ser_weights(st, set, rows, recs, weights, lane);
         for (int s = 0; s < nb; ++s) {
             const int first = s * 2 * plane;
             float *o = out + static_cast<size_t>(b0 + s) * __builtin_popcount(MASK) * K;
-            switch (set.regs) {
-            case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, K, o, lane); break;
-            case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, K, o, lane); break;
-            case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, K, o, lane); break;
-            default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, K, o, lane); break;
+            uint32_t plain = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows;
+            if (plain != 0xFFFFu) {
+                switch (set.regs) {
+                case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, plain, K, o, lane); break;
+                case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, plain, K, o, lane); break;
+                case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, plain, K, o, lane); break;
+                default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, plain, K, o, lane); break;
+                }
+            }
+            for (; plain != 0u; plain &= plain - 1u) {
+                const int k = rows[__builtin_ctz(plain)];
+                if (k >= 0) ser_plain<MASK>(k, recs, weights, x + static_cast<size_t>(b0 + s) * row_stride, L, sl, ns, K, o, lane);
             }
         }
     }
@@ -311,7 +366,7 @@ static int launch_forward_series(const rocket_kernels *h, const float *x, int64_
     // serve all of them.
     const int room = std::max(1, kSeriesLdsBytes / 4 * (waves / 4) / bytes);
     const int64_t tasks = static_cast<int64_t>(nsets) * B;
-    const int some = static_cast<int>(std::min<int64_t>({room, B, std::max<int64_t>(1, tasks / 16384)}));
+    const int some = static_cast<int>(std::min<int64_t>({room, kSerMost, B, std::max<int64_t>(1, tasks / 16384)}));
     const int64_t sblocks = (B + some - 1) / some;
     // sets of a workgroup: one, two or four to a wavefront
     const int per = waves * (sblocks * nsets >= 131072 ? 4 : sblocks * nsets >= 65536 ? 2 : 1);

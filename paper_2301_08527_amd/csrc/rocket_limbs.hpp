@@ -19,6 +19,24 @@ typedef uint32_t rk_u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t rk_u32x4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));      // four floats at any multiple of 4 bytes
 
+// Whether numbers are zeros or of magnitudes in [2^LO, 2^HI] (NaN is not).  The kernels that split take such numbers only, with
+// limits that keep every part and every product of parts clear of overflow and of subnormal numbers, and have another path for the
+// rest.  Three integer instructions a number.
+struct RkSpan {
+    uint32_t least = 0xFFFFFFFFu, most = 0u;       // of twice the magnitude's bits, less one (zeros come last) and as they are
+    __device__ __forceinline__ void add(float x)
+    {
+        const uint32_t twice = __builtin_bit_cast(uint32_t, x) << 1;
+        least = min(least, twice - 1u);
+        most = max(most, twice);
+    }
+    template <int LO, int HI>
+    __device__ __forceinline__ bool within() const
+    {
+        return least >= (static_cast<uint32_t>(LO + 127) << 24) - 1u && most <= static_cast<uint32_t>(HI + 127) << 24;
+    }
+};
+
 __device__ __forceinline__ rk_bf16x8 rk_frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
 {
     return __builtin_bit_cast(rk_bf16x8, rk_u32x4{a, b, c, d});

@@ -75,3 +75,42 @@ def test_series_shorter_than_a_vector_load(L):
     print("short series", L, flush=True)
     out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 7).cpu().numpy()
     check_forward(x, kr, out, 7)
+
+
+@pytest.mark.parametrize("what", ["large samples", "small samples", "large weights", "small weights"])
+def test_numbers_beyond_the_split(what):
+    """Finite samples and weights that three bf16 parts or their products do not carry, in one series of five and in one kernel
+    of 16: fp32 arithmetic handles them, so the outputs keep fp32's error, (length + 1) roundings of the sum of magnitudes."""
+    import torch
+    rng = np.random.default_rng(5)
+    B, L, K = 5, 300, 32
+    h, kr = _imported(rng, L, [7, 9, 11, 11] * 8, [1, 1, 1, 1, 3, 3, 3, 3] * 4)
+    x = rng.standard_normal((B, 1, L)).astype(np.float32)
+    w, bias = kr["weights"].copy(), np.zeros(K, np.float32)
+    lo, hi = int(kr["w_off"][7]), int(kr["w_off"][8])
+    if what == "large samples":
+        x[2, 0, ::37] = np.float32(3.4e38) * np.sign(x[2, 0, ::37])
+        w *= np.float32(0.01)
+    elif what == "small samples":
+        x[2] *= np.float32(2.0 ** -120)
+    elif what == "large weights":
+        w[lo:hi] *= np.float32(3e38) / np.abs(w[lo:hi]).max()
+        w[lo] = np.float32(3.4e38)
+        x *= np.float32(0.01)
+    else:
+        w[lo:hi] *= np.float32(2.0 ** -120)
+    rocket.rocket_kernels_set_params(h, w, bias)
+    kr = dict(kr, weights=w, bias=bias)
+    print("beyond the split:", what, flush=True)
+    out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 3).cpu().numpy().astype(np.float64)
+    for b in range(B):
+        for k in range(K):
+            ln, d, p = int(kr["length"][k]), int(kr["dilation"][k]), int(kr["padding"][k])
+            n = L + 2 * p - (ln - 1) * d
+            xp = np.pad(x[b, 0].astype(np.float64), p)
+            wk = w[kr["w_off"][k]:kr["w_off"][k + 1]].astype(np.float64)
+            terms = np.stack([wk[j] * xp[j * d:j * d + n] for j in range(ln)])
+            y, tol = terms.sum(0), (ln + 1) * 2.0 ** -24 * np.abs(terms).sum(0)
+            assert np.abs(out[b, k] - y.max()) <= tol.max(), (b, k, out[b, k], y.max())
+            count = np.rint(out[b, K + k] * n)
+            assert abs(count - (y > 0).sum()) <= (np.abs(y) <= tol).sum(), (b, k)
