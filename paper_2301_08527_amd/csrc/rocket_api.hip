@@ -1131,7 +1131,7 @@ static int minirocket_transform_impl(const char *fn, rocket_kernels *h, const vo
         return rk_fail(ROCKET_EHIP, "launch of the group kernel failed");
     rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;
-    if (!direct && rk_launch_minirocket_features(h, counts, B, out_dev, stream) != ROCKET_OK)
+    if (!direct && rk_launchers().minirocket_features(h, x, row_stride, counts, B, out_dev, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the feature kernel failed");
     return ROCKET_OK;
 }

@@ -336,16 +336,18 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
         for (int s = 0; s < nb; ++s) {
             const int first = s * 2 * plane;
             float *o = out + static_cast<size_t>(b0 + s) * __builtin_popcount(MASK) * K;
-            uint32_t plain = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows;
-            if (plain != 0xFFFFu) {
-                switch (set.regs) {
-                case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, plain, K, o, lane); break;
-                case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, plain, K, o, lane); break;
-                case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, plain, K, o, lane); break;
-                default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, plain, K, o, lane); break;
-                }
+            const uint32_t skip = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows;
+            switch (set.regs) {
+            case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, skip, K, o, lane); break;
+            case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, skip, K, o, lane); break;
+            case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, skip, K, o, lane); break;
+            default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, skip, K, o, lane); break;
             }
-            for (; plain != 0u; plain &= plain - 1u) {
+        }
+        if ((odd | odd_rows) == 0u) continue;
+        for (int s = 0; s < nb; ++s) {
+            float *o = out + static_cast<size_t>(b0 + s) * __builtin_popcount(MASK) * K;
+            for (uint32_t plain = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows; plain != 0u; plain &= plain - 1u) {
                 const int k = rows[__builtin_ctz(plain)];
                 if (k >= 0) ser_plain<MASK>(k, recs, weights, x + static_cast<size_t>(b0 + s) * row_stride, L, sl, ns, K, o, lane);
             }

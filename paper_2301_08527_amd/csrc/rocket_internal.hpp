@@ -157,9 +157,8 @@ int rk_launch_minirocket_outputs(const rocket_kernels *h, const float *xpad, con
 int rk_launch_minirocket_select(const rocket_kernels *h, const int32_t *rank_dev, int32_t k0, int32_t count,
                                 int64_t stride, const float *ybuf, void *stream);
 // rocket_minirocket_forward.hip: the PPV features of a MINIROCKET-style handle, group by group: clears the
-// B x K counters; turns them into features (the kernel that counts is in the table below)
+// B x K counters (the kernel that counts and the one that makes features of them are in the table below)
 int rk_launch_minirocket_clear(const rocket_kernels *h, int32_t B, int32_t *counts, void *stream);
-int rk_launch_minirocket_features(const rocket_kernels *h, const int32_t *counts, int32_t B, float *out, void *stream);
 // Launchers that the kernels' translation units enter here when the library is loaded, so that the host code links
 // without them.
 struct RkLaunchers {
@@ -171,6 +170,9 @@ struct RkLaunchers {
     // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
                               void *stream) = nullptr;
+    // The features of those counts (x again: for the few that the matrix cores cannot take).
+    int (*minirocket_features)(const rocket_kernels *h, const float *x, int64_t row_stride, const int32_t *counts, int32_t B, float *out,
+                               void *stream) = nullptr;
     bool (*minirocket_one_pass)(const rocket_kernels *h, int32_t B) = nullptr;
     // rk_launch_backward with one wavefront to a workgroup
     int (*backward_short)(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F, int plane_soft,

@@ -21,19 +21,22 @@ typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));      // four 
 
 // Whether numbers are zeros or of magnitudes in [2^LO, 2^HI] (NaN is not).  The kernels that split take such numbers only, with
 // limits that keep every part and every product of parts clear of overflow and of subnormal numbers, and have another path for the
-// rest.  Three integer instructions a number.
+// rest.  Five integer instructions for two numbers (v_min3 and v_max3 take two at a time).
 struct RkSpan {
-    uint32_t least = 0xFFFFFFFFu, most = 0u;       // of twice the magnitude's bits, less one (zeros come last) and as they are
+    uint32_t least = 0xFFFFFFFFu, negative = 0u;       // least: of twice the magnitude's bits, less one (zeros come last)
+    int32_t positive = 0;
     __device__ __forceinline__ void add(float x)
     {
-        const uint32_t twice = __builtin_bit_cast(uint32_t, x) << 1;
-        least = min(least, twice - 1u);
-        most = max(most, twice);
+        const uint32_t bits = __builtin_bit_cast(uint32_t, x);
+        least = min(least, (bits << 1) - 1u);
+        positive = max(positive, static_cast<int32_t>(bits));
+        negative = max(negative, bits);
     }
     template <int LO, int HI>
     __device__ __forceinline__ bool within() const
     {
-        return least >= (static_cast<uint32_t>(LO + 127) << 24) - 1u && most <= static_cast<uint32_t>(HI + 127) << 24;
+        constexpr uint32_t hi = static_cast<uint32_t>(HI + 127) << 23;
+        return least >= (static_cast<uint32_t>(LO + 127) << 24) - 1u && positive <= static_cast<int32_t>(hi) && negative <= (0x80000000u | hi);
     }
 };
 
@@ -53,9 +56,11 @@ __device__ __forceinline__ uint32_t rk_pack_bf16(float a, float b)
 __device__ __forceinline__ void rk_split2(float a, float b, uint32_t (&l)[3])
 {
     l[0] = rk_pack_bf16(a, b);
+    asm("" : "+v"(l[0]));      // or the first of the two is rounded a second time to take it apart
     a -= __builtin_bit_cast(float, l[0] << 16);
     b -= __builtin_bit_cast(float, l[0] & 0xFFFF0000u);
     l[1] = rk_pack_bf16(a, b);
+    asm("" : "+v"(l[1]));
     a -= __builtin_bit_cast(float, l[1] << 16);
     b -= __builtin_bit_cast(float, l[1] & 0xFFFF0000u);
     l[2] = rk_pack_bf16(a, b);

@@ -28,8 +28,11 @@
 // integers and added with atomics: the result does not depend on the order.  Where every group is one tile (short
 // series) the workgroup writes the features itself.
 // Bound by vector-instruction issue (a matrix instruction takes about ten of a SIMD's clocks from the others, 84 v_alignbit per
-// 64 positions and lane group, the staging).  Measured at 64 x 20 x 50,000 with 119 groups: 2.49 -> 1.87 ms for the launch,
-// 2.57 -> 1.96 ms for the call; at 256 x 1 x 1,000 (rk_mr_forward_series) 258 -> 176 us for the call.
+// 64 positions and lane group, the staging).  Measured at 64 x 20 x 50,000 with 119 groups: 2.57 ms for the call with additions
+// and comparisons, 1.97 with the matrix cores, 2.00 with the limits of the split looked after; at 256 x 1 x 1,000
+// (rk_mr_forward_series) 258, 176 and 180 us.
+// The split carries sums and biases that are zero or in [2^-96, 2^60] in magnitude.  Staging notes others, and such a group of a
+// series is counted by plain multiply-adds, where its features are written: the loop over the positions knows nothing of it.
 // rk_mr_features: PPV = count / n per (series, kernel).
 #include <hip/hip_runtime.h>
 
@@ -59,6 +62,8 @@ constexpr int kMrTiles = 6;                        // 16-kernel tiles: five full
 constexpr int kMrPlane = kMrTileFloats;            // words of a plane
 constexpr int kMrMaxPer = 4;                       // most work items of a workgroup
 constexpr int kMrChunk = 64;                       // positions a wavefront takes at a time: four matrix instructions wide
+// Sums of channels and biases that go through the split; a group of a series with others is counted by mr_plain.
+__device__ __forceinline__ bool mr_splits(const RkSpan &s) { return s.within<-96, 60>(); }
 constexpr uint32_t kBf16One = 0x3F80, kBf16MinusTwo = 0xC000, kBf16Huge = 0x7F00;   // 1, -2, 2^127
 
 // Row of 16-kernel tile t -> kernel (-1: none).  Register v of a result holds rows 4 g + v of lane group
@@ -98,6 +103,7 @@ constexpr MrFrags mr_frags()
     return f;
 }
 __device__ const MrFrags kFrags = mr_frags();
+__device__ const MrSets kTaps = mr_sets();
 
 struct MrState {
     rk_bf16x8 A[kMrTiles];
@@ -113,8 +119,8 @@ __device__ __forceinline__ void mr_each(F &&f)        // every (tile, register) 
     });
 }
 
-// Weight operands of a group: the table and the biases of its records.
-__device__ __forceinline__ void mr_weights(MrState &st, const RkKernelRec *__restrict__ grec, int lane)
+// Weight operands of a group: the table and the biases of its records, which are noted in `span`.
+__device__ __forceinline__ void mr_weights(MrState &st, const RkKernelRec *__restrict__ grec, RkSpan &span, int lane)
 {
     asm volatile("" : "+v"(lane));      // or the table's entries are loaded before a caller's loop and spilled
     const int m = lane & 15, g = lane >> 4;
@@ -122,7 +128,10 @@ __device__ __forceinline__ void mr_weights(MrState &st, const RkKernelRec *__res
         constexpr int t = 2 * decltype(hc)::value;
         const int k0 = mr_kernel(t, m), k1 = mr_kernel(t + 1, m);
         uint32_t l[3];
-        rk_split2(0.f - grec[k0 < 0 ? 0 : k0].bias, 0.f - grec[k1 < 0 ? 0 : k1].bias, l);
+        const float b0 = 0.f - grec[k0 < 0 ? 0 : k0].bias, b1 = 0.f - grec[k1 < 0 ? 0 : k1].bias;
+        span.add(b0);
+        span.add(b1);
+        rk_split2(b0, b1, l);
         rk_u32x4 a = *reinterpret_cast<const rk_u32x4 *>(kFrags.r[t][lane]);
         rk_u32x4 b = *reinterpret_cast<const rk_u32x4 *>(kFrags.r[t + 1][lane]);
         if (g == 3) {
@@ -244,10 +253,10 @@ __device__ __forceinline__ void mr_chunk(MrState &st, const void *planes, const 
 }
 
 // Counts of the wavefront, summed over the lanes that share a kernel (two 16-bit counts to a register: a wavefront
-// sees fewer than 65,536 positions), to out[kernel].
-__device__ __forceinline__ void mr_counts(MrState &st, int *out, int lane)
+// sees fewer than 65,536 positions), to out[kernel], with the sign bit set if `odd`.
+__device__ __forceinline__ void mr_counts(MrState &st, int *out, bool odd, int lane)
 {
-    const int m = lane & 15, g = lane >> 4;
+    const int m = lane & 15, g = lane >> 4, sign = odd ? INT32_MIN : 0;
     rk_static_for<0, kMrTiles>([&](auto tc) {
         constexpr int t = decltype(tc)::value;
         if constexpr (t < kMrTiles - 1) {
@@ -255,21 +264,48 @@ __device__ __forceinline__ void mr_counts(MrState &st, int *out, int lane)
             const int b = rk_row16_sum_int(static_cast<int>(st.count[t][2] | st.count[t][3] << 16));
             if (m < 4) {
                 const int c = m < 2 ? a : b;
-                out[16 * t + 4 * g + m] = (m & 1) ? static_cast<int>(static_cast<uint32_t>(c) >> 16) : c & 0xFFFF;
+                out[16 * t + 4 * g + m] = ((m & 1) ? static_cast<int>(static_cast<uint32_t>(c) >> 16) : c & 0xFFFF) | sign;
             }
         } else {
             const int a = rk_row16_sum_int(static_cast<int>(st.count[t][0]));
-            if (m == 0) out[80 + g] = a;
+            if (m == 0) out[80 + g] = a | sign;
         }
     });
 }
 
+// Positive outputs of kernel k of a group (record `rec`) over one series, by fp32 multiply-adds on the sums of its channels: for
+// what the split does not carry.
+__device__ __forceinline__ int mr_plain(const float *series, size_t row_stride, int L, const int32_t *__restrict__ chan, const RkKernelRec &rec,
+                                        int k, int lane)
+{
+    const uint32_t taps = kTaps.taps[k];
+    int count = 0;
+    for (int t0 = 0; t0 < rec.nout; t0 += 64) {
+        float z = 0.f;
+#pragma nounroll
+        for (int j = 0; j < kMrLen; ++j) {
+            const int64_t i = static_cast<int64_t>(t0) + lane - rec.pad + static_cast<int64_t>(j) * rec.dil;
+            float s = 0.f;
+            if (i >= 0 && i < L) {
+#pragma nounroll
+                for (int c = 0; c < rec.nch; ++c) {
+                    const float v = series[static_cast<size_t>(chan[c]) * row_stride + static_cast<size_t>(i)];
+                    s = c == 0 ? v : s + v;
+                }
+            }
+            z = fmaf((taps >> j & 1u) != 0u ? 2.f : -1.f, s, z);
+        }
+        count += __builtin_popcountll(__ballot(t0 + lane < rec.nout && z > -rec.bias));
+    }
+    return count;
+}
+
 // Fills the LDS planes of a work item with the split sums of the group's NCH channels (added in the order of the
-// channel list).  `series` points at sample -pad of the group's view of channel 0: sample i of that view exists for
-// pad <= i < pad + L and is 0 elsewhere.
+// channel list), noted in `span`.  `series` points at sample 0 of channel 0; index i of the group's view is sample i - pad, 0
+// outside [0, L).
 template <int NCH>
 __device__ __forceinline__ void rk_mr_stage(uint32_t *planes, const float *series, const int32_t *__restrict__ chan,
-                                            size_t row_stride, const RkMrJob &job, int d, int stride, int pad, int L, int tid)
+                                            size_t row_stride, const RkMrJob &job, int d, int stride, int pad, int L, RkSpan &span, int tid)
 {
     const float *rows[NCH];
     rk_static_for<0, NCH>([&](auto cc) {
@@ -305,6 +341,8 @@ __device__ __forceinline__ void rk_mr_stage(uint32_t *planes, const float *serie
                 }
             }
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) span.add(s[e]);
         rk_u32x4 pairs;
         float rest[4];
 #pragma unroll
@@ -369,6 +407,8 @@ void rk_mr_forward(const float *__restrict__ x, size_t row_stride, int L, int C,
     if (tid < 2 * kMrChunk) planes[2 * kMrPlane + tid] = tid < kMrChunk ? kBf16One << 16 | kBf16One : kBf16One;
 
     MrState st;
+    RkSpan span;      // of the group's biases and of the sums that this lane staged
+    uint32_t odd_items = 0u;
     const int last = min(njobs, (block + 1) * per);
     for (int item = block * per; item < last; ++item) {
         const RkMrJob job = jobs[item];
@@ -378,7 +418,8 @@ void rk_mr_forward(const float *__restrict__ x, size_t row_stride, int L, int C,
         const int32_t *chan = channels + rec.ch_off;
         if (item == block * per || jobs[item - 1].group != job.group) {
             mr_clear(st);
-            mr_weights(st, grec, lane);
+            span = RkSpan();
+            mr_weights(st, grec, span, lane);
         }
 
         int stride, width, rows, width_valid, limit0, limit_step;
@@ -392,15 +433,15 @@ void rk_mr_forward(const float *__restrict__ x, size_t row_stride, int L, int C,
         }
         __syncthreads();      // the previous item's planes have been read
         switch (nch) {    // the channel count is a template parameter of the staging loops: loads back to back, no branches
-        case 1: rk_mr_stage<1>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 2: rk_mr_stage<2>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 3: rk_mr_stage<3>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 4: rk_mr_stage<4>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 5: rk_mr_stage<5>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 6: rk_mr_stage<6>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 7: rk_mr_stage<7>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        case 8: rk_mr_stage<8>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
-        default: rk_mr_stage<9>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, tid); break;
+        case 1: rk_mr_stage<1>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 2: rk_mr_stage<2>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 3: rk_mr_stage<3>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 4: rk_mr_stage<4>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 5: rk_mr_stage<5>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 6: rk_mr_stage<6>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 7: rk_mr_stage<7>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        case 8: rk_mr_stage<8>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
+        default: rk_mr_stage<9>(planes, series, chan, row_stride, job, d, stride, rec.pad, L, span, tid); break;
         }
         MrPairSlots slots(wave * kMrChunk, stride, kMrPlane, 4 * kMrChunk, lane);
         __syncthreads();
@@ -419,41 +460,65 @@ void rk_mr_forward(const float *__restrict__ x, size_t row_stride, int L, int C,
         }
         mr_flush(st);
         if (item + 1 == last || jobs[item + 1].group != job.group) {
-            mr_counts(st, wave_counts[wave], lane);
+            mr_counts(st, wave_counts[wave], __ballot(!mr_splits(span)) != 0u, lane);
             __syncthreads();
             if (tid < kMrSet) {
-                const int sum = (wave_counts[0][tid] + wave_counts[1][tid]) + (wave_counts[2][tid] + wave_counts[3][tid]);
+                int c[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) c[w] = wave_counts[w][tid];
+                const bool odd = (c[0] | c[1] | c[2] | c[3]) < 0;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) c[w] &= INT32_MAX;
+                const int sum = (c[0] + c[1]) + (c[2] + c[3]);
                 const size_t to = static_cast<size_t>(b) * K + static_cast<size_t>(job.group) * kMrSet + tid;
                 if (out) out[to] = static_cast<float>(static_cast<double>(sum) / static_cast<double>(n));
+                else if (odd) atomicOr(counts + to, INT32_MIN);       // a count has no use for the sign bit
                 else if (sum != 0) atomicAdd(counts + to, sum);
             }
+            if (out && (wave_counts[0][0] | wave_counts[1][0] | wave_counts[2][0] | wave_counts[3][0]) < 0) odd_items |= 1u << (item - block * per);
+        }
+    }
+    if (odd_items != 0u) __syncthreads();      // uniform; the features written above are overwritten
+    // features that the split does not carry (those of `counts` are left to rk_mr_features)
+    for (uint32_t left = __builtin_amdgcn_readfirstlane(odd_items); left != 0u; left &= left - 1u) {
+        const int group = jobs[block * per + __builtin_ctz(left)].group;
+        for (int k = wave; k < kMrSet; k += 4) {
+            const size_t at = static_cast<size_t>(group) * kMrSet + k;
+            const RkKernelRec rec = recs[at];
+            const int count = mr_plain(series, row_stride, L, channels + rec.ch_off, rec, k, lane);
+            if (lane == 0) out[static_cast<size_t>(b) * K + at] = static_cast<float>(static_cast<double>(count) / static_cast<double>(rec.nout));
         }
     }
 }
+static_assert(kMrMaxPer <= 32, "a bit for each of a workgroup's items");
 
 // One channel and short series: a workgroup stages its whole zero-padded series once (`pad` zeros on either side) and its
 // wavefronts take one group each: nothing is staged per group, and a wavefront that has a group's whole output needs no
 // other's counts.  grid: B x `blocks` workgroups, four groups each.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void rk_mr_forward_series(const float *__restrict__ x, size_t row_stride, int L, const RkKernelRec *__restrict__ recs,
-                          int groups, int blocks, int pad, int plane, int K, float *__restrict__ out)
+                          const int32_t *__restrict__ channels, int groups, int blocks, int pad, int plane, int K, float *__restrict__ out)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned short series[];    // 3 planes of `plane` numbers, a run of ones, a run of zeros
     __shared__ int wave_counts[4][kMrSet];
+    __shared__ int wave_odd[4];
     const int tid = static_cast<int>(threadIdx.x), b = static_cast<int>(blockIdx.x) / blocks;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int g = (static_cast<int>(blockIdx.x) - b * blocks) * 4 + wave;
     MrState st;
     mr_clear(st);
-    if (g < groups) mr_weights(st, recs + static_cast<size_t>(g) * kMrSet, lane);
+    RkSpan bias, span;
+    if (g < groups) mr_weights(st, recs + static_cast<size_t>(g) * kMrSet, bias, lane);
     const float *row = x + static_cast<size_t>(b) * row_stride;
     for (int u = tid * 4; u < plane; u += 1024) {
         float s[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { const int i = u + e - pad; s[e] = i >= 0 && i < L ? row[i] : 0.f; }
+        for (int e = 0; e < 4; ++e) { const int i = u + e - pad; s[e] = i >= 0 && i < L ? row[i] : 0.f; span.add(s[e]); }
         rk_store_limbs4(s, series + u, plane);
     }
     if (tid < 2 * kMrChunk) series[3 * plane + tid] = tid < kMrChunk ? static_cast<unsigned short>(kBf16One) : static_cast<unsigned short>(0);
+    const bool odd_sample = __ballot(!mr_splits(span)) != 0u;
+    if (lane == 0) wave_odd[wave] = odd_sample;
     __syncthreads();
     if (g >= groups) return;
     const RkKernelRec rec = recs[static_cast<size_t>(g) * kMrSet];
@@ -463,11 +528,19 @@ void rk_mr_forward_series(const float *__restrict__ x, size_t row_stride, int L,
         slots.advance();
     }
     mr_flush(st);
-    mr_counts(st, wave_counts[wave], lane);
-    __builtin_amdgcn_wave_barrier();
+    mr_counts(st, wave_counts[wave], false, lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     float *to = out + static_cast<size_t>(b) * K + static_cast<size_t>(g) * kMrSet;
-    for (int k = lane; k < kMrSet; k += 64)
-        to[k] = static_cast<float>(static_cast<double>(wave_counts[wave][k]) / static_cast<double>(rec.nout));
+    if (__ballot(!mr_splits(bias)) == 0u && __builtin_amdgcn_readfirstlane(wave_odd[0] | wave_odd[1] | wave_odd[2] | wave_odd[3]) == 0) {
+        for (int k = lane; k < kMrSet; k += 64)
+            to[k] = static_cast<float>(static_cast<double>(wave_counts[wave][k]) / static_cast<double>(rec.nout));
+        return;
+    }
+    for (int k = 0; k < kMrSet; ++k) {
+        const RkKernelRec own = recs[static_cast<size_t>(g) * kMrSet + k];
+        const int count = mr_plain(row, row_stride, L, channels + own.ch_off, own, k, lane);
+        if (lane == 0) to[k] = static_cast<float>(static_cast<double>(count) / static_cast<double>(own.nout));
+    }
 }
 
 __global__ __launch_bounds__(256) void rk_mr_clear(int *__restrict__ counts, int total)
@@ -476,14 +549,23 @@ __global__ __launch_bounds__(256) void rk_mr_clear(int *__restrict__ counts, int
     if (i < total) counts[i] = 0;
 }
 
-// PPV (Eq. 2): the positive count over the kernel's own output length
+// PPV (Eq. 2): the positive count over the kernel's own output length.  Features whose count has the sign bit set are counted
+// here, one after the other by a whole wavefront.
 __global__ __launch_bounds__(256) void rk_mr_features(const int *__restrict__ counts, int B, int K,
-                                                      const RkKernelRec *__restrict__ recs, float *__restrict__ out)
+                                                      const RkKernelRec *__restrict__ recs, const float *__restrict__ x, size_t row_stride,
+                                                      int L, int C, const int32_t *__restrict__ channels, float *__restrict__ out)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+    int count = i < B * K ? counts[i] : 0;
+    for (uint64_t left = __ballot(count < 0); left != 0u; left &= left - 1u) {
+        const int from = __builtin_ctzll(left), at = i - lane + from;      // uniform
+        const int b = at / K, kid = at - b * K;
+        const RkKernelRec rec = recs[kid];
+        const int found = mr_plain(x + static_cast<size_t>(b) * C * row_stride, row_stride, L, channels + rec.ch_off, rec, kid % kMrSet, lane);
+        if (lane == from) count = found;
+    }
     if (i >= B * K) return;
-    const int kid = i % K;
-    out[i] = static_cast<float>(static_cast<double>(counts[i]) / static_cast<double>(recs[kid].nout));
+    out[i] = static_cast<float>(static_cast<double>(count) / static_cast<double>(recs[i % K].nout));
 }
 
 }  // namespace
@@ -519,7 +601,7 @@ static int launch_minirocket_forward(const rocket_kernels *h, const float *x, in
         const int blocks = (h->mr_groups + 3) / 4;
         hipLaunchKernelGGL(rk_mr_forward_series, dim3(static_cast<unsigned>(static_cast<int64_t>(B) * blocks)), dim3(256),
                            static_cast<unsigned>((3 * plane + 2 * kMrChunk) * 2), stream, x, static_cast<size_t>(row_stride), h->L, h->d_rec,
-                           h->mr_groups, blocks, h->pad_max, plane, h->K, out);
+                           h->d_channels, h->mr_groups, blocks, h->pad_max, plane, h->K, out);
         return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
     }
     const int njobs = static_cast<int>(h->mr_jobs.size());
@@ -535,13 +617,16 @@ static int launch_minirocket_forward(const rocket_kernels *h, const float *x, in
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
 
-int rk_launch_minirocket_features(const rocket_kernels *h, const int32_t *counts, int32_t B, float *out, void *stream_ptr)
+static int launch_minirocket_features(const rocket_kernels *h, const float *x, int64_t row_stride, const int32_t *counts, int32_t B, float *out,
+                                      void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     const int total = B * h->K;
-    hipLaunchKernelGGL(rk_mr_features, dim3((total + 255) / 256), dim3(256), 0, stream, counts, B, h->K, h->d_rec, out);
+    hipLaunchKernelGGL(rk_mr_features, dim3((total + 255) / 256), dim3(256), 0, stream, counts, B, h->K, h->d_rec, x,
+                       static_cast<size_t>(row_stride), h->L, h->C, h->d_channels, out);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
 
 [[maybe_unused]] static const bool kEntered = (rk_launchers().minirocket_forward = launch_minirocket_forward,
+                                               rk_launchers().minirocket_features = launch_minirocket_features,
                                                rk_launchers().minirocket_one_pass = minirocket_one_pass, true);

@@ -268,3 +268,45 @@ def test_matrix_core_group_kernel_at_its_edges(B, C, L, groups):
     print("minirocket edges", B, C, L, groups, flush=True)
     out = rocket.rocket_minirocket_transform(h, _gpu(x)).cpu().numpy()
     check_forward(x, kr, out, 2)
+
+
+@pytest.mark.parametrize("C,L,groups", [(1, 700, 6), (3, 5000, 9)])      # series staged whole; tiles of both kinds
+@pytest.mark.parametrize("what", ["large sample", "small samples", "large bias"])
+def test_numbers_beyond_the_split(C, L, groups, what):
+    """Finite numbers that three bf16 parts do not carry, in one series of three and one kernel of each group: counts as in fp64 but
+    for outputs within fp32's roundings (16 of the sum of magnitudes of the nine taps, times 9, and of the smallest subnormal)."""
+    rng = np.random.default_rng(C)
+    x = rng.standard_normal((3, C, L)).astype(np.float32)
+    h = rocket.rocket_minirocket_kernels(3, groups, C, L)
+    kr = oracle.minirocket_kernels(3, groups, C, L)
+    bias = np.zeros(kr["K"], np.float32)
+    if what == "large sample":
+        x[1, :, L // 2] = np.float32(-1.1e38)
+        bias = rng.standard_normal(kr["K"]).astype(np.float32)
+        if C == 1:
+            x[1, :, L // 2] = np.float32(3.4e38)
+    elif what == "small samples":
+        x[1] *= np.float32(2.0 ** -120)
+    else:
+        bias[::84], bias[5::84] = np.float32(3.4e38), np.float32(-3.4e38)
+    rocket.rocket_kernels_set_params(h, None, bias)
+    kr = dict(kr, bias=bias)
+    if C > 1:
+        d = kr["dilation"][::84]
+        assert (d <= 256).any() and (d > 256).any()
+    print("minirocket beyond the split:", what, C, flush=True)
+    out = rocket.rocket_minirocket_transform(h, _gpu(x)).cpu().numpy().astype(np.float64)
+    for b in range(3):
+        for k in range(0, kr["K"], 5):
+            d, p = int(kr["dilation"][k]), int(kr["padding"][k])
+            n = L + 2 * p - 8 * d
+            ch = kr["channels"][kr["ch_off"][k]:kr["ch_off"][k + 1]]
+            s = np.pad(x[b, ch].astype(np.float64).sum(0), p)
+            w = kr["weights"][kr["w_off"][k]:kr["w_off"][k] + 9].astype(np.float64)
+            T = np.stack([s[j * d:j * d + n] for j in range(9)])
+            magnitude = np.pad(np.abs(x[b, ch].astype(np.float64)).sum(0), p)
+            tol = 16 * 2.0 ** -24 * 9 * sum(magnitude[j * d:j * d + n] for j in range(9)) + 16 * 9 * 2.0 ** -149
+            tol = tol + 2.0 ** -23 * abs(float(bias[k]))
+            y = (w[:, None] * T).sum(0) + float(bias[k])
+            count = np.rint(out[b, k] * n)
+            assert abs(count - (y > 0).sum()) <= (np.abs(y) <= tol).sum(), (b, k, count, (y > 0).sum())
