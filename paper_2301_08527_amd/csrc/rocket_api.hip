@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -671,8 +672,10 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     if (rc != ROCKET_OK) return rc;
     if (series) {
         const float *x = is_u8 ? xpad + h->lead : static_cast<const float *>(x_dev);
+        // The kernel gives positions that a kernel does not have an output of +infinity, which an infinite shift would make a NaN.
+        const float finite_ns = std::min(std::max(ns, -FLT_MAX), FLT_MAX);
         if (!(split && h->thick_sets == 0) &&
-            rk_launchers().forward_series(h, x, is_u8 ? h->row_len : h->L, B, mask, nl, ns, split, out_dev, stream) != ROCKET_OK)
+            rk_launchers().forward_series(h, x, is_u8 ? h->row_len : h->L, B, mask, nl, finite_ns, split, out_dev, stream) != ROCKET_OK)
             return rk_fail(ROCKET_EHIP, "launch of the series kernel failed");
         if (!split) return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
     }

@@ -114,3 +114,15 @@ def test_numbers_beyond_the_split(what):
             assert np.abs(out[b, k] - y.max()) <= tol.max(), (b, k, out[b, k], y.max())
             count = np.rint(out[b, K + k] * n)
             assert abs(count - (y > 0).sum()) <= (np.abs(y) <= tol).sum(), (b, k)
+
+
+@pytest.mark.parametrize("lam,shift,want", [(10.0, 3e38, 1.0), (10.0, -3e38, 0.0), (-2.0, 3e38, 1.0), (0.0, -3e38, 0.0)])
+def test_extreme_shift(lam, shift, want):
+    """every sigmoid saturates, those of positions that only some kernels of a set have included"""
+    import torch
+    rng = np.random.default_rng(8)
+    h = rocket.rocket_make_kernels(8, 200, 1, 150)
+    x = torch.from_numpy(rng.standard_normal((3, 1, 150)).astype(np.float32)).cuda()
+    print("extreme shift", lam, shift, flush=True)
+    out = rocket.rocket_transform(h, x, 4, lam, shift).cpu().numpy()
+    assert np.all(out == np.float32(want))
