@@ -124,7 +124,7 @@ static void plan_sets(rocket_kernels &h)
             rows[4 * (q % 4) + q / 4] = k;
         }
         spread_taps(s.dil, s.len, s.tap, s.read);
-        s.lo = -((-s.lo + 15) / 16 * 16);      // every lane then meets the same positions of a kernel in any set
+        s.lo = -((-s.lo + 31) / 32 * 32);      // every lane then meets the same positions of a kernel in any set
         const int64_t last = s.lo + round_up(s.hi - s.lo, 32) + static_cast<int64_t>(s.len - 1) * s.dil;
         reach = static_cast<int32_t>(std::max<int64_t>(reach, last));
         first = std::min(first, s.lo);

@@ -67,7 +67,7 @@ constexpr int kSeriesLdsBytes = 159744;  // LDS of a CU that its workgroups may 
 struct RkSet {
     int32_t dil;
     int32_t len;               // longest kernel
-    int32_t lo, hi;            // positions that any kernel has, lo rounded down to a multiple of 16
+    int32_t lo, hi;            // positions that any kernel has, lo rounded down to a multiple of 32
     int32_t in_lo, in_hi;      // positions that all kernels have
     int32_t regs;              // result registers in use: ceil(kernels / 4)
     int32_t reserved;

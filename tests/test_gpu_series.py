@@ -126,3 +126,23 @@ def test_extreme_shift(lam, shift, want):
     print("extreme shift", lam, shift, flush=True)
     out = rocket.rocket_transform(h, x, 4, lam, shift).cpu().numpy()
     assert np.all(out == np.float32(want))
+
+
+def test_soft_features_are_as_precise_as_the_job_kernels():
+    """The same kernels through the sets (one channel) and through the job kernels (a second channel that none of them reads):
+    the sums of sigmoids of the first must not have the larger error.  Over 102,400 features the rms errors scatter by some
+    0.3 %; 2 % are allowed.  (One chain of additions per lane had 8 % more.)"""
+    import torch
+    import oracle
+    rng = np.random.default_rng(6)
+    B, L, K = 64, 1500, 1600
+    h, kr = sampled(17, K, 1, L)
+    h2 = rocket.rocket_kernels_import(K, 2, L, kr["length"], kr["dilation"], kr["padding"], kr["bias"], kr["n_ch"], kr["channels"], kr["weights"])
+    x = rng.standard_normal((B, 1, L)).astype(np.float32)
+    print("precision of soft features", flush=True)
+    sets = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 4).cpu().numpy().astype(np.float64)
+    jobs = rocket.rocket_transform(h2, torch.from_numpy(np.concatenate([x, np.zeros_like(x)], axis=1)).cuda(), 4).cpu().numpy().astype(np.float64)
+    ref = oracle.transform(x, kr)["softppv"]
+    rms = [float(np.sqrt(np.mean((got - ref) ** 2))) for got in (sets, jobs)]
+    print("rms error: sets %.4e, job kernels %.4e" % tuple(rms), flush=True)
+    assert rms[0] <= 1.02 * rms[1], rms
