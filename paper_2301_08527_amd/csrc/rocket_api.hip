@@ -52,8 +52,9 @@ static inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * 
 
 // Which taps the four lane groups read together.  Instruction e of a set reads, 16 samples to a lane group, one tap in each
 // of the four groups; two taps whose samples lie k * 64 words apart, give or take 15, meet in LDS banks (the same
-// words do not).  Of four ways to spread the taps over the four instructions, the one where the fewest meet; a group without
-// a tap repeats another's addresses, which costs nothing.  (A search over all ways cost more on the host than it gave.)
+// words do not).  Of four ways to spread the taps over the four instructions, the one where the fewest of eleven meet: the
+// dilation alone decides where a tap's products enter the sum, not which kernels share the set.  A group without a tap of the set's
+// longest kernel (`len`) repeats another's addresses, which costs nothing.  (A search over all ways cost more on the host than it gave.)
 static void spread_taps(int32_t d, int32_t len, int8_t (&tap)[16], int8_t (&read)[16])
 {
     static const int8_t ways[4][4][4] = {
@@ -63,8 +64,8 @@ static void spread_taps(int32_t d, int32_t len, int8_t (&tap)[16], int8_t (&read
         {{0, 4, 8, -1}, {1, 5, 9, -1}, {2, 6, 10, -1}, {3, 7, -1, -1}},
     };
     bool meet[11] = {};
-    for (int32_t k = 0; k < len; ++k) {
-        const int64_t delta = static_cast<int64_t>(k) * d, r = delta % 64;
+    for (int32_t k = 0; k < 11; ++k) {
+        const int32_t delta = k * d, r = delta % 64;
         meet[k] = delta >= 49 && (r < 16 || r > 48);
     }
     int best = 0, least = INT32_MAX;
@@ -73,7 +74,7 @@ static void spread_taps(int32_t d, int32_t len, int8_t (&tap)[16], int8_t (&read
         for (int e = 0; e < 4; ++e)
             for (int i = 0; i < 4; ++i)
                 for (int j = i + 1; j < 4; ++j)
-                    if (const int a = ways[w][e][i], b = ways[w][e][j]; a >= 0 && b >= 0 && b < len && meet[b - a]) ++cost;
+                    if (const int a = ways[w][e][i], b = ways[w][e][j]; a >= 0 && b >= 0 && meet[b - a]) ++cost;
         if (cost < least) { least = cost; best = w; }
     }
     for (int e = 0; e < 4; ++e)
@@ -86,62 +87,51 @@ static void spread_taps(int32_t d, int32_t len, int8_t (&tap)[16], int8_t (&read
 
 // Sets of the series kernel (rocket_forward_series.hip): kernels of equal dilation, 16 to a set, equal padding and length
 // side by side so that most positions of a set exist for all of its kernels.
-static void plan_sets(rocket_kernels &h)
+static void plan_sets(rocket_kernels &h, RkPath path)
 {
-    h.sets.clear(); h.set_rows.clear(); h.thin.clear();
-    h.thick_sets = 0; h.thin_steps = 0;
-    if (h.C != 1) return;
-    // A plane holds the zeros before the series and the series.  (Checked first: an imported kernel may be padded to 2^31.)
-    int64_t words = h.L;
-    for (int32_t k = 0; k < h.K; ++k) words = std::max<int64_t>(words, static_cast<int64_t>(h.padding[k]) + h.L);
-    if (8 * words > kSeriesLdsBytes) return;
+    h.sets.clear(); h.set_rows.clear();
+    if (path == RkPath::jobs || h.C != 1 || h.L > kSeriesMost) return;
+    if (path == RkPath::by_size && h.L > kSeriesShort && h.K < h.L) return;
+    // An LDS plane holds the positions before the series, the series, and what the longest kernel that a set may have reads after its
+    // last step.  (In 64 bits: an imported kernel may be padded to 2^31.  Not looked up in the sets, whose make-up pruning
+    // changes: what holds for a handle holds for any pruned one.)
+    int64_t before = 0, after = 0;
+    for (int32_t k = 0; k < h.K; ++k) {
+        before = std::max<int64_t>(before, h.padding[k]);
+        after = std::max(after, h.L + static_cast<int64_t>(h.padding[k]) + static_cast<int64_t>(11 - h.length[k]) * h.dilation[k]);
+    }
+    if (8 * (before + after + 128) > kSeriesLdsBytes) return;
     std::vector<int64_t> keyed(h.K);      // dilation, padded or not, length, kernel
     for (int32_t k = 0; k < h.K; ++k)
         keyed[k] = (static_cast<int64_t>(h.dilation[k]) * 32 + (h.padding[k] > 0 ? 16 : 0) + h.length[k]) << 31 | k;
     std::sort(keyed.begin(), keyed.end());
     std::vector<int32_t> order(h.K);
     for (int32_t k = 0; k < h.K; ++k) order[k] = static_cast<int32_t>(keyed[k] & INT32_MAX);
-    std::vector<std::pair<int32_t, int32_t>> spans;      // [begin, end) in `order`; thick sets first
-    for (int32_t i = 0, end; i < h.K; i = end) {
-        end = i;
-        while (end < h.K && end < i + 16 && h.dilation[order[end]] == h.dilation[order[i]]) ++end;
-        spans.push_back({i, end});
-    }
-    std::stable_partition(spans.begin(), spans.end(), [](const std::pair<int32_t, int32_t> &s) { return s.second - s.first >= 4; });
     int32_t first = 0, reach = 0;        // smallest position, one past the last sample read
-    for (const auto &span : spans) {
+    for (int32_t i = 0, end; i < h.K; i = end) {
         RkSet s{};
-        s.dil = h.dilation[order[span.first]];
+        s.dil = h.dilation[order[i]];
         s.lo = INT32_MAX; s.hi = INT32_MIN; s.in_lo = INT32_MIN; s.in_hi = INT32_MAX;
-        s.regs = (span.second - span.first + 3) / 4;
         h.set_rows.resize(h.set_rows.size() + 16, -1);
         int32_t *rows = h.set_rows.data() + h.set_rows.size() - 16;
-        for (int32_t q = 0; q < span.second - span.first; ++q) {
-            const int32_t k = order[span.first + q], lo = -h.padding[k], hi = h.L + h.padding[k] - (h.length[k] - 1) * s.dil;
+        for (end = i; end < h.K && end < i + 16 && h.dilation[order[end]] == s.dil; ++end) {
+            const int32_t k = order[end], q = end - i, lo = -h.padding[k], hi = h.L + h.padding[k] - (h.length[k] - 1) * s.dil;
             s.len = std::max(s.len, h.length[k]);
             s.lo = std::min(s.lo, lo); s.hi = std::max(s.hi, hi);
             s.in_lo = std::max(s.in_lo, lo); s.in_hi = std::min(s.in_hi, hi);
             rows[4 * (q % 4) + q / 4] = k;
         }
+        s.regs = (end - i + 3) / 4;
         spread_taps(s.dil, s.len, s.tap, s.read);
         s.lo = -((-s.lo + 31) / 32 * 32);      // every lane then meets the same positions of a kernel in any set
-        const int64_t last = s.lo + round_up(s.hi - s.lo, 32) + static_cast<int64_t>(s.len - 1) * s.dil;
-        reach = static_cast<int32_t>(std::max<int64_t>(reach, last));
+        reach = std::max(reach, s.lo + static_cast<int32_t>(round_up(s.hi - s.lo, 32)) + (s.len - 1) * s.dil);
         first = std::min(first, s.lo);
         h.sets.push_back(s);
-        if (span.second - span.first >= 4) { ++h.thick_sets; continue; }
-        h.thin.insert(h.thin.end(), order.begin() + span.first, order.begin() + span.second);
-        h.thin_steps += (s.hi - s.lo + 15) / 16;
     }
     h.set_origin = static_cast<int32_t>(round_up(-first, 4));
     h.set_plane = static_cast<int32_t>(round_up(reach + h.set_origin, 4));
-    if (8LL * h.set_plane > kSeriesLdsBytes) {
-        h.sets.clear(); h.set_rows.clear(); h.thin.clear();
-        h.thick_sets = 0; h.thin_steps = 0;
-    }
 }
-
-int rk_finish_handle(rocket_kernels &h)
+int rk_finish_handle(rocket_kernels &h, RkPath path)
 {
     const int32_t K = h.K;
     // byte offsets inside a padded row (up to 42 dilation steps of at most L/6 floats)
@@ -168,9 +158,7 @@ int rk_finish_handle(rocket_kernels &h)
     }
     if (h.w_off[K] > INT32_MAX || h.ch_off[K] > INT32_MAX)
         return rk_fail(ROCKET_EINVAL, "too many weights for 32-bit offsets");
-    plan_sets(h);
-    std::vector<char> is_thin(K, 0);
-    for (int32_t k : h.thin) is_thin[k] = 1;
+    plan_sets(h, path);
     // Jobs of the forward and the backward pass.  A kernel's rows are cut into tiles of at least kTilePositions output
     // positions (whole LDS chunks or whole 32-row bands); jobs are ordered by the time
     // window they start in, so the workgroups that run together read one stretch of the
@@ -230,8 +218,6 @@ int rk_finish_handle(rocket_kernels &h)
         std::vector<int32_t> perm(J);
         for (size_t i = 0; i < J; ++i) perm[i] = static_cast<int32_t>(i);
         std::stable_sort(perm.begin(), perm.end(), [&](int32_t a, int32_t b) {
-            const char ta = is_thin[h.jobs[a].kernel], tb = is_thin[h.jobs[b].kernel];
-            if (ta != tb) return ta > tb;
             if (keys[a].window != keys[b].window) return keys[a].window < keys[b].window;
             return keys[a].cost > keys[b].cost;
         });
@@ -239,8 +225,6 @@ int rk_finish_handle(rocket_kernels &h)
         std::vector<int32_t> where(J);
         for (size_t i = 0; i < J; ++i) { sorted[i] = h.jobs[perm[i]]; where[perm[i]] = static_cast<int32_t>(i); }
         h.jobs.swap(sorted);
-        h.thin_jobs = 0;
-        while (h.thin_jobs < static_cast<int32_t>(J) && is_thin[h.jobs[h.thin_jobs].kernel]) ++h.thin_jobs;
         h.kjob_idx.swap(where);         // jobs were made kernel after kernel
         // backward pass: words of partial results per job (its kernel's gradient sums, the sum of
         // q, the largest output and its position, one spare)
@@ -295,10 +279,9 @@ extern "C" int rocket_make_kernels(uint64_t seed, int32_t K, int32_t C, int32_t 
     return ROCKET_OK;
 }
 
-extern "C" int rocket_kernels_import(int32_t K, int32_t C, int32_t L,
-                                     const int32_t *length, const int32_t *dilation, const int32_t *padding,
-                                     const float *bias, const int32_t *n_ch, const int32_t *channels,
-                                     const float *weights, rocket_kernels **out)
+static int import_kernels(int32_t K, int32_t C, int32_t L, const int32_t *length, const int32_t *dilation,
+                          const int32_t *padding, const float *bias, const int32_t *n_ch, const int32_t *channels,
+                          const float *weights, RkPath path, rocket_kernels **out)
 {
     if (!out) return rk_fail(ROCKET_EINVAL, "rocket_kernels_import: out is NULL");
     *out = nullptr;
@@ -339,7 +322,7 @@ extern "C" int rocket_kernels_import(int32_t K, int32_t C, int32_t L,
         h->bias.assign(bias, bias + K);
         h->channels.assign(channels, channels + nc);
         h->weights.assign(weights, weights + nw);
-        int rc = rk_finish_handle(*h);
+        int rc = rk_finish_handle(*h, path);
         if (rc != ROCKET_OK) { delete h; return rc; }
     } catch (const std::bad_alloc &) {
         delete h;
@@ -347,6 +330,14 @@ extern "C" int rocket_kernels_import(int32_t K, int32_t C, int32_t L,
     }
     *out = h;
     return ROCKET_OK;
+}
+
+extern "C" int rocket_kernels_import(int32_t K, int32_t C, int32_t L,
+                                     const int32_t *length, const int32_t *dilation, const int32_t *padding,
+                                     const float *bias, const int32_t *n_ch, const int32_t *channels,
+                                     const float *weights, rocket_kernels **out)
+{
+    return import_kernels(K, C, L, length, dilation, padding, bias, n_ch, channels, weights, RkPath::by_size, out);
 }
 
 // After rocket_sgd_update the device mirror holds the newest parameters: fetch them.
@@ -541,11 +532,10 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
     const size_t kidx_b = round_up(static_cast<int64_t>(h->kjob_idx.size()) * 4, 256);
     const size_t set_b = round_up(static_cast<int64_t>(h->sets.size()) * sizeof(RkSet), 256);
     const size_t row_b = round_up(static_cast<int64_t>(h->set_rows.size()) * 4, 256);
-    const size_t thin_b = round_up(static_cast<int64_t>(h->thin.size()) * 4, 256);
     if (h->d_blob && h->device != cur)
         return rk_fail(ROCKET_EINVAL, "handle was first used on another device");
     if (!h->d_blob) {
-        h->blob_bytes = rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b + thin_b;
+        h->blob_bytes = rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b;
         RK_HIP(hipMalloc(&h->d_blob, h->blob_bytes));
         h->device = cur;
         char *base = static_cast<char *>(h->d_blob);
@@ -558,7 +548,6 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b);
         h->d_sets = reinterpret_cast<const RkSet *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b);
         h->d_set_rows = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b);
-        h->d_thin = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b);
         h->params_dirty = true;
     }
     if (h->params_dirty) {
@@ -582,7 +571,6 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         if (!h->sets.empty()) {
             RK_HIP(hipMemcpyAsync(const_cast<RkSet *>(h->d_sets), h->sets.data(), h->sets.size() * sizeof(RkSet), hipMemcpyHostToDevice, stream));
             RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_set_rows), h->set_rows.data(), h->set_rows.size() * 4, hipMemcpyHostToDevice, stream));
-            if (!h->thin.empty()) RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_thin), h->thin.data(), h->thin.size() * 4, hipMemcpyHostToDevice, stream));
         }
         RK_HIP(hipStreamSynchronize(stream));
         h->params_dirty = false;
@@ -594,7 +582,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront forward kernel
 constexpr int kOneWaveSeries = 1024;     // some 64 strips of 16 or more rows: one for each lane of a wavefront
 constexpr int64_t kManyJobs = 8192;      // eight wavefronts to each of 1,024 SIMDs
-constexpr int64_t kThinSteps = 500000;    // 50 clk x 500,000 tiles over 1,024 SIMDs: some 10 us
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
 // ------------------------------------------------------------------ launches
@@ -653,18 +640,10 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     float *xpad = static_cast<float *>(ws);
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
     // Short univariate series: sets of kernels of one dilation, straight from the samples (raw bytes are normalised into
-    // the padded copy).  Its edges rest on lambda > 0.
-    // A set walks over all of a series on one wavefront, whether it holds sixteen kernels or one.  The job kernels are faster
-    // where a series is long and the chip not full of sets, and where most sets hold one or two kernels (series
-    // against job kernels, max and PPV: 4 x 8,000, 2,000 kernels 153 and 56 us; 64 x 4,000, 500 kernels 87 and 79;
-    // 16 x 2,000, 500 kernels 25 and 23; 64 x 1,000, 200 kernels with softPPV 26 and 22; but 64 x 2,000, 2,000 kernels 112 and 150;
-    // 64 x 1,000, 500 kernels 31 and 37; 4 x 1,000, 200 kernels, launches only, 11 and 17).
-    const int64_t pairs = static_cast<int64_t>(B) * h->K;
-    const bool thin_or_long = h->L <= kOneWaveSeries ? 3LL * h->K < h->L && pairs > 4096 : h->K < h->L || pairs < 100000;
-    const bool series = !h->sets.empty() && !thin_or_long && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
-    // The thin sets take some 50 clk of a SIMD more per 16-position tile than the job kernels; those need three launches.
-    const bool split = series && h->thin_jobs > 0 && h->thin_steps * B > kThinSteps;
-    if (is_u8 || split || !series) {
+    // the padded copy); the sets' edges rest on lambda > 0.  Which path a call takes follows from the handle and from lambda, never
+    // from the batch.
+    const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
+    if (is_u8 || !series) {
         rc = pad_batch(h, x_dev, is_u8, B, ws, 0, stream);
         if (rc != ROCKET_OK) return rc;
     }
@@ -674,12 +653,10 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
         const float *x = is_u8 ? xpad + h->lead : static_cast<const float *>(x_dev);
         // The kernel gives positions that a kernel does not have an output of +infinity, which an infinite shift would make a NaN.
         const float finite_ns = std::min(std::max(ns, -FLT_MAX), FLT_MAX);
-        if (!(split && h->thick_sets == 0) &&
-            rk_launchers().forward_series(h, x, is_u8 ? h->row_len : h->L, B, mask, nl, finite_ns, split, out_dev, stream) != ROCKET_OK)
+        if (rk_launchers().forward_series(h, x, is_u8 ? h->row_len : h->L, B, mask, nl, finite_ns, out_dev, stream) != ROCKET_OK)
             return rk_fail(ROCKET_EHIP, "launch of the series kernel failed");
-        if (!split) return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
+        return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
     }
-    h->thin_only = split;
     // series of at most kShortSeries samples: one wavefront per (series, kernel) instead of four
     float *partials = reinterpret_cast<float *>(static_cast<char *>(ws) + padded_batch_bytes(h, B));
     const int launched = h->L <= kShortSeries ? rk_launch_forward_short(h, xpad, B, mask, nl, ns, partials, stream)
@@ -1172,8 +1149,8 @@ extern "C" int rocket_kernels_subset(const rocket_kernels *h, const int32_t *ind
             channels.insert(channels.end(), h->channels.begin() + h->ch_off[k], h->channels.begin() + h->ch_off[k + 1]);
             weights.insert(weights.end(), h->weights.begin() + h->w_off[k], h->weights.begin() + h->w_off[k + 1]);
         }
-        return rocket_kernels_import(count, h->C, h->L, length.data(), dilation.data(), padding.data(), bias.data(),
-                                     n_ch.data(), channels.data(), weights.data(), out);
+        return import_kernels(count, h->C, h->L, length.data(), dilation.data(), padding.data(), bias.data(), n_ch.data(),
+                              channels.data(), weights.data(), h->sets.empty() ? RkPath::jobs : RkPath::sets, out);
     } catch (const std::bad_alloc &) {
         return rk_fail(ROCKET_ENOMEM, "rocket_kernels_subset: out of host memory");
     }

@@ -59,7 +59,7 @@ int rk_launch_forward(const rocket_kernels *h, const float *xpad, int32_t B, uin
                       float *partials, void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    const int J = h->thin_only ? h->thin_jobs : static_cast<int>(h->jobs.size());
+    const int J = static_cast<int>(h->jobs.size());
     const int spread = rk_spread(h, B);
     hipLaunchKernelGGL(rk_forward<kThreads>, dim3(static_cast<unsigned>(rk_grid_groups(B, J, spread))), dim3(kThreads), 0, stream, xpad,
                        static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs, h->d_channels,
@@ -67,17 +67,17 @@ int rk_launch_forward(const rocket_kernels *h, const float *xpad, int32_t B, uin
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
 
-// One thread per (series, kernel; of the list `which`, if given, N of the K kernels): combines the kernel's job partials in job order and
+// One thread per (series, kernel): combines the kernel's job partials in job order and
 // writes the feature planes out[b*F*K + f*K + k] (max + bias, count / n, sum / n).
-__global__ __launch_bounds__(256) void rk_finalize(const float *__restrict__ partials, int B, int K, int N, const int32_t *__restrict__ which, int J,
+__global__ __launch_bounds__(256) void rk_finalize(const float *__restrict__ partials, int B, int K, int J,
                                                    const RkKernelRec *__restrict__ recs,
                                                    const int32_t *__restrict__ kjob_off,
                                                    const int32_t *__restrict__ kjob_idx, uint32_t mask,
                                                    float *__restrict__ out)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= B * N) return;
-    const int b = i / N, kid = which ? which[i - b * N] : i - b * N;
+    if (i >= B * K) return;
+    const int b = i / K, kid = i - b * K;
     const size_t plane = static_cast<size_t>(B) * J;
     const size_t base = static_cast<size_t>(b) * J;
     float m = -INFINITY, sm = 0.f;
@@ -101,8 +101,8 @@ int rk_launch_finalize(const rocket_kernels *h, const float *partials, int32_t B
                        void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    const int N = h->thin_only ? static_cast<int>(h->thin.size()) : h->K, total = B * N;
-    hipLaunchKernelGGL(rk_finalize, dim3((total + 255) / 256), dim3(256), 0, stream, partials, B, h->K, N,
-                       h->thin_only ? h->d_thin : nullptr, h->thin_only ? h->thin_jobs : static_cast<int>(h->jobs.size()), h->d_rec, h->d_kjob_off, h->d_kjob_idx, mask, out);
+    const int total = B * h->K;
+    hipLaunchKernelGGL(rk_finalize, dim3((total + 255) / 256), dim3(256), 0, stream, partials, B, h->K,
+                       static_cast<int>(h->jobs.size()), h->d_rec, h->d_kjob_off, h->d_kjob_idx, mask, out);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }

@@ -79,7 +79,6 @@ __device__ __forceinline__ int ser_byte(const int8_t (&table)[16], int g, int e)
 __device__ __forceinline__ uint32_t ser_weights(SerState &st, const RkSet &set, const int32_t *__restrict__ rows, const RkKernelRec *__restrict__ recs,
                                             const float *__restrict__ weights, int lane)
 {
-    asm volatile("" : "+v"(lane));      // as in ser_plain
     const int m = lane & 15, g = lane >> 4;
     const int k = rows[m];
     int len = 0;
@@ -107,6 +106,7 @@ __device__ __forceinline__ uint32_t ser_weights(SerState &st, const RkSet &set, 
         if (kk >= 0) { st.C[v] = 0.f - recs[kk].bias; st.lo[v] = -recs[kk].pad; st.n[v] = recs[kk].nout; }
     }
     const uint64_t lanes = __ballot(!ser_weights_split(span));
+    if (lanes == 0u) return 0u;
     return static_cast<uint32_t>(lanes | lanes >> 16 | lanes >> 32 | lanes >> 48) & 0xFFFFu;
 }
 
@@ -233,11 +233,10 @@ __device__ __forceinline__ void ser_run(SerState &st, const RkSet &set, const ui
     ser_steps<MASK, NV, true>(st, at, step, planes, u0, end, sl, ns, lane);
 }
 
-// Features of the rows in registers v < NV, those in `skip` excepted.
+// Features of the rows in registers v < NV of one series.
 template <int MASK, int NV>
-__device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restrict__ rows, uint32_t skip, int K, float *__restrict__ out, int lane)
+__device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restrict__ rows, int K, float *__restrict__ out, int lane)
 {
-    asm volatile("" : "+v"(lane));      // as in ser_plain
     const int m = lane & 15, g = lane >> 4;
     float low = 0.f, soft = 0.f;
     uint32_t count = 0u;
@@ -252,7 +251,7 @@ __device__ __forceinline__ void ser_write(SerState &st, const int32_t *__restric
         }
         n = m == v ? st.n[v] : n;
     });
-    const int k = m < NV && (skip >> (4 * g + m) & 1u) == 0u ? rows[4 * g + m] : -1;
+    const int k = m < NV ? rows[4 * g + m] : -1;
     if (k < 0) return;
     float *o = out + k;
     if constexpr ((MASK & ROCKET_F_MAX) != 0) { *o = 0.f - low; o += K; }
@@ -303,16 +302,15 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
                        int K, float *__restrict__ out)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t planes[];    // per series two planes of `plane` words
-    __shared__ uint32_t wave_odd[16];
+    __shared__ uint32_t wave_fits[16];
     const int waves = static_cast<int>(blockDim.x) / 64;
     const int tid = static_cast<int>(threadIdx.x);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int sb = static_cast<int>(blockIdx.x) / blocks, block = static_cast<int>(blockIdx.x) - sb * blocks;
     const int b0 = sb * some, nb = min(some, B - b0);
-    uint32_t odd = 0u;       // bit s: series b0 + s has a sample that the split does not carry
+    RkSpan span;
     for (int s = 0; s < nb; ++s) {
         const float *row = x + static_cast<size_t>(b0 + s) * row_stride;
-        RkSpan span;
         for (int u = tid * 4; u < plane; u += waves * 256) {
             float v[4];
             const int i = u - origin;
@@ -335,12 +333,19 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
             *reinterpret_cast<rk_u32x4 *>(planes + static_cast<size_t>(s) * 2 * plane + u) = p;
             *reinterpret_cast<rk_u32x4 *>(planes + static_cast<size_t>(s) * 2 * plane + plane + u) = q;
         }
-        if (__ballot(!ser_samples_split(span)) != 0u) odd |= 1u << s;
     }
-    if (lane == 0) wave_odd[wave] = odd;
+    const bool fits = __ballot(!ser_samples_split(span)) == 0u;
+    if (lane == 0) wave_fits[wave] = fits;
     __syncthreads();
-    for (int w = 0; w < waves; ++w) odd |= wave_odd[w];
-    odd = __builtin_amdgcn_readfirstlane(odd);
+    uint32_t odd = 0u;       // bit s: series b0 + s has a sample that the split does not carry
+    if (__ballot(wave_fits[lane % waves] == 0u) != 0u) {      // uniform
+        for (int s = 0; s < nb; ++s) {
+            const float *row = x + static_cast<size_t>(b0 + s) * row_stride;
+            RkSpan one;
+            for (int i = lane; i < L; i += 64) one.add(row[i]);
+            if (__ballot(!ser_samples_split(one)) != 0u) odd |= 1u << s;
+        }
+    }
     asm volatile("" : "+v"(sl), "+v"(ns));
     const int last = min(nsets, (block + 1) * per);
     for (int i = block * per + wave; i < last; i += waves) {
@@ -351,15 +356,15 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
         for (int s = 0; s < nb; ++s) {
             const int first = s * 2 * plane;
             float *o = out + static_cast<size_t>(b0 + s) * __builtin_popcount(MASK) * K;
-            const uint32_t skip = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows;
             switch (set.regs) {
-            case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, skip, K, o, lane); break;
-            case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, skip, K, o, lane); break;
-            case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, skip, K, o, lane); break;
-            default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, skip, K, o, lane); break;
+            case 1: ser_run<MASK, 1>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 1>(st, rows, K, o, lane); break;
+            case 2: ser_run<MASK, 2>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 2>(st, rows, K, o, lane); break;
+            case 3: ser_run<MASK, 3>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 3>(st, rows, K, o, lane); break;
+            default: ser_run<MASK, 4>(st, set, planes, first, plane, origin, sl, ns, lane); ser_write<MASK, 4>(st, rows, K, o, lane); break;
             }
         }
         if ((odd | odd_rows) == 0u) continue;
+        __builtin_amdgcn_s_waitcnt(0);      // the features written above are overwritten, by other lanes
         for (int s = 0; s < nb; ++s) {
             float *o = out + static_cast<size_t>(b0 + s) * __builtin_popcount(MASK) * K;
             for (uint32_t plain = (odd >> s & 1u) != 0u ? 0xFFFFu : odd_rows; plain != 0u; plain &= plain - 1u) {
@@ -371,10 +376,10 @@ void rk_forward_series(const float *__restrict__ x, size_t row_stride, int L, co
 }
 
 static int launch_forward_series(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, uint32_t mask, float nl,
-                                 float ns, bool thick_only, float *out, void *stream_ptr)
+                                 float ns, float *out, void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    const int nsets = thick_only ? h->thick_sets : static_cast<int>(h->sets.size());
+    const int nsets = static_cast<int>(h->sets.size());
     // A CU holds 16 of these wavefronts: four workgroups of four while a series takes a quarter of its LDS, then two of
     // eight, then one of sixteen.
     const int bytes = 8 * h->set_plane;

@@ -64,6 +64,13 @@ struct RkJob {
 
 // Up to 16 kernels of one dilation for rk_forward_series (64 bytes).  Positions are u = t - padding.
 constexpr int kSeriesLdsBytes = 159744;  // LDS of a CU that its workgroups may fill
+// Whether a handle's kernels go through the sets is decided when it is made, from its length and its number of kernels, and a
+// pruned handle keeps what its parent has: a series' features are the same bits in any batch, a kernel's in any pruned handle.
+// Up to kSeriesShort samples always, up to kSeriesMost where there are as many kernels as samples.  Sets against job kernels, max and PPV, 64
+// series, in us: 1,000 samples and 200, 500, 1,000, 10,000 kernels 20/20, 29/34, 38/58, 156/496; 1,400: 27/23, 44/41, 56/72,
+// 222/624; 2,000: 38/27, 65/47, 89/81, 322/691; 4,000: 91/44, 155/78, 227/134, 780/1,170; 8,000 with 2,000: 924/459.  (Few kernels leave
+// most sets part-filled, and the more so the more dilations there are.)
+constexpr int kSeriesShort = 1024, kSeriesMost = 5000;
 struct RkSet {
     int32_t dil;
     int32_t len;               // longest kernel
@@ -96,18 +103,11 @@ struct rocket_kernels {
     double outputs = 0.0;    // sum_k n_k
     int32_t max_terms = 0;   // largest n_ch * length of any kernel
 
-    // one channel and short series: sets of kernels of one dilation (empty: rk_forward_series does not apply), the kernels
-    // in their 16 rows (-1: none), words of an LDS plane and the index of sample 0 in it
+    // one channel and short series: sets of kernels of one dilation (empty where the kernels go through the job kernels), the
+    // kernels in their 16 rows (-1: none), words of an LDS plane and the index of sample 0 in it
     std::vector<RkSet> sets;
     std::vector<int32_t> set_rows;
     int32_t set_plane = 0, set_origin = 0;
-    // Sets of fewer than four kernels come last, after thick_sets others: their kernels (`thin`) are cheaper one by one
-    // in the job kernels where there is much of them.  Their jobs are the first thin_jobs of the list, and thin_steps is
-    // the number of 16-position tiles of those sets.
-    int32_t thick_sets = 0, thin_jobs = 0;
-    int64_t thin_steps = 0;
-    std::vector<int32_t> thin;
-    bool thin_only = false;    // the forward launchers take the thin kernels only (set for the call)
 
     // device mirror (allocated on first use on `device`)
     int device = -1;
@@ -123,7 +123,6 @@ struct rocket_kernels {
     const int32_t *d_bjob_off = nullptr;
     const RkSet *d_sets = nullptr;
     const int32_t *d_set_rows = nullptr;
-    const int32_t *d_thin = nullptr;
     const int32_t *d_channels = nullptr;
     float *d_weights = nullptr;
 
@@ -162,10 +161,9 @@ int rk_launch_minirocket_clear(const rocket_kernels *h, int32_t B, int32_t *coun
 // Launchers that the kernels' translation units enter here when the library is loaded, so that the host code links
 // without them.
 struct RkLaunchers {
-    // rocket_forward_series.hip: the transform of a handle's sets (thick_only: without the thin ones; nl < 0 where the
-    // mask has softPPV).  x as below.
+    // rocket_forward_series.hip: the transform of a handle's sets (nl < 0 where the mask has softPPV).  x as below.
     int (*forward_series)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, uint32_t mask, float nl, float ns,
-                          bool thick_only, float *out, void *stream) = nullptr;
+                          float *out, void *stream) = nullptr;
     // rocket_minirocket_forward.hip.  x: rows of L samples that start row_stride floats apart.  Adds every work item's
     // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,
@@ -179,8 +177,9 @@ struct RkLaunchers {
                           int plane_max, float lambda, float nl, float ns, float *partial, void *stream) = nullptr;
 };
 RkLaunchers &rk_launchers();      // rocket_api.hip
-// rocket_api.hip: offsets, job plan, padded row geometry; returns ROCKET_OK or an error
-int rk_finish_handle(rocket_kernels &h);
+// rocket_api.hip: offsets, sets, job plan, padded row geometry; returns ROCKET_OK or an error
+enum class RkPath { by_size, sets, jobs };      // of one-channel kernels: by the rule at kSeriesShort, or as another handle has them
+int rk_finish_handle(rocket_kernels &h, RkPath path = RkPath::by_size);
 
 // Whether a launch over B series uses the per-XCD series mapping (rk_block_to_pair in
 // rocket_device.hpp): when the series divide evenly among the XCDs (with 60 series four XCDs

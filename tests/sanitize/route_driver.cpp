@@ -47,7 +47,7 @@ int rk_launch_minirocket_features(const rocket_kernels *, const int32_t *, int32
 extern "C" int rocket_ridge_predict(const float *, int32_t, int32_t, const double *, const double *, double *, void *)
     RECORD("ridge_predict")
 
-static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, bool, float *, void *) RECORD("series")
+static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, float *, void *) RECORD("series")
 static int backward_short_stub(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
                                float *, void *) RECORD("backward_short")
 [[maybe_unused]] static const bool kEntered = (rk_launchers().forward_series = series_stub,
@@ -84,13 +84,45 @@ static int wide_kernels()
     rocket_kernels *h = padded_kernels(100, {1, 7, 300000000, 400000000});
     CHECK(h != nullptr);
     CHECK(transform_route(h, 2, 7) == "pad short finalize ");      // too wide for the LDS planes of the series kernel
+    const int32_t narrow = 1;
+    rocket_kernels *part = nullptr;
+    CHECK(rocket_kernels_subset(h, &narrow, 1, &part) == ROCKET_OK);
+    CHECK(transform_route(part, 2, 7) == "pad short finalize ");
+    rocket_free_kernels(part);
     rocket_free_kernels(h);
+    return 0;
+}
+
+// The path of a transform follows from the handle (and from lambda's sign), never from the batch, and a pruned handle has its
+// parent's.
+static int one_path_for_all_batches()
+{
+    const std::string sets = "series ", jobs = "pad short finalize ";
+    const struct { int32_t C, L, K; std::string route; } want[] = {
+        {1, 11, 1, sets}, {1, 1000, 4000, sets}, {1, 1024, 1, sets}, {1, 1025, 1024, jobs}, {1, 1025, 1025, sets},
+        {1, 5000, 5000, sets}, {1, 5001, 6000, jobs}, {1, 9000, 9500, "pad forward finalize "}, {2, 1000, 4000, jobs}};
+    for (const auto &w : want) {
+        rocket_kernels *h = nullptr, *part = nullptr;
+        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        const int32_t keep = w.K / 2;
+        CHECK(rocket_kernels_subset(h, &keep, 1, &part) == ROCKET_OK);
+        for (const int32_t B : {1, 16, 256, 4096}) {
+            CHECK(transform_route(h, B, 7) == w.route);
+            CHECK(transform_route(part, B, 3) == w.route);
+        }
+        if (w.route == sets) {
+            CHECK(transform_route(h, 16, 7, 0.f) == jobs);      // the sets' edges rest on lambda > 0
+            CHECK(transform_route(h, 16, 3, 0.f) == sets);      // which max and PPV know nothing of
+        }
+        rocket_free_kernels(h);
+        rocket_free_kernels(part);
+    }
     return 0;
 }
 
 int main()
 {
-    if (wide_kernels()) return 1;
+    if (wide_kernels() || one_path_for_all_batches()) return 1;
     std::puts("route driver: ok");
     return 0;
 }

@@ -146,3 +146,34 @@ def test_soft_features_are_as_precise_as_the_job_kernels():
     rms = [float(np.sqrt(np.mean((got - ref) ** 2))) for got in (sets, jobs)]
     print("rms error: sets %.4e, job kernels %.4e" % tuple(rms), flush=True)
     assert rms[0] <= 1.02 * rms[1], rms
+
+
+@pytest.mark.parametrize("L", [97, 500, 1000, 1025, 2000, 3199, 3201])       # 3,200 kernels: up to 3,200 samples in sets
+def test_features_depend_on_neither_the_batch_nor_the_other_kernels(L):
+    """a series alone, in a small and in a large batch, and through handles that keep many or few of the kernels: the same bits"""
+    import torch
+    rng = np.random.default_rng(L)
+    K, B = 3200, 64
+    h = rocket.rocket_make_kernels(8, K, 1, L)
+    x = torch.from_numpy(rng.standard_normal((B, 1, L)).astype(np.float32)).cuda()
+    print("independent of batch and handle", L, flush=True)
+    full = rocket.rocket_transform(h, x, 7).view(B, 3, K)
+    for n in (1, 5):
+        assert torch.equal(rocket.rocket_transform(h, x[:n].contiguous(), 7).view(n, 3, K), full[:n]), n
+    for count in (1600, 150, 1):
+        keep = np.sort(rng.choice(K, size=count, replace=False)).astype(np.int32)
+        part = rocket.rocket_transform(rocket.rocket_kernels_subset(h, keep), x, 7).view(B, 3, count)
+        assert torch.equal(full[:, :, torch.from_numpy(keep.astype(np.int64)).cuda()], part), count
+
+
+def test_kernels_wider_than_their_series():
+    """imported dilations up to and beyond the length, beside ordinary ones: with as much padding as one LDS plane holds, and more"""
+    import torch
+    rng = np.random.default_rng(12)
+    for L, widest in ((40, 1000003), (40, 1410), (40, 2100), (1000, 1330), (1000, 2000)):
+        d = [1, 2, 5, L // 6, L // 2, L - 1, L, L + 1, widest, widest // 2] * 3
+        h, kr = _imported(rng, L, [7, 9, 11] * 10, d)
+        x = rng.standard_normal((3, 1, L)).astype(np.float32)
+        print("wide kernels", L, flush=True)
+        out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 7).cpu().numpy()
+        check_forward(x, kr, out, 7)
