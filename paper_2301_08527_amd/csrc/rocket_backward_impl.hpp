@@ -73,6 +73,20 @@ __device__ __forceinline__ void rk_bwd_deposit(float (&g)[LEN], int c, float *sl
     }
 }
 
+// The sum of q of a pass of one wavefront that has all strips of a job to itself goes to LDS slots as well, after those of the
+// weights.  Kept in the lanes it would be a chain four times as long as with 256 lanes (rms error of the bias gradients at
+// 20 x 3 x 8,192 samples 9.0e-8; 256 lanes, and so, 7.4e-8), and a second register for it costs a fifth wavefront.
+template <int NT>
+__device__ __forceinline__ void rk_bwd_put_away(BwdState &st, float *slots)
+{
+    if constexpr (NT == 64) {
+        const float sum = rk_row16_sum(st.qsum);
+        const int tid = static_cast<int>(threadIdx.x);
+        if ((tid & 15) == 0) slots[kBwdMaxTerms * rk_bwd_slots(NT) + (tid >> 4)] += sum;
+        st.qsum = 0.f;
+    }
+}
+
 template <int NT, int LEN, int R>
 __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int nbands, int ncols, float coef,
                                                bool want_max, float *slots, BwdState &st)
@@ -174,6 +188,7 @@ __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int
             });
             rk_bwd_deposit<NT, LEN>(g, c, slots);
         }
+        rk_bwd_put_away<NT>(st, slots);
     }
 }
 
@@ -265,6 +280,7 @@ __device__ __forceinline__ void rk_bwd_band(const KernelCtx &k, int row0, int nc
             });
             rk_bwd_deposit<NT, LEN>(g, c, slots);
         }
+        rk_bwd_put_away<NT>(st, slots);
     }
 }
 
@@ -367,6 +383,7 @@ __device__ __forceinline__ void rk_bwd_few_rows(const KernelCtx &k, int row0, in
             });
             rk_bwd_deposit<NT, LEN>(g, c, slots);
         }
+        rk_bwd_put_away<NT>(st, slots);
     }
 }
 
@@ -443,6 +460,7 @@ __device__ __forceinline__ int rk_bwd_lds_bands(const KernelCtx &k, int first_ro
             });
             rk_bwd_deposit<NT, LEN>(g, c, slots);
         }
+        rk_bwd_put_away<NT>(st, slots);
     }
     return first_row + nb * R;
 }
@@ -515,7 +533,7 @@ __global__ __launch_bounds__(NT) void rk_backward(const float *__restrict__ xpad
                                                         float *__restrict__ partial, int stride, int B, int spread)
 {
     __shared__ __attribute__((aligned(16))) float tile[rk_tile_words(NT)];   // 16-byte pieces are written straight into it
-    __shared__ float slots[kBwdMaxTerms * rk_bwd_slots(NT)];
+    __shared__ float slots[(kBwdMaxTerms + 1) * rk_bwd_slots(NT)];
     __shared__ float s_q[NT / 64];
     __shared__ float s_max[NT / 64];
     __shared__ int s_arg[NT / 64];
@@ -530,6 +548,7 @@ __global__ __launch_bounds__(NT) void rk_backward(const float *__restrict__ xpad
 
     const int nterms = rec.nch * rec.len;
     for (int i = threadIdx.x; i < nterms * rk_bwd_slots(NT); i += NT) slots[i] = 0.f;
+    if (NT == 64 && threadIdx.x < rk_bwd_slots(NT)) slots[kBwdMaxTerms * rk_bwd_slots(NT) + threadIdx.x] = 0.f;
     __syncthreads();
 
     const float *g_row = grad_out + static_cast<size_t>(b) * F * K;
@@ -559,6 +578,10 @@ __global__ __launch_bounds__(NT) void rk_backward(const float *__restrict__ xpad
     if ((threadIdx.x & 63) == 0) { s_q[wave] = qsum; s_max[wave] = vmax; s_arg[wave] = targ; }
     __syncthreads();   // also orders the slot updates before the slot sums below
     float gq = s_q[0], gm = s_max[0];
+    if constexpr (NT == 64) {
+        const float *q = slots + kBwdMaxTerms * rk_bwd_slots(NT);
+        gq = (q[0] + q[1]) + (q[2] + q[3]);
+    }
     int ga = s_arg[0];
 #pragma unroll
     for (int w = 1; w < NT / 64; ++w) {
