@@ -174,7 +174,8 @@ int rocket_transform_noalloc(rocket_kernels *kernels, const float *x_dev, int32_
  * respect to x.  workspace: rocket_workspace_bytes(kernels, B, mask, 1) bytes.
  * Kernels with more than 9 channels (possible only through rocket_kernels_import)
  * are rejected with ROCKET_ESHAPE.  Every sum (over positions, over the batch) is taken
- * in a fixed order without atomics, so two runs on the same inputs agree bit for bit.
+ * in a fixed order without atomics, so two runs on the same inputs agree bit for bit (the
+ * order of the sum over positions may be another one for another B).
  */
 int rocket_soft_ppv_backward(rocket_kernels *kernels, const float *x_dev, int32_t B, uint32_t feature_mask,
                              const float *grad_out_dev, float lambda, float shift, int include_max,

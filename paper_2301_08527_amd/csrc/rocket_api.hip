@@ -581,7 +581,6 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront forward kernel
 constexpr int kOneWaveSeries = 1024;     // some 64 strips of 16 or more rows: one for each lane of a wavefront
-constexpr int64_t kManyJobs = 8192;      // eight wavefronts to each of 1,024 SIMDs
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
 // ------------------------------------------------------------------ launches
@@ -773,11 +772,13 @@ static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, b
     rc = profile_mark(h, stream, true);
     if (rc != ROCKET_OK) return rc;
     // Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
-    // 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 428 us against 169 with 64 lanes).  Longer ones take longer on one
-    // wavefront, which only pays where others fill the chip: 4 x 4 x 8,000, 200 kernels, 800 jobs: 41 us against 81;
-    // 8 x 1 x 4,000, 2,400 jobs: 31 against 33; 16 x 4 x 6,000, 16,000 jobs: 251 against 246; 60 x 3 x 8,192, 120,000
-    // jobs: 1779 against 1421.
-    const bool narrow = h->L <= kShortSeries && (h->L <= kOneWaveSeries || static_cast<int64_t>(B) * h->jobs.size() >= kManyJobs);
+    // 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 460 us against 183 with 64 lanes; 64 x 20 x 2,000, 200 kernels 267 and 171;
+    // 4 x 20 x 1,400, 200 kernels 50 and 61).  Longer ones take longer on one wavefront, the more so with many channels, which pays where
+    // enough others run beside it: 256 against 64 lanes at 12,800 jobs 64 x 20 x 3,000 275 and 251 us, 64 x 20 x 8,192 437 and
+    // 575, 64 x 6 x 6,000 291 and 270, 64 x 1 x 8,192 177 and 162; at 64,000 64 x 20 x 8,192 1,628 and 1,505; at 3,200
+    // 16 x 1 x 4,000 43 and 43, 16 x 6 x 4,000 77 and 88, 16 x 20 x 3,000 95 and 137.
+    const int64_t work = static_cast<int64_t>(B) * h->jobs.size();
+    const bool narrow = h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
     if ((narrow ? rk_launchers().backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
     rc = profile_mark(h, stream, false);

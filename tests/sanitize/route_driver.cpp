@@ -120,9 +120,32 @@ static int one_path_for_all_batches()
     return 0;
 }
 
+// One wavefront to a job of the backward pass where that is the faster way: short series, and longer ones with many jobs for
+// their length and channels.
+static int backward_paths()
+{
+    const struct { int32_t B, C, L, K; const char *route; } want[] = {
+        {1, 1, 11, 1, "pad backward_short reduce "}, {4, 20, 1024, 200, "pad backward_short reduce "},
+        {4, 20, 1400, 200, "pad backward reduce "}, {64, 20, 1400, 200, "pad backward_short reduce "}, {64, 20, 8192, 200, "pad backward reduce "},
+        {64, 20, 8192, 1000, "pad backward_short reduce "}, {64, 20, 8193, 1000, "pad backward reduce "},
+        {64, 1, 8192, 200, "pad backward_short reduce "}, {4, 1, 8192, 1000, "pad backward reduce "},
+        {16, 6, 4000, 200, "pad backward reduce "}, {64, 6, 4000, 200, "pad backward_short reduce "}};
+    for (const auto &w : want) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        g_route.clear();
+        alignas(256) static char there[256];
+        float *at = reinterpret_cast<float *>(there);
+        CHECK(rocket_soft_ppv_backward(h, at, w.B, 4, at, 10.f, -3.f, 0, at, at, there, static_cast<size_t>(1) << 50, nullptr) == ROCKET_OK);
+        CHECK(g_route == w.route);
+        rocket_free_kernels(h);
+    }
+    return 0;
+}
+
 int main()
 {
-    if (wide_kernels() || one_path_for_all_batches()) return 1;
+    if (wide_kernels() || one_path_for_all_batches() || backward_paths()) return 1;
     std::puts("route driver: ok");
     return 0;
 }
