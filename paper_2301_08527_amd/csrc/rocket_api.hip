@@ -15,6 +15,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -518,63 +519,56 @@ extern "C" size_t rocket_workspace_bytes(const rocket_kernels *h, int32_t B, uin
 
 // ------------------------------------------------------------------ device mirror
 
+// The mirror is one allocation, filled by one copy (a pageable copy costs some 10 us, whatever its size).
 static int ensure_device(rocket_kernels *h, hipStream_t stream)
 {
     int cur = 0;
     RK_HIP(hipGetDevice(&cur));
-    const int32_t K = h->K;
-    const size_t rec_b = round_up(static_cast<int64_t>(K) * sizeof(RkKernelRec), 256);
-    const size_t boff_b = round_up(static_cast<int64_t>(h->bjob_off.size()) * 4, 256);
-    const size_t ch_b = round_up(static_cast<int64_t>(h->channels.size()) * 4, 256);
-    const size_t w_b = round_up(static_cast<int64_t>(h->weights.size()) * 4, 256);
-    const size_t job_b = round_up(static_cast<int64_t>(h->jobs.size()) * sizeof(RkJob), 256);
-    const size_t koff_b = round_up(static_cast<int64_t>(K + 1) * 4, 256);
-    const size_t kidx_b = round_up(static_cast<int64_t>(h->kjob_idx.size()) * 4, 256);
-    const size_t set_b = round_up(static_cast<int64_t>(h->sets.size()) * sizeof(RkSet), 256);
-    const size_t row_b = round_up(static_cast<int64_t>(h->set_rows.size()) * 4, 256);
     if (h->d_blob && h->device != cur)
         return rk_fail(ROCKET_EINVAL, "handle was first used on another device");
+    if (h->d_blob && !h->params_dirty) return ROCKET_OK;
+    const size_t K = static_cast<size_t>(h->K);
+    size_t total = 0;
+    auto place = [&](size_t bytes) {
+        const size_t at = total;
+        total += static_cast<size_t>(round_up(static_cast<int64_t>(bytes), 256));
+        return at;
+    };
+    const size_t rec = place(K * sizeof(RkKernelRec)), boff = place(h->bjob_off.size() * 4), channels = place(h->channels.size() * 4),
+                 weights = place(h->weights.size() * 4), jobs = place(h->jobs.size() * sizeof(RkJob)), koff = place((K + 1) * 4),
+                 kidx = place(h->kjob_idx.size() * 4), sets = place(h->sets.size() * sizeof(RkSet)), rows = place(h->set_rows.size() * 4);
+    const std::unique_ptr<char[]> host(new (std::nothrow) char[total]);
+    if (!host) return rk_fail(ROCKET_ENOMEM, "out of host memory for the upload of the parameters");
+    RkKernelRec *r = reinterpret_cast<RkKernelRec *>(host.get() + rec);
+    for (int32_t k = 0; k < h->K; ++k, ++r) {
+        r->len = h->length[k]; r->dil = h->dilation[k]; r->pad = h->padding[k];
+        r->nout = static_cast<int32_t>(h->L + 2LL * h->padding[k] - static_cast<int64_t>(h->length[k] - 1) * h->dilation[k]);
+        r->bias = h->bias[k]; r->nch = h->n_ch[k];
+        r->ch_off = static_cast<int32_t>(h->ch_off[k]);
+        r->w_off = static_cast<int32_t>(h->w_off[k]);
+    }
+    auto put = [&](size_t at, const auto &v) { std::copy_n(reinterpret_cast<const char *>(v.data()), v.size() * sizeof(v[0]), host.get() + at); };
+    put(boff, h->bjob_off); put(channels, h->channels); put(weights, h->weights); put(jobs, h->jobs);
+    put(koff, h->kjob_off); put(kidx, h->kjob_idx); put(sets, h->sets); put(rows, h->set_rows);
     if (!h->d_blob) {
-        h->blob_bytes = rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b + row_b;
-        RK_HIP(hipMalloc(&h->d_blob, h->blob_bytes));
+        h->blob_bytes = total;
+        RK_HIP(hipMalloc(&h->d_blob, total));
         h->device = cur;
         char *base = static_cast<char *>(h->d_blob);
-        h->d_rec = reinterpret_cast<const RkKernelRec *>(base);
-        h->d_bjob_off = reinterpret_cast<const int32_t *>(base + rec_b);
-        h->d_channels = reinterpret_cast<const int32_t *>(base + rec_b + boff_b);
-        h->d_weights = reinterpret_cast<float *>(base + rec_b + boff_b + ch_b);
-        h->d_jobs = reinterpret_cast<const RkJob *>(base + rec_b + boff_b + ch_b + w_b);
-        h->d_kjob_off = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b);
-        h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b);
-        h->d_sets = reinterpret_cast<const RkSet *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b);
-        h->d_set_rows = reinterpret_cast<const int32_t *>(base + rec_b + boff_b + ch_b + w_b + job_b + koff_b + kidx_b + set_b);
+        h->d_rec = reinterpret_cast<const RkKernelRec *>(base + rec);
+        h->d_bjob_off = reinterpret_cast<const int32_t *>(base + boff);
+        h->d_channels = reinterpret_cast<const int32_t *>(base + channels);
+        h->d_weights = reinterpret_cast<float *>(base + weights);
+        h->d_jobs = reinterpret_cast<const RkJob *>(base + jobs);
+        h->d_kjob_off = reinterpret_cast<const int32_t *>(base + koff);
+        h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + kidx);
+        h->d_sets = reinterpret_cast<const RkSet *>(base + sets);
+        h->d_set_rows = reinterpret_cast<const int32_t *>(base + rows);
         h->params_dirty = true;
     }
-    if (h->params_dirty) {
-        std::vector<RkKernelRec> rec(K);
-        for (int32_t k = 0; k < K; ++k) {
-            RkKernelRec &r = rec[k];
-            r.len = h->length[k]; r.dil = h->dilation[k]; r.pad = h->padding[k];
-            r.nout = static_cast<int32_t>(h->L + 2LL * h->padding[k] - static_cast<int64_t>(h->length[k] - 1) * h->dilation[k]);
-            r.bias = h->bias[k]; r.nch = h->n_ch[k];
-            r.ch_off = static_cast<int32_t>(h->ch_off[k]);
-            r.w_off = static_cast<int32_t>(h->w_off[k]);
-        }
-        // pageable sources: these copies return once the source has been read
-        RK_HIP(hipMemcpyAsync(const_cast<RkKernelRec *>(h->d_rec), rec.data(), K * sizeof(RkKernelRec), hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_bjob_off), h->bjob_off.data(), h->bjob_off.size() * 4, hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_channels), h->channels.data(), h->channels.size() * 4, hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(h->d_weights, h->weights.data(), h->weights.size() * 4, hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(const_cast<RkJob *>(h->d_jobs), h->jobs.data(), h->jobs.size() * sizeof(RkJob), hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_kjob_off), h->kjob_off.data(), (K + 1) * 4, hipMemcpyHostToDevice, stream));
-        RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_kjob_idx), h->kjob_idx.data(), h->kjob_idx.size() * 4, hipMemcpyHostToDevice, stream));
-        if (!h->sets.empty()) {
-            RK_HIP(hipMemcpyAsync(const_cast<RkSet *>(h->d_sets), h->sets.data(), h->sets.size() * sizeof(RkSet), hipMemcpyHostToDevice, stream));
-            RK_HIP(hipMemcpyAsync(const_cast<int32_t *>(h->d_set_rows), h->set_rows.data(), h->set_rows.size() * 4, hipMemcpyHostToDevice, stream));
-        }
-        RK_HIP(hipStreamSynchronize(stream));
-        h->params_dirty = false;
-    }
+    RK_HIP(hipMemcpyAsync(h->d_blob, host.get(), total, hipMemcpyHostToDevice, stream));
+    RK_HIP(hipStreamSynchronize(stream));
+    h->params_dirty = false;
     return ROCKET_OK;
 }
 

@@ -143,9 +143,40 @@ static int backward_paths()
     return 0;
 }
 
+// The parameters reach the device in one allocation and one copy, on first use and after they were replaced.
+static int uploads()
+{
+    for (const int32_t C : {1, 3}) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(5, 70, C, 300, &h) == ROCKET_OK);
+        g_copies = g_mallocs = 0;
+        transform_route(h, 2, 7);
+        CHECK(g_copies == 1 && g_mallocs == 1);
+        transform_route(h, 9, 7);
+        CHECK(g_copies == 1 && g_mallocs == 1);
+        CHECK(std::memcmp(h->d_weights, h->weights.data(), h->weights.size() * 4) == 0);
+        CHECK(std::memcmp(h->d_channels, h->channels.data(), h->channels.size() * 4) == 0);
+        CHECK(std::memcmp(h->d_jobs, h->jobs.data(), h->jobs.size() * sizeof(RkJob)) == 0);
+        CHECK(std::memcmp(h->d_bjob_off, h->bjob_off.data(), h->bjob_off.size() * 4) == 0);
+        CHECK(std::memcmp(h->d_kjob_off, h->kjob_off.data(), h->kjob_off.size() * 4) == 0);
+        CHECK(std::memcmp(h->d_kjob_idx, h->kjob_idx.data(), h->kjob_idx.size() * 4) == 0);
+        CHECK(h->sets.empty() == (C > 1));
+        CHECK(h->sets.empty() || std::memcmp(h->d_sets, h->sets.data(), h->sets.size() * sizeof(RkSet)) == 0);
+        CHECK(h->sets.empty() || std::memcmp(h->d_set_rows, h->set_rows.data(), h->set_rows.size() * 4) == 0);
+        for (int32_t k = 0; k < h->K; ++k) CHECK(h->d_rec[k].bias == h->bias[k] && h->d_rec[k].w_off == h->w_off[k] && h->d_rec[k].dil == h->dilation[k]);
+        std::vector<float> bias(h->bias);
+        bias[3] += 1.f;
+        CHECK(rocket_kernels_set_params(h, nullptr, bias.data()) == ROCKET_OK);
+        transform_route(h, 2, 7);
+        CHECK(g_copies == 2 && g_mallocs == 1 && h->d_rec[3].bias == bias[3]);
+        rocket_free_kernels(h);
+    }
+    return 0;
+}
+
 int main()
 {
-    if (wide_kernels() || one_path_for_all_batches() || backward_paths()) return 1;
+    if (wide_kernels() || one_path_for_all_batches() || backward_paths() || uploads()) return 1;
     std::puts("route driver: ok");
     return 0;
 }
