@@ -29,8 +29,8 @@
 // series) the workgroup writes the features itself.
 // Bound by vector-instruction issue (a matrix instruction takes about ten of a SIMD's clocks from the others, 84 v_alignbit per
 // 64 positions and lane group, the staging).  Measured at 64 x 20 x 50,000 with 119 groups: 2.57 ms for the call with additions
-// and comparisons, 1.97 with the matrix cores, 2.00 with the limits of the split looked after; at 256 x 1 x 1,000
-// (rk_mr_forward_series) 258, 176 and 180 us.
+// and comparisons, 1.97 with the matrix cores, 1.99 with the limits of the split looked after; at 256 x 1 x 1,000
+// (rk_mr_forward_series) 258, 175 and 176 us.
 // The split carries sums and biases that are zero or in [2^-96, 2^60] in magnitude.  Staging notes others, and such a group of a
 // series is counted by plain multiply-adds, where its features are written: the loop over the positions knows nothing of it.
 // rk_mr_features: PPV = count / n per (series, kernel).
@@ -124,23 +124,27 @@ __device__ __forceinline__ void mr_weights(MrState &st, const RkKernelRec *__res
 {
     asm volatile("" : "+v"(lane));      // or the table's entries are loaded before a caller's loop and spilled
     const int m = lane & 15, g = lane >> 4;
-    rk_static_for<0, kMrTiles / 2>([&](auto hc) {
-        constexpr int t = 2 * decltype(hc)::value;
-        const int k0 = mr_kernel(t, m), k1 = mr_kernel(t + 1, m);
-        uint32_t l[3];
-        const float b0 = 0.f - grec[k0 < 0 ? 0 : k0].bias, b1 = 0.f - grec[k1 < 0 ? 0 : k1].bias;
-        span.add(b0);
-        span.add(b1);
-        rk_split2(b0, b1, l);
-        rk_u32x4 a = *reinterpret_cast<const rk_u32x4 *>(kFrags.r[t][lane]);
-        rk_u32x4 b = *reinterpret_cast<const rk_u32x4 *>(kFrags.r[t + 1][lane]);
-        if (g == 3) {
-            if (k0 >= 0) { a[2] = (l[0] & 0xFFFFu) | l[1] << 16; a[3] |= l[2] & 0xFFFFu; }
-            if (k1 >= 0) { b[2] = l[0] >> 16 | (l[1] & 0xFFFF0000u); b[3] |= l[2] >> 16; }
-        }
-        st.A[t] = __builtin_bit_cast(rk_bf16x8, a);
-        st.A[t + 1] = __builtin_bit_cast(rk_bf16x8, b);
+    rk_u32x4 r[kMrTiles];
+    float bias[kMrTiles];
+    rk_static_for<0, kMrTiles>([&](auto tc) {       // all on their way at once: nothing else of a small call is waited for as long
+        constexpr int t = decltype(tc)::value;
+        const int k = mr_kernel(t, m);
+        bias[t] = grec[k < 0 ? 0 : k].bias;
+        r[t] = *reinterpret_cast<const rk_u32x4 *>(kFrags.r[t][lane]);
     });
+    if (g == 3) {
+        rk_static_for<0, kMrTiles / 2>([&](auto hc) {
+            constexpr int t = 2 * decltype(hc)::value;
+            const float b0 = 0.f - bias[t], b1 = 0.f - bias[t + 1];
+            uint32_t l[3];
+            rk_split2(b0, b1, l);
+            span.add(b0);
+            span.add(b1);
+            if (mr_kernel(t, m) >= 0) { r[t][2] = (l[0] & 0xFFFFu) | l[1] << 16; r[t][3] |= l[2] & 0xFFFFu; }
+            if (mr_kernel(t + 1, m) >= 0) { r[t + 1][2] = l[0] >> 16 | (l[1] & 0xFFFF0000u); r[t + 1][3] |= l[2] >> 16; }
+        });
+    }
+    rk_static_for<0, kMrTiles>([&](auto tc) { st.A[decltype(tc)::value] = __builtin_bit_cast(rk_bf16x8, r[decltype(tc)::value]); });
 }
 __device__ __forceinline__ void mr_clear(MrState &st)
 {
