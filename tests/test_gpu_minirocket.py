@@ -255,8 +255,8 @@ def test_group_kernel_from_bytes():
 
 @pytest.mark.parametrize("B,C,L,groups", [
     (3, 1, 9, 2), (2, 1, 63, 3), (1, 1, 129, 5),      # one channel, shorter and longer than a chunk of 64 positions
-    (2, 1, 3217, 5), (2, 1, 3249, 5),                 # either side of the largest series that is staged whole
-    (5, 2, 2431, 9), (9, 12, 4871, 4), (8, 3, 20011, 6),   # tiles of one group, several to a workgroup, ragged ends
+    (2, 1, 3217, 5), (2, 1, 3249, 5),                 # longer series of a small batch: tiles
+    (5, 2, 2431, 9), (9, 12, 4871, 4), (8, 3, 20011, 6),   # one and several tiles to a group, ragged ends
 ])
 def test_matrix_core_group_kernel_at_its_edges(B, C, L, groups):
     rng = np.random.default_rng(L)
@@ -310,3 +310,43 @@ def test_numbers_beyond_the_split(C, L, groups, what):
             y = (w[:, None] * T).sum(0) + float(bias[k])
             count = np.rint(out[b, k] * n)
             assert abs(count - (y > 0).sum()) <= (np.abs(y) <= tol).sum(), (b, k, count, (y > 0).sum())
+
+
+def _rows_match_oracle(B, C, L, groups, rows, step):
+    rng = np.random.default_rng(L)
+    x = rng.standard_normal((B, C, L)).astype(np.float32)
+    h = rocket.rocket_minirocket_kernels(L, groups, C, L)
+    bias = rng.standard_normal(h.K).astype(np.float32)
+    rocket.rocket_kernels_set_params(h, bias=bias)
+    kr = dict(oracle.minirocket_kernels(L, groups, C, L), bias=bias)
+    print("minirocket rows", B, C, L, groups, flush=True)
+    out = rocket.rocket_minirocket_transform(h, _gpu(x)).cpu().numpy()
+    check_forward(x, kr, out, 2, rows=rows, sel=np.arange(0, h.K, step, dtype=np.int32))
+    return h, kr
+
+
+@pytest.mark.parametrize("whole", [True, False])
+def test_series_around_the_largest_that_is_staged_whole(whole):
+    """one channel and 8,192 groups of series: up to 6,500 numbers to a plane (the series, its widest padding on both sides, 64 more,
+    rounded up) are staged whole, more go through the tiles; lengths on either side are looked up, not assumed"""
+    B, groups = 128, 64
+
+    def plane(L):
+        return (L + 2 * int(oracle.minirocket_kernels(L, groups, 1, L)["padding"].max()) + 64 + 63) // 64 * 64 + 32
+
+    planes = {L: plane(L) for L in range(3200, 3500, 4)}
+    L = {words: L for L, words in planes.items()}[6496 if whole else 6560]
+    _rows_match_oracle(B, 1, L, groups, [0, 127], 53)
+
+
+@pytest.mark.parametrize("B,per", [(300, 2), (400, 3), (700, 4)])
+def test_several_work_items_to_a_workgroup(B, per):
+    """batches of so many work items that a workgroup takes `per` of a series': neighbours of one group (weights and counts stay),
+    of two groups, and a last workgroup with fewer"""
+    C, L, groups = 2, 6000, 35
+    h, _ = _rows_match_oracle(B, C, L, groups, [0, B // 2, B - 1], 41)
+    items = rocket.rocket_minirocket_jobs_view_get(h)
+    group = np.asarray([it[0] for it in items])
+    assert min(4, B * len(group) // 8192) == per and len(group) % per != 0, (len(group), B * len(group) // 8192)
+    blocks = [group[i:i + per] for i in range(0, len(group), per)]
+    assert any(len(set(b)) < len(b) for b in blocks) and any(len(set(b)) > 1 for b in blocks)

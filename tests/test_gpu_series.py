@@ -33,12 +33,11 @@ def test_every_mask_on_small_series(B, L, K, mask):
 
 
 @pytest.mark.parametrize("B,L,K,mask", [
-    (3, 2400, 600, 7), (2, 4900, 300, 3),       # four, two and one workgroup to a CU
-    (2, 9700, 100, 7), (2, 10400, 100, 7),      # either side of the longest series that LDS holds
-    (11, 9700, 9700, 3), (10, 10400, 10400, 2),     # the same, with enough kernels for the sets to be taken
-    (40, 3000, 3000, 3), (25, 4900, 4900, 7),
-    (40, 1500, 3000, 3),                        # several sets to a wavefront
-    (64, 3000, 300, 7), (40, 8000, 200, 2),     # few kernels to a dilation: those go through the job kernels
+    (3, 2400, 600, 7), (2, 4900, 300, 3), (2, 9700, 100, 7), (2, 10400, 100, 7),     # longer series, few kernels: the job kernels
+    (11, 9700, 9700, 3), (10, 10400, 10400, 2),     # longer than the sets take
+    (40, 3000, 3000, 3), (25, 4900, 4900, 7),       # workgroups of eight and of sixteen wavefronts
+    (40, 1500, 3000, 3),
+    (64, 3000, 300, 7), (40, 8000, 200, 2),
 ])
 def test_long_and_thin(B, L, K, mask):
     _run(B, L, K, mask)
@@ -177,3 +176,40 @@ def test_kernels_wider_than_their_series():
         print("wide kernels", L, flush=True)
         out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), 7).cpu().numpy()
         check_forward(x, kr, out, 7)
+
+
+def _launch(kr, L, B):
+    """(wavefronts to a workgroup, series to a workgroup, sets to a wavefront) of the sets' launch, from the kernels alone"""
+    d, pad, ln = (np.asarray(kr[name], np.int64) for name in ("dilation", "padding", "length"))
+    order = np.lexsort((np.arange(len(d)), ln, pad > 0, d))
+    sets = [g[i:i + 16] for v in np.unique(d) for g in [order[d[order] == v]] for i in range(0, len(g), 16)]
+    first = reach = 0
+    for g in sets:
+        lo = -((int(pad[g].max()) + 31) // 32 * 32)
+        hi = int((L + pad[g] - (ln[g] - 1) * d[g]).max())
+        first, reach = min(first, lo), max(reach, lo + (hi - lo + 31) // 32 * 32 + (int(ln[g].max()) - 1) * int(d[g[0]]))
+    origin = (-first + 3) // 4 * 4
+    nbytes = 8 * ((reach + origin + 3) // 4 * 4)
+    waves = 4 if nbytes <= 39936 else 8 if nbytes <= 79872 else 16
+    some = min(max(1, 39936 * (waves // 4) // nbytes), 32, B, max(1, len(sets) * B // 16384))
+    tasks = -(-B // some) * len(sets)
+    return waves, some, 4 if tasks >= 131072 else 2 if tasks >= 65536 else 1
+
+
+@pytest.mark.parametrize("B,L,K,mask,want,last", [
+    (3, 2000, 2000, 7, (4, 1, 1), 1), (2, 3000, 3000, 7, (8, 1, 1), 1), (2, 4900, 4900, 7, (16, 1, 1), 1),
+    (302, 200, 3000, 5, (4, 3, 1), 2),            # several series to a workgroup, the last one with fewer
+    (1502, 64, 1000, 3, (4, 6, 1), 2),
+    (131, 1000, 10000, 3, (4, 2, 1), 1),
+    (201, 1000, 10000, 7, (4, 2, 2), 1),          # two and four sets to a wavefront
+    (401, 1000, 10000, 3, (4, 2, 4), 1),
+])
+def test_launch_shapes(B, L, K, mask, want, last):
+    import torch
+    h, kr = sampled(L + K, K, 1, L)
+    waves, some, per = _launch(kr, L, B)
+    assert (waves, some, per) == want and (B - 1) % some + 1 == last, (waves, some, per, (B - 1) % some + 1)
+    x = np.random.default_rng(L).standard_normal((B, 1, L)).astype(np.float32)
+    print("launch shape", B, L, K, mask, want, flush=True)
+    out = rocket.rocket_transform(h, torch.from_numpy(x).cuda(), mask).cpu().numpy()
+    check_forward(x, kr, out, mask, rows=sorted({0, B // 2, B - 2, B - 1}), sel=np.arange(0, K, max(1, K // 600), dtype=np.int32))
