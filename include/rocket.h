@@ -368,11 +368,12 @@ int rocket_train_step(rocket_kernels *kernels, const void *x_dev, int x_is_u8, i
  * them like those of any other kernels, and
  *
  * rocket_minirocket_transform computes the same features with a kernel made for the predetermined set: the
- * 84 kernels of a group share their channel-summed input and the nine tap values of every position, so that
- * one kernel's output costs one addition and one comparison ("convolution by additions", section 2).
- * x_dev: device, B x C x L float32; out_dev: device, B x K float32, out[b * K + k] = PPV of kernel k.  It
- * evaluates 3 y = U_a + U_b + U_c with U_j = 9 T_j - (T_0 + ... + T_8) in fp32, a different rounding order
- * from rocket_transform's multiply-adds: the two agree except at outputs within rounding of zero.
+ * 84 kernels of a group share their channel-summed input and the nine tap values of every position, which makes
+ * them a matrix product with two-valued weights.
+ * x_dev: device, B x C x L float32; out_dev: device, B x K float32, out[b * K + k] = PPV of kernel k.  It sums
+ * the channels first and then the taps, in fp32 on the matrix cores (samples split exactly into three bf16 parts),
+ * a different rounding order from rocket_transform's multiply-adds: the two agree except at outputs within rounding
+ * of zero.
  * workspace_dev: rocket_minirocket_workspace_bytes(kernels, B) bytes, 256-byte aligned.  Only for handles of
  * rocket_minirocket_kernels whose weights have not been changed since (biases may be: rocket_minirocket_fit_bias,
  * rocket_kernels_set_params with weights = NULL); ROCKET_EINVAL otherwise, and the workspace size is 0.
@@ -395,7 +396,7 @@ int rocket_minirocket_transform_u8(rocket_kernels *kernels, const uint8_t *x_u8_
  * mode 0: output positions [first, first + count) of the group; it stages count + 8 d channel-summed samples.
  * mode 1: rows [first, first + rows) x columns [col0, col0 + width) of the group's output viewed as rows of d
  * positions (position = row * d + column; columns beyond d and positions beyond the output are skipped); it
- * stages (rows + 8) * width samples.  No item stages more than 6,144 samples; width is a multiple of 64.
+ * stages (rows + 8) * width samples.  No item stages more than 4,864 samples; width is a multiple of 64.
  * ROCKET_EINVAL if the handle does not hold the predetermined set.
  */
 int rocket_minirocket_jobs_view_get(const rocket_kernels *kernels, int32_t *count, const int32_t **items);
@@ -404,7 +405,8 @@ int rocket_minirocket_jobs_view_get(const rocket_kernels *kernels, int32_t *coun
  * Pruning (section 6: many of the random kernels are of little use to a given problem and can
  * be dropped by the regressor's feature importance).  Creates a new handle that holds kernels
  * index[0..count) of `kernels` (host array; any order, repeats allowed) with their current
- * parameters.  The choice of which kernels to keep is the caller's.
+ * parameters.  The choice of which kernels to keep is the caller's.  rocket_transform gives the kept
+ * kernels' features bit for bit as the original handle does, in any batch.
  */
 int rocket_kernels_subset(const rocket_kernels *kernels, const int32_t *index, int32_t count, rocket_kernels **out);
 

@@ -15,7 +15,6 @@
 #ifndef RK_WPE
 #define RK_WPE 6
 #endif
-constexpr int kWaves = kThreads / 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
 
@@ -154,7 +153,6 @@ constexpr int kLdsStage = 4;                                      // staged word
 // words of the LDS tile of a workgroup of NT lanes: the largest chunk (NT strips of kLdsRows rows
 // plus the halo of the widest kernel at the largest LDS-path dilation), rounded up to whole staging rounds
 constexpr int rk_tile_words(int nt) { return ((kLdsRows * nt + 10 * (kLdsMaxD - 1)) / (nt * kLdsStage) + 1) * nt * kLdsStage; }
-constexpr int kLdsTileWords = rk_tile_words(kThreads);
 
 // Copies `nin` floats starting `chunk_bytes` into a row to the LDS tile (rounded up to whole rounds of
 // NT*kLdsStage words: the tile and the workspace slack are sized for that).  The data go from memory straight

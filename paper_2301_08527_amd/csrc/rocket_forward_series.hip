@@ -10,17 +10,18 @@
 // planes of such words, (x1, x2) and (x1, x3); against them stand (w1, w1) and (w2, w2), and (w3, w1): three
 // instructions, whatever the lengths, on operands that are LDS words as they stand.
 //
-// Sets of up to 16 kernels of one dilation are made on the host (rk_plan_sets).  A workgroup stages whole zero-padded
-// series in LDS once, as three planes of parts, and its wavefronts take one set after the other: no padded copy of the
-// batch, no partial results, one launch for the whole transform.  The kernel computes E = -y: its sign bit says
+// Sets of up to 16 kernels of one dilation are made on the host (plan_sets).  A workgroup stages whole zero-padded
+// series in LDS once, as those two planes, and its wavefronts take one set after the other: no partial results, and from floats
+// no padded copy of the batch and one launch for the whole transform (raw bytes are normalised into the padded copy
+// first).  Which series come here: the rule at kSeriesShort.  The kernel computes E = -y: its sign bit says
 // y > 0 (an exact zero comes out as +0), collected with one v_alignbit per output and counted every 32 outputs (a comparison
 // would cost two scalar instructions per output, and a SIMD issues one per four clocks).  Kernel i of a set sits in
 // row 4 (i % 4) + i / 4, so that a set of f kernels leaves results in ceil(f / 4) of the four result registers and the
 // others are not pooled.
 // Bound: vector-instruction issue of the pooling (soft PPV: 25 clk of a SIMD per 64 outputs, max 2, PPV 4, the three
 // matrix instructions about 7), LDS reads for max and PPV alone on series of thousands of samples.  Measured against the
-// job kernels that took these series before: 256 x 1,000 samples, 10,000 kernels, all features 2.15 -> 0.93 ms, max and PPV
-// 1.94 -> 0.58 ms; 64 x 500 samples 444 -> 86 us; 64 x 4,000 samples 1.17 -> 0.72 ms (max and PPV); 16 x 512
+// job kernels that took these series before: 256 x 1,000 samples, 10,000 kernels, all features 2.15 -> 0.95 ms, max and PPV
+// 1.94 -> 0.59 ms; 64 x 400 samples 439 -> 78 us; 64 x 4,000 samples 1.17 -> 0.78 ms (max and PPV); 16 x 512
 // samples, 500 kernels, launch-bound 16.5 -> 10 us.
 #include <hip/hip_runtime.h>
 

@@ -158,7 +158,8 @@ int rk_launch_minirocket_select(const rocket_kernels *h, const int32_t *rank_dev
 // rocket_minirocket_forward.hip: the PPV features of a MINIROCKET-style handle, group by group: clears the
 // B x K counters (the kernel that counts and the one that makes features of them are in the table below)
 int rk_launch_minirocket_clear(const rocket_kernels *h, int32_t B, int32_t *counts, void *stream);
-// Launchers that the kernels' translation units enter here when the library is loaded, so that the host code links
+// Launchers that the kernels' translation units enter here when the library is loaded: those of the kernels that are an
+// alternative to one called directly below (the matrix-core kernels, the one-wavefront backward pass).  The host code links
 // without them.
 struct RkLaunchers {
     // rocket_forward_series.hip: the transform of a handle's sets (nl < 0 where the mask has softPPV).  x as below.
@@ -186,7 +187,7 @@ int rk_finish_handle(rocket_kernels &h, RkPath path = RkPath::by_size);
 // would get 8 and four 7, and the launch takes as long as 64), and while the kXcds padded series
 // that are then in flight together fit in half of the 256 MB Infinity Cache.  (Measured at
 // 64 x 20 x 50,000: 1 % faster, 22 % less L2 fill traffic; slower at 8 x 20 x 200,000, whose eight
-// padded series are 192 MB, and for the short-series kernel, which does not use it.)
+// padded series are 192 MB, and for the short-series forward kernel, which does not use it.)
 inline int rk_spread(const rocket_kernels *h, int32_t B)
 {
     const int64_t series_bytes = static_cast<int64_t>(h->C) * h->row_len * 4;

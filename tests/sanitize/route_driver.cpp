@@ -43,7 +43,6 @@ int rk_launch_minirocket_outputs(const rocket_kernels *, const float *, const in
 int rk_launch_minirocket_select(const rocket_kernels *, const int32_t *, int32_t, int32_t, int64_t, const float *, void *)
     RECORD("mr_select")
 int rk_launch_minirocket_clear(const rocket_kernels *, int32_t, int32_t *, void *) RECORD("mr_clear")
-int rk_launch_minirocket_features(const rocket_kernels *, const int32_t *, int32_t, float *, void *) RECORD("mr_features")
 extern "C" int rocket_ridge_predict(const float *, int32_t, int32_t, const double *, const double *, double *, void *)
     RECORD("ridge_predict")
 

@@ -181,7 +181,7 @@ def test_minirocket_kernel_set_without_gpu():
 @pytest.mark.parametrize("groups,C,L", [(1, 1, 9), (4, 2, 10), (9, 3, 73), (20, 4, 4105), (40, 20, 50000), (12, 9, 200001)])
 def test_minirocket_plan_covers_every_position_once(groups, C, L):
     """host-only: the work items of the group kernel cover every output position of every group exactly once,
-    and none stages more than the 6,144 samples of its LDS tile"""
+    and none stages more than the 4,864 samples of its LDS planes"""
     h = rocket.rocket_minirocket_kernels(17, groups, C, L)
     v = rocket.rocket_kernels_view_get(h)
     items = rocket.rocket_minirocket_jobs_view_get(h)
@@ -197,10 +197,10 @@ def test_minirocket_plan_covers_every_position_once(groups, C, L):
             assert width % 64 == 0 and width >= 64
             kinds.add(mode)
             if mode == 0:
-                assert d <= 256 and 1 <= count <= width < count + 64 and count + 8 * d <= 6144 and rows == 1
+                assert d <= 256 and 1 <= count <= width < count + 64 and width + 8 * d <= 4864 and rows == 1
                 seen[first:first + count] += 1
             else:
-                assert d > 256 and width <= 256 and rows >= 1 and (rows + 8) * width <= 6144 and col0 < d
+                assert d > 256 and width <= 256 and rows >= 1 and (rows + 8) * width <= 4864 and col0 < d
                 cols = np.arange(col0, min(col0 + width, d))
                 t = (first + np.arange(rows))[:, None] * d + cols[None, :]
                 t = t[t < n]
