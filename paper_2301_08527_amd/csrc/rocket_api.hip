@@ -519,7 +519,10 @@ extern "C" size_t rocket_workspace_bytes(const rocket_kernels *h, int32_t B, uin
 
 // ------------------------------------------------------------------ device mirror
 
-// The mirror is one allocation, filled by one copy (a pageable copy costs some 10 us, whatever its size).
+// The mirror is one allocation.  Up to kOneCopy bytes it is put together on the host and filled by one copy (a pageable copy costs
+// some 10 us however small it is); larger arrays are copied from where they are, as touching that much new host memory costs more
+// (1 x 20 x 50,000, 10,000 kernels, 3 MB: first pass 0.90 ms array by array, 0.93 at once).
+constexpr size_t kOneCopy = 1 << 20;
 static int ensure_device(rocket_kernels *h, hipStream_t stream)
 {
     int cur = 0;
@@ -528,46 +531,56 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
         return rk_fail(ROCKET_EINVAL, "handle was first used on another device");
     if (h->d_blob && !h->params_dirty) return ROCKET_OK;
     const size_t K = static_cast<size_t>(h->K);
-    size_t total = 0;
-    auto place = [&](size_t bytes) {
-        const size_t at = total;
-        total += static_cast<size_t>(round_up(static_cast<int64_t>(bytes), 256));
-        return at;
-    };
-    const size_t rec = place(K * sizeof(RkKernelRec)), boff = place(h->bjob_off.size() * 4), channels = place(h->channels.size() * 4),
-                 weights = place(h->weights.size() * 4), jobs = place(h->jobs.size() * sizeof(RkJob)), koff = place((K + 1) * 4),
-                 kidx = place(h->kjob_idx.size() * 4), sets = place(h->sets.size() * sizeof(RkSet)), rows = place(h->set_rows.size() * 4);
-    const std::unique_ptr<char[]> host(new (std::nothrow) char[total]);
-    if (!host) return rk_fail(ROCKET_ENOMEM, "out of host memory for the upload of the parameters");
-    RkKernelRec *r = reinterpret_cast<RkKernelRec *>(host.get() + rec);
-    for (int32_t k = 0; k < h->K; ++k, ++r) {
-        r->len = h->length[k]; r->dil = h->dilation[k]; r->pad = h->padding[k];
-        r->nout = static_cast<int32_t>(h->L + 2LL * h->padding[k] - static_cast<int64_t>(h->length[k] - 1) * h->dilation[k]);
-        r->bias = h->bias[k]; r->nch = h->n_ch[k];
-        r->ch_off = static_cast<int32_t>(h->ch_off[k]);
-        r->w_off = static_cast<int32_t>(h->w_off[k]);
+    const std::unique_ptr<RkKernelRec[]> recs(new (std::nothrow) RkKernelRec[K]);
+    if (!recs) return rk_fail(ROCKET_ENOMEM, "out of host memory for the upload of the parameters");
+    for (int32_t k = 0; k < h->K; ++k) {
+        RkKernelRec &r = recs[k];
+        r.len = h->length[k]; r.dil = h->dilation[k]; r.pad = h->padding[k];
+        r.nout = static_cast<int32_t>(h->L + 2LL * h->padding[k] - static_cast<int64_t>(h->length[k] - 1) * h->dilation[k]);
+        r.bias = h->bias[k]; r.nch = h->n_ch[k];
+        r.ch_off = static_cast<int32_t>(h->ch_off[k]);
+        r.w_off = static_cast<int32_t>(h->w_off[k]);
     }
-    auto put = [&](size_t at, const auto &v) { std::copy_n(reinterpret_cast<const char *>(v.data()), v.size() * sizeof(v[0]), host.get() + at); };
-    put(boff, h->bjob_off); put(channels, h->channels); put(weights, h->weights); put(jobs, h->jobs);
-    put(koff, h->kjob_off); put(kidx, h->kjob_idx); put(sets, h->sets); put(rows, h->set_rows);
+    struct Part { const void *from; size_t bytes, at; };
+    enum { kRec, kBoff, kChannels, kWeights, kJobs, kKoff, kKidx, kSets, kRows, kParts };
+    Part part[kParts] = {
+        {recs.get(), K * sizeof(RkKernelRec), 0}, {h->bjob_off.data(), h->bjob_off.size() * 4, 0}, {h->channels.data(), h->channels.size() * 4, 0},
+        {h->weights.data(), h->weights.size() * 4, 0}, {h->jobs.data(), h->jobs.size() * sizeof(RkJob), 0},
+        {h->kjob_off.data(), h->kjob_off.size() * 4, 0}, {h->kjob_idx.data(), h->kjob_idx.size() * 4, 0},
+        {h->sets.data(), h->sets.size() * sizeof(RkSet), 0}, {h->set_rows.data(), h->set_rows.size() * 4, 0}};
+    size_t total = 0;
+    for (Part &p : part) {
+        p.at = total;
+        total += static_cast<size_t>(round_up(static_cast<int64_t>(p.bytes), 256));
+    }
     if (!h->d_blob) {
         h->blob_bytes = total;
         RK_HIP(hipMalloc(&h->d_blob, total));
         h->device = cur;
         char *base = static_cast<char *>(h->d_blob);
-        h->d_rec = reinterpret_cast<const RkKernelRec *>(base + rec);
-        h->d_bjob_off = reinterpret_cast<const int32_t *>(base + boff);
-        h->d_channels = reinterpret_cast<const int32_t *>(base + channels);
-        h->d_weights = reinterpret_cast<float *>(base + weights);
-        h->d_jobs = reinterpret_cast<const RkJob *>(base + jobs);
-        h->d_kjob_off = reinterpret_cast<const int32_t *>(base + koff);
-        h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + kidx);
-        h->d_sets = reinterpret_cast<const RkSet *>(base + sets);
-        h->d_set_rows = reinterpret_cast<const int32_t *>(base + rows);
+        h->d_rec = reinterpret_cast<const RkKernelRec *>(base + part[kRec].at);
+        h->d_bjob_off = reinterpret_cast<const int32_t *>(base + part[kBoff].at);
+        h->d_channels = reinterpret_cast<const int32_t *>(base + part[kChannels].at);
+        h->d_weights = reinterpret_cast<float *>(base + part[kWeights].at);
+        h->d_jobs = reinterpret_cast<const RkJob *>(base + part[kJobs].at);
+        h->d_kjob_off = reinterpret_cast<const int32_t *>(base + part[kKoff].at);
+        h->d_kjob_idx = reinterpret_cast<const int32_t *>(base + part[kKidx].at);
+        h->d_sets = reinterpret_cast<const RkSet *>(base + part[kSets].at);
+        h->d_set_rows = reinterpret_cast<const int32_t *>(base + part[kRows].at);
         h->params_dirty = true;
     }
-    RK_HIP(hipMemcpyAsync(h->d_blob, host.get(), total, hipMemcpyHostToDevice, stream));
-    RK_HIP(hipStreamSynchronize(stream));
+    // pageable sources: these copies return once the source has been read
+    if (total <= kOneCopy) {
+        const std::unique_ptr<char[]> host(new (std::nothrow) char[total]);
+        if (!host) return rk_fail(ROCKET_ENOMEM, "out of host memory for the upload of the parameters");
+        for (const Part &p : part) std::copy_n(static_cast<const char *>(p.from), p.bytes, host.get() + p.at);
+        RK_HIP(hipMemcpyAsync(h->d_blob, host.get(), total, hipMemcpyHostToDevice, stream));
+        RK_HIP(hipStreamSynchronize(stream));
+    } else {
+        for (const Part &p : part)
+            if (p.bytes != 0) RK_HIP(hipMemcpyAsync(static_cast<char *>(h->d_blob) + p.at, p.from, p.bytes, hipMemcpyHostToDevice, stream));
+        RK_HIP(hipStreamSynchronize(stream));
+    }
     h->params_dirty = false;
     return ROCKET_OK;
 }
