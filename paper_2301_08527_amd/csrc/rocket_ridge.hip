@@ -46,7 +46,7 @@ constexpr int kMaxRowSplits = 16;
 #endif
 // 32-row tiles left up to which a panel and its update are one launch.  Beyond it the factoring that every tile repeats costs
 // more than the second launch.  Whole fits with 64 features, always one launch against always two: n = 1,000
-// 585 / 750 us, 1,500 1,137 / 1,323, 2,000 2,000 / 2,099, 2,500 3,054 / 2,972, 3,500 6,562 / 5,510; with this line 1,925 at
+// 585 / 750 us (with the longer panel of that time), 1,500 1,137 / 1,323, 2,000 2,000 / 2,099, 2,500 3,054 / 2,972, 3,500 6,562 / 5,510; with this line 1,925 at
 // 2,000, 2,779 at 2,500, 5,339 at 3,500.
 constexpr int kFusedTiles = RK_FUSED_TILES;
 constexpr int kWideRow = 2048;      // features from which a prediction's row takes 1,024 lanes
@@ -191,6 +191,14 @@ __global__ __launch_bounds__(256) void rr_gram_finish(const double *__restrict__
     if (gi < n && gj < n && gj >= gi) M[static_cast<size_t>(gj) * ld + gi] = s + (gi == gj ? alpha : 0.0);
 }
 
+// LDS that one wavefront alone writes and reads: its accesses take effect in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void rr_wave_lds()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // 1/sqrt(x): the hardware's estimate (about 2^-24) and one third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2, whose
 // error (e^3) is far below that of the last rounding.  NaN for x <= 0, as the square root would give.
 __device__ __forceinline__ double rr_rsqrt(double x)
@@ -200,16 +208,70 @@ __device__ __forceinline__ double rr_rsqrt(double x)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// Keeps a value's computation where it stands: left alone the compiler turns the updates below around, so that a column's are
+// one dependent chain, each waiting for its own two readlanes.
+__device__ __forceinline__ void rr_here(double &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void rr_here_s(double &v) { asm volatile("" : "+s"(v)); }
+
+// Columns K0 .. K0 + 15 of the 64 rows in the lanes: factored, and taken out of those of them that follow.  The chain from one
+// column's diagonal to the next (readlane, reciprocal square root, five dependent operations) runs between the updates of
+// the columns after it, which do not need its result.
+template <int K0>
+__device__ __forceinline__ void rr_half(double (&row)[kNB])
+{
+    constexpr int kEnd = K0 + 16;
+    const int l = threadIdx.x & 63;
+    double inv = rr_rsqrt(rr_lane(row[K0], K0));
+#pragma unroll
+    for (int k = K0; k < kEnd; ++k) {
+        const double lrk = row[k] * inv;
+        row[k] = l == k ? inv : lrk;
+        if (k + 1 == kEnd) break;
+        row[k + 1] = fma(-lrk, rr_lane(lrk, k + 1), row[k + 1]);   // meaningful where column <= lane
+        rr_here(row[k + 1]);
+        const double d = rr_lane(row[k + 1], k + 1);
+        double y = __builtin_amdgcn_rsq(d), xy = 0.0, e = 0.0, f = 0.0, ye = 0.0;
+        rr_here(y);
+        const int others = kEnd - (k + 2);
+        int stage = 0;
+        double next = others > 0 ? rr_lane(lrk, k + 2) : 0.0;      // an update ahead: a readlane's result takes two cycles of waiting
+#pragma unroll
+        for (int i = 0; i <= others; ++i) {
+#pragma unroll
+            for (; stage < 4 && 5 * i >= (stage + 1) * others; ++stage) {      // rr_rsqrt, a step at a time
+                if (stage == 0) { xy = -d * y; rr_here(xy); }
+                if (stage == 1) { e = fma(xy, y, 1.0); rr_here(e); }
+                if (stage == 2) { f = fma(0.375, e, 0.5); ye = y * e; rr_here(f); rr_here(ye); }
+                if (stage == 3) { inv = fma(ye, f, y); rr_here(inv); }
+            }
+            if (i < others) {
+                const int j = k + 2 + i;
+                const double factor = next;
+                if (i + 1 < others) {
+                    next = rr_lane(lrk, j + 1);
+                    rr_here_s(next);
+                }
+                row[j] = fma(-lrk, factor, row[j]);
+                rr_here(row[j]);
+            }
+        }
+    }
+}
+
 // One panel of the factorisation for 32 rows, inside one wavefront.  Lanes 0..31 hold the rows of the diagonal block at
-// (k0, k0) of width nb <= 32 (padded with the identity), lanes 32..63 the rows first .. first + 31 of M below it (rows past the
+// (k0, k0) of width nb <= 32 (padded with the identity; right of the diagonal they hold what stood there, which no other lane
+// reads), lanes 32..63 the rows first .. first + 31 of M below it (rows past the
 // last repeat it).  Column by column all 64 rows are scaled and updated with values of lanes 0..31 that come through
 // readlane: the same instructions factor the block and solve the rows against it.  Afterwards lanes 0..31 hold the factor
-// with the reciprocals of its diagonal, lanes 32..63 the rows of L.  What bounds it is the chain of 32 reciprocal square
-// roots and about 500 x (two readlanes + one fp64 multiply-add).
+// with the reciprocals of its diagonal, lanes 32..63 the rows of L.  Between the two halves of the columns the second is
+// updated by the first on the matrix unit, through `half` (LDS of this wavefront alone), which does in 12 instructions what
+// takes 256 x (two readlanes + one multiply-add).  What bounds it is the chain of 32 columns.  Fit and prediction, 137 x 3,000
+// and 677 x 20,000: 105.3 -> 94.5 and 576.7 -> 517.5 us; the error of the coefficients against 80-bit sums is the same.
+constexpr int kHalfPitch = 18;      // doubles a row of `half`: 16-byte reads, and rows start in different banks
 __device__ __forceinline__ void rr_factor_rows(const double *__restrict__ M, int ld, int nrows, int k0, int nb, int first,
-                                               double (&row)[kNB])
+                                               double (&row)[kNB], double (&half)[64][kHalfPitch])
 {
-    const int l = threadIdx.x & 63;
+    const int l = threadIdx.x & 63, r = l & 15, q = l >> 4;
     const double *src = M + static_cast<size_t>(l < kNB ? k0 + min(l, nb - 1) : min(first + l - kNB, nrows - 1)) * ld + k0;
     if (nb == kNB) {
 #pragma unroll
@@ -220,19 +282,32 @@ __device__ __forceinline__ void rr_factor_rows(const double *__restrict__ M, int
         }
     } else {
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) row[c] = c < nb ? src[c] : 0.0;
+        for (int c = 0; c < kNB; ++c) row[c] = l >= nb && l < kNB ? (c == l ? 1.0 : 0.0) : c < nb ? src[c] : 0.0;
     }
+    rr_half<0>(row);
+    // rows 16..63: row[16 + c] -= sum over k < 16 of row[k] * (row 16 + c)[k]; lane q takes four neighbouring k of its row
 #pragma unroll
-    for (int c = 0; c < kNB; ++c)
-        if (l < kNB && (c > l || l >= nb)) row[c] = c == l ? 1.0 : 0.0;
+    for (int c = 0; c < 16; ++c) half[l][c] = row[c];
+    rr_wave_lds();
+    double op[3][4];
 #pragma unroll
-    for (int k = 0; k < kNB; ++k) {
-        const double inv = rr_rsqrt(rr_lane(row[k], k));
-        const double lrk = row[k] * inv;
-        row[k] = l == k ? inv : lrk;
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int j = k + 1; j < kNB; ++j) row[j] = fma(-lrk, rr_lane(lrk, j), row[j]);   // meaningful where j <= lane
-    }
+        for (int e = 0; e < 4; ++e) op[a][e] = half[16 + 16 * a + r][4 * q + e];
+    d4 sum[3] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sum[a] = rr_mfma(op[a][e], op[0][e], sum[a]);
+    rr_wave_lds();
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) half[16 + 16 * a + 4 * v + q][r] = sum[a][v];
+    rr_wave_lds();
+#pragma unroll
+    for (int c = 0; c < 16; ++c) row[16 + c] -= half[l][c];
+    rr_half<16>(row);
 }
 
 // The lanes' results to memory: the rows of L go, transposed, to the upper triangle of M (L[i][k] to M[k][i]; nobody reads
@@ -260,13 +335,15 @@ __device__ __forceinline__ void rr_store_block(double *__restrict__ D, int k0, c
 // One panel in one launch: a workgroup of two wavefronts per 32 x 32 tile (ti >= tj) of what is left.  Each wavefront factors
 // the diagonal block itself and solves the 32 rows of one side of the tile; the rows meet in LDS and the tile gets its
 // rank-32 update.  The factoring is repeated by every tile, on units that would idle: a step takes its latency as long as the
-// tiles are about as many as the chip holds at once (n = 677: 10.6 us a panel, 30 as two launches that took turns).
+// tiles are about as many as the chip holds at once (n = 677: 10.5 us a panel, 30 as two launches that took turns; 7.8 since
+// the halves of the block meet on the matrix unit and its updates do not wait for their readlanes).
 __global__ __launch_bounds__(128) void rr_step(double *__restrict__ M, int ld, int nrows, int k0, int nb,
                                                double *__restrict__ D)
 {
     const int ti = blockIdx.y, tj = blockIdx.x;
     if (tj > ti) return;
     __shared__ double side[2][32][kNB + 1];
+    __shared__ __attribute__((aligned(16))) double half[2][64][kHalfPitch];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
     const int first = k0 + nb, rows = nrows - first, cols = rows - 1;   // the row of yc has no column
     double old[2][4];
@@ -280,7 +357,7 @@ __global__ __launch_bounds__(128) void rr_step(double *__restrict__ M, int ld, i
         }
     double row[kNB];
     const int mine = first + 32 * (w == 0 ? ti : tj);
-    rr_factor_rows(M, ld, nrows, k0, nb, mine, row);
+    rr_factor_rows(M, ld, nrows, k0, nb, mine, row, half[w]);
     if (l >= kNB) {
 #pragma unroll
         for (int c = 0; c < kNB; ++c) side[w][l - kNB][c] = row[c];
@@ -310,8 +387,9 @@ __global__ __launch_bounds__(64) void rr_panel(double *__restrict__ M, int ld, i
                                                double *__restrict__ P, double *__restrict__ D)
 {
     const int l = threadIdx.x, first = k0 + nb, mine = first + 32 * static_cast<int>(blockIdx.x);
+    __shared__ __attribute__((aligned(16))) double half[64][kHalfPitch];
     double row[kNB];
-    rr_factor_rows(M, ld, nrows, k0, nb, mine, row);
+    rr_factor_rows(M, ld, nrows, k0, nb, mine, row, half);
     rr_store_rows(M, ld, nrows, k0, nb, mine, row);
     if (blockIdx.x == 0) rr_store_block(D, k0, row);
     const int i = mine + l - kNB;
