@@ -335,13 +335,17 @@ __device__ __forceinline__ void rr_store_block(double *__restrict__ D, int k0, c
 // One panel in one launch: a workgroup of two wavefronts per 32 x 32 tile (ti >= tj) of what is left.  Each wavefront factors
 // the diagonal block itself and solves the 32 rows of one side of the tile; the rows meet in LDS and the tile gets its
 // rank-32 update.  The factoring is repeated by every tile, on units that would idle: a step takes its latency as long as the
-// tiles are about as many as the chip holds at once (n = 677: 10.5 us a panel, 30 as two launches that took turns; 7.8 since
+// tiles are about as many as the chip holds at once, which is why only the triangle is launched: with the empty half of the square
+// beside it two workgroups share a CU from 17 tiles a side on instead of 23 (a panel 10 us instead of 7.2).  (n = 677: 10.5 us a panel, 30 as two launches that took turns; 7.3 since
 // the halves of the block meet on the matrix unit and its updates do not wait for their readlanes).
 __global__ __launch_bounds__(128) void rr_step(double *__restrict__ M, int ld, int nrows, int k0, int nb,
                                                double *__restrict__ D)
 {
-    const int ti = blockIdx.y, tj = blockIdx.x;
-    if (tj > ti) return;
+    // tile blockIdx.x of the lower triangle, row by row; the root is off by one at most (48 rows of tiles)
+    int ti = static_cast<int>((sqrtf(8.0f * static_cast<float>(blockIdx.x) + 1.0f) - 1.0f) * 0.5f);
+    if ((ti + 1) * (ti + 2) / 2 <= static_cast<int>(blockIdx.x)) ++ti;
+    if (ti * (ti + 1) / 2 > static_cast<int>(blockIdx.x)) --ti;
+    const int tj = static_cast<int>(blockIdx.x) - ti * (ti + 1) / 2;
     __shared__ double side[2][32][kNB + 1];
     __shared__ __attribute__((aligned(16))) double half[2][64][kHalfPitch];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
@@ -701,7 +705,7 @@ extern "C" int rocket_ridge_fit(const float *features_dev, const float *targets_
         const int first = k0 + nb, rows = nrows - first;   // rows >= 1: the row of yc is always below
         const int t = (rows + 31) / 32;
         if (t <= kFusedTiles) {
-            hipLaunchKernelGGL(rr_step, dim3(t, t), dim3(128), 0, stream, M, q.ld, nrows, k0, nb, D);
+            hipLaunchKernelGGL(rr_step, dim3(t * (t + 1) / 2), dim3(128), 0, stream, M, q.ld, nrows, k0, nb, D);
         } else {   // so many rows are left that the panel is 32 columns wide and columns follow it
             hipLaunchKernelGGL(rr_panel, dim3(t), dim3(64), 0, stream, M, q.ld, nrows, k0, nb, P, D);
             hipLaunchKernelGGL(rr_trailing, dim3(t, t), dim3(64), 0, stream, M, q.ld, first, rows, rows - 1, P);
