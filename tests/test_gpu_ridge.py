@@ -54,6 +54,17 @@ def test_systems_around_the_fused_panels(n):
     _check(X, y, 0.7)
 
 
+@pytest.mark.parametrize("n", [15, 16, 17, 47, 48, 49, 63, 64, 79, 543, 545])
+def test_systems_around_half_a_panel(n):
+    """last panels that end in either half of their 32 columns or at its edge, and row slices around the 16 rows that the
+    column sums load together; fp64, so the bound of the other sizes holds"""
+    print("ridge half panels", n, flush=True)
+    rng = np.random.default_rng(n)
+    X = (rng.standard_normal((n, 70)) * rng.uniform(0.2, 3.0, 70) + rng.uniform(-2, 2, 70)).astype(np.float32)
+    y = (X[:, :4].sum(axis=1) * 0.25 + 1.0 + 0.05 * rng.standard_normal(n)).astype(np.float32)
+    _check(X, y, 0.7)
+
+
 @pytest.mark.parametrize("p", [1, 3, 4, 1027, 2047, 2048, 2049, 4097, 8195])
 def test_predict_row_widths(p):
     """feature counts around a lane's four columns and the change of the workgroup's width at 2,048; rows of odd length start
