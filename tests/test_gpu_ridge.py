@@ -65,6 +65,89 @@ def test_systems_around_half_a_panel(n):
     _check(X, y, 0.7)
 
 
+@pytest.mark.parametrize("n", [48, 64, 79, 545, 1601])
+def test_workspace_contents_do_not_matter(n):
+    """the same bits from a workspace full of NaN bytes, again from what the first fit left there, and after a smaller fit has
+    moved the pieces of the workspace: last panels of 16, 32, 15 and 1 columns, and a size that starts with panels of two launches.
+    (Right of a diagonal block's diagonal, and past the last column, the factorisation loads what stands there.)"""
+    import torch
+    print("ridge dirty workspace", n, flush=True)
+    rng = np.random.default_rng(n)
+    X = torch.from_numpy((rng.standard_normal((n, 70)) + rng.uniform(-2, 2, 70)).astype(np.float32)).cuda()
+    y = torch.from_numpy(rng.standard_normal(n).astype(np.float32)).cuda()
+    ws = torch.zeros(rocket.rocket_ridge_workspace_bytes(n, 70), dtype=torch.uint8, device="cuda")
+    coef, b = rocket.rocket_ridge_fit(X, y, 0.7, workspace=ws)
+    assert torch.isfinite(coef).all() and torch.isfinite(b).all()
+    ws.fill_(0xFF)
+    for _ in range(2):
+        again, b_again = rocket.rocket_ridge_fit(X, y, 0.7, workspace=ws)
+        assert torch.equal(again, coef) and torch.equal(b_again, b)
+    rocket.rocket_ridge_fit(X[:37, :33].contiguous(), y[:37].contiguous(), 0.7, workspace=ws)
+    again, b_again = rocket.rocket_ridge_fit(X, y, 0.7, workspace=ws)
+    assert torch.equal(again, coef) and torch.equal(b_again, b)
+
+
+def _fit_in_80_bits(X, y, alpha):
+    """the same model with every sum in 80 bits: coefficients, intercept, dual solution"""
+    X, y = X.astype(np.longdouble), y.astype(np.longdouble)
+    n, mu = len(y), X.mean(axis=0)
+    Xc, z = X - mu, y - y.mean()
+    L = Xc @ Xc.T + np.longdouble(alpha) * np.eye(n, dtype=np.longdouble)
+    for k in range(n):          # Cholesky, the right-hand side along with it
+        L[k, k] = np.sqrt(L[k, k])
+        L[k + 1:, k] /= L[k, k]
+        L[k + 1:, k + 1:] -= np.outer(L[k + 1:, k], L[k + 1:, k])
+        z[k] /= L[k, k]
+        z[k + 1:] -= L[k + 1:, k] * z[k]
+    for k in range(n - 1, -1, -1):
+        z[k] /= L[k, k]
+        z[:k] -= L[k, :k] * z[k]
+    w = Xc.T @ z
+    return w, y.mean() - mu @ w, z
+
+
+def _fp64_error_bounds(X, y, alpha, w, a):
+    """What fp64 arithmetic may change in the coefficients (2-norm) and the intercept, to first order, in units that every
+    order of summation keeps: a sum of m terms errs by m eps times its magnitudes, a Cholesky factorisation with its two solves
+    by (3 n + 1) eps trace(A) in A (|R^T||R| has the trace of A as its bound); a reciprocal square root and the multiplications
+    that take the place of divisions have 2 roundings more each, hence 4 n + 16 here."""
+    eps = 2.0 ** -53
+    X, y, a, w = X.astype(np.float64), y.astype(np.float64), a.astype(np.float64), w.astype(np.float64)
+    n, p = X.shape
+    Xc, yc = X - X.mean(axis=0), y - y.mean()
+    A = Xc @ Xc.T + alpha * np.eye(n)
+    values = np.linalg.eigvalsh(A)
+    low, size, frob = values[0], np.sqrt(values[-1]), np.linalg.norm(Xc)
+    dX = eps * np.linalg.norm(np.abs(Xc) + (n + 2) * np.abs(X).mean(axis=0))
+    dA = 2.0 * size * dX + (p + 2) * eps * frob ** 2 + eps * alpha + (4 * n + 16) * eps * np.trace(A)
+    dy = eps * np.linalg.norm(np.abs(yc) + (n + 2) * np.abs(y).mean())
+    da = (dA * np.linalg.norm(a) + dy) / low
+    dw = size * da + dX * np.linalg.norm(a) + (n + 2) * eps * frob * np.linalg.norm(a)
+    db = (n + 2) * eps * np.abs(y).mean() + np.linalg.norm(X.mean(axis=0)) * dw \
+        + (n + p + 4) * eps * (np.abs(X).mean(axis=0) @ np.abs(w))
+    return dw, db
+
+
+@pytest.mark.parametrize("n,p", [(5, 40), (16, 70), (33, 300), (64, 500), (137, 1000)])
+def test_well_conditioned_systems_keep_fp64_accuracy(n, p):
+    """against 80-bit sums, within what fp64 arithmetic explains (1e-13 to 6e-11 of the coefficients): a step of the
+    factorisation that loses a few digits would stay below the 1e-8 of the other tests.  The centred rows add up to zero, so
+    alpha is the smallest eigenvalue of the system; with alpha = p its condition is a small number."""
+    alpha = float(p)
+    print("ridge accuracy", n, p, flush=True)
+    rng = np.random.default_rng(n + p)
+    X = (rng.standard_normal((n, p)) + rng.uniform(-1, 1, p)).astype(np.float32)
+    y = (X[:, :4].sum(axis=1) * 0.25 + 1.0 + 0.05 * rng.standard_normal(n)).astype(np.float32)
+    w_ref, b_ref, a_ref = _fit_in_80_bits(X, y, alpha)
+    dw, db = _fp64_error_bounds(X, y, alpha, w_ref, a_ref)
+    norm = float(np.sqrt((w_ref ** 2).sum()))
+    assert dw < 1e-10 * norm                 # the bound says something
+    w, b, _ = _fit(X, y, alpha)
+    err = float(np.sqrt(((w - w_ref) ** 2).sum()))
+    print("error", err / norm, "bound", dw / norm, flush=True)
+    assert err <= dw and abs(b - float(b_ref)) <= db
+
+
 @pytest.mark.parametrize("p", [1, 3, 4, 1027, 2047, 2048, 2049, 4097, 8195])
 def test_predict_row_widths(p):
     """feature counts around a lane's four columns and the change of the workgroup's width at 2,048; rows of odd length start
