@@ -14,8 +14,9 @@
 //   rr_gram_finish              sums the slices, adds alpha on the diagonal, writes the lower
 //                               triangle of the (n+1) x (n+1) system whose last row is yc
 //   per 32 columns: rr_step     Cholesky of the 32 x 32 diagonal block and the rows below it solved against
-//                               that block inside each wavefront's registers, then the rank-32 update
-//                               of what is left, 32 x 32 tiles on the MFMA units (rr_panel and
+//                               that block, 16 columns at a time in each wavefront's registers (the second
+//                               half updated by the first through LDS and the MFMA units), then the rank-32
+//                               update of what is left, 32 x 32 tiles on the MFMA units (rr_panel and
 //                               rr_trailing where much is left).  The row of yc takes part like any
 //                               other row, so when the factorisation ends it holds L^-1 yc (forward
 //                               substitution costs nothing extra).
@@ -44,14 +45,23 @@ constexpr int kMaxRowSplits = 16;
 // Rows of X whose loads a lane of the column sums and of the coefficients has on their way together (added in order, so the
 // sums are the same bits): one column is a chain of trips to memory otherwise.  677 x 20,000: rr_col_sums 18.2 -> 10.5 us
 // (54 MB), rr_coef_partial 16.2 -> 11.0, and the sums of their splits, loaded together too, 5.5 -> 3.6 and 6.1 -> 4.7.
+// Slices of fewer rows load their last row again: whole fits of 8 x 3,000 43.3 -> 42.8 us, of 2 x 500 35.8 -> 36.3, of
+// 1 x 200,000 480 -> 483.
 constexpr int kRowsInFlight = 16;
 #ifndef RK_FUSED_TILES
 #define RK_FUSED_TILES 48
 #endif
 // 32-row tiles left up to which a panel and its update are one launch.  Beyond it the factoring that every tile repeats costs
-// more than the second launch.  Whole fits with 64 features, always one launch against always two: n = 1,000
-// 585 / 750 us (with the longer panel of that time), 1,500 1,137 / 1,323, 2,000 2,000 / 2,099, 2,500 3,054 / 2,972, 3,500 6,562 / 5,510; with this line 1,925 at
-// 2,000, 2,779 at 2,500, 5,339 at 3,500.
+// more than the second launch.  Whole fits with 64 features in us, by the number of tiles at which the line lies (0: always
+// two launches; 2,000: always one):
+//      n       0      32      40      48      64    2,000
+//    500     301     193     193     193     193     193
+//  1,000     656     455     455     455     455     455
+//  1,500   1,189     982     945     922     922     922
+//  2,000   1,920   1,724   1,690   1,666   1,663   1,666
+//  2,500   2,746   2,535   2,494   2,474   2,479   2,561
+//  3,000   4,077   3,869   3,830   3,806   3,818   4,042
+//  3,500   5,205   5,002   4,967   4,944   4,972   5,538
 constexpr int kFusedTiles = RK_FUSED_TILES;
 constexpr int kWideRow = 2048;      // features from which a prediction's row takes 1,024 lanes
 
@@ -212,7 +222,8 @@ __device__ __forceinline__ void rr_wave_lds()
 }
 
 // 1/sqrt(x): the hardware's estimate (about 2^-24) and one third-order step, y (1 + e/2 + 3 e^2/8) with e = 1 - x y^2, whose
-// error (e^3) is far below that of the last rounding.  NaN for x <= 0, as the square root would give.
+// error (e^3) is far below that of the last rounding.  NaN for x <= 0, as the square root would give.  rr_half spells the same
+// steps out between its updates, operation by operation: the two change together.
 __device__ __forceinline__ double rr_rsqrt(double x)
 {
     const double y = __builtin_amdgcn_rsq(x);
@@ -272,13 +283,15 @@ __device__ __forceinline__ void rr_half(double (&row)[kNB])
 
 // One panel of the factorisation for 32 rows, inside one wavefront.  Lanes 0..31 hold the rows of the diagonal block at
 // (k0, k0) of width nb <= 32 (padded with the identity; right of the diagonal they hold what stood there, which no other lane
-// reads), lanes 32..63 the rows first .. first + 31 of M below it (rows past the
-// last repeat it).  Column by column all 64 rows are scaled and updated with values of lanes 0..31 that come through
+// reads), lanes 32..63 the rows first .. first + 31 of M below it (rows past the last repeat it).  Column by column, in two
+// halves of 16, all 64 rows are scaled and updated with values of lanes 0..31 that come through
 // readlane: the same instructions factor the block and solve the rows against it.  Afterwards lanes 0..31 hold the factor
 // with the reciprocals of its diagonal, lanes 32..63 the rows of L.  Between the two halves of the columns the second is
 // updated by the first on the matrix unit, through `half` (LDS of this wavefront alone), which does in 12 instructions what
 // takes 256 x (two readlanes + one multiply-add).  What bounds it is the chain of 32 columns.  Fit and prediction, 137 x 3,000
-// and 677 x 20,000: 105.3 -> 94.5 and 576.7 -> 517.5 us; the error of the coefficients against 80-bit sums is the same.
+// and 677 x 20,000: 105.3 -> 94.5 and 576.7 -> 517.5 us.  Relative error of the coefficients against 80-bit sums, before -> now
+// (2-norm, four data sets each): 33 x 300 1.1e-15 -> 1.3e-15, 64 x 500 2.06e-15 -> 2.08e-15, 137 x 1,000 3.78e-15 ->
+// 3.81e-15, 200 x 900 at alpha = 0.001 6.4e-15 -> 6.2e-15, 260 x 1,300 7.4e-15 -> 7.2e-15.
 constexpr int kHalfPitch = 18;      // doubles a row of `half`: 16-byte reads, and rows start in different banks
 __device__ __forceinline__ void rr_factor_rows(const double *__restrict__ M, int ld, int nrows, int k0, int nb, int first,
                                                double (&row)[kNB], double (&half)[64][kHalfPitch])
@@ -347,9 +360,9 @@ __device__ __forceinline__ void rr_store_block(double *__restrict__ D, int k0, c
 // One panel in one launch: a workgroup of two wavefronts per 32 x 32 tile (ti >= tj) of what is left.  Each wavefront factors
 // the diagonal block itself and solves the 32 rows of one side of the tile; the rows meet in LDS and the tile gets its
 // rank-32 update.  The factoring is repeated by every tile, on units that would idle: a step takes its latency as long as the
-// tiles are about as many as the chip holds at once, which is why only the triangle is launched: with the empty half of the square
-// beside it two workgroups share a CU from 17 tiles a side on instead of 23 (a panel 10 us instead of 7.2).  (n = 677: 10.5 us a panel, 30 as two launches that took turns; 7.3 since
-// the halves of the block meet on the matrix unit and its updates do not wait for their readlanes).
+// tiles are about as many as the chip holds at once, which is why only the triangle is launched: with the empty half of the
+// square beside it two workgroups share a CU from 17 tiles a side on instead of 23 (a panel 10 us instead of 7.2).  A panel at
+// n = 677: 30 us as two launches, 10.5 as one launch of the square whose updates waited for their readlanes, 7.3 now.
 __global__ __launch_bounds__(128) void rr_step(double *__restrict__ M, int ld, int nrows, int k0, int nb,
                                                double *__restrict__ D)
 {
