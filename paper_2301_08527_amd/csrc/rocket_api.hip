@@ -752,6 +752,62 @@ extern "C" int rocket_infer(rocket_kernels *h, const void *x_dev, int x_is_u8, i
                                 hip_stream);
 }
 
+// Workspace of a backward pass over groups: bytes of the interleaved copy (8 KB of slack as in padded_batch_bytes), then the
+// gradient sums of every group where there are several.
+static size_t grouped_copy_bytes(const rocket_kernels *h, const RkGroups &g)
+{
+    return static_cast<size_t>(round_up(rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192, 256));
+}
+static size_t grouped_partial_bytes(const rocket_kernels *h, const RkGroups &g)
+{
+    return g.count > 1 ? static_cast<size_t>(g.count) * static_cast<size_t>(h->w_off[h->K] + h->K) * 4 : 0;
+}
+
+// Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
+// 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 460 us against 183 with 64 lanes; 64 x 20 x 2,000, 200 kernels 267 and 171;
+// 4 x 20 x 1,400, 200 kernels 50 and 61).  Longer ones take longer on one wavefront, the more so with many channels, which pays where
+// enough others run beside it: 256 against 64 lanes at 12,800 jobs 64 x 20 x 3,000 275 and 251 us, 64 x 20 x 8,192 437 and
+// 575, 64 x 6 x 6,000 291 and 270, 64 x 1 x 8,192 177 and 162; at 64,000 64 x 20 x 8,192 1,628 and 1,505; at 3,200
+// 16 x 1 x 4,000 43 and 43, 16 x 6 x 4,000 77 and 88, 16 x 20 x 3,000 95 and 137.
+static bool one_wavefront_jobs(const rocket_kernels *h, int32_t B)
+{
+    const int64_t work = static_cast<int64_t>(B) * h->jobs.size();
+    return h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
+}
+
+// The groups in which a backward pass takes the batch (rocket_backward_groups.hip); width 1: none, one series at a time.
+// What a lane spends on an output is 2 n_ch len multiply-adds and the like of 25 more for the sigmoid and the largest output; a
+// wavefront's shares of the bands that do not fill it come to some 20 outputs more for each lane (10 in each of four wavefronts; a
+// third more for one series at a time).  That work is spread over the chip's 1,024 SIMDs, and the longest job, which shares
+// its SIMD with four others, adds 3.5 times its own time: wide groups waste less on each series, narrow ones make more and
+// shorter jobs.  Of 20 shapes measured at every width the rule takes the fastest or one within 5 % of it for 19; what it
+// chooses, against one series at a time, in us: 64 x 1 x 1,000 and 1,000 kernels 92/184 (4 series; 8: 91, 2: 111, 16: 107),
+// 98 x 1 x 246 and 1,082 54/279 (16; 4: 75, 64: 94), 28 x 18 x 158 and 15,408 307/1,820 (16; 4: 470), 27 x 19 x 595 and 2,590 197/365
+// (4; 2: 226, 8: 236), 167 x 9 x 1,205 and 1,737 1,060/1,870 (4; 8: 1,057, 32: 1,474).  Series of more than some 4,000 samples gain little
+// or nothing (23 x 6 x 4,099 and 1,537 389/413, 16 x 3 x 4,099 and 500 103/93).  The 20th: 9 x 5 x 500 and 10,000 kernels, one
+// and eight series 219 us, one, four and four 178.
+static RkGroups backward_groups(const rocket_kernels *h, int32_t B)
+{
+    RkGroups best = rk_groups(B, 1);
+    if (!rk_launchers().backward_groups || h->jobs.size() != static_cast<size_t>(h->K)) return best;       // a job is a whole kernel
+    const double n = h->outputs / h->K, mean = 2.0 * h->conv_fma / h->outputs + 25.0, most = 2.0 * h->max_terms + 25.0;
+    auto estimate = [&](double jobs, int wavefronts, double series, double rest) {     // jobs of `series` series, in instructions
+        const double each = series * n / (64.0 * wavefronts) + rest;
+        return std::make_pair(jobs * wavefronts * each * mean / 1024.0, 3.5 * each * most);
+    };
+    const auto plain = one_wavefront_jobs(h, B) ? estimate(1.3 * B * h->K, 1, 1, 20) : estimate(1.0 * B * h->K, 4, 1, 10);
+    double least = plain.first + plain.second;
+    for (int32_t width = 2; width <= RkGroups::kWidest && width < 2 * B; width *= 2) {
+        const RkGroups g = rk_groups(B, width);
+        if (grouped_copy_bytes(h, g) + grouped_partial_bytes(h, g) > row_stats_offset(h, B, 1)) continue;     // the workspace is what it is
+        if (h->row_len * width > (1 << 24)) break;      // 32-bit byte offsets of 42 dilation steps
+        const auto first = estimate(h->K, 1, g.first_width, 20), rest = estimate(static_cast<double>(h->K) * (g.count - 1), 1, width, 20);
+        const double t = first.first + rest.first + std::max(first.second, g.count > 1 ? rest.second : 0.0);
+        if (t < least) { least = t; best = g; }
+    }
+    return best;
+}
+
 static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, bool is_u8, int32_t B, uint32_t mask,
                          const float *grad_out_dev, float lambda, float shift, int include_max, float *grad_w_dev,
                          float *grad_b_dev, void *ws, size_t ws_bytes, void *hip_stream)
@@ -770,23 +826,27 @@ static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, b
     if (rc != ROCKET_OK) return rc;
     float *xpad = static_cast<float *>(ws);
     float *partial = reinterpret_cast<float *>(static_cast<char *>(ws) + padded_batch_bytes(h, B));
-    rc = pad_batch(h, x_dev, is_u8, B, ws, 1, stream);
-    if (rc != ROCKET_OK) return rc;
     const int F = rocket_num_features(mask);
     const int plane_soft = F - 1;                 // planes are in bit order: softPPV is last
     const int plane_max = include_max ? 0 : -1;   // and max, when present, is first
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
+    const RkGroups groups = backward_groups(h, B);
+    if (groups.width > 1) {
+        char *base = static_cast<char *>(ws);
+        if (rk_launchers().pad_groups(h, x_dev, is_u8, B, groups, xpad, base + row_stats_offset(h, B, 1), stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
+        rc = profile_mark(h, stream, true);
+        if (rc != ROCKET_OK) return rc;
+        if (rk_launchers().backward_groups(h, xpad, groups, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns,
+                                           reinterpret_cast<float *>(base + grouped_copy_bytes(h, groups)), grad_w_dev, grad_b_dev, stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
+        return profile_mark(h, stream, false);
+    }
+    rc = pad_batch(h, x_dev, is_u8, B, ws, 1, stream);
+    if (rc != ROCKET_OK) return rc;
     rc = profile_mark(h, stream, true);
     if (rc != ROCKET_OK) return rc;
-    // Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
-    // 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 460 us against 183 with 64 lanes; 64 x 20 x 2,000, 200 kernels 267 and 171;
-    // 4 x 20 x 1,400, 200 kernels 50 and 61).  Longer ones take longer on one wavefront, the more so with many channels, which pays where
-    // enough others run beside it: 256 against 64 lanes at 12,800 jobs 64 x 20 x 3,000 275 and 251 us, 64 x 20 x 8,192 437 and
-    // 575, 64 x 6 x 6,000 291 and 270, 64 x 1 x 8,192 177 and 162; at 64,000 64 x 20 x 8,192 1,628 and 1,505; at 3,200
-    // 16 x 1 x 4,000 43 and 43, 16 x 6 x 4,000 77 and 88, 16 x 20 x 3,000 95 and 137.
-    const int64_t work = static_cast<int64_t>(B) * h->jobs.size();
-    const bool narrow = h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
-    if ((narrow ? rk_launchers().backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
+    if ((one_wavefront_jobs(h, B) ? rk_launchers().backward_short : rk_launch_backward)(h, xpad, B, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, stream) != ROCKET_OK)
         return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
     rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;

@@ -87,7 +87,16 @@ __device__ __forceinline__ void rk_bwd_put_away(BwdState &st, float *slots)
     }
 }
 
-template <int NT, int LEN, int R>
+// How far from the end of a row lies the last column that a lane without a strip may redo: in a group of interleaved series the last
+// one of the lane's own series, for the largest output that it tracks.
+template <bool GROUPS>
+__device__ __forceinline__ int rk_bwd_back(const KernelCtx &k)
+{
+    if constexpr (GROUPS) return k.width - (static_cast<int>(threadIdx.x) & (k.width - 1));
+    return 1;
+}
+
+template <int NT, bool GROUPS, int LEN, int R>
 __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int nbands, int ncols, float coef,
                                                bool want_max, float *slots, BwdState &st)
 {
@@ -105,7 +114,7 @@ __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int
         const float lane_coef = valid ? coef : 0.f;
         // idle lanes of a wavefront that still has strips redo the segment's last strip with weight 0
         const int band = valid ? band_run : nbands - 1;
-        const int r = valid ? r_run : ncols - 1;
+        const int r = valid ? r_run : ncols - rk_bwd_back<GROUPS>(k);
         const int t0 = (row0 + band * R) * k.d + r;
         const uint32_t voff = static_cast<uint32_t>(t0) * 4u;
         float acc[R];
@@ -197,7 +206,7 @@ __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int
 // reduction, not the multiply-adds, would otherwise dominate (a kernel with dilation in the
 // thousands has a dozen rows in all).  Column blocks that lie wholly beyond the band for this
 // wavefront are skipped by wavefront-uniform branches.
-template <int NT, int LEN, int R, int S>
+template <int NT, bool GROUPS, int LEN, int R, int S>
 __device__ __forceinline__ void rk_bwd_band(const KernelCtx &k, int row0, int ncols, float coef, bool want_max,
                                             float *slots, BwdState &st)
 {
@@ -217,7 +226,7 @@ __device__ __forceinline__ void rk_bwd_band(const KernelCtx &k, int row0, int nc
             const bool valid = col < ncols;
             live[s] = base + s * NT + wave0 < ncols;          // wavefront-uniform
             lane_coef[s] = valid ? coef : 0.f;
-            t0[s] = row0 * k.d + (valid ? col : ncols - 1);         // idle lanes redo the last column with weight 0
+            t0[s] = row0 * k.d + (valid ? col : ncols - rk_bwd_back<GROUPS>(k));     // idle lanes redo the last column with weight 0
             voff[s] = static_cast<uint32_t>(t0[s]) * 4u;
 #pragma unroll
             for (int i = 0; i < R; ++i) acc[s][i] = 0.f;
@@ -465,19 +474,20 @@ __device__ __forceinline__ int rk_bwd_lds_bands(const KernelCtx &k, int first_ro
     return first_row + nb * R;
 }
 
-template <int NT, int LEN, int D>
+// (The dilations of a group are multiples of its width, which is 2 or more: even.)
+template <int NT, bool GROUPS, int LEN, int D>
 __device__ __forceinline__ int rk_bwd_lds_dispatch(const KernelCtx &k, int first_row, int end_row, float coef,
                                                    bool want_max, float *tile, float *slots, BwdState &st)
 {
     if constexpr (D < kLdsMaxD) {
         if (k.d == D) return rk_bwd_lds_bands<NT, LEN, D>(k, first_row, end_row, coef, want_max, tile, slots, st);
-        return rk_bwd_lds_dispatch<NT, LEN, D + 1>(k, first_row, end_row, coef, want_max, tile, slots, st);
+        return rk_bwd_lds_dispatch<NT, GROUPS, LEN, D + (GROUPS ? 2 : 1)>(k, first_row, end_row, coef, want_max, tile, slots, st);
     } else {
         return first_row;
     }
 }
 
-template <int NT, int LEN>
+template <int NT, bool GROUPS, int LEN>
 __device__ __forceinline__ void rk_backward_body(const KernelCtx &k, int nout, const RkJob job, float coef,
                                                  bool want_max, float *tile, float *slots, BwdState &st)
 {
@@ -486,31 +496,34 @@ __device__ __forceinline__ void rk_backward_body(const KernelCtx &k, int nout, c
     const int tail = nout - total_rows * d;
     // the job's rows: whole LDS chunks first (small dilations), then bands of 32 rows, then what is left
     int row0 = job.row0;
-    if (d < kLdsMaxD) row0 = rk_bwd_lds_dispatch<NT, LEN, 1>(k, row0, job.row1, coef, want_max, tile, slots, st);
+    if (d < kLdsMaxD) row0 = rk_bwd_lds_dispatch<NT, GROUPS, LEN, GROUPS ? 2 : 1>(k, row0, job.row1, coef, want_max, tile, slots, st);
     int rows = job.row1 - row0;   // rows left for the register path
     const int nb32 = rows >> 5;
-    if (nb32) { rk_bwd_segment<NT, LEN, 32>(k, row0, nb32, d, coef, want_max, slots, st); row0 += nb32 << 5; rows &= 31; }
+    if (nb32) { rk_bwd_segment<NT, GROUPS, LEN, 32>(k, row0, nb32, d, coef, want_max, slots, st); row0 += nb32 << 5; rows &= 31; }
     const int own_tail = (job.flags & 1) ? tail : 0;
-    if (d >= kFewMinD) {          // uniform
-        // With at least kFewMinD columns to a row the rows that are left (fewer than 32, and the partial last
-        // row) form one strip per column with a run-time row count: a whole kernel when it has few rows.
-        if (rows + (own_tail > 0 ? 1 : 0) > kBwdFewRowsMax) {
-            rk_bwd_band<NT, LEN, 16, 2>(k, row0, d, coef, want_max, slots, st);
+    // With at least kFewMinD columns to a row the rows that are left (fewer than 32, and the partial last
+    // row) form one strip per column with a run-time row count: a whole kernel when it has few rows.  With one wavefront a row
+    // of fewer columns is worth it too: no pass of the cascade below fills it either (28 x 18 x 158, groups of 16: from 256
+    // columns on 342 us, from 64 on 313, from 16 on 307).
+    if (d >= (GROUPS ? kLdsMaxD : kFewMinD)) {          // uniform
+        constexpr int few = GROUPS ? 16 : kBwdFewRowsMax;       // (a group has one more thing for each lane: its series' coefficient)
+        if (rows + (own_tail > 0 ? 1 : 0) > few) {
+            rk_bwd_band<NT, GROUPS, LEN, 16, 2>(k, row0, d, coef, want_max, slots, st);
             row0 += 16; rows -= 16;
         }
         const int nrows = rows + (own_tail > 0 ? 1 : 0);
         if (nrows == 0) return;
         if (nrows <= 8) { rk_bwd_few_rows<NT, LEN, 8>(k, row0, rows, own_tail, coef, want_max, slots, st); return; }
-        rk_bwd_few_rows<NT, LEN, kBwdFewRowsMax>(k, row0, rows, own_tail, coef, want_max, slots, st);
+        rk_bwd_few_rows<NT, LEN, few>(k, row0, rows, own_tail, coef, want_max, slots, st);
         return;
     }
     // smaller dilations: the binary remainder; the job that owns the partial last row does it last
-    if (rows & 16) { rk_bwd_band<NT, LEN, 16, 2>(k, row0, d, coef, want_max, slots, st); row0 += 16; }
-    if (rows & 8) { rk_bwd_band<NT, LEN, 8, 4>(k, row0, d, coef, want_max, slots, st); row0 += 8; }
-    if (rows & 4) { rk_bwd_band<NT, LEN, 4, 8>(k, row0, d, coef, want_max, slots, st); row0 += 4; }
-    if (rows & 2) { rk_bwd_band<NT, LEN, 2, 8>(k, row0, d, coef, want_max, slots, st); row0 += 2; }
-    if (rows & 1) { rk_bwd_band<NT, LEN, 1, 8>(k, row0, d, coef, want_max, slots, st); row0 += 1; }
-    if (own_tail) rk_bwd_band<NT, LEN, 1, 8>(k, total_rows, own_tail, coef, want_max, slots, st);
+    if (rows & 16) { rk_bwd_band<NT, GROUPS, LEN, 16, 2>(k, row0, d, coef, want_max, slots, st); row0 += 16; }
+    if (rows & 8) { rk_bwd_band<NT, GROUPS, LEN, 8, 4>(k, row0, d, coef, want_max, slots, st); row0 += 8; }
+    if (rows & 4) { rk_bwd_band<NT, GROUPS, LEN, 4, 8>(k, row0, d, coef, want_max, slots, st); row0 += 4; }
+    if (rows & 2) { rk_bwd_band<NT, GROUPS, LEN, 2, 8>(k, row0, d, coef, want_max, slots, st); row0 += 2; }
+    if (rows & 1) { rk_bwd_band<NT, GROUPS, LEN, 1, 8>(k, row0, d, coef, want_max, slots, st); row0 += 1; }
+    if (own_tail) rk_bwd_band<NT, GROUPS, LEN, 1, 8>(k, total_rows, own_tail, coef, want_max, slots, st);
 }
 
 // grid: one workgroup per (series, job), mapped by rk_block_to_pair; a job is a time tile of one
@@ -560,9 +573,9 @@ __global__ __launch_bounds__(NT) void rk_backward(const float *__restrict__ xpad
     st.qsum = 0.f;
     st.vmax = -INFINITY;
     st.targ = 0;
-    if (rec.len == 7) rk_backward_body<NT, 7>(k, rec.nout, job, coef, want_max, tile, slots, st);
-    else if (rec.len == 9) rk_backward_body<NT, 9>(k, rec.nout, job, coef, want_max, tile, slots, st);
-    else rk_backward_body<NT, 11>(k, rec.nout, job, coef, want_max, tile, slots, st);
+    if (rec.len == 7) rk_backward_body<NT, false, 7>(k, rec.nout, job, coef, want_max, tile, slots, st);
+    else if (rec.len == 9) rk_backward_body<NT, false, 9>(k, rec.nout, job, coef, want_max, tile, slots, st);
+    else rk_backward_body<NT, false, 11>(k, rec.nout, job, coef, want_max, tile, slots, st);
 
     // close the lane reductions: sum of q, and (max, first position) pairs
     float qsum = st.qsum, vmax = st.vmax;

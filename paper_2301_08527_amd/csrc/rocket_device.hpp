@@ -136,6 +136,7 @@ struct KernelCtx {
     const float *wts;      // this kernel's weights, channel-major
     int nch, d;
     int pad, L;            // the kernel's padding and the series length
+    int width;             // series that lie interleaved (backward pass over groups: d, pad and L are then that many times as large)
     float negbias;         // -bias
     uint32_t mask;
     float nl, ns;          // softPPV: exp2(z*nl + ns) = exp(-(lambda*y + shift))
@@ -194,6 +195,7 @@ __device__ __forceinline__ KernelCtx rk_make_ctx(const RkKernelRec &rec, const f
     k.d = rec.dil;
     k.pad = rec.pad;
     k.L = L;
+    k.width = 1;
     k.negbias = -rec.bias;
     k.mask = 0;
     k.nl = 0.f;

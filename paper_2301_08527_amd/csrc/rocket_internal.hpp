@@ -82,6 +82,39 @@ struct RkSet {
     int8_t read[16];           // ... or, where that is -1, reads this tap's samples against zero weights
 };
 
+// The series of a batch in groups of `width` (a power of two) that lie interleaved in the padded copy: a row of group g holds sample
+// t of its series s at t * width_of(g) + s, zeros in front as in the plain copy (lead * width_of(g) of them); the C rows of a
+// group and the groups follow one another.  The first group is the one that may be narrower, so that the zeros in front of a
+// row are always enough for the reads past the end of the one before.
+#ifdef __HIP__
+#define RK_BOTH __host__ __device__
+#else
+#define RK_BOTH
+#endif
+struct RkGroups {
+    static constexpr int kWidest = 64;     // one series for each lane of a wavefront
+    int32_t width, count, first_series, first_width;
+    RK_BOTH int width_of(int g) const { return g == 0 ? first_width : width; }
+    RK_BOTH int series_of(int g) const { return g == 0 ? first_series : width; }
+    RK_BOTH int series_before(int g) const { return g == 0 ? 0 : first_series + (g - 1) * width; }      // in the batch
+    RK_BOTH int slots_before(int g) const { return g == 0 ? 0 : first_width + (g - 1) * width; }        // in the copy
+};
+inline RkGroups rk_groups(int32_t B, int32_t width)
+{
+    RkGroups g;
+    g.width = width;
+    g.count = (B + width - 1) / width;
+    g.first_series = B - (g.count - 1) * width;
+    g.first_width = 1;
+    while (g.first_width < g.first_series) g.first_width *= 2;
+    return g;
+}
+// floats of the interleaved copy: its rows, and the zeros that end the last one
+inline int64_t rk_groups_floats(const RkGroups &g, int64_t rows, int64_t row_len, int64_t lead)
+{
+    return g.slots_before(g.count) * rows * row_len + lead * g.width_of(g.count - 1);
+}
+
 struct rocket_kernels {
     int32_t K = 0, C = 0, L = 0;
     std::vector<int32_t> length, dilation, padding, n_ch, channels;
@@ -176,6 +209,13 @@ struct RkLaunchers {
     // rk_launch_backward with one wavefront to a workgroup
     int (*backward_short)(const rocket_kernels *h, const float *xpad, int32_t B, const float *grad_out, int F, int plane_soft,
                           int plane_max, float lambda, float nl, float ns, float *partial, void *stream) = nullptr;
+    // rocket_prologue.hip: the interleaved padded copy, from floats or (`stats` as in rk_launch_pad_u8) from raw bytes
+    int (*pad_groups)(const rocket_kernels *h, const void *x, bool is_u8, int32_t B, const RkGroups &groups, float *xg, void *stats,
+                      void *stream) = nullptr;
+    // rocket_backward_groups.hip: the whole backward pass over such a copy; `partial` as in rk_groups_partial_floats
+    int (*backward_groups)(const rocket_kernels *h, const float *xg, const RkGroups &groups, const float *grad_out, int F,
+                           int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, float *grad_w,
+                           float *grad_b, void *stream) = nullptr;
 };
 RkLaunchers &rk_launchers();      // rocket_api.hip
 // rocket_api.hip: offsets, sets, job plan, padded row geometry; returns ROCKET_OK or an error

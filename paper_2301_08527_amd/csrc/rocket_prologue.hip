@@ -12,6 +12,8 @@
 //                     divide, rounded once to fp32.  A row with zero variance becomes zeros.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "rocket_internal.hpp"
 
 namespace {
@@ -125,19 +127,91 @@ __global__ __launch_bounds__(256) void rk_pad_rows_u8(const uint8_t *__restrict_
     }
 }
 
+// The padded copy of groups of interleaved series (RkGroups).  A workgroup turns a piece of kTurn floats of one row: it reads
+// `width` series, each a run of consecutive samples, and writes through LDS in the order of the copy.  Row number
+// count * C is the zeros that end the last row.
+constexpr int kTurn = 4096;
+template <class T>
+__global__ __launch_bounds__(256) void rk_pad_groups(const T *__restrict__ x, const double2 *__restrict__ stats, float *__restrict__ xg,
+                                                     int L, int lead, int row_len, int C, RkGroups groups)
+{
+    __shared__ float turn[kTurn + RkGroups::kWidest];      // `width` rows of kTurn / width + 1
+    const int tid = static_cast<int>(threadIdx.x), rows = groups.count * C;
+    for (int row = static_cast<int>(blockIdx.y); row <= rows; row += static_cast<int>(gridDim.y)) {
+        const int g = min(row / C, groups.count - 1), c = row - g * C;
+        const int width = groups.width_of(g), series = row < rows ? groups.series_of(g) : 0;
+        const int log = __builtin_ctz(width), run = kTurn >> log;
+        const int first = static_cast<int>(blockIdx.x) * kTurn;      // of the row's floats
+        const int floats = (row < rows ? row_len : lead) * width;
+        if (first < floats) {       // uniform
+            const int t0 = (first >> log) - lead;
+            for (int i = tid; i < kTurn; i += 256) {
+                const int s = i / run, t = i - s * run, at = t0 + t;
+                float v = 0.f;
+                if (s < series && at >= 0 && at < L) {
+                    const size_t from = static_cast<size_t>(groups.series_before(g) + s) * C + c;
+                    const T sample = x[from * L + at];
+                    if constexpr (sizeof(T) == 1) {
+                        const double2 ms = stats[from];
+                        v = ms.y > 0.0 ? static_cast<float>((static_cast<double>(sample) - ms.x) / ms.y) : 0.f;
+                    } else {
+                        v = sample;
+                    }
+                }
+                turn[s * (run + 1) + t] = v;
+            }
+            __syncthreads();
+            float *to = xg + (static_cast<size_t>(groups.slots_before(g)) * C + static_cast<size_t>(c) * width) * row_len + first;
+            for (int i = tid * 4; i < kTurn && first + i < floats; i += 1024) {     // whole quads: floats is a multiple of 64
+                float4 v;
+                float *e = &v.x;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e[q] = turn[((i + q) & (width - 1)) * (run + 1) + ((i + q) >> log)];
+                *reinterpret_cast<float4 *>(to + i) = v;
+            }
+            __syncthreads();        // done with `turn`
+        }
+    }
+}
+
+static int launch_row_stats_u8(const rocket_kernels *h, const uint8_t *x, int nrows, double2 *stats, hipStream_t stream)
+{
+    // 1,024 lanes where a row gives each of them samples
+    const dim3 rows(static_cast<unsigned>(nrows < 65536 ? nrows : 65536));
+    if (h->L >= 16384) hipLaunchKernelGGL(rk_row_stats_u8<1024>, rows, dim3(1024), 0, stream, x, h->L, nrows, stats);
+    else hipLaunchKernelGGL(rk_row_stats_u8<256>, rows, dim3(256), 0, stream, x, h->L, nrows, stats);
+    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+}
+
 int rk_launch_pad_u8(const rocket_kernels *h, const uint8_t *x, int32_t B, float *xpad, void *stats_ptr,
                      void *stream_ptr)
 {
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     double2 *stats = static_cast<double2 *>(stats_ptr);
     const int nrows = B * h->C;
-    // 1,024 lanes where a row gives each of them samples
-    const dim3 rows(static_cast<unsigned>(nrows < 65536 ? nrows : 65536));
-    if (h->L >= 16384) hipLaunchKernelGGL(rk_row_stats_u8<1024>, rows, dim3(1024), 0, stream, x, h->L, nrows, stats);
-    else hipLaunchKernelGGL(rk_row_stats_u8<256>, rows, dim3(256), 0, stream, x, h->L, nrows, stats);
-    if (hipGetLastError() != hipSuccess) return ROCKET_EHIP;
+    if (launch_row_stats_u8(h, x, nrows, stats, stream) != ROCKET_OK) return ROCKET_EHIP;
     dim3 grid(static_cast<unsigned>((h->row_len + 1024 * kPadRounds - 1) / (1024 * kPadRounds)), static_cast<unsigned>(nrows < 32768 ? nrows + 1 : 32768));
     hipLaunchKernelGGL(rk_pad_rows_u8, grid, dim3(256), 0, stream, x, stats, xpad, h->L, h->lead,
                        static_cast<int>(h->row_len), nrows);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
+
+static int launch_pad_groups(const rocket_kernels *h, const void *x, bool is_u8, int32_t B, const RkGroups &groups, float *xg,
+                             void *stats_ptr, void *stream_ptr)
+{
+    hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
+    double2 *stats = static_cast<double2 *>(stats_ptr);
+    if (is_u8 && launch_row_stats_u8(h, static_cast<const uint8_t *>(x), B * h->C, stats, stream) != ROCKET_OK) return ROCKET_EHIP;
+    const int64_t rows = static_cast<int64_t>(groups.count) * h->C + 1, widest = std::max(groups.first_width, groups.width_of(groups.count - 1));
+    const dim3 grid(static_cast<unsigned>((h->row_len * widest + kTurn - 1) / kTurn), static_cast<unsigned>(std::min<int64_t>(rows, 32768)));
+    const int row_len = static_cast<int>(h->row_len);
+    if (is_u8)
+        hipLaunchKernelGGL(rk_pad_groups<uint8_t>, grid, dim3(256), 0, stream, static_cast<const uint8_t *>(x), stats, xg, h->L, h->lead,
+                           row_len, h->C, groups);
+    else
+        hipLaunchKernelGGL(rk_pad_groups<float>, grid, dim3(256), 0, stream, static_cast<const float *>(x), stats, xg, h->L, h->lead,
+                           row_len, h->C, groups);
+    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+}
+
+[[maybe_unused]] static const bool kEntered = (rk_launchers().pad_groups = launch_pad_groups, true);

@@ -1,0 +1,140 @@
+// Drives the choice of the backward pass's groups of interleaved series under AddressSanitizer and UndefinedBehaviorSanitizer without
+// a GPU: the launchers are stubs that record what they were given.  Linked like host_driver.cpp.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+
+#include "rocket_internal.hpp"
+
+static std::string g_route;
+static RkGroups g_groups;
+static uintptr_t g_copy, g_partial, g_stats;
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { *p = std::malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+}
+
+#define RECORD(name) { g_route += name " "; return ROCKET_OK; }
+int rk_launch_pad(const rocket_kernels *, const float *, int32_t, float *, void *) RECORD("pad")
+int rk_launch_mse_grad(const double *, const float *, const double *, int32_t, int32_t, float *, double *, void *) RECORD("mse")
+int rk_launch_sgd_update(const rocket_kernels *, const float *, const float *, float, int, void *) RECORD("sgd")
+int rk_launch_pad_u8(const rocket_kernels *, const uint8_t *, int32_t, float *, void *, void *) RECORD("pad_u8")
+int rk_launch_forward(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("forward")
+int rk_launch_forward_short(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("short")
+int rk_launch_finalize(const rocket_kernels *, const float *, int32_t, uint32_t, float *, void *) RECORD("finalize")
+int rk_launch_backward(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
+                       float *, void *) RECORD("backward")
+int rk_launch_reduce_jobs(const rocket_kernels *, const float *, const float *, int32_t, const float *, int, int, float *,
+                          float *, void *) RECORD("reduce")
+int rk_launch_minirocket_outputs(const rocket_kernels *, const float *, const int32_t *, int32_t, int32_t, int64_t, float *,
+                                 void *) RECORD("mr_outputs")
+int rk_launch_minirocket_select(const rocket_kernels *, const int32_t *, int32_t, int32_t, int64_t, const float *, void *)
+    RECORD("mr_select")
+int rk_launch_minirocket_clear(const rocket_kernels *, int32_t, int32_t *, void *) RECORD("mr_clear")
+extern "C" int rocket_ridge_predict(const float *, int32_t, int32_t, const double *, const double *, double *, void *)
+    RECORD("ridge_predict")
+
+static int backward_short_stub(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
+                               float *, void *) RECORD("backward_short")
+static int pad_groups_stub(const rocket_kernels *, const void *, bool is_u8, int32_t, const RkGroups &g, float *xg, void *stats, void *)
+{
+    g_groups = g;
+    g_copy = reinterpret_cast<uintptr_t>(xg);
+    g_stats = reinterpret_cast<uintptr_t>(stats);
+    g_route += is_u8 ? "pad_groups_u8 " : "pad_groups ";
+    return ROCKET_OK;
+}
+static int backward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, const float *, int, int, int, float, float, float,
+                                float *partial, float *, float *, void *)
+{
+    g_partial = reinterpret_cast<uintptr_t>(partial);
+    g_route += "backward_groups ";
+    return ROCKET_OK;
+}
+[[maybe_unused]] static const bool kEntered = (rk_launchers().backward_short = backward_short_stub, rk_launchers().pad_groups = pad_groups_stub,
+                                               rk_launchers().backward_groups = backward_groups_stub, true);
+
+#define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s (route: %s, width %d of %d)\n", __LINE__, #cond, g_route.c_str(), g_groups.width, g_groups.first_series); return 1; } } while (0)
+
+alignas(256) static char there[256];
+
+static int backward(rocket_kernels *h, int32_t B, bool u8 = false)
+{
+    g_route.clear();
+    g_groups = rk_groups(B, 1);
+    float *at = reinterpret_cast<float *>(there);
+    const size_t bytes = rocket_workspace_bytes(h, B, 4, 1);
+    return u8 ? rocket_soft_ppv_backward_u8(h, reinterpret_cast<const uint8_t *>(there), B, 4, at, 10.f, -3.f, 0, at, at, there, bytes, nullptr)
+              : rocket_soft_ppv_backward(h, at, B, 4, at, 10.f, -3.f, 0, at, at, there, bytes, nullptr);
+}
+
+// The series of a batch are in one group each, and what the groups need is inside the workspace.
+static int inside(rocket_kernels *h, int32_t B)
+{
+    const RkGroups &g = g_groups;
+    int next = 0, slots = 0;
+    for (int i = 0; i < g.count; ++i) {
+        CHECK(g.series_before(i) == next && g.slots_before(i) == slots);
+        CHECK(g.series_of(i) >= 1 && g.series_of(i) <= g.width_of(i) && g.width_of(i) <= g.width && g.width <= RkGroups::kWidest);
+        next += g.series_of(i);
+        slots += g.width_of(i);
+    }
+    CHECK(next == B);
+    const uintptr_t first = reinterpret_cast<uintptr_t>(there), end = first + rocket_workspace_bytes(h, B, 4, 1);
+    CHECK(g_copy == first && g_partial >= first + rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192);
+    const uintptr_t sums = g.count > 1 ? (h->w_off[h->K] + h->K) * 4 * g.count : 0;
+    CHECK(g_partial + sums <= g_stats && g_stats + static_cast<uintptr_t>(B) * h->C * 16 <= end);
+    return 0;
+}
+
+int main()
+{
+    // the widths that tests/test_gpu_groups.py relies on, then the edges of the rule: one series, few kernels, long series, more tiles
+    const struct { int32_t B, C, L, K, width, first; } want[] = {
+        {9, 2, 2000, 4000, 2, 1}, {13, 3, 700, 3000, 4, 1}, {27, 2, 400, 2500, 8, 3}, {13, 2, 128, 6000, 16, 13}, {70, 1, 100, 4000, 32, 6},
+    {200, 1, 40, 6000, 64, 8}, {130, 1, 25, 4000, 64, 2}, {3, 1, 61, 9000, 4, 3}, {200, 9, 90, 700, 16, 8}, {6, 1, 11, 3000, 8, 6},
+        {1, 5, 300, 4000, 1, 1}, {16, 3, 4099, 500, 1, 1}, {64, 20, 17000, 300, 1, 1}};
+    for (const auto &w : want) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        CHECK(backward(h, w.B) == ROCKET_OK);
+        CHECK(g_groups.width == w.width && (w.width == 1 || g_groups.first_series == w.first));
+        CHECK((g_route == "pad_groups backward_groups ") == (w.width > 1));
+        if (w.width > 1) {
+            if (inside(h, w.B)) return 1;
+            CHECK(backward(h, w.B, true) == ROCKET_OK && g_route == "pad_groups_u8 backward_groups ");
+            if (inside(h, w.B)) return 1;
+        }
+        rocket_free_kernels(h);
+    }
+    // all batches of a few handles, one with hardly any partial results to make room in
+    const int32_t handles[][3] = {{1, 1, 3000}, {1, 20, 500}, {7, 3, 64}, {300, 2, 200}, {2000, 1, 333}};
+    for (const auto &s : handles) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(4, s[0], s[1], s[2], &h) == ROCKET_OK);
+        for (int32_t B = 1; B <= 300; ++B) {
+            CHECK(backward(h, B) == ROCKET_OK);
+            if (g_groups.width > 1 && inside(h, B)) return 1;
+        }
+        rocket_free_kernels(h);
+    }
+    // an imported kernel wider than its series by far stays out of the groups
+    const int32_t length = 11, dilation = 300000000, padding = 1500000000, n_ch = 1, channel = 0;
+    const float bias = 0.f, weights[11] = {1.f};
+    rocket_kernels *h = nullptr;
+    CHECK(rocket_kernels_import(1, 1, 100, &length, &dilation, &padding, &bias, &n_ch, &channel, weights, &h) == ROCKET_OK);
+    CHECK(backward(h, 64) == ROCKET_OK && g_route == "pad backward_short reduce ");
+    rocket_free_kernels(h);
+    std::puts("groups driver: ok");
+    return 0;
+}

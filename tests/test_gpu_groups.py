@@ -1,0 +1,109 @@
+"""The backward pass over groups of interleaved short series (needs an MI355X): against the oracle, against the same kernels one
+series at a time, and its rule for exact ties."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2301_08527_amd import rocket
+from parity import check_backward
+
+pytestmark = pytest.mark.gpu
+
+
+def _gpu(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _raw(rng, shape):
+    """8-bit samples and the floats that the entry points make of them"""
+    x = rng.integers(0, 256, size=shape, dtype=np.uint8)
+    v = x.astype(np.float64)
+    return x, ((v - v.mean(axis=-1, keepdims=True)) / v.std(axis=-1, keepdims=True)).astype(np.float32)
+
+
+# Widths that the rule gives (tests/sanitize/groups_driver.cpp checks them), as (width, series of the first group).  Narrow groups reach
+# the staged small dilations (width x dilation below 16) and bands of 32 rows, wide ones of short series the few-rows strips only; first
+# groups of one series, as wide as the others and narrower, with all their series and with idle ones (3 of 4, 13 of 16).
+CASES = [
+    (9, 2, 2000, 4000, (2, 1)), (13, 3, 700, 3000, (4, 1)), (27, 2, 400, 2500, (8, 3)), (13, 2, 128, 6000, (16, 13)), (70, 1, 100, 4000, (32, 6)),
+    (200, 1, 40, 6000, (64, 8)), (130, 1, 25, 4000, (64, 2)), (3, 1, 61, 9000, (4, 3)), (200, 9, 90, 700, (16, 8)), (6, 1, 11, 3000, (8, 6)),
+]
+
+
+@pytest.mark.parametrize("B,C,L,K,groups", CASES)
+@pytest.mark.parametrize("u8", [False, True])
+def test_groups_against_the_oracle(B, C, L, K, groups, u8):
+    import torch
+    rng = np.random.default_rng(L + B)
+    if u8:
+        raw, x = _raw(rng, (B, C, L))
+        entry, xd = rocket.rocket_soft_ppv_backward_u8, _gpu(raw)
+    else:
+        x = rng.standard_normal((B, C, L)).astype(np.float32)
+        entry, xd = rocket.rocket_soft_ppv_backward, _gpu(x)
+    h = rocket.rocket_make_kernels(L, K, C, L)
+    kr = rocket.rocket_kernels_view_get(h)
+    g = rng.standard_normal((B, 2 * K)).astype(np.float32)
+    sel = np.arange(0, K, max(1, K // 150), dtype=np.int32)
+    print("groups", B, C, L, K, groups, "u8" if u8 else "f32", flush=True)
+    gw, gb = entry(h, xd, 4, _gpu(g[:, K:]), 4.0, -3.0, False)
+    check_backward(x, kr, gw.cpu().numpy(), gb.cpu().numpy(), g[:, K:], None, 4.0, -3.0, sel=sel)
+    gw, gb = entry(h, xd, 5, _gpu(g), 4.0, -3.0, True)
+    sel = sel[oracle.transform(x, kr, sel=sel)["gap"].min(axis=0) > 1e-4]      # the largest output is the same one in fp32 and fp64
+    assert len(sel) > 20
+    check_backward(x, kr, gw.cpu().numpy(), gb.cpu().numpy(), g[:, K:], g[:, :K], 4.0, -3.0, sel=sel)
+    again = entry(h, xd, 5, _gpu(g), 4.0, -3.0, True)
+    assert torch.equal(again[0], gw) and torch.equal(again[1], gb)
+
+
+@pytest.mark.parametrize("B,C,L,K,groups", CASES)
+def test_groups_equal_single_series(B, C, L, K, groups):
+    """gradients add up over the batch: every kernel, with both planes, where no series alone is a group"""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn((B, C, L), generator=gen, device="cuda")
+    gout = torch.randn((B, 2 * K), generator=gen, device="cuda")
+    h = rocket.rocket_make_kernels(L + 1, K, C, L)
+    print("groups and single series", B, C, L, K, groups, flush=True)
+    ws = torch.full((rocket.rocket_workspace_bytes(h, B, 5, True),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing writes
+    whole = rocket.rocket_soft_ppv_backward(h, x, 5, gout, 10.0, -3.0, True, workspace=ws)
+    parts = [rocket.rocket_soft_ppv_backward(h, x[b:b + 1].contiguous(), 5, gout[b:b + 1].contiguous(), 10.0, -3.0, True) for b in range(B)]
+    for i in (0, 1):
+        a, want = whole[i].double(), sum(p[i].double() for p in parts)
+        # fp32 sums of the same terms in another order: 2^-24 sqrt(B L terms) of sums around their rms, tenfold
+        assert float((a - want).norm()) <= 1e-5 * float(want.norm())
+        assert float((a - want).abs().max()) <= 1e-4 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("B,L", [(9, 1500), (24, 700), (30, 150)])
+def test_exact_ties_in_groups(B, L):
+    """small-integer samples and one non-zero tap per channel: all sums are exact, nearly every largest output is attained many times, and
+    the first position of each series must get its gradient"""
+    import torch
+    rng = np.random.default_rng(L)
+    C = 3
+    spec = [(ln, d, p) for ln in (7, 9, 11) for d in sorted({1, 2, 3, 5, 7, 8, 15, 16, 31, 40, (L - 1) // (ln - 1)}) if d * (ln - 1) < L
+            for p in (False, True)] * 20
+    K = len(spec)
+    length, dil = (np.array([s[i] for s in spec], np.int32) for i in (0, 1))
+    pad = np.array([(s[0] - 1) * s[1] // 2 if s[2] else 0 for s in spec], np.int32)
+    nch = rng.integers(1, C + 1, K).astype(np.int32)
+    chans = np.concatenate([rng.permutation(C)[:m] for m in nch]).astype(np.int32)
+    rows = []
+    for k in range(K):
+        for _ in range(nch[k]):
+            row = np.zeros(length[k], np.float32)
+            row[rng.integers(0, length[k])] = float(rng.choice([1.0, 2.0, -1.0]))
+            rows.append(row)
+    h = rocket.rocket_kernels_import(K, C, L, length, dil, pad, rng.integers(-2, 3, K).astype(np.float32) * 0.25, nch, chans, np.concatenate(rows))
+    kr = rocket.rocket_kernels_view_get(h)
+    x = rng.integers(-2, 3, size=(B, C, L)).astype(np.float32)
+    g = np.zeros((B, 2 * K), np.float32)
+    g[:, :K] = rng.integers(1, 4, size=(B, K)).astype(np.float32)
+    print("ties in groups", B, L, flush=True)
+    gw, gb = rocket.rocket_soft_ppv_backward(h, _gpu(x), 5, _gpu(g), 10.0, -3.0, True)
+    torch.cuda.synchronize()
+    gw_ref, gb_ref = oracle.backward(x, kr, g[:, K:].astype(np.float64), g[:, :K].astype(np.float64), lam=10.0, shift=-3.0)
+    assert np.array_equal(gw.cpu().numpy().astype(np.float64), gw_ref)
+    assert np.array_equal(gb.cpu().numpy().astype(np.float64), gb_ref)
