@@ -622,6 +622,88 @@ static int pad_batch(const rocket_kernels *h, const void *x_dev, bool is_u8, int
     return rc == ROCKET_OK ? ROCKET_OK : rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
 }
 
+// ------------------------------------------------------------------ groups of interleaved series
+
+// Workspace of a pass over groups: bytes of the interleaved copy (8 KB of slack as in padded_batch_bytes), and the gradient sums that the
+// backward pass keeps of every group where there are several.
+static size_t grouped_copy_bytes(const rocket_kernels *h, const RkGroups &g)
+{
+    return static_cast<size_t>(round_up(rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192, 256));
+}
+static size_t grouped_partial_bytes(const rocket_kernels *h, const RkGroups &g)
+{
+    return g.count > 1 ? static_cast<size_t>(g.count) * static_cast<size_t>(h->w_off[h->K] + h->K) * 4 : 0;
+}
+
+// The work of `jobs` jobs of `series` series each on `wavefronts` wavefronts, spread over the chip's 1,024 SIMDs, and what the longest
+// of them adds, in instructions of a wavefront.  An output costs its lane a multiply-add (the backward pass: two) for each weight, and
+// `pooling` more; the strips that do not fill a wavefront come to `rest` outputs more for each lane.  The longest job shares
+// its SIMD with others and adds 3.5 times its own time.
+struct Estimate { double work, last; };
+static Estimate estimate(const rocket_kernels *h, double jobs, int wavefronts, double series, double rest, double passes, double pooling)
+{
+    const double each = series * h->outputs / h->K / (64.0 * wavefronts) + rest;
+    return {jobs * wavefronts * each * (passes * h->conv_fma / h->outputs + pooling) / 1024.0, 3.5 * each * (passes * h->max_terms + pooling)};
+}
+
+// The groups with the least estimate: wide ones waste less on each series, narrow ones make more and shorter jobs.  Width 1 (no groups)
+// where `plain`, the estimate of one series at a time, is less, or where a job is not a whole kernel or the workspace, whose size
+// does not depend on any of this, does not hold the groups.
+static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, double pooling, double plain, int backward)
+{
+    const int64_t series_bytes = h->row_len * h->C * 4;
+    RkGroups best = rk_groups(B, 1, series_bytes);
+    if (h->jobs.size() != static_cast<size_t>(h->K)) return best;
+    for (int32_t width = 2; width <= RkGroups::kWidest && width < 2 * B; width *= 2) {
+        if (h->row_len * width > (1 << 24)) break;      // 32-bit byte offsets of 42 dilation steps
+        const RkGroups g = rk_groups(B, width, series_bytes);
+        if (grouped_copy_bytes(h, g) + (backward ? grouped_partial_bytes(h, g) : 0) > row_stats_offset(h, B, backward)) continue;
+        const Estimate first = estimate(h, h->K, 1, g.first_width, 20, passes, pooling);
+        const Estimate others = estimate(h, static_cast<double>(h->K) * (g.count - 1), 1, width, 20, passes, pooling);
+        const double t = first.work + others.work + (g.count > 1 ? others.last : first.last);
+        if (t < plain) { plain = t; best = g; }
+    }
+    return best;
+}
+
+// The groups of a transform without softPPV (rocket_forward_groups.hip).  Of 21 shapes measured at every width the rule takes the
+// fastest or one within 8 % of it; what it chooses, against one series at a time, max and PPV, in us: 28 x 15 x 134 and 2,351 kernels
+// 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236 88/402 (32 series; 16: 91, 64: 103), 4 x 5 x 300 and 10,000 33/49 (4), 149 x 18 x 1,263 and
+// 4,822 1,076/1,640 (8; 2: 1,315, 32: 1,415), 227 x 16 x 930 and 5,723 1,386/2,210 (16; 4: 1,575).  Series of thousands of samples gain
+// little or nothing (23 x 6 x 4,099 and 1,537 185/181, 16 x 3 x 2,000 and 300 30/24), so the estimate has to be a tenth better.
+static RkGroups forward_groups(const rocket_kernels *h, int32_t B, uint32_t mask)
+{
+    if (!rk_launchers().forward_groups || (mask & ROCKET_F_SOFTPPV) || h->L > kShortSeries) return rk_groups(B, 1, 1);
+    const Estimate plain = estimate(h, static_cast<double>(B) * h->K, 1, 1, 20, 1, 6);
+    return best_groups(h, B, 1, 6, 0.9 * (plain.work + plain.last), 0);
+}
+
+// Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
+// 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 460 us against 183 with 64 lanes; 64 x 20 x 2,000, 200 kernels 267 and 171;
+// 4 x 20 x 1,400, 200 kernels 50 and 61).  Longer ones take longer on one wavefront, the more so with many channels, which pays where
+// enough others run beside it: 256 against 64 lanes at 12,800 jobs 64 x 20 x 3,000 275 and 251 us, 64 x 20 x 8,192 437 and
+// 575, 64 x 6 x 6,000 291 and 270, 64 x 1 x 8,192 177 and 162; at 64,000 64 x 20 x 8,192 1,628 and 1,505; at 3,200
+// 16 x 1 x 4,000 43 and 43, 16 x 6 x 4,000 77 and 88, 16 x 20 x 3,000 95 and 137.
+static bool one_wavefront_jobs(const rocket_kernels *h, int32_t B)
+{
+    const int64_t work = static_cast<int64_t>(B) * h->jobs.size();
+    return h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
+}
+
+// The groups of a backward pass (rocket_backward_groups.hip).  Of 20 shapes measured at every width the rule takes the fastest or one
+// within 6 % of it for 19; what it chooses, against one series at a time, in us: 64 x 1 x 1,000 and 1,000 kernels 95/184 (4 series; 8: 92,
+// 2: 113, 16: 108), 98 x 1 x 246 and 1,082 55/279 (16; 4: 76), 28 x 18 x 158 and 15,408 309/1,820 (16; 4: 475), 27 x 19 x 595 and 2,590
+// 199/365 (4; 2: 229, 8: 228), 167 x 9 x 1,205 and 1,737 998/1,875 (4; 8: 949, 32: 1,688).  Series of more than some 4,000 samples gain
+// little or nothing (23 x 6 x 4,099 and 1,537 390/416, 16 x 3 x 4,099 and 500 103/93).  The 20th: 9 x 5 x 500 and 10,000 kernels, one and
+// eight series 219 us, one, four and four 179.
+static RkGroups backward_groups(const rocket_kernels *h, int32_t B)
+{
+    if (!rk_launchers().backward_groups) return rk_groups(B, 1, 1);
+    // one series at a time: four wavefronts waste 10 outputs of a lane each, single ones 20 and, with the sum over the series, a third more
+    const Estimate plain = one_wavefront_jobs(h, B) ? estimate(h, 1.3 * B * h->K, 1, 1, 20, 2, 25) : estimate(h, 1.0 * B * h->K, 4, 1, 10, 2, 25);
+    return best_groups(h, B, 2, 25, plain.work + plain.last, 1);
+}
+
 // `resident_only`: the call may not allocate, so the handle's device mirror must already be there
 // and current (ensure_device would allocate and copy), and no timing events are created.
 static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, bool is_u8, int32_t B, uint32_t mask,
@@ -649,6 +731,16 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     // the padded copy); the sets' edges rest on lambda > 0.  Which path a call takes follows from the handle and from lambda, never
     // from the batch.
     const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
+    const RkGroups groups = series ? RkGroups{} : forward_groups(h, B, mask);
+    if (!series && groups.width > 1) {
+        if (rk_launchers().pad_groups(h, x_dev, is_u8, B, groups, xpad, static_cast<char *>(ws) + row_stats_offset(h, B, 0), stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
+        if (!resident_only) rc = profile_mark(h, stream, true);
+        if (rc != ROCKET_OK) return rc;
+        if (rk_launchers().forward_groups(h, xpad, groups, mask, out_dev, stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the forward kernel failed");
+        return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
+    }
     if (is_u8 || !series) {
         rc = pad_batch(h, x_dev, is_u8, B, ws, 0, stream);
         if (rc != ROCKET_OK) return rc;
@@ -750,62 +842,6 @@ extern "C" int rocket_infer(rocket_kernels *h, const void *x_dev, int x_is_u8, i
     if (rc != ROCKET_OK) return rc;
     return rocket_ridge_predict(features_dev, B, rocket_num_features(mask) * h->K, coef_dev, intercept_dev, pred_dev,
                                 hip_stream);
-}
-
-// Workspace of a backward pass over groups: bytes of the interleaved copy (8 KB of slack as in padded_batch_bytes), then the
-// gradient sums of every group where there are several.
-static size_t grouped_copy_bytes(const rocket_kernels *h, const RkGroups &g)
-{
-    return static_cast<size_t>(round_up(rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192, 256));
-}
-static size_t grouped_partial_bytes(const rocket_kernels *h, const RkGroups &g)
-{
-    return g.count > 1 ? static_cast<size_t>(g.count) * static_cast<size_t>(h->w_off[h->K] + h->K) * 4 : 0;
-}
-
-// Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
-// 256 lanes idle (64 x 1 x 1,000, 1,000 kernels: 460 us against 183 with 64 lanes; 64 x 20 x 2,000, 200 kernels 267 and 171;
-// 4 x 20 x 1,400, 200 kernels 50 and 61).  Longer ones take longer on one wavefront, the more so with many channels, which pays where
-// enough others run beside it: 256 against 64 lanes at 12,800 jobs 64 x 20 x 3,000 275 and 251 us, 64 x 20 x 8,192 437 and
-// 575, 64 x 6 x 6,000 291 and 270, 64 x 1 x 8,192 177 and 162; at 64,000 64 x 20 x 8,192 1,628 and 1,505; at 3,200
-// 16 x 1 x 4,000 43 and 43, 16 x 6 x 4,000 77 and 88, 16 x 20 x 3,000 95 and 137.
-static bool one_wavefront_jobs(const rocket_kernels *h, int32_t B)
-{
-    const int64_t work = static_cast<int64_t>(B) * h->jobs.size();
-    return h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
-}
-
-// The groups in which a backward pass takes the batch (rocket_backward_groups.hip); width 1: none, one series at a time.
-// What a lane spends on an output is 2 n_ch len multiply-adds and the like of 25 more for the sigmoid and the largest output; a
-// wavefront's shares of the bands that do not fill it come to some 20 outputs more for each lane (10 in each of four wavefronts; a
-// third more for one series at a time).  That work is spread over the chip's 1,024 SIMDs, and the longest job, which shares
-// its SIMD with four others, adds 3.5 times its own time: wide groups waste less on each series, narrow ones make more and
-// shorter jobs.  Of 20 shapes measured at every width the rule takes the fastest or one within 5 % of it for 19; what it
-// chooses, against one series at a time, in us: 64 x 1 x 1,000 and 1,000 kernels 92/184 (4 series; 8: 91, 2: 111, 16: 107),
-// 98 x 1 x 246 and 1,082 54/279 (16; 4: 75, 64: 94), 28 x 18 x 158 and 15,408 307/1,820 (16; 4: 470), 27 x 19 x 595 and 2,590 197/365
-// (4; 2: 226, 8: 236), 167 x 9 x 1,205 and 1,737 1,060/1,870 (4; 8: 1,057, 32: 1,474).  Series of more than some 4,000 samples gain little
-// or nothing (23 x 6 x 4,099 and 1,537 389/413, 16 x 3 x 4,099 and 500 103/93).  The 20th: 9 x 5 x 500 and 10,000 kernels, one
-// and eight series 219 us, one, four and four 178.
-static RkGroups backward_groups(const rocket_kernels *h, int32_t B)
-{
-    RkGroups best = rk_groups(B, 1);
-    if (!rk_launchers().backward_groups || h->jobs.size() != static_cast<size_t>(h->K)) return best;       // a job is a whole kernel
-    const double n = h->outputs / h->K, mean = 2.0 * h->conv_fma / h->outputs + 25.0, most = 2.0 * h->max_terms + 25.0;
-    auto estimate = [&](double jobs, int wavefronts, double series, double rest) {     // jobs of `series` series, in instructions
-        const double each = series * n / (64.0 * wavefronts) + rest;
-        return std::make_pair(jobs * wavefronts * each * mean / 1024.0, 3.5 * each * most);
-    };
-    const auto plain = one_wavefront_jobs(h, B) ? estimate(1.3 * B * h->K, 1, 1, 20) : estimate(1.0 * B * h->K, 4, 1, 10);
-    double least = plain.first + plain.second;
-    for (int32_t width = 2; width <= RkGroups::kWidest && width < 2 * B; width *= 2) {
-        const RkGroups g = rk_groups(B, width);
-        if (grouped_copy_bytes(h, g) + grouped_partial_bytes(h, g) > row_stats_offset(h, B, 1)) continue;     // the workspace is what it is
-        if (h->row_len * width > (1 << 24)) break;      // 32-bit byte offsets of 42 dilation steps
-        const auto first = estimate(h->K, 1, g.first_width, 20), rest = estimate(static_cast<double>(h->K) * (g.count - 1), 1, width, 20);
-        const double t = first.first + rest.first + std::max(first.second, g.count > 1 ? rest.second : 0.0);
-        if (t < least) { least = t; best = g; }
-    }
-    return best;
 }
 
 static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, bool is_u8, int32_t B, uint32_t mask,

@@ -37,30 +37,15 @@ __global__ __launch_bounds__(kGroupLanes) __attribute__((amdgpu_waves_per_eu(5))
     __shared__ float slots[(kBwdMaxTerms + 1) * kSlots];
     __shared__ float s_g[RkGroups::kWidest];
     __shared__ int s_at[RkGroups::kWidest];
-    // Kernels in the order of their cost, the groups of a kernel side by side.  The XCDs take workgroups in turn: with a narrower first
-    // group the groups rotate, or an even number of them would give that group's short jobs to the same XCDs every time.
-    const int jid = static_cast<int>(blockIdx.x) / groups.count;
-    int g = static_cast<int>(blockIdx.x) - jid * groups.count;
-    if (groups.first_width != groups.width) g = (g + jid / kXcds) % groups.count;
+    int jid, g;
+    rk_group_pair(groups, K, jid, g);
     const RkJob job = jobs[jid];
     const int kid = job.kernel;
     const RkKernelRec rec = recs[kid];
     const int tid = static_cast<int>(threadIdx.x);
     const int width = groups.width_of(g), series = groups.series_of(g);
     const int s = tid & (width - 1);
-    KernelCtx k;
-    k.row_bytes = static_cast<size_t>(row_len) * width * 4;
-    k.xk = reinterpret_cast<const char *>(xg + static_cast<size_t>(groups.slots_before(g)) * C * row_len + static_cast<size_t>(lead - rec.pad) * width);
-    k.span_bytes = static_cast<uint32_t>((row_len + rec.pad) * width) * 4u;    // to the end of the next row's gap
-    k.chans = channels + rec.ch_off;
-    k.wts = weights + rec.w_off;
-    k.nch = rec.nch;
-    k.d = rec.dil * width;
-    k.pad = rec.pad * width;
-    k.L = L * width;
-    k.width = width;
-    k.negbias = -rec.bias;
-    k.mask = 0;
+    KernelCtx k = rk_make_group_ctx(rec, xg, row_len, lead, L, C, groups, g, channels, weights);
     k.nl = nl;
     k.ns = fmaf(rec.bias, nl, ns);
 

@@ -21,7 +21,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct PoolState {
     float vmax;   // per lane
     float ssum;   // per lane
-    int cnt;      // wavefront-uniform: positives seen by this wavefront
+    int cnt;      // wavefront-uniform: positives seen by this wavefront (groups of interleaved series: per lane)
 };
 
 // Raw buffer descriptor (stride 0, 32-bit data format) over `bytes` bytes at `base`.
@@ -82,8 +82,10 @@ __device__ __forceinline__ void rk_taps(const float (&w)[LEN], float xv, float (
 // Pooling of R finished sums z = y - bias (section 3.2).  The bias is folded into
 // the pooling: max(y) = max(z) + bias (added once per kernel at the end),
 // y > 0 <=> z > -bias, and lambda*y + shift = lambda*z + (shift + lambda*bias).
-// `mask` is uniform; ns already contains the bias term.
-template <int R>
+// `mask` is uniform; ns already contains the bias term.  With GROUPS the lanes of a wavefront have positions of different series and
+// count for themselves: v_cmp and v_addc instead of v_cmp and two scalar instructions (written out: from the C form the compiler
+// made selects and sums of them, and spilled).
+template <int R, bool GROUPS = false>
 __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, float negbias, float nl, float ns,
                                         PoolState &st)
 {
@@ -93,7 +95,11 @@ __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, fl
     }
     if (mask & ROCKET_F_PPV) {   // Eq. 1-2: strict y > 0, counted per wavefront in a scalar register
 #pragma unroll
-        for (int i = 0; i < R; ++i) st.cnt += __builtin_popcountll(__ballot(acc[i] > negbias));
+        for (int i = 0; i < R; ++i) {
+            if constexpr (GROUPS)
+                asm("v_cmp_lt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc" : "+v"(st.cnt) : "s"(negbias), "v"(acc[i]) : "vcc");
+            else st.cnt += __builtin_popcountll(__ballot(acc[i] > negbias));
+        }
     }
     if (mask & ROCKET_F_SOFTPPV) {
 #pragma unroll
@@ -201,4 +207,27 @@ __device__ __forceinline__ KernelCtx rk_make_ctx(const RkKernelRec &rec, const f
     k.nl = 0.f;
     k.ns = 0.f;
     return k;
+}
+
+// The same for group g of interleaved series (RkGroups): one series of width times the samples on which the kernel's dilation and
+// padding are width times as large.
+__device__ __forceinline__ KernelCtx rk_make_group_ctx(const RkKernelRec &rec, const float *xg, int row_len, int lead, int L, int C,
+                                                       const RkGroups &groups, int g, const int32_t *channels, const float *weights)
+{
+    const int width = groups.width_of(g);
+    KernelCtx k = rk_make_ctx(rec, xg, row_len, lead, L, C, 0, channels, weights);
+    k.row_bytes = static_cast<size_t>(row_len) * width * 4;
+    k.xk = reinterpret_cast<const char *>(xg + static_cast<size_t>(groups.slots_before(g)) * C * row_len + static_cast<size_t>(lead - rec.pad) * width);
+    k.span_bytes = static_cast<uint32_t>((row_len + rec.pad) * width) * 4u;    // to the end of the next row's gap
+    k.d = rec.dil * width;
+    k.pad = rec.pad * width;
+    k.L = L * width;
+    k.width = width;
+    return k;
+}
+
+// Workgroup index -> (kernel in the order of cost, group).
+__device__ __forceinline__ void rk_group_pair(const RkGroups &groups, int K, int &jid, int &g)
+{
+    rk_group_pair_at(groups, K, static_cast<int>(blockIdx.x), jid, g);
 }

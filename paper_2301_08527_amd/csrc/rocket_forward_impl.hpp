@@ -7,7 +7,7 @@
 // Register path.  All strips of `nbands` bands of R rows x `ncols` columns starting at
 // row `row0`; every lane reads its R+LEN-1 inputs straight from global memory
 // (consecutive lanes read consecutive floats once d >= 64).
-template <int LEN, int R, int NT>
+template <int LEN, int R, int NT, bool GROUPS = false>
 __device__ __forceinline__ void rk_segment(const KernelCtx &k, int row0, int nbands, int ncols, PoolState &st)
 {
     const int nstrips = nbands * ncols;
@@ -34,12 +34,12 @@ __device__ __forceinline__ void rk_segment(const KernelCtx &k, int row0, int nba
             };
             channel(0, std::true_type{});       // starts the sums: no zeroing of the accumulators
             for (int c = 1; c < k.nch; ++c) channel(c, std::false_type{});
-            rk_pool<R>(acc, k.mask, k.negbias, k.nl, k.ns, st);
+            rk_pool<R, GROUPS>(acc, k.mask, k.negbias, k.nl, k.ns, st);
         }
     }
 }
 
-template <int LEN, int D, int NT>
+template <int LEN, int D, int NT, bool GROUPS = false>
 __device__ __forceinline__ int rk_lds_bands(const KernelCtx &k, int first_row, int end_row, float *tile, PoolState &st)
 {
     constexpr int R = kLdsRows;
@@ -72,16 +72,17 @@ __device__ __forceinline__ int rk_lds_bands(const KernelCtx &k, int first_row, i
         };
         channel(0, std::true_type{});                  // starts the sums (lanes without a strip neither sum nor pool)
         for (int c = 1; c < k.nch; ++c) channel(c, std::false_type{});
-        if (active) rk_pool<R>(acc, k.mask, k.negbias, k.nl, k.ns, st);
+        if (active) rk_pool<R, GROUPS>(acc, k.mask, k.negbias, k.nl, k.ns, st);
     }
     return first_row + nb * R;
 }
 
 // Pooling of one finished sum (see rk_pool).
+template <bool GROUPS = false>
 __device__ __forceinline__ void rk_pool1(float z, uint32_t mask, float negbias, float nl, float ns, PoolState &st)
 {
     const float one[1] = {z};
-    rk_pool<1>(one, mask, negbias, nl, ns, st);
+    rk_pool<1, GROUPS>(one, mask, negbias, nl, ns, st);
 }
 
 // Few-rows path for large dilations: rows [row0, row0 + rows) and the partial row after them
@@ -94,7 +95,7 @@ __device__ __forceinline__ void rk_pool1(float z, uint32_t mask, float negbias, 
 // with a large dilation puts (len-1)/2 such rows on either side) are skipped too,
 // loads and multiply-adds alike.  The partial last row is handled in the same
 // strip and masked per lane in the pooling.
-template <int LEN, int RM, int NT>
+template <int LEN, int RM, int NT, bool GROUPS = false>
 __device__ __forceinline__ void rk_few_rows(const KernelCtx &k, int row0, int rows, int tail, PoolState &st)
 {
     const int nrows = rows + (tail > 0 ? 1 : 0);            // rows with at least one output
@@ -153,25 +154,26 @@ __device__ __forceinline__ void rk_few_rows(const KernelCtx &k, int row0, int ro
             int lim = nrows;
             asm volatile("" : "+s"(lim));
             if (o < lim) {                                  // uniform
-                if (o < own_rows) rk_pool1(acc[o], k.mask, k.negbias, k.nl, k.ns, st);
+                if (o < own_rows) rk_pool1<GROUPS>(acc[o], k.mask, k.negbias, k.nl, k.ns, st);
             }
         });
     }
 }
 
-// Calls rk_lds_bands<LEN, D> for the D that equals the kernel's dilation (D < kLdsMaxD).
-template <int LEN, int D, int NT>
+// Calls rk_lds_bands<LEN, D> for the D that equals the kernel's dilation (D < kLdsMaxD).  The dilations of a group of two or more
+// interleaved series are even.
+template <int LEN, int D, int NT, bool GROUPS = false>
 __device__ __forceinline__ int rk_lds_dispatch(const KernelCtx &k, int first_row, int end_row, float *tile, PoolState &st)
 {
     if constexpr (D < kLdsMaxD) {
-        if (k.d == D) return rk_lds_bands<LEN, D, NT>(k, first_row, end_row, tile, st);
-        return rk_lds_dispatch<LEN, D + 1, NT>(k, first_row, end_row, tile, st);
+        if (k.d == D) return rk_lds_bands<LEN, D, NT, GROUPS>(k, first_row, end_row, tile, st);
+        return rk_lds_dispatch<LEN, D + (GROUPS ? 2 : 1), NT, GROUPS>(k, first_row, end_row, tile, st);
     } else {
         return first_row;
     }
 }
 
-template <int LEN, int NT>
+template <int LEN, int NT, bool GROUPS = false>
 __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, const RkJob job, float *tile, PoolState &st)
 {
     const int d = k.d;
@@ -179,7 +181,7 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
     const int tail = nout - rows * d;     // outputs of the partial last row
     // every branch below is uniform per workgroup
     int row0 = job.row0;
-    if (d < kLdsMaxD) row0 = rk_lds_dispatch<LEN, 1, NT>(k, row0, job.row1, tile, st);
+    if (d < kLdsMaxD) row0 = rk_lds_dispatch<LEN, GROUPS ? 2 : 1, NT, GROUPS>(k, row0, job.row1, tile, st);
     // Register path for the remaining rows: bands of 32 rows first.  A band height is used when its
     // strips fill the workgroup (bands x d >= NT).
     int left = job.row1 - row0;
@@ -187,7 +189,7 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
         constexpr int R = decltype(rc)::value;
         const int nb = left / R;
         if (nb > 0 && (force || nb * d >= NT)) {
-            rk_segment<LEN, R, NT>(k, row0, nb, d, st);
+            rk_segment<LEN, R, NT, GROUPS>(k, row0, nb, d, st);
             row0 += nb * R;
             left -= nb * R;
         }
@@ -199,16 +201,19 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
     bands_of(std::integral_constant<int, 32>{}, false);
 #endif
     const int own_tail = (job.flags & 1) ? tail : 0;
-    if (d >= kFewMinD) {
+    if (d >= (GROUPS ? kLdsMaxD : kFewMinD)) {
         // With a row of at least kFewMinD columns the rows that are left (fewer than 32, and the partial last
         // row) go through one strip per column with a run-time row count instead of a cascade of bands of 16, 8,
-        // 4, 2, 1 rows, each of which would load its own window: a whole kernel when it has few rows.
-        if (left + (own_tail > 0 ? 1 : 0) > kFewRowsMax) bands_of(std::integral_constant<int, 16>{}, true);
+        // 4, 2, 1 rows, each of which would load its own window: a whole kernel when it has few rows.  (Groups of interleaved series:
+        // no pass of a cascade fills a wavefront whose rows have 16 columns or more either; strips of up to 16 rows leave registers for
+        // a seventh wavefront per SIMD, 1 to 3 % faster than 24 rows and six.)
+        constexpr int few = GROUPS ? 16 : kFewRowsMax;
+        if (left + (own_tail > 0 ? 1 : 0) > few) bands_of(std::integral_constant<int, 16>{}, true);
         const int nrows = left + (own_tail > 0 ? 1 : 0);
         if (nrows == 0) return;
-        if (nrows <= 8) { rk_few_rows<LEN, 8, NT>(k, row0, left, own_tail, st); return; }
-        if (nrows <= 16) { rk_few_rows<LEN, 16, NT>(k, row0, left, own_tail, st); return; }
-        rk_few_rows<LEN, 24, NT>(k, row0, left, own_tail, st);
+        if (nrows <= 8) { rk_few_rows<LEN, 8, NT, GROUPS>(k, row0, left, own_tail, st); return; }
+        if (nrows <= 16) { rk_few_rows<LEN, 16, NT, GROUPS>(k, row0, left, own_tail, st); return; }
+        rk_few_rows<LEN, few, NT, GROUPS>(k, row0, left, own_tail, st);
         return;
     }
     // smaller dilations: bands of 16, 8, 4, 2 rows, tallest first; rows that are left go to the next
@@ -218,7 +223,7 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
     bands_of(std::integral_constant<int, 4>{}, false);
     bands_of(std::integral_constant<int, 2>{}, false);
     bands_of(std::integral_constant<int, 1>{}, true);
-    if (own_tail) rk_segment<LEN, 1, NT>(k, rows, 1, own_tail, st);
+    if (own_tail) rk_segment<LEN, 1, NT, GROUPS>(k, rows, 1, own_tail, st);
 }
 
 // grid: one workgroup per (series, job), a job being a row range of one kernel; the index

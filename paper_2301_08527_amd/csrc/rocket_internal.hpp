@@ -94,12 +94,16 @@ struct RkSet {
 struct RkGroups {
     static constexpr int kWidest = 64;     // one series for each lane of a wavefront
     int32_t width, count, first_series, first_width;
+    int32_t chunk;         // groups that are worked on together once the first count % kXcds are done (a multiple of kXcds)
+    int32_t by_kernel;     // those first ones: kernel by kernel (1) or group by group (0)
     RK_BOTH int width_of(int g) const { return g == 0 ? first_width : width; }
     RK_BOTH int series_of(int g) const { return g == 0 ? first_series : width; }
     RK_BOTH int series_before(int g) const { return g == 0 ? 0 : first_series + (g - 1) * width; }      // in the batch
     RK_BOTH int slots_before(int g) const { return g == 0 ? 0 : first_width + (g - 1) * width; }        // in the copy
 };
-inline RkGroups rk_groups(int32_t B, int32_t width)
+// `series_bytes`: of one series in the padded copy.  The order of the (kernel, group) pairs (rk_group_pair) keeps what is worked on together in the L2s.
+constexpr int64_t kGroupBytesOfL2 = 3 << 20;     // of an XCD's 4 MB
+inline RkGroups rk_groups(int32_t B, int32_t width, int64_t series_bytes)
 {
     RkGroups g;
     g.width = width;
@@ -107,7 +111,37 @@ inline RkGroups rk_groups(int32_t B, int32_t width)
     g.first_series = B - (g.count - 1) * width;
     g.first_width = 1;
     while (g.first_width < g.first_series) g.first_width *= 2;
+    const int64_t bytes = series_bytes * width;
+    const int64_t each = kGroupBytesOfL2 / bytes, all = (g.count + kXcds - 1) / kXcds;     // groups of an XCD
+    g.chunk = kXcds * static_cast<int32_t>(each < 1 ? 1 : each < all ? each : all);
+    g.by_kernel = g.count % kXcds * bytes <= kGroupBytesOfL2;
     return g;
+}
+// Workgroup `i` -> (kernel in the order of cost, group).  The hardware deals consecutive workgroups out to the XCDs in turn, so of
+// kXcds groups side by side each XCD keeps one, whose samples stay in its L2, while all of them go through the kernels, the
+// heaviest first.  As many such rounds at a time as the L2s hold; the groups that are left over come first (the end of a launch should
+// be light jobs): where all of them fit one L2 side by side too, otherwise one after the other, each on all XCDs.  149 x 18 x 1,263
+// samples, 4,822 kernels, max and PPV, eight series to a group: all groups side by side 1,908 us, so 1,132.
+RK_BOTH inline void rk_group_pair_at(const RkGroups &groups, int K, int i, int &jid, int &g)
+{
+    const int rest = groups.count % kXcds;
+    if (i < rest * K) {
+        if (groups.by_kernel) {
+            // by turns, or an even number of groups would give the narrower first one's short jobs to the same XCDs every time
+            jid = i / rest;
+            g = (i - jid * rest + jid / kXcds) % rest;
+        } else {
+            g = i / K;
+            jid = i - g * K;
+        }
+        return;
+    }
+    i -= rest * K;
+    const int from = i / (groups.chunk * K) * groups.chunk;
+    i -= from * K;
+    const int left = groups.count - rest - from, some = groups.chunk < left ? groups.chunk : left;
+    jid = i / some;
+    g = rest + from + (i - jid * some);
 }
 // floats of the interleaved copy: its rows, and the zeros that end the last one
 inline int64_t rk_groups_floats(const RkGroups &g, int64_t rows, int64_t row_len, int64_t lead)
@@ -212,7 +246,10 @@ struct RkLaunchers {
     // rocket_prologue.hip: the interleaved padded copy, from floats or (`stats` as in rk_launch_pad_u8) from raw bytes
     int (*pad_groups)(const rocket_kernels *h, const void *x, bool is_u8, int32_t B, const RkGroups &groups, float *xg, void *stats,
                       void *stream) = nullptr;
-    // rocket_backward_groups.hip: the whole backward pass over such a copy; `partial` as in rk_groups_partial_floats
+    // rocket_forward_groups.hip: max and PPV (mask without softPPV) over such a copy, features and all
+    int (*forward_groups)(const rocket_kernels *h, const float *xg, const RkGroups &groups, uint32_t mask, float *out, void *stream) = nullptr;
+    // rocket_backward_groups.hip: the whole backward pass over such a copy; `partial`: a row of gradients for each group where there
+    // are several
     int (*backward_groups)(const rocket_kernels *h, const float *xg, const RkGroups &groups, const float *grad_out, int F,
                            int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, float *grad_w,
                            float *grad_b, void *stream) = nullptr;

@@ -1,4 +1,4 @@
-// Drives the choice of the backward pass's groups of interleaved series under AddressSanitizer and UndefinedBehaviorSanitizer without
+// Drives the choice of the groups of interleaved series under AddressSanitizer and UndefinedBehaviorSanitizer without
 // a GPU: the launchers are stubs that record what they were given.  Linked like host_driver.cpp.
 #include <hip/hip_runtime.h>
 
@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <vector>
 
 #include "rocket_internal.hpp"
 
@@ -61,8 +62,11 @@ static int backward_groups_stub(const rocket_kernels *, const float *, const RkG
     g_route += "backward_groups ";
     return ROCKET_OK;
 }
+static int forward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, uint32_t, float *, void *) RECORD("forward_groups")
+static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, float *, void *) RECORD("series")
 [[maybe_unused]] static const bool kEntered = (rk_launchers().backward_short = backward_short_stub, rk_launchers().pad_groups = pad_groups_stub,
-                                               rk_launchers().backward_groups = backward_groups_stub, true);
+                                               rk_launchers().backward_groups = backward_groups_stub,
+                                               rk_launchers().forward_groups = forward_groups_stub, rk_launchers().forward_series = series_stub, true);
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s (route: %s, width %d of %d)\n", __LINE__, #cond, g_route.c_str(), g_groups.width, g_groups.first_series); return 1; } } while (0)
 
@@ -71,15 +75,44 @@ alignas(256) static char there[256];
 static int backward(rocket_kernels *h, int32_t B, bool u8 = false)
 {
     g_route.clear();
-    g_groups = rk_groups(B, 1);
+    g_groups = rk_groups(B, 1, 1);
     float *at = reinterpret_cast<float *>(there);
     const size_t bytes = rocket_workspace_bytes(h, B, 4, 1);
     return u8 ? rocket_soft_ppv_backward_u8(h, reinterpret_cast<const uint8_t *>(there), B, 4, at, 10.f, -3.f, 0, at, at, there, bytes, nullptr)
               : rocket_soft_ppv_backward(h, at, B, 4, at, 10.f, -3.f, 0, at, at, there, bytes, nullptr);
 }
 
+static int forward(rocket_kernels *h, int32_t B, uint32_t mask, bool u8 = false)
+{
+    g_route.clear();
+    g_groups = rk_groups(B, 1, 1);
+    float *at = reinterpret_cast<float *>(there);
+    const size_t bytes = rocket_workspace_bytes(h, B, mask, 0);
+    return u8 ? rocket_transform_u8(h, reinterpret_cast<const uint8_t *>(there), B, mask, 10.f, -3.f, at, there, bytes, nullptr)
+              : rocket_transform(h, at, B, mask, 10.f, -3.f, at, there, bytes, nullptr);
+}
+
+// The pairs of a launch, as rk_group_pair deals them out: each once.
+static int pairs(int32_t K)
+{
+    const RkGroups &g = g_groups;
+    const int rest = g.count % kXcds;
+    std::vector<char> seen(static_cast<size_t>(g.count) * K);
+    CHECK(g.chunk >= kXcds && g.chunk % kXcds == 0);
+    for (int i = 0; i < g.count * K; ++i) {
+        int jid, group;
+        rk_group_pair_at(g, K, i, jid, group);
+        CHECK(jid >= 0 && jid < K && group >= 0 && group < g.count);
+        CHECK(seen[static_cast<size_t>(group) * K + jid]++ == 0);
+        CHECK((i < rest * K) == (group < rest));
+        // an XCD has the same few groups all the way through a round
+        if (i >= rest * K) CHECK((group - rest) % kXcds == (i - rest * K) % kXcds);
+    }
+    return 0;
+}
+
 // The series of a batch are in one group each, and what the groups need is inside the workspace.
-static int inside(rocket_kernels *h, int32_t B)
+static int inside(rocket_kernels *h, int32_t B, bool is_backward = true)
 {
     const RkGroups &g = g_groups;
     int next = 0, slots = 0;
@@ -90,6 +123,12 @@ static int inside(rocket_kernels *h, int32_t B)
         slots += g.width_of(i);
     }
     CHECK(next == B);
+    if (!is_backward) {
+        const uintptr_t from = reinterpret_cast<uintptr_t>(there), stats = g_stats;
+        CHECK(g_copy == from && from + rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192 <= stats);
+        CHECK(stats + static_cast<uintptr_t>(B) * h->C * 16 <= from + rocket_workspace_bytes(h, B, 3, 0));
+        return 0;
+    }
     const uintptr_t first = reinterpret_cast<uintptr_t>(there), end = first + rocket_workspace_bytes(h, B, 4, 1);
     CHECK(g_copy == first && g_partial >= first + rk_groups_floats(g, h->C, h->row_len, h->lead) * 4 + 8192);
     const uintptr_t sums = g.count > 1 ? (h->w_off[h->K] + h->K) * 4 * g.count : 0;
@@ -113,10 +152,30 @@ int main()
         if (w.width > 1) {
             if (inside(h, w.B)) return 1;
             CHECK(backward(h, w.B, true) == ROCKET_OK && g_route == "pad_groups_u8 backward_groups ");
-            if (inside(h, w.B)) return 1;
+            if (inside(h, w.B) || pairs(w.K)) return 1;
         }
         rocket_free_kernels(h);
     }
+    // transforms: max and PPV in groups, sums of sigmoids and one-channel sets not
+    const struct { int32_t B, C, L, K, width, first; } ahead[] = {
+        {28, 15, 134, 2351, 8, 4}, {149, 3, 166, 3236, 32, 21}, {3, 2, 200, 9000, 4, 3}, {149, 18, 1263, 4822, 8, 5}, {9, 4, 600, 6000, 4, 1},
+        {130, 2, 60, 4000, 64, 2}, {1, 5, 300, 4000, 1, 1}, {16, 3, 4099, 500, 1, 1}, {64, 5, 8193, 300, 1, 1}};
+    for (const auto &w : ahead) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        for (uint32_t mask = 1; mask <= 3; ++mask) {
+            CHECK(forward(h, w.B, mask) == ROCKET_OK && g_groups.width == w.width && (w.width == 1 || g_groups.first_series == w.first));
+            CHECK((g_route == "pad_groups forward_groups ") == (w.width > 1));
+            if (w.width == 1) continue;
+            if (inside(h, w.B, false) || pairs(w.K)) return 1;
+            CHECK(forward(h, w.B, mask, true) == ROCKET_OK && g_route == "pad_groups_u8 forward_groups ");
+        }
+        CHECK(forward(h, w.B, 7) == ROCKET_OK && g_groups.width == 1);
+        rocket_free_kernels(h);
+    }
+    rocket_kernels *sets = nullptr;
+    CHECK(rocket_make_kernels(3, 1000, 1, 500, &sets) == ROCKET_OK && forward(sets, 64, 3) == ROCKET_OK && g_route == "series ");
+    rocket_free_kernels(sets);
     // all batches of a few handles, one with hardly any partial results to make room in
     const int32_t handles[][3] = {{1, 1, 3000}, {1, 20, 500}, {7, 3, 64}, {300, 2, 200}, {2000, 1, 333}};
     for (const auto &s : handles) {
@@ -125,6 +184,8 @@ int main()
         for (int32_t B = 1; B <= 300; ++B) {
             CHECK(backward(h, B) == ROCKET_OK);
             if (g_groups.width > 1 && inside(h, B)) return 1;
+            CHECK(forward(h, B, 3) == ROCKET_OK);
+            if (g_groups.width > 1 && (inside(h, B, false) || pairs(s[0]))) return 1;
         }
         rocket_free_kernels(h);
     }

@@ -1,11 +1,11 @@
-"""The backward pass over groups of interleaved short series (needs an MI355X): against the oracle, against the same kernels one
-series at a time, and its rule for exact ties."""
+"""Transform and backward pass over groups of interleaved short series (needs an MI355X): against the oracle, against the same kernels one
+series at a time, and the backward pass's rule for exact ties."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2301_08527_amd import rocket
-from parity import check_backward
+from parity import check_backward, check_forward
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +107,87 @@ def test_exact_ties_in_groups(B, L):
     gw_ref, gb_ref = oracle.backward(x, kr, g[:, K:].astype(np.float64), g[:, :K].astype(np.float64), lam=10.0, shift=-3.0)
     assert np.array_equal(gw.cpu().numpy().astype(np.float64), gw_ref)
     assert np.array_equal(gb.cpu().numpy().astype(np.float64), gb_ref)
+
+
+# (width, series of the first group) of a transform without softPPV; one series alone is never a group
+AHEAD = [(28, 15, 134, 2351, (8, 4)), (149, 3, 166, 3236, (32, 21)), (3, 2, 200, 9000, (4, 3)), (20, 18, 1263, 4822, (4, 4)), (9, 4, 600, 6000, (4, 1)),
+         (130, 2, 60, 4000, (64, 2)), (100, 4, 600, 200, (2, 2))]
+
+
+@pytest.mark.parametrize("B,C,L,K,groups", AHEAD)
+@pytest.mark.parametrize("u8", [False, True])
+def test_features_of_groups(B, C, L, K, groups, u8):
+    """the same bits as one series at a time, and within the oracle's tolerance; without allocation too"""
+    import torch
+    rng = np.random.default_rng(L)
+    if u8:
+        raw, x = _raw(rng, (B, C, L))
+        entry, xd = rocket.rocket_transform_u8, _gpu(raw)
+    else:
+        x = rng.standard_normal((B, C, L)).astype(np.float32)
+        entry, xd = rocket.rocket_transform, _gpu(x)
+    h = rocket.rocket_make_kernels(L, K, C, L)
+    print("features of groups", B, C, L, K, groups, "u8" if u8 else "f32", flush=True)
+    alone = torch.cat([entry(h, xd[b:b + 1].contiguous(), 3) for b in range(B)])
+    ws = torch.full((rocket.rocket_workspace_bytes(h, B, 3, False),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing writes
+    both = entry(h, xd, 3, workspace=ws)
+    assert torch.equal(both, alone)
+    assert torch.equal(entry(h, xd, 1), alone[:, :K]) and torch.equal(entry(h, xd, 2), alone[:, K:])
+    kr = rocket.rocket_kernels_view_get(h)
+    check_forward(x, kr, both.cpu().numpy(), 3, rows=sorted({0, B // 2, B - 1}), sel=np.arange(0, K, max(1, K // 200), dtype=np.int32))
+    if not u8 and rocket.rocket_workspace_bytes(h, B, 3, False) <= 64 << 20:
+        import ctypes
+        out = torch.full_like(both, float("nan"))
+        rc = rocket.load_library().rocket_transform_noalloc(h.handle, xd.data_ptr(), B, 3, 10.0, -3.0, out.data_ptr(),
+                                                            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == rocket.ROCKET_OK and torch.equal(out, both)
+
+
+def test_groups_keep_their_series_apart():
+    """infinite, undefined and huge samples in some series of a group leave the others' features as they are"""
+    import torch
+    B, C, L, K = 30, 3, 300, 2500
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((B, C, L), generator=gen, device="cuda")
+    x[3, :, 70] = float("nan")
+    x[5, 1, 10] = float("inf")
+    x[12, 0] = 3e38
+    h = rocket.rocket_make_kernels(6, K, C, L)
+    print("groups keep their series apart", flush=True)
+    both = rocket.rocket_transform(h, x, 3)
+    alone = torch.cat([rocket.rocket_transform(h, x[b:b + 1].contiguous(), 3) for b in range(B)])
+    assert torch.equal(torch.nan_to_num(both, nan=-7.0), torch.nan_to_num(alone, nan=-7.0))
+    clean = [b for b in range(B) if b not in (3, 5, 12)]
+    assert torch.isfinite(both[clean]).all()
+
+
+def test_groups_in_a_graph():
+    """copy and kernel of a transform and of a backward pass are captured and replayed on new samples"""
+    import torch
+    B, C, L, K = 40, 3, 400, 1500
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    h = rocket.rocket_make_kernels(7, K, C, L)
+    x = torch.randn((B, C, L), generator=gen, device="cuda")
+    gout = torch.randn((B, 2 * K), generator=gen, device="cuda")
+    out = torch.empty((B, 2 * K), device="cuda")
+    gw, gb = torch.empty(h.total_weights, device="cuda"), torch.empty(K, device="cuda")
+    ws = torch.empty(max(rocket.rocket_workspace_bytes(h, B, 5, True), rocket.rocket_workspace_bytes(h, B, 3, False)), dtype=torch.uint8, device="cuda")
+
+    def step():
+        rocket.rocket_transform(h, x, 3, out=out, workspace=ws)
+        rocket.rocket_soft_ppv_backward(h, x, 5, gout, 10.0, -3.0, True, grad_w=gw, grad_b=gb, workspace=ws)
+
+    print("groups in a graph", flush=True)
+    step()
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for _ in range(3):
+        x.copy_(torch.randn((B, C, L), generator=gen, device="cuda"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (out, gw, gb)]
+        step()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, (out, gw, gb)))
