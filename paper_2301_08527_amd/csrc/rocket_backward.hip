@@ -89,7 +89,7 @@ int rk_launch_backward(const rocket_kernels *h, const float *xpad, int32_t B, co
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     const int J = static_cast<int>(h->jobs.size());
     const int spread = rk_spread(h, B);
-    hipLaunchKernelGGL(rk_backward<kThreads>, dim3(static_cast<unsigned>(rk_grid_groups(B, J, spread))), dim3(kThreads), 0, stream, xpad,
+    hipLaunchKernelGGL(rk_backward<kThreads>, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(kThreads), 0, stream, xpad,
                        static_cast<int>(h->row_len), h->lead, h->L, h->C, h->K, J, h->d_rec, h->d_jobs, h->d_bjob_off,
                        h->d_channels, h->d_weights, grad_out, F, plane_soft, plane_max, lambda, nl, ns, partial,
                        static_cast<int>(h->bjob_off.back()), B, spread);

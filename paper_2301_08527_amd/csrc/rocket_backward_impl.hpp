@@ -551,7 +551,7 @@ __global__ __launch_bounds__(NT) void rk_backward(const float *__restrict__ xpad
     __shared__ float s_max[NT / 64];
     __shared__ int s_arg[NT / 64];
     int b, jid;
-    if (!rk_block_to_pair(J, B, spread, b, jid)) return;
+    rk_block_to_pair(J, B, spread, b, jid);
     const RkJob job = jobs[jid];
     const int kid = job.kernel;
     const RkKernelRec rec = recs[kid];

@@ -11,7 +11,7 @@ static int launch_backward_short(const rocket_kernels *h, const float *xpad, int
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     const int J = static_cast<int>(h->jobs.size());
     const int spread = rk_spread(h, B);     // 64 x 1 x 1,000, 1,000 kernels 191 -> 183 us, 240 x 20 x 8,192, 200 kernels 1,980 -> 1,469
-    hipLaunchKernelGGL(rk_backward<64>, dim3(static_cast<unsigned>(rk_grid_groups(B, J, spread))), dim3(64), 0, stream, xpad,
+    hipLaunchKernelGGL(rk_backward<64>, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(64), 0, stream, xpad,
                        static_cast<int>(h->row_len), h->lead, h->L, h->C, h->K, J, h->d_rec, h->d_jobs, h->d_bjob_off,
                        h->d_channels, h->d_weights, grad_out, F, plane_soft, plane_max, lambda, nl, ns, partial,
                        static_cast<int>(h->bjob_off.back()), B, spread);

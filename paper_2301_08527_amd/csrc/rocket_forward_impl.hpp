@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NT) void rk_forward(const float *__restrict__ xpad,
 {
     __shared__ __attribute__((aligned(16))) float tile[rk_tile_words(NT)];   // 16-byte pieces are written straight into it
     int b, jid;
-    if (!rk_block_to_pair(J, B, spread, b, jid)) return;
+    rk_block_to_pair(J, B, spread, b, jid);
     const RkJob job = jobs[jid];
     const RkKernelRec rec = recs[job.kernel];
     KernelCtx k = rk_make_ctx(rec, xpad, row_len, lead, L, C, b, channels, weights);

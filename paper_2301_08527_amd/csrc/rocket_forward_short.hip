@@ -10,7 +10,7 @@ int rk_launch_forward_short(const rocket_kernels *h, const float *xpad, int32_t 
     hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
     const int J = static_cast<int>(h->jobs.size());
     const int spread = 0;   // measured: the per-XCD series mapping makes the short-series launch 2 % slower
-    hipLaunchKernelGGL(rk_forward<64>, dim3(static_cast<unsigned>(rk_grid_groups(B, J, spread))), dim3(64), 0, stream, xpad,
+    hipLaunchKernelGGL(rk_forward<64>, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(64), 0, stream, xpad,
                        static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs, h->d_channels,
                        h->d_weights, mask, nl, ns, partials, B, spread);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;

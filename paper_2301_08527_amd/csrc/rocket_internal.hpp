@@ -260,21 +260,20 @@ enum class RkPath { by_size, sets, jobs };      // of one-channel kernels: by th
 int rk_finish_handle(rocket_kernels &h, RkPath path = RkPath::by_size);
 
 // Whether a launch over B series uses the per-XCD series mapping (rk_block_to_pair in
-// rocket_device.hpp): when the series divide evenly among the XCDs (with 60 series four XCDs
-// would get 8 and four 7, and the launch takes as long as 64), and while the kXcds padded series
-// that are then in flight together fit in half of the 256 MB Infinity Cache.  (Measured at
-// 64 x 20 x 50,000: 1 % faster, 22 % less L2 fill traffic; slower at 8 x 20 x 200,000, whose eight
-// padded series are 192 MB, and for the short-series forward kernel, which does not use it.)
+// rocket_device.hpp): while the kXcds padded series that are then in flight together fit in half of
+// the 256 MB Infinity Cache.  (Measured at 64 x 20 x 50,000, 10,000 kernels: 1 % faster, 22 % less
+// L2 fill traffic; fewer kernels re-use a series less: 74 x 14 x 32,734, 342 kernels 1,319 -> 978 us, 13 x 20 x 50,000, 300 kernels
+// 540 -> 358; slower at 8 x 20 x 200,000, whose eight padded series are 192 MB, and for the short-series forward kernel, which does
+// not use it.)
 inline int rk_spread(const rocket_kernels *h, int32_t B)
 {
     const int64_t series_bytes = static_cast<int64_t>(h->C) * h->row_len * 4;
-    return (B % kXcds == 0 && kXcds * series_bytes <= (128LL << 20)) ? 1 : 0;
+    return (B >= kXcds && kXcds * series_bytes <= (128LL << 20)) ? 1 : 0;
 }
-// Workgroups of a launch over B series x `items` work items each.
-inline int64_t rk_grid_groups(int32_t B, int64_t items, int spread)
+// Workgroups of a launch over B series x `items` work items each, as the limit on a launch counts them (whole rounds of XCDs).
+inline int64_t rk_grid_groups(int32_t B, int64_t items)
 {
-    const int64_t series = spread ? static_cast<int64_t>((B + kXcds - 1) / kXcds) * kXcds : B;
-    return series * items;
+    return static_cast<int64_t>((B + kXcds - 1) / kXcds) * kXcds * items;
 }
 
 // Kernel launchers (rocket_forward.hip, rocket_backward.hip).  `stream` is a hipStream_t.

@@ -404,7 +404,7 @@ void rk_mr_forward(const float *__restrict__ x, size_t row_stride, int L, int C,
     __shared__ __attribute__((aligned(16))) uint32_t planes[2 * kMrPlane + 2 * kMrChunk];    // see MrPairSlots
     __shared__ int wave_counts[4][kMrSet];
     int b, block;
-    if (!rk_block_to_pair((njobs + per - 1) / per, B, spread, b, block)) return;
+    rk_block_to_pair((njobs + per - 1) / per, B, spread, b, block);
     const int tid = static_cast<int>(threadIdx.x);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const float *series = x + static_cast<size_t>(b) * C * row_stride;
@@ -614,7 +614,7 @@ static int launch_minirocket_forward(const rocket_kernels *h, const float *x, in
     // leave some eight workgroups for each of a CU's four places
     const int64_t most = static_cast<int64_t>(B) * njobs / 8192;
     const int per = static_cast<int>(most < 1 ? 1 : most > kMrMaxPer ? kMrMaxPer : most);
-    const int64_t groups = rk_grid_groups(B, (njobs + per - 1) / per, spread);
+    const int64_t groups = static_cast<int64_t>(B) * ((njobs + per - 1) / per);
     hipLaunchKernelGGL(rk_mr_forward, dim3(static_cast<unsigned>(groups)), dim3(256), 0, stream, x,
                        static_cast<size_t>(row_stride), h->L, h->C, h->d_rec, h->d_channels, h->d_mr_jobs, njobs, per, B,
                        spread, h->K, counts, out);
