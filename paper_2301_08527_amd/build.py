@@ -16,7 +16,7 @@ LIB = os.environ.get("ROCKET_LIB_OUT", LIB)
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-KERNEL_TUS = ("rocket_forward.hip", "rocket_forward_short.hip", "rocket_forward_series.hip", "rocket_forward_groups.hip", "rocket_backward.hip", "rocket_backward_short.hip", "rocket_backward_groups.hip", "rocket_ridge.hip",
+KERNEL_TUS = ("rocket_forward.hip", "rocket_forward_soft.hip", "rocket_forward_short.hip", "rocket_forward_short_soft.hip", "rocket_forward_series.hip", "rocket_forward_groups.hip", "rocket_backward.hip", "rocket_backward_short.hip", "rocket_backward_groups.hip", "rocket_ridge.hip",
               "rocket_prologue.hip", "rocket_train.hip", "rocket_calibrate.hip", "rocket_minirocket.hip",
               "rocket_minirocket_forward.hip")   # translation units that hold device code
 HOST_TUS = ("rocket_api.hip",)

@@ -21,7 +21,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct PoolState {
     float vmax;   // per lane
     float ssum;   // per lane
-    int cnt;      // wavefront-uniform: positives seen by this wavefront (groups of interleaved series: per lane)
+    int cnt;      // positives: per lane, or of the wavefront (rk_counts_by_lane)
 };
 
 // Raw buffer descriptor (stride 0, 32-bit data format) over `bytes` bytes at `base`.
@@ -79,13 +79,17 @@ __device__ __forceinline__ void rk_taps(const float (&w)[LEN], float xv, float (
     });
 }
 
+// Whether positive outputs are counted by each lane, in two vector instructions an output, or by the wavefront, in one and two scalar
+// instructions, of which a SIMD issues one in four clocks.  Beside sigmoids the vector instructions are what is short (16 x 20 x 50,000,
+// 10,000 kernels, all features: by lane 8.94 ms, by wavefront 8.84), without them the scalar ones (1 x 20 x 50,000, max and PPV:
+// 542 us and 552).
+__host__ __device__ constexpr bool rk_counts_by_lane(uint32_t mask) { return (mask & ROCKET_F_SOFTPPV) == 0; }
+
 // Pooling of R finished sums z = y - bias (section 3.2).  The bias is folded into
 // the pooling: max(y) = max(z) + bias (added once per kernel at the end),
 // y > 0 <=> z > -bias, and lambda*y + shift = lambda*z + (shift + lambda*bias).
-// `mask` is uniform; ns already contains the bias term.  With GROUPS the lanes of a wavefront have positions of different series and
-// count for themselves: v_cmp and v_addc instead of v_cmp and two scalar instructions (written out: from the C form the compiler
-// made selects and sums of them, and spilled).
-template <int R, bool GROUPS = false>
+// `mask` is uniform; ns already contains the bias term.
+template <int R>
 __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, float negbias, float nl, float ns,
                                         PoolState &st)
 {
@@ -93,10 +97,11 @@ __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, fl
 #pragma unroll
         for (int i = 0; i < R; ++i) st.vmax = fmaxf(st.vmax, acc[i]);
     }
-    if (mask & ROCKET_F_PPV) {   // Eq. 1-2: strict y > 0, counted per wavefront in a scalar register
+    if (mask & ROCKET_F_PPV) {   // Eq. 1-2: strict y > 0
+        // (Written out: from the C form the compiler made selects, and spilled.)
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-            if constexpr (GROUPS)
+            if (rk_counts_by_lane(mask))
                 asm("v_cmp_lt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc" : "+v"(st.cnt) : "s"(negbias), "v"(acc[i]) : "vcc");
             else st.cnt += __builtin_popcountll(__ballot(acc[i] > negbias));
         }

@@ -56,15 +56,13 @@ int rk_launch_pad(const rocket_kernels *h, const float *x, int32_t B, float *xpa
 }
 
 int rk_launch_forward(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns,
-                      float *partials, void *stream_ptr)
+                      float *partials, void *stream)
 {
-    hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    const int J = static_cast<int>(h->jobs.size());
     const int spread = rk_spread(h, B);
-    hipLaunchKernelGGL(rk_forward<kThreads>, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(kThreads), 0, stream, xpad,
-                       static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs, h->d_channels,
-                       h->d_weights, mask, nl, ns, partials, B, spread);
-    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+    if (mask & ROCKET_F_SOFTPPV) return rk_launch_forward_soft(h, xpad, B, mask, nl, ns, partials, spread, stream);
+    if (mask == ROCKET_F_MAX) return rk_forward_launch<kThreads, ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
+    if (mask == ROCKET_F_PPV) return rk_forward_launch<kThreads, ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
+    return rk_forward_launch<kThreads, ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
 }
 
 // One thread per (series, kernel): combines the kernel's job partials in job order and

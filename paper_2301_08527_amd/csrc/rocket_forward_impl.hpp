@@ -7,7 +7,7 @@
 // Register path.  All strips of `nbands` bands of R rows x `ncols` columns starting at
 // row `row0`; every lane reads its R+LEN-1 inputs straight from global memory
 // (consecutive lanes read consecutive floats once d >= 64).
-template <int LEN, int R, int NT, bool GROUPS = false>
+template <int LEN, int R, int NT>
 __device__ __forceinline__ void rk_segment(const KernelCtx &k, int row0, int nbands, int ncols, PoolState &st)
 {
     const int nstrips = nbands * ncols;
@@ -34,12 +34,12 @@ __device__ __forceinline__ void rk_segment(const KernelCtx &k, int row0, int nba
             };
             channel(0, std::true_type{});       // starts the sums: no zeroing of the accumulators
             for (int c = 1; c < k.nch; ++c) channel(c, std::false_type{});
-            rk_pool<R, GROUPS>(acc, k.mask, k.negbias, k.nl, k.ns, st);
+            rk_pool<R>(acc, k.mask, k.negbias, k.nl, k.ns, st);
         }
     }
 }
 
-template <int LEN, int D, int NT, bool GROUPS = false>
+template <int LEN, int D, int NT>
 __device__ __forceinline__ int rk_lds_bands(const KernelCtx &k, int first_row, int end_row, float *tile, PoolState &st)
 {
     constexpr int R = kLdsRows;
@@ -72,17 +72,16 @@ __device__ __forceinline__ int rk_lds_bands(const KernelCtx &k, int first_row, i
         };
         channel(0, std::true_type{});                  // starts the sums (lanes without a strip neither sum nor pool)
         for (int c = 1; c < k.nch; ++c) channel(c, std::false_type{});
-        if (active) rk_pool<R, GROUPS>(acc, k.mask, k.negbias, k.nl, k.ns, st);
+        if (active) rk_pool<R>(acc, k.mask, k.negbias, k.nl, k.ns, st);
     }
     return first_row + nb * R;
 }
 
 // Pooling of one finished sum (see rk_pool).
-template <bool GROUPS = false>
 __device__ __forceinline__ void rk_pool1(float z, uint32_t mask, float negbias, float nl, float ns, PoolState &st)
 {
     const float one[1] = {z};
-    rk_pool<1, GROUPS>(one, mask, negbias, nl, ns, st);
+    rk_pool<1>(one, mask, negbias, nl, ns, st);
 }
 
 // Few-rows path for large dilations: rows [row0, row0 + rows) and the partial row after them
@@ -95,7 +94,7 @@ __device__ __forceinline__ void rk_pool1(float z, uint32_t mask, float negbias, 
 // with a large dilation puts (len-1)/2 such rows on either side) are skipped too,
 // loads and multiply-adds alike.  The partial last row is handled in the same
 // strip and masked per lane in the pooling.
-template <int LEN, int RM, int NT, bool GROUPS = false>
+template <int LEN, int RM, int NT>
 __device__ __forceinline__ void rk_few_rows(const KernelCtx &k, int row0, int rows, int tail, PoolState &st)
 {
     const int nrows = rows + (tail > 0 ? 1 : 0);            // rows with at least one output
@@ -154,7 +153,7 @@ __device__ __forceinline__ void rk_few_rows(const KernelCtx &k, int row0, int ro
             int lim = nrows;
             asm volatile("" : "+s"(lim));
             if (o < lim) {                                  // uniform
-                if (o < own_rows) rk_pool1<GROUPS>(acc[o], k.mask, k.negbias, k.nl, k.ns, st);
+                if (o < own_rows) rk_pool1(acc[o], k.mask, k.negbias, k.nl, k.ns, st);
             }
         });
     }
@@ -166,7 +165,7 @@ template <int LEN, int D, int NT, bool GROUPS = false>
 __device__ __forceinline__ int rk_lds_dispatch(const KernelCtx &k, int first_row, int end_row, float *tile, PoolState &st)
 {
     if constexpr (D < kLdsMaxD) {
-        if (k.d == D) return rk_lds_bands<LEN, D, NT, GROUPS>(k, first_row, end_row, tile, st);
+        if (k.d == D) return rk_lds_bands<LEN, D, NT>(k, first_row, end_row, tile, st);
         return rk_lds_dispatch<LEN, D + (GROUPS ? 2 : 1), NT, GROUPS>(k, first_row, end_row, tile, st);
     } else {
         return first_row;
@@ -189,7 +188,7 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
         constexpr int R = decltype(rc)::value;
         const int nb = left / R;
         if (nb > 0 && (force || nb * d >= NT)) {
-            rk_segment<LEN, R, NT, GROUPS>(k, row0, nb, d, st);
+            rk_segment<LEN, R, NT>(k, row0, nb, d, st);
             row0 += nb * R;
             left -= nb * R;
         }
@@ -211,9 +210,9 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
         if (left + (own_tail > 0 ? 1 : 0) > few) bands_of(std::integral_constant<int, 16>{}, true);
         const int nrows = left + (own_tail > 0 ? 1 : 0);
         if (nrows == 0) return;
-        if (nrows <= 8) { rk_few_rows<LEN, 8, NT, GROUPS>(k, row0, left, own_tail, st); return; }
-        if (nrows <= 16) { rk_few_rows<LEN, 16, NT, GROUPS>(k, row0, left, own_tail, st); return; }
-        rk_few_rows<LEN, few, NT, GROUPS>(k, row0, left, own_tail, st);
+        if (nrows <= 8) { rk_few_rows<LEN, 8, NT>(k, row0, left, own_tail, st); return; }
+        if (nrows <= 16) { rk_few_rows<LEN, 16, NT>(k, row0, left, own_tail, st); return; }
+        rk_few_rows<LEN, few, NT>(k, row0, left, own_tail, st);
         return;
     }
     // smaller dilations: bands of 16, 8, 4, 2 rows, tallest first; rows that are left go to the next
@@ -223,13 +222,16 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
     bands_of(std::integral_constant<int, 4>{}, false);
     bands_of(std::integral_constant<int, 2>{}, false);
     bands_of(std::integral_constant<int, 1>{}, true);
-    if (own_tail) rk_segment<LEN, 1, NT, GROUPS>(k, rows, 1, own_tail, st);
+    if (own_tail) rk_segment<LEN, 1, NT>(k, rows, 1, own_tail, st);
 }
 
 // grid: one workgroup per (series, job), a job being a row range of one kernel; the index
 // mapping is rk_block_to_pair's.  It writes the job's partial pooling results: partials holds three planes
 // of B*J words (max of y - bias, count of y > 0, sum of sigmoids).
-template <int NT>
+// The pooled features are a template parameter: with the mask at run time every kernel was held to the registers of the sigmoids (79, six
+// wavefronts per SIMD) and tested the mask strip by strip.  72 without PPV or without softPPV, seven wavefronts: 64 x 20 x 50,000,
+// 10,000 kernels, max and PPV 33.0 -> 31.5 ms, 40 x 1 x 30,000, 2,000 kernels 983 -> 891 us, max and softPPV 1,121 -> 1,071.
+template <int NT, uint32_t MASK>
 #if RK_WPE
 __attribute__((amdgpu_waves_per_eu(RK_WPE)))
 #endif
@@ -237,8 +239,8 @@ __global__ __launch_bounds__(NT) void rk_forward(const float *__restrict__ xpad,
                                                        const RkKernelRec *__restrict__ recs,
                                                        const RkJob *__restrict__ jobs,
                                                        const int32_t *__restrict__ channels,
-                                                       const float *__restrict__ weights, uint32_t mask, float nl,
-                                                       float ns, float *__restrict__ partials, int B, int spread)
+                                                       const float *__restrict__ weights, float nl, float ns,
+                                                       float *__restrict__ partials, int B, int spread)
 {
     __shared__ __attribute__((aligned(16))) float tile[rk_tile_words(NT)];   // 16-byte pieces are written straight into it
     int b, jid;
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(NT) void rk_forward(const float *__restrict__ xpad,
     const RkJob job = jobs[jid];
     const RkKernelRec rec = recs[job.kernel];
     KernelCtx k = rk_make_ctx(rec, xpad, row_len, lead, L, C, b, channels, weights);
-    k.mask = mask;
+    k.mask = MASK;
     k.nl = nl;
     k.ns = fmaf(rec.bias, nl, ns);
 
@@ -260,16 +262,18 @@ __global__ __launch_bounds__(NT) void rk_forward(const float *__restrict__ xpad,
 
     // close the reductions: lanes -> wavefront (shuffles) -> workgroup (LDS)
     float vmax = st.vmax, ssum = st.ssum;
+    int cnt = st.cnt;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         vmax = fmaxf(vmax, __shfl_xor(vmax, off));
         ssum += __shfl_xor(ssum, off);
+        if constexpr (rk_counts_by_lane(MASK)) cnt += __shfl_xor(cnt, off);
     }
     __shared__ float s_max[(NT / 64)];
     __shared__ float s_sum[(NT / 64)];
     __shared__ int s_cnt[(NT / 64)];
     const int wave = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) { s_max[wave] = vmax; s_sum[wave] = ssum; s_cnt[wave] = st.cnt; }
+    if ((threadIdx.x & 63) == 0) { s_max[wave] = vmax; s_sum[wave] = ssum; s_cnt[wave] = cnt; }
     __syncthreads();
     if (threadIdx.x == 0) {
         float m = s_max[0], sm = s_sum[0];
@@ -283,3 +287,19 @@ __global__ __launch_bounds__(NT) void rk_forward(const float *__restrict__ xpad,
         partials[2 * plane + slot] = sm;
     }
 }
+
+template <int NT, uint32_t MASK>
+inline int rk_forward_launch(const rocket_kernels *h, const float *xpad, int32_t B, float nl, float ns, float *partials, int spread, void *stream)
+{
+    const int J = static_cast<int>(h->jobs.size());
+    hipLaunchKernelGGL((rk_forward<NT, MASK>), dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(NT), 0,
+                       static_cast<hipStream_t>(stream), xpad, static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs,
+                       h->d_channels, h->d_weights, nl, ns, partials, B, spread);
+    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+}
+
+// The kernels of the masks with softPPV are translation units of their own (rocket_forward_soft.hip, rocket_forward_short_soft.hip).
+int rk_launch_forward_soft(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns, float *partials, int spread,
+                           void *stream);
+int rk_launch_forward_short_soft(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns, float *partials,
+                                 int spread, void *stream);

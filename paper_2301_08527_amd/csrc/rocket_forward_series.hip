@@ -283,8 +283,9 @@ __device__ __forceinline__ void ser_plain(int k, const RkKernelRec *__restrict__
     for (int off = 32; off > 0; off >>= 1) {
         st.vmax = fmaxf(st.vmax, __shfl_xor(st.vmax, off));
         st.ssum += __shfl_xor(st.ssum, off);
+        if constexpr (rk_counts_by_lane(MASK)) st.cnt += __shfl_xor(st.cnt, off);
     }
-    if (lane != 0) return;       // the first lane has a position in every round and so all counts
+    if (lane != 0) return;       // the first lane has a position in every round, and so the wavefront's count
     float *o = out + k;
     if constexpr ((MASK & ROCKET_F_MAX) != 0) { *o = st.vmax + rec.bias; o += K; }
     if constexpr ((MASK & ROCKET_F_PPV) != 0) { *o = static_cast<float>(static_cast<double>(st.cnt) / static_cast<double>(rec.nout)); o += K; }

@@ -5,13 +5,11 @@
 #include "rocket_forward_impl.hpp"
 
 int rk_launch_forward_short(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns,
-                            float *partials, void *stream_ptr)
+                            float *partials, void *stream)
 {
-    hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
-    const int J = static_cast<int>(h->jobs.size());
     const int spread = 0;   // measured: the per-XCD series mapping makes the short-series launch 2 % slower
-    hipLaunchKernelGGL(rk_forward<64>, dim3(static_cast<unsigned>(B) * static_cast<unsigned>(J)), dim3(64), 0, stream, xpad,
-                       static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs, h->d_channels,
-                       h->d_weights, mask, nl, ns, partials, B, spread);
-    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+    if (mask & ROCKET_F_SOFTPPV) return rk_launch_forward_short_soft(h, xpad, B, mask, nl, ns, partials, spread, stream);
+    if (mask == ROCKET_F_MAX) return rk_forward_launch<64, ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
+    if (mask == ROCKET_F_PPV) return rk_forward_launch<64, ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
+    return rk_forward_launch<64, ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
 }
