@@ -48,6 +48,24 @@ __device__ __forceinline__ void rk_track_max(float z, int t, BwdState &st)
     if (z > st.vmax || (z == st.vmax && t < st.targ)) { st.vmax = z; st.targ = t; }
 }
 
+// The same for the outputs t0, t0 + d, ... of a strip: their maximum first, half an instruction an output, and its first position only if
+// some lane of the wavefront needs it, two.  (Output by output the rule takes five and two scalar ones:
+// 15 x 20 x 50,000, 10,000 kernels 16.85 -> 16.40 ms, 64 x 1 x 1,000, 1,000 kernels 95 -> 88 us, 30 x 1 x 20,000, 2,000 kernels 1,230 -> 1,104.
+// The few-rows strips, whose last row only some lanes have, keep it: there this form cost a wavefront per SIMD.)
+template <int R>
+__device__ __forceinline__ void rk_track_strip(const float (&z)[R], int t0, int d, BwdState &st)
+{
+    float m = z[0];
+#pragma unroll
+    for (int i = 1; i < R; ++i) m = fmaxf(m, z[i]);
+    if (__ballot(m >= st.vmax) == 0u) return;      // uniform
+    int first = 0;
+#pragma unroll
+    for (int i = R - 1; i > 0; --i) first = z[i] == m ? i : first;
+    first = z[0] == m ? 0 : first;
+    rk_track_max(m, t0 + first * d, st);
+}
+
 // Sum over each row of 16 lanes (all 16 lanes end up with the row sum).
 __device__ __forceinline__ float rk_row16_sum(float v)
 {
@@ -153,12 +171,7 @@ __device__ __forceinline__ void rk_bwd_segment(const KernelCtx &k, int row0, int
                 rk_taps<LEN, R, i>(w, xlast[i], acc);
             });
         }
-        if (want_max) {
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-                rk_track_max(acc[i], t0 + i * k.d, st);
-            }
-        }
+        if (want_max) rk_track_strip<R>(acc, t0, k.d, st);
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             acc[i] = rk_q(acc[i], lane_coef, k.nl, k.ns);   // acc now holds q
@@ -252,12 +265,7 @@ __device__ __forceinline__ void rk_bwd_band(const KernelCtx &k, int row0, int nc
         rk_static_for<0, S>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             if (live[s]) {
-                if (want_max) {
-#pragma unroll
-                    for (int i = 0; i < R; ++i) {
-                        rk_track_max(acc[s][i], t0[s] + i * k.d, st);
-                    }
-                }
+                if (want_max) rk_track_strip<R>(acc[s], t0[s], k.d, st);
 #pragma unroll
                 for (int i = 0; i < R; ++i) {
                     acc[s][i] = rk_q(acc[s][i], lane_coef[s], k.nl, k.ns);   // acc now holds q
@@ -434,12 +442,7 @@ __device__ __forceinline__ int rk_bwd_lds_bands(const KernelCtx &k, int first_ro
         }
         {
             const int t0 = (first_row + (band0 + bl) * R) * D + r;
-            if (want_max) {
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    rk_track_max(acc[i], t0 + i * D, st);
-                }
-            }
+            if (want_max) rk_track_strip<R>(acc, t0, D, st);
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 acc[i] = rk_q(acc[i], lane_coef, k.nl, k.ns);
