@@ -20,7 +20,8 @@
 //                               rr_trailing where much is left).  The row of yc takes part like any
 //                               other row, so when the factorisation ends it holds L^-1 yc (forward
 //                               substitution costs nothing extra).
-//   rr_back_substitute          L^T a = L^-1 yc, panel by panel, one workgroup
+//   rr_back_substitute          L^T a = L^-1 yc, panel by panel, one workgroup, with the inverses of the diagonal
+//                               blocks that a workgroup of the next panel's launch makes (rr_invert_block)
 //   rr_coef_partial, rr_coef_finish, rr_intercept     w = Xc^T a and b
 //   rr_predict                  yhat = X w + b, one workgroup per row
 #include <hip/hip_runtime.h>
@@ -28,6 +29,8 @@
 #include <algorithm>
 #include <cmath>
 #include <string>
+#include <type_traits>
+#include <utility>
 
 #include "rocket_internal.hpp"
 
@@ -357,6 +360,57 @@ __device__ __forceinline__ void rr_store_block(double *__restrict__ D, int k0, c
     for (int c = 0; c < kNB; ++c) dst[c] = c <= l ? row[c] : 0.0;
 }
 
+// A factored diagonal block (32 x 32: the rows of L, with the reciprocals of its diagonal) to L^-1, in place, by one wavefront, through
+// `block` (LDS of this wavefront alone).  The two 16 x 16 blocks on the diagonal side by side, lane m row m of its block's inverse,
+// with no value of another lane; the one below them, -C^-1 B A^-1, on the matrix unit.  The back substitution multiplies by these
+// instead of substituting; a panel's block is inverted beside the next panel, which it does not hold up.
+constexpr int kBlockPitch = kNB + 1;
+__device__ __forceinline__ void rr_invert_block(double *__restrict__ D, double *block)
+{
+    const int l = threadIdx.x & 63, r = l & 15, q = l >> 4, corner = l & 16;       // lanes 32..63 repeat lanes 0..31
+#pragma unroll
+    for (int i = 0; i < kNB * kNB / 64; ++i) block[(2 * i + (l >> 5)) * kBlockPitch + (l & 31)] = D[64 * i + l];
+    rr_wave_lds();
+    double u[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) u[c] = c == r ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 15; k >= 0; --k) {
+        const double *row = block + (corner + k) * kBlockPitch + corner;
+        u[k] *= row[k];
+#pragma unroll
+        for (int c = 0; c < k; ++c) {
+            u[c] = fma(-row[c], u[k], u[c]);
+            rr_here(u[c]);
+        }
+    }
+    rr_wave_lds();
+    if (l < kNB) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) block[l * kBlockPitch + corner + c] = u[c];
+    }
+    rr_wave_lds();
+    // a product with the block below: of its 16 inner indices lane q takes 4 q .. 4 q + 3, on both sides
+    auto times = [&](int lrow, int lcol, int rrow, int rcol) {
+        d4 sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            sum = rr_mfma(block[(lrow + r) * kBlockPitch + lcol + 4 * q + e], block[(rrow + 4 * q + e) * kBlockPitch + rcol + r], sum);
+        rr_wave_lds();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) block[(16 + 4 * v + q) * kBlockPitch + r] = sum[v];
+        rr_wave_lds();
+    };
+    times(16, 0, 0, 0);         // B A^-1
+    times(16, 16, 16, 0);       // C^-1 (B A^-1)
+#pragma unroll
+    for (int i = 0; i < kNB * kNB / 64; ++i) {
+        const int m = 2 * i + (l >> 5), c = l & 31;
+        const double v = block[m * kBlockPitch + c];
+        D[64 * i + l] = m >= 16 && c < 16 ? -v : v;
+    }
+}
+
 // One panel in one launch: a workgroup of two wavefronts per 32 x 32 tile (ti >= tj) of what is left.  Each wavefront factors
 // the diagonal block itself and solves the 32 rows of one side of the tile; the rows meet in LDS and the tile gets its
 // rank-32 update.  The factoring is repeated by every tile, on units that would idle: a step takes its latency as long as the
@@ -366,12 +420,16 @@ __device__ __forceinline__ void rr_store_block(double *__restrict__ D, int k0, c
 __global__ __launch_bounds__(128) void rr_step(double *__restrict__ M, int ld, int nrows, int k0, int nb,
                                                double *__restrict__ D)
 {
+    __shared__ double side[2][32][kNB + 1];
+    if (k0 > 0 && blockIdx.x + 1 == gridDim.x) {        // the last workgroup: the block of the panel before
+        if (threadIdx.x < 64) rr_invert_block(D + static_cast<size_t>(k0 / kNB - 1) * (kNB * kNB), &side[0][0][0]);
+        return;
+    }
     // tile blockIdx.x of the lower triangle, row by row; the root is off by one at most (48 rows of tiles)
     int ti = static_cast<int>((sqrtf(8.0f * static_cast<float>(blockIdx.x) + 1.0f) - 1.0f) * 0.5f);
     if ((ti + 1) * (ti + 2) / 2 <= static_cast<int>(blockIdx.x)) ++ti;
     if (ti * (ti + 1) / 2 > static_cast<int>(blockIdx.x)) --ti;
     const int tj = static_cast<int>(blockIdx.x) - ti * (ti + 1) / 2;
-    __shared__ double side[2][32][kNB + 1];
     __shared__ __attribute__((aligned(16))) double half[2][64][kHalfPitch];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
     const int first = k0 + nb, rows = nrows - first, cols = rows - 1;   // the row of yc has no column
@@ -417,6 +475,11 @@ __global__ __launch_bounds__(64) void rr_panel(double *__restrict__ M, int ld, i
 {
     const int l = threadIdx.x, first = k0 + nb, mine = first + 32 * static_cast<int>(blockIdx.x);
     __shared__ __attribute__((aligned(16))) double half[64][kHalfPitch];
+    static_assert(64 * kHalfPitch >= kNB * kBlockPitch, "the block to be inverted lies there");
+    if (k0 > 0 && blockIdx.x + 1 == gridDim.x) {        // as in rr_step
+        rr_invert_block(D + static_cast<size_t>(k0 / kNB - 1) * (kNB * kNB), &half[0][0]);
+        return;
+    }
     double row[kNB];
     rr_factor_rows(M, ld, nrows, k0, nb, mine, row, half);
     rr_store_rows(M, ld, nrows, k0, nb, mine, row);
@@ -468,29 +531,40 @@ __global__ __launch_bounds__(64) void rr_trailing(double *__restrict__ M, int ld
             }
 }
 
-// One workgroup.  The upper triangle of M holds L^T, its column n z = L^-1 yc, D the factored diagonal blocks with the
-// reciprocals of their diagonals.  Solves L^T a = z from the last panel to the first: the first wavefront solves a panel, then
-// every thread takes it out of the right-hand sides above it.  Thread t keeps right-hand sides t and t + kBackThreads in
-// registers (those further on are in `a`) and their 32 factors of the next panel are on their way while the panel before is
-// solved; the chain of 32 x (multiply, readlane, multiply-add) per panel is what is left.  n = 677: 188 -> 73 us.
+// One workgroup.  The upper triangle of M holds L^T, its column n z = L^-1 yc, D the inverted diagonal blocks, the last one as it was
+// factored.  Solves L^T a = z from the last panel to the first: the first wavefront multiplies a panel's right-hand sides by its block
+// (the chain of 32 x (multiply, readlane, multiply-add) that a substitution is was 2.6 of the 3.3 us of a panel), then
+// everyone takes it out of the right-hand sides above it.  Eight lanes share a row, so that a load instruction takes whole
+// lines (a lane that walks a row of its own finds its lines evicted before it has used them), each keeps its own part of the
+// row's right-hand side, and the parts meet when the row's panel comes up.  Group g owns rows g, g + 64, ...; rows from
+// kBackRows on are in `a`.  The factors of the next panel are on their way while the panel before is solved.  n = 677: 72 -> 45 us;
+// whole fits 677 x 20,000 470 -> 452 us, 1,000 x 500 469 -> 419, 2,000 x 3,000 1,936 -> 1,745.  Relative errors of the coefficients
+// against 80-bit sums (2-norm, rms of four data sets), substituted -> multiplied: 33 x 300 1.29e-15 -> 1.34e-15, 64 x 500 2.08e-15
+// both, 137 x 1,000 3.81e-15 -> 3.79e-15, 200 x 900 at alpha = 0.001 6.18e-15 -> 6.17e-15, 260 x 1,300 7.22e-15 -> 7.17e-15.
 constexpr int kBackThreads = 512;
-constexpr int kBackOwn = 2;
+constexpr int kBackGroups = kBackThreads / 8;
+constexpr int kBackOwn = 16;
+constexpr int kBackRows = kBackGroups * kBackOwn;
 __global__ __launch_bounds__(kBackThreads) void rr_back_substitute(const double *__restrict__ M, int ld, int n,
                                                                    const double *__restrict__ D, double *a)
 {
-    __shared__ double rhs[kNB], found[kNB];
+    __shared__ __attribute__((aligned(16))) double rhs[kNB], found[kNB];
     __shared__ double block[2][kNB][kNB + 1];
     const int t = threadIdx.x, c = t & 31, g = t >> 5;
+    const int group = t >> 3, part = t & 7;
     const int last = (n - 1) / kNB * kNB;
-    double mine[kBackOwn], factor[kBackOwn][kNB];
+    double mine[kBackOwn], factor[kBackOwn][4];      // this lane's columns of a panel: 2 part, 2 part + 1, and 16 further on
 #pragma unroll
     for (int o = 0; o < kBackOwn; ++o) {
-        const int j = t + o * kBackThreads;
-        mine[o] = j < n ? M[static_cast<size_t>(j) * ld + n] : 0.0;
+        const int j = group + o * kBackGroups;
+        mine[o] = part == 0 && j < n ? M[static_cast<size_t>(j) * ld + n] : 0.0;
 #pragma unroll
-        for (int m = 0; m < kNB; ++m) factor[o][m] = j < last && last + m < n ? M[static_cast<size_t>(j) * ld + last + m] : 0.0;
+        for (int e = 0; e < 4; ++e) {
+            const int m = last + 2 * part + 16 * (e / 2) + e % 2;
+            factor[o][e] = j < last && m < n ? M[static_cast<size_t>(j) * ld + m] : 0.0;
+        }
     }
-    for (int j = t + kBackOwn * kBackThreads; j < n; j += kBackThreads) a[j] = M[static_cast<size_t>(j) * ld + n];
+    for (int j = t + kBackRows; j < n; j += kBackThreads) a[j] = M[static_cast<size_t>(j) * ld + n];
     const double *src_block = D + static_cast<size_t>(last / kNB) * (kNB * kNB) + t;
     block[0][g][c] = src_block[0];
     block[0][g + 16][c] = src_block[512];
@@ -503,24 +577,43 @@ __global__ __launch_bounds__(kBackThreads) void rr_back_substitute(const double 
             next0 = src_block[0];
             next1 = src_block[512];
         }
-        if (k0 < kBackOwn * kBackThreads) {      // panels do not straddle the owners: 32 divides kBackThreads
+        if (k0 < kBackRows) {      // a panel's rows have one place among their owners': 32 divides kBackGroups
+            const int at = group - k0 % kBackGroups;
+            if (at >= 0 && at < kNB) {
+                double v = 0.0;
 #pragma unroll
-            for (int o = 0; o < kBackOwn; ++o) {
-                const int at = t + o * kBackThreads - k0;
-                if (at >= 0 && at < kNB) rhs[at] = mine[o];     // 0 past the last
+                for (int o = 0; o < kBackOwn; ++o)
+                    if (o == k0 / kBackGroups) v = mine[o];     // 0 past the last
+                v += __shfl_xor(v, 1);
+                v += __shfl_xor(v, 2);
+                v += __shfl_xor(v, 4);
+                if (part == 0) rhs[at] = v;
             }
         } else if (t < kNB) {
             rhs[t] = k0 + t < n ? a[k0 + t] : 0.0;
         }
         __syncthreads();
         if (t < 64) {
-            double v = rhs[c], x = 0.0;
-            const double inv = block[turn][c][c];
+            double x = 0.0;
+            if (k0 == last) {
+                double v = rhs[c];
+                const double inv = block[turn][c][c];
 #pragma unroll 16
-            for (int m = kNB - 1; m >= 0; --m) {
-                const double xm = rr_lane(v * inv, m);
-                if (c == m) x = xm;
-                v = fma(-block[turn][m][c], xm, v);              // meaningful where c < m
+                for (int m = kNB - 1; m >= 0; --m) {
+                    const double xm = rr_lane(v * inv, m);
+                    if (c == m) x = xm;
+                    v = fma(-block[turn][m][c], xm, v);          // meaningful where c < m
+                }
+            } else {        // lane (c, half of the panel)
+                const int from = t >> 5 << 4;
+                double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                for (int m = 0; m < kNB / 2; m += 2) {
+                    s0 = fma(block[turn][from + m][c], rhs[from + m], s0);
+                    s1 = fma(block[turn][from + m + 1][c], rhs[from + m + 1], s1);
+                }
+                x = s0 + s1;
+                x += __shfl_xor(x, 32);
             }
             if (t < kNB) {
                 found[t] = x;
@@ -530,25 +623,31 @@ __global__ __launch_bounds__(kBackThreads) void rr_back_substitute(const double 
         block[turn ^ 1][g][c] = next0;
         block[turn ^ 1][g + 16][c] = next1;
         __syncthreads();
+        const double2 x0 = *reinterpret_cast<const double2 *>(found + 2 * part);
+        const double2 x1 = *reinterpret_cast<const double2 *>(found + 16 + 2 * part);
 #pragma unroll
         for (int o = 0; o < kBackOwn; ++o) {
-            const int j = t + o * kBackThreads;
-            if (j < k0) {
-#pragma unroll
-                for (int m = 0; m < kNB; ++m) mine[o] = fma(-factor[o][m], found[m], mine[o]);
-            }
-            if (j < k0 - kNB) {
-                const double2 *src = reinterpret_cast<const double2 *>(M + static_cast<size_t>(j) * ld + k0 - kNB);
-#pragma unroll
-                for (int m = 0; m < kNB; m += 2) {
-                    const double2 f = src[m / 2];
-                    factor[o][m] = f.x;
-                    factor[o][m + 1] = f.y;
-                }
-            }
+            if (o * kBackGroups >= k0) continue;
+            mine[o] = fma(-factor[o][0], x0.x, mine[o]);     // rows from k0 on have been solved: nobody reads theirs again
+            mine[o] = fma(-factor[o][1], x0.y, mine[o]);
+            mine[o] = fma(-factor[o][2], x1.x, mine[o]);
+            mine[o] = fma(-factor[o][3], x1.y, mine[o]);
+            rr_here(mine[o]);      // now, and not after the next factors have come to stand beside these
         }
-        if (k0 > kBackOwn * kBackThreads) {
-            for (int j = t + kBackOwn * kBackThreads; j < k0; j += kBackThreads) {
+#pragma unroll
+        for (int o = 0; o < kBackOwn; ++o) {
+            if (o * kBackGroups >= k0 - kNB) continue;
+            // rows that need no more repeat the last one that does; ld is a multiple of 4, M 256-byte aligned
+            const int j = min(group + o * kBackGroups, k0 - kNB - 1);
+            const double2 *src = reinterpret_cast<const double2 *>(M + static_cast<size_t>(j) * ld + k0 - kNB) + part;
+            const double2 f0 = src[0], f1 = src[8];
+            factor[o][0] = f0.x;
+            factor[o][1] = f0.y;
+            factor[o][2] = f1.x;
+            factor[o][3] = f1.y;
+        }
+        if (k0 > kBackRows) {
+            for (int j = t + kBackRows; j < k0; j += kBackThreads) {
                 double s = a[j];
 #pragma unroll 4
                 for (int m = 0; m < kNB; ++m) s = fma(k0 + m < n ? -M[static_cast<size_t>(j) * ld + k0 + m] : 0.0, found[m], s);
@@ -559,6 +658,7 @@ __global__ __launch_bounds__(kBackThreads) void rr_back_substitute(const double 
     }
 }
 static_assert(kBackThreads == 16 * kNB, "the diagonal blocks are copied as two halves");
+static_assert(kBackGroups % kNB == 0 && kBackRows % kNB == 0, "panels do not straddle the owners");
 
 // wpart[r][j] = sum over the rows i of slice r of a[i] * (X[i][j] - mean_j)
 __global__ __launch_bounds__(256) void rr_coef_partial(const float *__restrict__ X, const double *__restrict__ means,
@@ -739,11 +839,11 @@ extern "C" int rocket_ridge_fit(const float *features_dev, const float *targets_
     for (int k0 = 0; k0 < n; k0 += kNB) {
         const int nb = std::min(kNB, n - k0);
         const int first = k0 + nb, rows = nrows - first;   // rows >= 1: the row of yc is always below
-        const int t = (rows + 31) / 32;
+        const int t = (rows + 31) / 32, more = k0 > 0 ? 1 : 0;      // a workgroup more inverts the block of the panel before
         if (t <= kFusedTiles) {
-            hipLaunchKernelGGL(rr_step, dim3(t * (t + 1) / 2), dim3(128), 0, stream, M, q.ld, nrows, k0, nb, D);
+            hipLaunchKernelGGL(rr_step, dim3(t * (t + 1) / 2 + more), dim3(128), 0, stream, M, q.ld, nrows, k0, nb, D);
         } else {   // so many rows are left that the panel is 32 columns wide and columns follow it
-            hipLaunchKernelGGL(rr_panel, dim3(t), dim3(64), 0, stream, M, q.ld, nrows, k0, nb, P, D);
+            hipLaunchKernelGGL(rr_panel, dim3(t + more), dim3(64), 0, stream, M, q.ld, nrows, k0, nb, P, D);
             hipLaunchKernelGGL(rr_trailing, dim3(t, t), dim3(64), 0, stream, M, q.ld, first, rows, rows - 1, P);
         }
     }
