@@ -119,21 +119,15 @@ __global__ __launch_bounds__(256) void rr_means(const double *__restrict__ part,
 // so that one XCD (workgroup ids go round the eight of them) takes all tile pairs of a slice one
 // after the other: the slab of X for that slice then stays in that XCD's L2.  The order of the
 // features inside a step of 16 is permuted (lane q = l / 16 takes features 4q..4q+3 as one
-// 16-byte load); a sum does not care, and both operands use the same permutation.
-__global__ __launch_bounds__(64) void rr_gram(const float *__restrict__ X, const double *__restrict__ means, int n,
-                                              int p, int tiles, int pairs, int chunk, int splits,
-                                              double *__restrict__ part)
+// 16-byte load); a sum does not care, and both operands use the same permutation.  Of a pair of equal tiles only the blocks on
+// and above the diagonal are computed, and the loads of a step are on their way while the last quarter of the step before is
+// multiplied (1,024 clk of the matrix unit): 677 x 20,000 whole fits 452 -> 439 us, 70 x 30,000 136 -> 127.  What bounds it is
+// the matrix unit with the conversions, which do not run beside it (f64 both): together 160 of the launch's 200 us.
+template <bool DIAG>
+__device__ __forceinline__ void rr_gram_pair(const float *__restrict__ X, const double *__restrict__ means, int n, int p, int ti, int tj,
+                                             int kbeg, int kend, double *__restrict__ dst)
 {
-    const int total = pairs * splits, per = (total + 7) / 8;
-    const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (blockIdx.x / 8 >= per || w >= total) return;
-    const int split = w / pairs, pair = w % pairs;
-    int ti = 0, rem = pair;
-    while (rem >= tiles - ti) { rem -= tiles - ti; ++ti; }
-    const int tj = ti + rem;
-    const bool diag = ti == tj;
     const int l = threadIdx.x, r = l & 15, q = l >> 4;
-    const int kbeg = split * chunk, kend = min(p, kbeg + chunk);
 
     const float *pa[4], *pb[4];   // rows past n repeat row n - 1: their results are never stored
 #pragma unroll
@@ -147,14 +141,14 @@ __global__ __launch_bounds__(64) void rr_gram(const float *__restrict__ X, const
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
 
-    for (int k0 = kbeg; k0 < kend; k0 += 16) {
+    f4u xa[4], xb[4];
+    d4 mu;
+    auto load = [&](int k0) {
         const int k = k0 + 4 * q;
-        f4u xa[4], xb[4];
-        d4 mu;
         if (k0 + 16 <= kend) {
 #pragma unroll
             for (int a = 0; a < 4; ++a) xa[a] = *reinterpret_cast<const f4u *>(pa[a] + k);
-            if (!diag) {
+            if (!DIAG) {
 #pragma unroll
                 for (int a = 0; a < 4; ++a) xb[a] = *reinterpret_cast<const f4u *>(pb[a] + k);
             }
@@ -167,30 +161,53 @@ __global__ __launch_bounds__(64) void rr_gram(const float *__restrict__ X, const
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     xa[a][e] = ok ? pa[a][k + e] : 0.0f;
-                    xb[a][e] = ok ? pb[a][k + e] : 0.0f;
+                    if (!DIAG) xb[a][e] = ok ? pb[a][k + e] : 0.0f;
                 }
             }
         }
+    };
+    load(kbeg);
+    for (int k0 = kbeg; k0 < kend; k0 += 16) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             double am[4], bm[4];
 #pragma unroll
             for (int a = 0; a < 4; ++a) am[a] = static_cast<double>(xa[a][e]) - mu[e];
 #pragma unroll
-            for (int a = 0; a < 4; ++a) bm[a] = diag ? am[a] : static_cast<double>(xb[a][e]) - mu[e];
+            for (int a = 0; a < 4; ++a) bm[a] = DIAG ? am[a] : static_cast<double>(xb[a][e]) - mu[e];
+            if (e == 3) {       // the step's features have all been converted: the next ones come while the last are multiplied
+                __builtin_amdgcn_sched_barrier(0);
+                if (k0 + 16 < kend) load(k0 + 16);      // uniform
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = rr_mfma(am[a], bm[b], acc[a][b]);
+                for (int b = DIAG ? a : 0; b < 4; ++b) acc[a][b] = rr_mfma(am[a], bm[b], acc[a][b]);
         }
     }
-    double *dst = part + (static_cast<size_t>(pair) * splits + split) * (kGramTile * kGramTile);
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = DIAG ? a : 0; b < 4; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) dst[(16 * a + 4 * v + q) * kGramTile + 16 * b + r] = acc[a][b][v];
+}
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void rr_gram(const float *__restrict__ X, const double *__restrict__ means, int n, int p, int tiles, int pairs, int chunk, int splits,
+             double *__restrict__ part)
+{
+    const int total = pairs * splits, per = (total + 7) / 8;
+    const int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= per || w >= total) return;
+    const int split = w / pairs, pair = w % pairs;
+    int ti = 0, rem = pair;
+    while (rem >= tiles - ti) { rem -= tiles - ti; ++ti; }
+    const int tj = ti + rem, kbeg = split * chunk, kend = min(p, kbeg + chunk);
+    double *dst = part + (static_cast<size_t>(pair) * splits + split) * (kGramTile * kGramTile);
+    if (ti == tj) rr_gram_pair<true>(X, means, n, p, ti, tj, kbeg, kend, dst);
+    else rr_gram_pair<false>(X, means, n, p, ti, tj, kbeg, kend, dst);
 }
 
 // M (n+1 rows, leading dimension ld): the lower triangle of Xc Xc^T + alpha I in rows 0..n-1,
