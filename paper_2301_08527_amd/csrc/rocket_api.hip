@@ -586,7 +586,7 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
 }
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront forward kernel
+constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront kernels
 constexpr int kOneWaveSeries = 1024;     // some 64 strips of 16 or more rows: one for each lane of a wavefront
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
@@ -666,16 +666,27 @@ static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, d
     return best;
 }
 
-// The groups of a transform without softPPV (rocket_forward_groups.hip).  Of 21 shapes measured at every width the rule takes the
-// fastest or one within 8 % of it; what it chooses, against one series at a time, max and PPV, in us: 28 x 15 x 134 and 2,351 kernels
-// 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236 88/402 (32 series; 16: 91, 64: 103), 4 x 5 x 300 and 10,000 33/49 (4), 149 x 18 x 1,263 and
-// 4,822 1,076/1,640 (8; 2: 1,315, 32: 1,415), 227 x 16 x 930 and 5,723 1,386/2,210 (16; 4: 1,575).  Series of thousands of samples gain
-// little or nothing (23 x 6 x 4,099 and 1,537 185/181, 16 x 3 x 2,000 and 300 30/24), so the estimate has to be a tenth better.
-static RkGroups forward_groups(const rocket_kernels *h, int32_t B, uint32_t mask)
+// How a transform of short series without softPPV goes: in groups (rocket_forward_groups.hip), or one series at a time on one wavefront
+// or, where a few kernels of a few series leave most of the chip idle and the longest of them is what takes the time, on four.  (All ways
+// give the same bits.  Sums of sigmoids depend on the way, which must follow from the handle alone: they stay on one wavefront.)
+// Four wavefronts need a tenth's lead over one by the estimates, groups a twentieth more (4 x 20 x 1,200 and 10,000 kernels: ahead by 12 %
+// there, 106 us against 99).  Max and PPV, in us.  Groups, of 21 shapes measured at every width the fastest or one
+// within 8 % of it, against one wavefront: 28 x 15 x 134 samples and 2,351 kernels 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236
+// 88/402 (32 series; 16: 91, 64: 103), 4 x 5 x 300 and 10,000 33/49 (4), 149 x 18 x 1,263 and 4,822 1,076/1,640 (8; 2: 1,315, 32: 1,415),
+// 227 x 16 x 930 and 5,723 1,386/2,210 (16; 4: 1,575).  Series of thousands of samples gain little or nothing (23 x 6 x 4,099 and 1,537
+// 185/181, 16 x 3 x 2,000 and 300 30/24).  Four wavefronts against one: 1 x 14 x 2,857 and 1,724 26/54, 1 x 20 x 8,000 and 1,000
+// 46/128, 24 x 20 x 8,000 and 1,000 265/335, 8 x 6 x 4,099 and 300 26/49, 2 x 20 x 5,000 and 10,000 167/175, 4 x 20 x 5,000 and
+// 10,000 311/289, 8 x 2 x 3,000 and 2,000 54/46.
+struct ForwardWay { RkGroups groups; bool wide; };
+static ForwardWay forward_way(const rocket_kernels *h, int32_t B, uint32_t mask)
 {
-    if (!rk_launchers().forward_groups || (mask & ROCKET_F_SOFTPPV) || h->L > kShortSeries) return rk_groups(B, 1, 1);
-    const Estimate plain = estimate(h, static_cast<double>(B) * h->K, 1, 1, 20, 1, 6);
-    return best_groups(h, B, 1, 6, 0.9 * (plain.work + plain.last), 0);
+    ForwardWay way = {rk_groups(B, 1, 1), h->L > kShortSeries};
+    if (way.wide || (mask & ROCKET_F_SOFTPPV) || h->jobs.size() != static_cast<size_t>(h->K)) return way;
+    const Estimate one = estimate(h, static_cast<double>(B) * h->K, 1, 1, 20, 1, 6), four = estimate(h, static_cast<double>(B) * h->K, 4, 1, 10, 1, 6);
+    double least = 0.9 * (one.work + one.last);
+    if (rk_launchers().forward_wide && four.work + four.last < least) { least = four.work + four.last; way.wide = true; }
+    if (rk_launchers().forward_groups) way.groups = best_groups(h, B, 1, 6, 0.95 * least, 0);
+    return way;
 }
 
 // Series of which one wavefront takes all strips of a kernel in a pass or two leave the other three of a workgroup of
@@ -731,8 +742,9 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     // the padded copy); the sets' edges rest on lambda > 0.  Which path a call takes follows from the handle and from lambda, never
     // from the batch.
     const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
-    const RkGroups groups = series ? RkGroups{} : forward_groups(h, B, mask);
-    if (!series && groups.width > 1) {
+    const ForwardWay way = series ? ForwardWay{rk_groups(B, 1, 1), false} : forward_way(h, B, mask);
+    const RkGroups &groups = way.groups;
+    if (groups.width > 1) {
         if (rk_launchers().pad_groups(h, x_dev, is_u8, B, groups, xpad, static_cast<char *>(ws) + row_stats_offset(h, B, 0), stream) != ROCKET_OK)
             return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
         if (!resident_only) rc = profile_mark(h, stream, true);
@@ -755,10 +767,9 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
             return rk_fail(ROCKET_EHIP, "launch of the series kernel failed");
         return resident_only ? ROCKET_OK : profile_mark(h, stream, false);
     }
-    // series of at most kShortSeries samples: one wavefront per (series, kernel) instead of four
     float *partials = reinterpret_cast<float *>(static_cast<char *>(ws) + padded_batch_bytes(h, B));
-    const int launched = h->L <= kShortSeries ? rk_launch_forward_short(h, xpad, B, mask, nl, ns, partials, stream)
-                                              : rk_launch_forward(h, xpad, B, mask, nl, ns, partials, stream);
+    const auto forward = !way.wide ? rk_launch_forward_short : h->L > kShortSeries ? rk_launch_forward : rk_launchers().forward_wide;
+    const int launched = forward(h, xpad, B, mask, nl, ns, partials, stream);
     if (launched != ROCKET_OK) return rk_fail(ROCKET_EHIP, "launch of the forward kernel failed");
     if (!resident_only) rc = profile_mark(h, stream, false);
     if (rc != ROCKET_OK) return rc;

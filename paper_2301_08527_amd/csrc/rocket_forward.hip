@@ -104,3 +104,5 @@ int rk_launch_finalize(const rocket_kernels *h, const float *partials, int32_t B
                        static_cast<int>(h->jobs.size()), h->d_rec, h->d_kjob_off, h->d_kjob_idx, mask, out);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
+
+[[maybe_unused]] static const bool kEntered = (rk_launchers().forward_wide = rk_launch_forward, true);

@@ -232,6 +232,9 @@ struct RkLaunchers {
     // rocket_forward_series.hip: the transform of a handle's sets (nl < 0 where the mask has softPPV).  x as below.
     int (*forward_series)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, uint32_t mask, float nl, float ns,
                           float *out, void *stream) = nullptr;
+    // rocket_forward.hip: rk_launch_forward, for short series too
+    int (*forward_wide)(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns, float *partials,
+                        void *stream) = nullptr;
     // rocket_minirocket_forward.hip.  x: rows of L samples that start row_stride floats apart.  Adds every work item's
     // positive counts to `counts`, or, where minirocket_one_pass says so, writes the features to `out`.
     int (*minirocket_forward)(const rocket_kernels *h, const float *x, int64_t row_stride, int32_t B, int32_t *counts, float *out,

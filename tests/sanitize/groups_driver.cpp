@@ -64,9 +64,11 @@ static int backward_groups_stub(const rocket_kernels *, const float *, const RkG
 }
 static int forward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, uint32_t, float *, void *) RECORD("forward_groups")
 static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, float *, void *) RECORD("series")
+static int forward_wide_stub(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("wide")
 [[maybe_unused]] static const bool kEntered = (rk_launchers().backward_short = backward_short_stub, rk_launchers().pad_groups = pad_groups_stub,
                                                rk_launchers().backward_groups = backward_groups_stub,
-                                               rk_launchers().forward_groups = forward_groups_stub, rk_launchers().forward_series = series_stub, true);
+                                               rk_launchers().forward_groups = forward_groups_stub, rk_launchers().forward_series = series_stub,
+                                               rk_launchers().forward_wide = forward_wide_stub, true);
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s (route: %s, width %d of %d)\n", __LINE__, #cond, g_route.c_str(), g_groups.width, g_groups.first_series); return 1; } } while (0)
 
@@ -171,6 +173,18 @@ int main()
             CHECK(forward(h, w.B, mask, true) == ROCKET_OK && g_route == "pad_groups_u8 forward_groups ");
         }
         CHECK(forward(h, w.B, 7) == ROCKET_OK && g_groups.width == 1);
+        rocket_free_kernels(h);
+    }
+    // four wavefronts to a job where one would be what takes the time; sums of sigmoids stay on one
+    const struct { int32_t B, C, L, K; const char *route; } width[] = {
+        {1, 14, 2857, 1724, "pad wide finalize "}, {24, 14, 2857, 1724, "pad short finalize "}, {24, 20, 8000, 1000, "pad wide finalize "},
+        {8, 2, 3000, 2000, "pad short finalize "}, {1, 20, 1200, 10000, "pad short finalize "}, {1, 20, 8193, 1000, "pad forward finalize "}};
+    for (const auto &w : width) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        for (uint32_t mask = 1; mask <= 3; ++mask) CHECK(forward(h, w.B, mask) == ROCKET_OK && g_route == w.route);
+        for (uint32_t mask = 4; mask <= 7; ++mask)
+            CHECK(forward(h, w.B, mask) == ROCKET_OK && g_route == (w.L > 8192 ? "pad forward finalize " : "pad short finalize "));
         rocket_free_kernels(h);
     }
     rocket_kernels *sets = nullptr;

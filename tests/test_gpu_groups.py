@@ -143,6 +143,22 @@ def test_features_of_groups(B, C, L, K, groups, u8):
         assert rc == rocket.ROCKET_OK and torch.equal(out, both)
 
 
+@pytest.mark.parametrize("C,L,K,B", [(14, 2857, 1724, 24), (2, 3000, 2000, 9), (5, 8192, 700, 40), (1, 1500, 300, 120), (3, 1030, 1100, 3)])
+def test_four_wavefronts_give_the_same_bits(C, L, K, B):
+    """one series alone takes four wavefronts to a kernel (tests/sanitize/groups_driver.cpp), a batch one or groups: all their features"""
+    import torch
+    x = np.random.default_rng(K).standard_normal((B, C, L)).astype(np.float32)
+    h = rocket.rocket_make_kernels(K, K, C, L)
+    xd = _gpu(x)
+    print("four wavefronts", C, L, K, B, flush=True)
+    for mask in (1, 2, 3):
+        batch = rocket.rocket_transform(h, xd, mask)
+        for b in (0, B // 2, B - 1):
+            assert torch.equal(rocket.rocket_transform(h, xd[b:b + 1].contiguous(), mask), batch[b:b + 1]), (mask, b)
+    kr = rocket.rocket_kernels_view_get(h)
+    check_forward(x[:1], kr, rocket.rocket_transform(h, xd[:1].contiguous(), 3).cpu().numpy(), 3, sel=np.arange(0, K, max(1, K // 200), dtype=np.int32))
+
+
 def test_groups_keep_their_series_apart():
     """infinite, undefined and huge samples in some series of a group leave the others' features as they are"""
     import torch
