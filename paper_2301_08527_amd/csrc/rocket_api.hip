@@ -1,14 +1,16 @@
 // ROCKET transform for MI355X (gfx950): C-ABI entry points (handles, validation, host-side
 // plan, device mirror, launch sequencing).  See include/rocket.h for the contract of every
-// entry point.  The kernels live in rocket_forward.hip / rocket_forward_short.hip (transform),
-// rocket_backward.hip (soft-PPV backward), rocket_prologue.hip (8-bit input), rocket_ridge.hip
-// (regressor), rocket_train.hip (loss gradient, parameter update) and rocket_calibrate.hip.
+// entry point.  The kernels live in rocket_forward*.hip (transform), rocket_backward*.hip (soft-PPV
+// backward), rocket_prologue.hip (8-bit input, interleaved copies), rocket_ridge.hip (regressor),
+// rocket_train.hip (loss gradient, parameter update) and rocket_calibrate.hip.
 //
 // One transform call is: zero-padding copy of the batch into the workspace -> forward kernel
 // (one workgroup per series and job; a job is a time tile of one kernel's outputs and writes
 // partial pooled values) -> rk_finalize (combines a kernel's jobs into the feature planes).
 // One backward call is: the same copy -> backward kernel (one workgroup per series and job,
 // per-job partial gradients) -> rk_reduce_jobs (sum over jobs and batch in a fixed order).
+// Short series go through other kernels where those are faster: sets of kernels (plan_sets), groups
+// of interleaved series (best_groups).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1,6 +1,7 @@
 // Forward kernel of the ROCKET transform, templated on the workgroup size NT
 // (256 lanes for long series, one 64-lane wavefront per (series, kernel) for short
-// ones).  Included by rocket_forward.hip and rocket_forward_short.hip.
+// ones) and the pooled features.  Included by rocket_forward.hip, rocket_forward_short.hip, the two *_soft.hip and
+// rocket_forward_groups.hip.
 #pragma once
 #include "rocket_device.hpp"
 
