@@ -123,17 +123,18 @@ __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, fl
 // only; the B % kXcds series that do not divide among the XCDs go first, each on all of them.
 __device__ __forceinline__ void rk_block_to_pair(int items, int B, int spread, int &b, int &item)
 {
-    int g = static_cast<int>(blockIdx.x);
-    const int rest = spread ? B % kXcds : B;
-    if (g < rest * items) {
-        b = g / items;
-        item = g - b * items;
-        return;
+    const int g = static_cast<int>(blockIdx.x);
+    if (spread) {
+        const int first = B % kXcds * items, x = (g - first) % kXcds;
+        if (g >= first) {
+            const int slot = (g - first) / kXcds, bl = slot / items;
+            item = slot - bl * items;
+            b = B % kXcds + bl * kXcds + x;
+            return;
+        }
     }
-    g -= rest * items;
-    const int slot = g / kXcds, bl = slot / items;
-    item = slot - bl * items;
-    b = rest + bl * kXcds + g % kXcds;
+    b = g / items;
+    item = g - b * items;
 }
 
 struct KernelCtx {
