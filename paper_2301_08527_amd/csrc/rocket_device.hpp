@@ -85,6 +85,30 @@ __device__ __forceinline__ void rk_taps(const float (&w)[LEN], float xv, float (
 // 542 us and 552).
 __host__ __device__ constexpr bool rk_counts_by_lane(uint32_t mask) { return (mask & ROCKET_F_SOFTPPV) == 0; }
 
+// Adds to `cnt` how many of the lane's R sums exceed the uniform `bound`: a comparison and an addition of its carry each.  (Written
+// out: from the C form the compiler makes selects, and spills.)  On gfx950 two wait states have to lie between a vector
+// instruction that writes a scalar register and a vector instruction that reads it, and nobody puts them into assembly but its author:
+// three comparisons come first and their additions after them, and what does not divide by three waits.  Max and PPV, every
+// addition right behind its comparison (no wait at all) and so: 64 x 20 x 50,000, 10,000 kernels 31.34 ms both, 149 x 18 x 1,263, 4,822
+// kernels 1,070 us and 1,067, 1 x 20 x 50,000, 10,000 kernels 526 us both.  (Comparison, two wait states, addition: 31.39 ms, 1,070, 527.)
+template <int R, int FROM = 0>
+__device__ __forceinline__ void rk_count_above(const float (&z)[R], float bound, int &cnt)
+{
+    if constexpr (R - FROM >= 3) {
+        uint64_t second, third;
+        asm("v_cmp_lt_f32 vcc, %3, %4\n\tv_cmp_lt_f32 %1, %3, %5\n\tv_cmp_lt_f32 %2, %3, %6\n\t"
+            "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32 %0, vcc, 0, %0, %1\n\tv_addc_co_u32 %0, vcc, 0, %0, %2"
+            : "+v"(cnt), "=&s"(second), "=&s"(third) : "s"(bound), "v"(z[FROM]), "v"(z[FROM + 1]), "v"(z[FROM + 2]) : "vcc");
+        rk_count_above<R, FROM + 3>(z, bound, cnt);
+    } else if constexpr (R - FROM == 2) {
+        uint64_t second;
+        asm("v_cmp_lt_f32 vcc, %2, %3\n\tv_cmp_lt_f32 %1, %2, %4\n\ts_nop 0\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\tv_addc_co_u32 %0, vcc, 0, %0, %1"
+            : "+v"(cnt), "=&s"(second) : "s"(bound), "v"(z[FROM]), "v"(z[FROM + 1]) : "vcc");
+    } else if constexpr (R - FROM == 1) {
+        asm("v_cmp_lt_f32 vcc, %1, %2\n\ts_nop 1\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc" : "+v"(cnt) : "s"(bound), "v"(z[FROM]) : "vcc");
+    }
+}
+
 // Pooling of R finished sums z = y - bias (section 3.2).  The bias is folded into
 // the pooling: max(y) = max(z) + bias (added once per kernel at the end),
 // y > 0 <=> z > -bias, and lambda*y + shift = lambda*z + (shift + lambda*bias).
@@ -93,17 +117,21 @@ template <int R>
 __device__ __forceinline__ void rk_pool(const float (&acc)[R], uint32_t mask, float negbias, float nl, float ns,
                                         PoolState &st)
 {
+    if (R == 1 && mask == (ROCKET_F_MAX | ROCKET_F_PPV)) {      // the maximum lies in the wait (64 x 20 x 8,000, 1,000 kernels: after it 707 us, so 703)
+        asm("v_cmp_lt_f32 vcc, %2, %3\n\tv_max_f32 %1, %1, %3\n\ts_nop 0\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+            : "+v"(st.cnt), "+v"(st.vmax) : "s"(negbias), "v"(acc[0]) : "vcc");
+        return;
+    }
     if (mask & ROCKET_F_MAX) {
 #pragma unroll
         for (int i = 0; i < R; ++i) st.vmax = fmaxf(st.vmax, acc[i]);
     }
     if (mask & ROCKET_F_PPV) {   // Eq. 1-2: strict y > 0
-        // (Written out: from the C form the compiler made selects, and spilled.)
+        if (rk_counts_by_lane(mask)) {
+            rk_count_above<R>(acc, negbias, st.cnt);
+        } else {
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            if (rk_counts_by_lane(mask))
-                asm("v_cmp_lt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc" : "+v"(st.cnt) : "s"(negbias), "v"(acc[i]) : "vcc");
-            else st.cnt += __builtin_popcountll(__ballot(acc[i] > negbias));
+            for (int i = 0; i < R; ++i) st.cnt += __builtin_popcountll(__ballot(acc[i] > negbias));
         }
     }
     if (mask & ROCKET_F_SOFTPPV) {
