@@ -121,6 +121,7 @@ static int inside(rocket_kernels *h, int32_t B, bool is_backward = true)
     for (int i = 0; i < g.count; ++i) {
         CHECK(g.series_before(i) == next && g.slots_before(i) == slots);
         CHECK(g.series_of(i) >= 1 && g.series_of(i) <= g.width_of(i) && g.width_of(i) <= g.width && g.width <= RkGroups::kWidest);
+        CHECK(g.width_of(i) >= 2);      // the kernels take a group's dilations to be even
         next += g.series_of(i);
         slots += g.width_of(i);
     }
