@@ -638,9 +638,10 @@ static size_t grouped_partial_bytes(const rocket_kernels *h, const RkGroups &g)
 }
 
 // The work of `jobs` jobs of `series` series each on `wavefronts` wavefronts, spread over the chip's 1,024 SIMDs, and what the longest
-// of them adds, in instructions of a wavefront.  An output costs its lane a multiply-add (the backward pass: two) for each weight, and
-// `pooling` more; the strips that do not fill a wavefront come to `rest` outputs more for each lane.  The longest job shares
-// its SIMD with others and adds 3.5 times its own time.
+// of them adds, in instructions of a wavefront (1.2 to 1.7 ns of a SIMD, the more channels the more).  An output costs its lane a multiply-add (the
+// backward pass: two) for each weight, and `pooling` more; the strips that do not fill a wavefront come to `rest` outputs more for each lane.  The
+// longest job shares its SIMD with others and adds 3.5 times its own time.  The numbers here and below (3.5, rests of 10 to 20 outputs, 6 and 25
+// instructions, the leads) are fits: they count what they are named for in the middle, and were set by what the shapes at the rules took.
 struct Estimate { double work, last; };
 static Estimate estimate(const rocket_kernels *h, double jobs, int wavefronts, double series, double rest, double passes, double pooling)
 {
@@ -648,7 +649,11 @@ static Estimate estimate(const rocket_kernels *h, double jobs, int wavefronts, d
     return {jobs * wavefronts * each * (passes * h->conv_fma / h->outputs + pooling) / 1024.0, 3.5 * each * (passes * h->max_terms + pooling)};
 }
 
-// The groups with the least estimate: wide ones waste less on each series, narrow ones make more and shorter jobs.  Width 1 (no groups)
+// The groups with the least estimate: wide ones waste less on each series, narrow ones make more and shorter jobs.  The more of an
+// XCD's 4 MB of L2 a group takes, the less of it is there still when the next kernel comes: a fiftieth more for each MB beyond one (backward
+// passes over pairs, measured against estimated: 1.00 at 2 MB a pair, 1.03 at 3, 1.04 at 4, 1.07 at 5, 1.09 at 6.  In us, one series at a time
+// and pairs: 82 x 19 x 25,253 and 2,518 kernels 11,974/12,761, 68 x 20 x 29,054 and 4,400 19,464/21,024, 60 x 20 x 20,000 and 10,000
+// 27,719/26,157, 68 x 16 x 13,627 and 1,870 4,717/4,289).  Width 1 (no groups)
 // where `plain`, the estimate of one series at a time, is less, or where a job is not a whole kernel or the workspace, whose size
 // does not depend on any of this, does not hold the groups.
 static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, double pooling, double plain, int backward)
@@ -662,7 +667,8 @@ static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, d
         if (grouped_copy_bytes(h, g) + (backward ? grouped_partial_bytes(h, g) : 0) > row_stats_offset(h, B, backward)) continue;
         const Estimate first = estimate(h, h->K, 1, g.first_width, 20, passes, pooling);
         const Estimate others = estimate(h, static_cast<double>(h->K) * (g.count - 1), 1, width, 20, passes, pooling);
-        const double t = first.work + others.work + (g.count > 1 ? others.last : first.last);
+        double t = first.work + others.work + (g.count > 1 ? others.last : first.last);
+        t *= 1.0 + 0.02 * std::max(0.0, static_cast<double>(width * series_bytes) / (1 << 20) - 1.0);
         if (t < plain) { plain = t; best = g; }
     }
     return best;
@@ -703,18 +709,22 @@ static bool one_wavefront_jobs(const rocket_kernels *h, int32_t B)
     return h->L <= kOneWaveSeries || (h->L <= kShortSeries && 30 * work >= static_cast<int64_t>(h->L) * (h->max_terms + 11));
 }
 
-// The groups of a backward pass (rocket_backward_groups.hip).  Of 20 shapes measured at every width the rule takes the fastest or one
-// within 6 % of it for 19; what it chooses, against one series at a time, in us: 64 x 1 x 1,000 and 1,000 kernels 95/184 (4 series; 8: 92,
-// 2: 113, 16: 108), 98 x 1 x 246 and 1,082 55/279 (16; 4: 76), 28 x 18 x 158 and 15,408 309/1,820 (16; 4: 475), 27 x 19 x 595 and 2,590
-// 199/365 (4; 2: 229, 8: 228), 167 x 9 x 1,205 and 1,737 998/1,875 (4; 8: 949, 32: 1,688).  Series of more than some 4,000 samples gain
-// little or nothing (23 x 6 x 4,099 and 1,537 390/416, 16 x 3 x 4,099 and 500 103/93).  The 20th: 9 x 5 x 500 and 10,000 kernels, one and
-// eight series 219 us, one, four and four 179.
+// The groups of a backward pass (rocket_backward_groups.hip).  Over 975 shapes, most drawn at random (2 to 256 series of 60 to 32,700
+// samples, 100 to 20,000 kernels), timed at every width, the rule's choice takes 0.8 % longer than the fastest on average, for 933 within 5 %; for
+// six it is more than 2 % slower than one series at a time, the worst 60 x 20 x 2,048 and 200 kernels 166/179.  (With the sum over the series as
+// a third of the work instead of a time of its own, and no term for L2: 1.3 %, and 31 shapes, 13 of them by more than 10 %, as 10 x 16 x 5,462
+// and 2,322 kernels 456/551, 8 x 13 x 1,339 and 1,525 99/117.)  What it chooses, one series at a time / in groups, in us: 64 x 1 x 1,000 and 1,000 kernels
+// 170/89 (4 series; 2: 105, 8: 88, 16: 108), 98 x 1 x 246 and 1,082 246/52 (16; 8: 55, 32: 62), 28 x 18 x 158 and 15,408 1,695/302 (16; 8: 349), 27 x 19 x 595
+// and 2,590 323/193 (4; 2: 223, 8: 224), 167 x 9 x 1,205 and 1,737 1,782/912 (8; 4: 951, 16: 1,022), 60 x 1 x 12,000 and 1,000 791/609 (2; 4: 648), 60 x 20 x
+// 12,000 and 10,000 18,364/15,618 (2; 4: 16,769).  Furthest from the fastest: wide groups of few series, as 9 x 5 x 500 and 10,000 kernels, one and eight
+// series 211, one, four and four 171.
 static RkGroups backward_groups(const rocket_kernels *h, int32_t B)
 {
     if (!rk_launchers().backward_groups) return rk_groups(B, 1, 1);
-    // one series at a time: four wavefronts waste 10 outputs of a lane each, single ones 20 and, with the sum over the series, a third more
-    const Estimate plain = one_wavefront_jobs(h, B) ? estimate(h, 1.3 * B * h->K, 1, 1, 20, 2, 25) : estimate(h, 1.0 * B * h->K, 4, 1, 10, 2, 25);
-    return best_groups(h, B, 2, 25, plain.work + plain.last, 1);
+    // one series at a time: four wavefronts waste 12 outputs of a lane each, single ones 20, and the sum over the series (rk_reduce_jobs) is
+    // a chain of trips to memory, 400 instructions' time (0.6 us) for each
+    const Estimate plain = one_wavefront_jobs(h, B) ? estimate(h, 1.0 * B * h->K, 1, 1, 20, 2, 25) : estimate(h, 1.0 * B * h->K, 4, 1, 12, 2, 25);
+    return best_groups(h, B, 2, 25, plain.work + plain.last + 400.0 * B, 1);
 }
 
 // `resident_only`: the call may not allocate, so the handle's device mirror must already be there

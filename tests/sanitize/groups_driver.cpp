@@ -145,7 +145,12 @@ int main()
     const struct { int32_t B, C, L, K, width, first; } want[] = {
         {9, 2, 2000, 4000, 2, 1}, {13, 3, 700, 3000, 4, 1}, {27, 2, 400, 2500, 8, 3}, {13, 2, 128, 6000, 16, 13}, {70, 1, 100, 4000, 32, 6},
     {200, 1, 40, 6000, 64, 8}, {130, 1, 25, 4000, 64, 2}, {3, 1, 61, 9000, 4, 3}, {200, 9, 90, 700, 16, 8}, {6, 1, 11, 3000, 8, 6},
-        {1, 5, 300, 4000, 1, 1}, {16, 3, 4099, 500, 1, 1}, {64, 20, 17000, 300, 1, 1}};
+        {1, 5, 300, 4000, 1, 1}, {16, 3, 4099, 500, 1, 1}, {64, 20, 17000, 300, 1, 1},
+        // too few jobs, or pairs that fill an XCD's L2: slower in groups by 4 to 21 %
+        {10, 16, 5462, 2322, 1, 1}, {8, 13, 1339, 1525, 1, 1}, {13, 9, 5401, 2697, 1, 1}, {3, 1, 4321, 8631, 1, 1}, {68, 20, 29054, 4400, 1, 1},
+        {80, 17, 29172, 3772, 1, 1}, {60, 20, 32700, 10000, 1, 1},
+        // long series that are faster in groups
+        {60, 1, 12000, 1000, 2, 2}, {256, 1, 20000, 10000, 8, 8}, {60, 20, 12000, 10000, 2, 2}};
     for (const auto &w : want) {
         rocket_kernels *h = nullptr;
         CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);

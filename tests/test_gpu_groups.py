@@ -24,10 +24,11 @@ def _raw(rng, shape):
 
 # Widths that the rule gives (tests/sanitize/groups_driver.cpp checks them), as (width, series of the first group).  Narrow groups reach
 # the staged small dilations (width x dilation below 16) and bands of 32 rows, wide ones of short series the few-rows strips only; first
-# groups of one series, as wide as the others and narrower, with all their series and with idle ones (3 of 4, 13 of 16).
+# groups of one series (and an empty place), as wide as the others and narrower, with all their series and with idle ones (3 of 4, 13 of 16).
 CASES = [
     (9, 2, 2000, 4000, (2, 1)), (13, 3, 700, 3000, (4, 1)), (27, 2, 400, 2500, (8, 3)), (13, 2, 128, 6000, (16, 13)), (70, 1, 100, 4000, (32, 6)),
     (200, 1, 40, 6000, (64, 8)), (130, 1, 25, 4000, (64, 2)), (3, 1, 61, 9000, (4, 3)), (200, 9, 90, 700, (16, 8)), (6, 1, 11, 3000, (8, 6)),
+    (60, 1, 12000, 1000, (2, 2)),      # beyond the one-wavefront kernels' series
 ]
 
 
