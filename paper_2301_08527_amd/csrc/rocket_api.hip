@@ -590,6 +590,7 @@ static int ensure_device(rocket_kernels *h, hipStream_t stream)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kShortSeries = 8192;       // longest series handled by the one-wavefront kernels
 constexpr int kOneWaveSeries = 1024;     // some 64 strips of 16 or more rows: one for each lane of a wavefront
+constexpr int kShortestWide = 512;       // longest series whose transform is never worth four wavefronts (forward_way)
 constexpr int kBwdMaxTerms = 9 * 11;     // the backward kernel holds at most 9 channels x 11 weights per kernel
 
 // ------------------------------------------------------------------ launches
@@ -678,7 +679,9 @@ static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, d
 // or, where a few kernels of a few series leave most of the chip idle and the longest of them is what takes the time, on four.  (All ways
 // give the same bits.  Sums of sigmoids depend on the way, which must follow from the handle alone: they stay on one wavefront.)
 // Four wavefronts need a tenth's lead over one by the estimates, groups a twentieth more (4 x 20 x 1,200 and 10,000 kernels: ahead by 12 %
-// there, 106 us against 99).  Max and PPV, in us.  Groups, of 21 shapes measured at every width the fastest or one
+// there, 106 us against 99).  Up to 512 samples one wavefront has the strips of a kernel in a pass or two and four only wait for one
+// another (5 x 19 x 417 and 870 kernels 22 us on one and 27 on four, 4 x 19 x 269 and 1,122 22/26, 5 x 11 x 375 and 775 22/25; 13 x 19 x 1,018 and 170
+// 36/21, 8 x 13 x 533 and 387 22/19).  Max and PPV, in us.  Groups, of 21 shapes measured at every width the fastest or one
 // within 8 % of it, against one wavefront: 28 x 15 x 134 samples and 2,351 kernels 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236
 // 88/402 (32 series; 16: 91, 64: 103), 4 x 5 x 300 and 10,000 33/49 (4), 149 x 18 x 1,263 and 4,822 1,076/1,640 (8; 2: 1,315, 32: 1,415),
 // 227 x 16 x 930 and 5,723 1,386/2,210 (16; 4: 1,575).  Series of thousands of samples gain little or nothing (23 x 6 x 4,099 and 1,537
@@ -692,7 +695,7 @@ static ForwardWay forward_way(const rocket_kernels *h, int32_t B, uint32_t mask)
     if (way.wide || (mask & ROCKET_F_SOFTPPV) || h->jobs.size() != static_cast<size_t>(h->K)) return way;
     const Estimate one = estimate(h, static_cast<double>(B) * h->K, 1, 1, 20, 1, 6), four = estimate(h, static_cast<double>(B) * h->K, 4, 1, 10, 1, 6);
     double least = 0.9 * (one.work + one.last);
-    if (rk_launchers().forward_wide && four.work + four.last < least) { least = four.work + four.last; way.wide = true; }
+    if (rk_launchers().forward_wide && h->L > kShortestWide && four.work + four.last < least) { least = four.work + four.last; way.wide = true; }
     if (rk_launchers().forward_groups) way.groups = best_groups(h, B, 1, 6, 0.95 * least, 0);
     return way;
 }

@@ -184,7 +184,9 @@ int main()
     // four wavefronts to a job where one would be what takes the time; sums of sigmoids stay on one
     const struct { int32_t B, C, L, K; const char *route; } width[] = {
         {1, 14, 2857, 1724, "pad wide finalize "}, {24, 14, 2857, 1724, "pad short finalize "}, {24, 20, 8000, 1000, "pad wide finalize "},
-        {8, 2, 3000, 2000, "pad short finalize "}, {1, 20, 1200, 10000, "pad short finalize "}, {1, 20, 8193, 1000, "pad forward finalize "}};
+        {8, 2, 3000, 2000, "pad short finalize "}, {1, 20, 1200, 10000, "pad short finalize "}, {1, 20, 8193, 1000, "pad forward finalize "},
+        {4, 19, 269, 1122, "pad short finalize "}, {5, 19, 417, 870, "pad short finalize "}, {1, 19, 512, 170, "pad short finalize "},
+        {1, 19, 513, 170, "pad wide finalize "}, {13, 19, 1018, 170, "pad wide finalize "}};
     for (const auto &w : width) {
         rocket_kernels *h = nullptr;
         CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
