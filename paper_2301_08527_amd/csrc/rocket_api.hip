@@ -899,10 +899,15 @@ static int backward_impl(const char *fn, rocket_kernels *h, const void *x_dev, b
             return rk_fail(ROCKET_EHIP, "launch of the padding kernel failed");
         rc = profile_mark(h, stream, true);
         if (rc != ROCKET_OK) return rc;
-        if (rk_launchers().backward_groups(h, xpad, groups, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns,
-                                           reinterpret_cast<float *>(base + grouped_copy_bytes(h, groups)), grad_w_dev, grad_b_dev, stream) != ROCKET_OK)
+        partial = reinterpret_cast<float *>(base + grouped_copy_bytes(h, groups));
+        if (rk_launchers().backward_groups(h, xpad, groups, grad_out_dev, F, plane_soft, plane_max, lambda, nl, ns, partial, grad_w_dev, grad_b_dev,
+                                           stream) != ROCKET_OK)
             return rk_fail(ROCKET_EHIP, "launch of the backward kernel failed");
-        return profile_mark(h, stream, false);
+        rc = profile_mark(h, stream, false);
+        if (rc != ROCKET_OK) return rc;
+        if (groups.count > 1 && rk_launchers().sum_groups(h, groups, partial, grad_w_dev, grad_b_dev, stream) != ROCKET_OK)
+            return rk_fail(ROCKET_EHIP, "launch of the gradient reduction kernel failed");
+        return ROCKET_OK;
     }
     rc = pad_batch(h, x_dev, is_u8, B, ws, 1, stream);
     if (rc != ROCKET_OK) return rc;

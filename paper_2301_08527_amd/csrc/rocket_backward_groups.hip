@@ -131,11 +131,16 @@ static int launch_backward_groups(const rocket_kernels *h, const float *xg, cons
                        stream, xg, static_cast<int>(h->row_len), h->lead, h->L, h->C, h->K, h->d_rec, h->d_jobs, h->d_channels,
                        h->d_weights, grad_out, F, plane_soft, plane_max, lambda, nl, ns, direct ? grad_w : partial,
                        direct ? grad_b : partial + nw, direct ? 0 : static_cast<size_t>(nw) + h->K, groups);
-    if (hipGetLastError() != hipSuccess) return ROCKET_EHIP;
-    if (direct) return ROCKET_OK;
-    hipLaunchKernelGGL(rk_sum_groups, dim3(static_cast<unsigned>((static_cast<int64_t>(nw) + h->K + kSumThreads - 1) / kSumThreads)),
-                       dim3(kSumThreads), 0, stream, partial, groups.count, nw, h->K, grad_w, grad_b);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
 }
 
-[[maybe_unused]] static const bool kEntered = (rk_launchers().backward_groups = launch_backward_groups, true);
+static int launch_sum_groups(const rocket_kernels *h, const RkGroups &groups, const float *partial, float *grad_w, float *grad_b, void *stream)
+{
+    const int nw = static_cast<int>(h->w_off[h->K]);
+    hipLaunchKernelGGL(rk_sum_groups, dim3(static_cast<unsigned>((static_cast<int64_t>(nw) + h->K + kSumThreads - 1) / kSumThreads)),
+                       dim3(kSumThreads), 0, static_cast<hipStream_t>(stream), partial, groups.count, nw, h->K, grad_w, grad_b);
+    return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+}
+
+[[maybe_unused]] static const bool kEntered = (rk_launchers().backward_groups = launch_backward_groups, rk_launchers().sum_groups = launch_sum_groups,
+                                               true);

@@ -252,11 +252,13 @@ struct RkLaunchers {
                       void *stream) = nullptr;
     // rocket_forward_groups.hip: max and PPV (mask without softPPV) over such a copy, features and all
     int (*forward_groups)(const rocket_kernels *h, const float *xg, const RkGroups &groups, uint32_t mask, float *out, void *stream) = nullptr;
-    // rocket_backward_groups.hip: the whole backward pass over such a copy; `partial`: a row of gradients for each group where there
-    // are several
+    // rocket_backward_groups.hip: the backward pass over such a copy; several groups leave a row of gradients each in `partial`, a single
+    // one its gradients
     int (*backward_groups)(const rocket_kernels *h, const float *xg, const RkGroups &groups, const float *grad_out, int F,
                            int plane_soft, int plane_max, float lambda, float nl, float ns, float *partial, float *grad_w,
                            float *grad_b, void *stream) = nullptr;
+    // the sum of those rows
+    int (*sum_groups)(const rocket_kernels *h, const RkGroups &groups, const float *partial, float *grad_w, float *grad_b, void *stream) = nullptr;
 };
 RkLaunchers &rk_launchers();      // rocket_api.hip
 // rocket_api.hip: offsets, sets, job plan, padded row geometry; returns ROCKET_OK or an error

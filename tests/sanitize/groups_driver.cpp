@@ -23,6 +23,9 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = reinterpret_cast<hipEvent_t>(&g_route); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { g_route += "mark "; return hipSuccess; }
 }
 
 #define RECORD(name) { g_route += name " "; return ROCKET_OK; }
@@ -62,11 +65,16 @@ static int backward_groups_stub(const rocket_kernels *, const float *, const RkG
     g_route += "backward_groups ";
     return ROCKET_OK;
 }
+static int sum_groups_stub(const rocket_kernels *, const RkGroups &, const float *partial, float *, float *, void *)
+{
+    if (reinterpret_cast<uintptr_t>(partial) == g_partial) g_route += "sum_groups ";
+    return ROCKET_OK;
+}
 static int forward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, uint32_t, float *, void *) RECORD("forward_groups")
 static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, float *, void *) RECORD("series")
 static int forward_wide_stub(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("wide")
 [[maybe_unused]] static const bool kEntered = (rk_launchers().backward_short = backward_short_stub, rk_launchers().pad_groups = pad_groups_stub,
-                                               rk_launchers().backward_groups = backward_groups_stub,
+                                               rk_launchers().backward_groups = backward_groups_stub, rk_launchers().sum_groups = sum_groups_stub,
                                                rk_launchers().forward_groups = forward_groups_stub, rk_launchers().forward_series = series_stub,
                                                rk_launchers().forward_wide = forward_wide_stub, true);
 
@@ -156,11 +164,15 @@ int main()
         CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
         CHECK(backward(h, w.B) == ROCKET_OK);
         CHECK(g_groups.width == w.width && (w.width == 1 || g_groups.first_series == w.first));
-        CHECK((g_route == "pad_groups backward_groups ") == (w.width > 1));
+        const std::string sum = g_groups.count > 1 ? "sum_groups " : "";       // a single group's sums are the gradients
+        CHECK((g_route == "pad_groups backward_groups " + sum) == (w.width > 1));
         if (w.width > 1) {
             if (inside(h, w.B)) return 1;
-            CHECK(backward(h, w.B, true) == ROCKET_OK && g_route == "pad_groups_u8 backward_groups ");
+            CHECK(backward(h, w.B, true) == ROCKET_OK && g_route == "pad_groups_u8 backward_groups " + sum);
             if (inside(h, w.B) || pairs(w.K)) return 1;
+            // the timed kernel is the backward kernel, without the sum over the groups
+            CHECK(rocket_profile_enable(h, 1) == ROCKET_OK && backward(h, w.B) == ROCKET_OK);
+            CHECK(g_route == "pad_groups mark backward_groups mark " + sum);
         }
         rocket_free_kernels(h);
     }
