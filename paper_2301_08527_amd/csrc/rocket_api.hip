@@ -695,8 +695,8 @@ static ForwardWay forward_way(const rocket_kernels *h, int32_t B, uint32_t mask)
     if (way.wide || (mask & ROCKET_F_SOFTPPV) || h->jobs.size() != static_cast<size_t>(h->K)) return way;
     const Estimate one = estimate(h, static_cast<double>(B) * h->K, 1, 1, 20, 1, 6), four = estimate(h, static_cast<double>(B) * h->K, 4, 1, 10, 1, 6);
     double least = 0.9 * (one.work + one.last);
-    if (rk_launchers().forward_wide && h->L > kShortestWide && four.work + four.last < least) { least = four.work + four.last; way.wide = true; }
-    if (rk_launchers().forward_groups) way.groups = best_groups(h, B, 1, 6, 0.95 * least, 0);
+    if (h->L > kShortestWide && four.work + four.last < least) { least = four.work + four.last; way.wide = true; }
+    way.groups = best_groups(h, B, 1, 6, 0.95 * least, 0);
     return way;
 }
 
@@ -723,7 +723,6 @@ static bool one_wavefront_jobs(const rocket_kernels *h, int32_t B)
 // series 211, one, four and four 171.
 static RkGroups backward_groups(const rocket_kernels *h, int32_t B)
 {
-    if (!rk_launchers().backward_groups) return rk_groups(B, 1, 1);
     // one series at a time: four wavefronts waste 12 outputs of a lane each, single ones 20, and the sum over the series (rk_reduce_jobs) is
     // a chain of trips to memory, 400 instructions' time (0.6 us) for each
     const Estimate plain = one_wavefront_jobs(h, B) ? estimate(h, 1.0 * B * h->K, 1, 1, 20, 2, 25) : estimate(h, 1.0 * B * h->K, 4, 1, 12, 2, 25);

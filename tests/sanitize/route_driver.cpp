@@ -49,8 +49,16 @@ extern "C" int rocket_ridge_predict(const float *, int32_t, int32_t, const doubl
 static int series_stub(const rocket_kernels *, const float *, int64_t, int32_t, uint32_t, float, float, float *, void *) RECORD("series")
 static int backward_short_stub(const rocket_kernels *, const float *, int32_t, const float *, int, int, int, float, float, float,
                                float *, void *) RECORD("backward_short")
-[[maybe_unused]] static const bool kEntered = (rk_launchers().forward_series = series_stub,
-                                               rk_launchers().backward_short = backward_short_stub, true);
+static int forward_wide_stub(const rocket_kernels *, const float *, int32_t, uint32_t, float, float, float *, void *) RECORD("wide")
+static int pad_groups_stub(const rocket_kernels *, const void *, bool, int32_t, const RkGroups &, float *, void *, void *) RECORD("pad_groups")
+static int forward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, uint32_t, float *, void *) RECORD("forward_groups")
+static int backward_groups_stub(const rocket_kernels *, const float *, const RkGroups &, const float *, int, int, int, float, float, float,
+                                float *, float *, float *, void *) RECORD("backward_groups")
+static int sum_groups_stub(const rocket_kernels *, const RkGroups &, const float *, float *, float *, void *) RECORD("sum_groups")
+[[maybe_unused]] static const bool kEntered = (rk_launchers().forward_series = series_stub, rk_launchers().backward_short = backward_short_stub,
+                                               rk_launchers().forward_wide = forward_wide_stub, rk_launchers().pad_groups = pad_groups_stub,
+                                               rk_launchers().forward_groups = forward_groups_stub,
+                                               rk_launchers().backward_groups = backward_groups_stub, rk_launchers().sum_groups = sum_groups_stub, true);
 
 #define CHECK(cond) do { if (!(cond)) { std::fprintf(stderr, "check failed at line %d: %s (route: %s)\n", __LINE__, #cond, g_route.c_str()); return 1; } } while (0)
 
@@ -92,8 +100,9 @@ static int wide_kernels()
     return 0;
 }
 
-// The path of a transform follows from the handle (and from lambda's sign), never from the batch, and a pruned handle has its
-// parent's.
+// Whether a transform goes over sets follows from the handle (and from lambda's sign), never from the batch, and a pruned handle has its
+// parent's path.  So it is with the jobs of masks with softPPV; max and PPV alone are the same numbers however they are gathered and go the
+// fastest way: one wavefront to a kernel, four, or groups of series.
 static int one_path_for_all_batches()
 {
     const std::string sets = "series ", jobs = "pad short finalize ";
@@ -107,7 +116,9 @@ static int one_path_for_all_batches()
         CHECK(rocket_kernels_subset(h, &keep, 1, &part) == ROCKET_OK);
         for (const int32_t B : {1, 16, 256, 4096}) {
             CHECK(transform_route(h, B, 7) == w.route);
-            CHECK(transform_route(part, B, 3) == w.route);
+            CHECK(transform_route(part, B, 7) == w.route);
+            const std::string hard = transform_route(part, B, 3);
+            CHECK(hard == w.route || (w.route == jobs && (hard == "pad wide finalize " || hard == "pad_groups forward_groups ")));
         }
         if (w.route == sets) {
             CHECK(transform_route(h, 16, 7, 0.f) == jobs);      // the sets' edges rest on lambda > 0
@@ -119,16 +130,15 @@ static int one_path_for_all_batches()
     return 0;
 }
 
-// One wavefront to a job of the backward pass where that is the faster way: short series, and longer ones with many jobs for
-// their length and channels.
+// Groups of series in the backward pass where they are the faster way; else one wavefront to a job where that is: short series, and longer ones
+// with many jobs for their length and channels.
 static int backward_paths()
 {
-    const struct { int32_t B, C, L, K; const char *route; } want[] = {
-        {1, 1, 11, 1, "pad backward_short reduce "}, {4, 20, 1024, 200, "pad backward_short reduce "},
-        {4, 20, 1400, 200, "pad backward reduce "}, {64, 20, 1400, 200, "pad backward_short reduce "}, {64, 20, 8192, 200, "pad backward reduce "},
-        {64, 20, 8192, 1000, "pad backward_short reduce "}, {64, 20, 8193, 1000, "pad backward reduce "},
-        {64, 1, 8192, 200, "pad backward_short reduce "}, {4, 1, 8192, 1000, "pad backward reduce "},
-        {16, 6, 4000, 200, "pad backward reduce "}, {64, 6, 4000, 200, "pad backward_short reduce "}};
+    const std::string one = "pad backward_short reduce ", four = "pad backward reduce ", groups = "pad_groups backward_groups sum_groups ";
+    const struct { int32_t B, C, L, K; std::string route; } want[] = {
+        {1, 1, 11, 1, one}, {4, 20, 1024, 200, one}, {4, 20, 1400, 200, four}, {64, 20, 1400, 200, groups}, {64, 20, 8192, 200, four},
+        {64, 20, 8192, 1000, one}, {64, 20, 8193, 1000, groups}, {16, 20, 8193, 1000, four}, {64, 1, 8192, 200, groups}, {4, 1, 8192, 1000, four},
+        {16, 6, 4000, 200, four}, {64, 6, 4000, 200, groups}, {10, 16, 5462, 2322, one}};
     for (const auto &w : want) {
         rocket_kernels *h = nullptr;
         CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
