@@ -176,6 +176,17 @@ int main()
         }
         rocket_free_kernels(h);
     }
+    // one wavefront to a kernel, and four, of tests/test_gpu_backward.py
+    const std::string narrow = "pad backward_short reduce ", wide = "pad backward reduce ";
+    const struct { int32_t seed, B, C, L, K; std::string route; } alone[] = {
+        {1500, 2, 1, 1500, 900, narrow}, {1500, 1, 1, 1500, 900, wide}, {3001, 6, 3, 3001, 900, narrow}, {3001, 3, 3, 3001, 900, wide},
+        {8192, 12, 2, 8192, 900, narrow}, {8192, 6, 2, 8192, 900, wide}, {2003, 6, 3, 8192, 4000, narrow}, {2003, 6, 3, 8200, 4000, wide},
+        {2003, 6, 3, 8192, 12000, "pad_groups backward_groups sum_groups "}};
+    for (const auto &w : alone) {
+        rocket_kernels *h = nullptr;
+        CHECK(rocket_make_kernels(w.seed, w.K, w.C, w.L, &h) == ROCKET_OK && backward(h, w.B) == ROCKET_OK && g_route == w.route);
+        rocket_free_kernels(h);
+    }
     // transforms: max and PPV in groups, sums of sigmoids and one-channel sets not
     const struct { int32_t B, C, L, K, width, first; } ahead[] = {
         {28, 15, 134, 2351, 8, 4}, {149, 3, 166, 3236, 32, 21}, {3, 2, 200, 9000, 4, 3}, {149, 18, 1263, 4822, 8, 5}, {9, 4, 600, 6000, 4, 1},
@@ -194,17 +205,20 @@ int main()
         rocket_free_kernels(h);
     }
     // four wavefronts to a job where one would be what takes the time; sums of sigmoids stay on one
-    const struct { int32_t B, C, L, K; const char *route; } width[] = {
-        {1, 14, 2857, 1724, "pad wide finalize "}, {24, 14, 2857, 1724, "pad short finalize "}, {24, 20, 8000, 1000, "pad wide finalize "},
-        {8, 2, 3000, 2000, "pad short finalize "}, {1, 20, 1200, 10000, "pad short finalize "}, {1, 20, 8193, 1000, "pad forward finalize "},
-        {4, 19, 269, 1122, "pad short finalize "}, {5, 19, 417, 870, "pad short finalize "}, {1, 19, 512, 170, "pad short finalize "},
-        {1, 19, 513, 170, "pad wide finalize "}, {13, 19, 1018, 170, "pad wide finalize "}};
+    const std::string one = "pad short finalize ", four = "pad wide finalize ", group = "pad_groups forward_groups ";
+    const struct { int32_t seed, B, C, L, K; std::string route; } width[] = {
+        {3, 1, 14, 2857, 1724, four}, {3, 24, 14, 2857, 1724, one}, {3, 24, 20, 8000, 1000, four}, {3, 8, 2, 3000, 2000, one}, {3, 1, 20, 1200, 10000, one},
+        {3, 1, 20, 8193, 1000, "pad forward finalize "}, {3, 4, 19, 269, 1122, one}, {3, 5, 19, 417, 870, one}, {3, 1, 19, 512, 170, one},
+        {3, 1, 19, 513, 170, four}, {3, 13, 19, 1018, 170, four},
+        // of tests/test_gpu_groups.py: a series alone, and its batch
+        {1724, 1, 14, 2857, 1724, four}, {1724, 24, 14, 2857, 1724, one}, {2000, 1, 2, 3000, 2000, four}, {2000, 9, 2, 3000, 2000, one},
+        {700, 1, 5, 8192, 700, four}, {700, 40, 5, 8192, 700, one}, {300, 1, 1, 1500, 300, four}, {300, 120, 1, 1500, 300, group},
+        {1100, 1, 3, 1030, 1100, four}, {1100, 40, 3, 1030, 1100, group}};
     for (const auto &w : width) {
         rocket_kernels *h = nullptr;
-        CHECK(rocket_make_kernels(3, w.K, w.C, w.L, &h) == ROCKET_OK);
+        CHECK(rocket_make_kernels(w.seed, w.K, w.C, w.L, &h) == ROCKET_OK);
         for (uint32_t mask = 1; mask <= 3; ++mask) CHECK(forward(h, w.B, mask) == ROCKET_OK && g_route == w.route);
-        for (uint32_t mask = 4; mask <= 7; ++mask)
-            CHECK(forward(h, w.B, mask) == ROCKET_OK && g_route == (w.L > 8192 ? "pad forward finalize " : "pad short finalize "));
+        for (uint32_t mask = 4; mask <= 7; ++mask) CHECK(forward(h, w.B, mask) == ROCKET_OK && g_route == (w.L > 8192 ? "pad forward finalize " : one));
         rocket_free_kernels(h);
     }
     rocket_kernels *sets = nullptr;

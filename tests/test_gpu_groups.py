@@ -22,13 +22,32 @@ def _raw(rng, shape):
     return x, ((v - v.mean(axis=-1, keepdims=True)) / v.std(axis=-1, keepdims=True)).astype(np.float32)
 
 
-# Widths that the rule gives (tests/sanitize/groups_driver.cpp checks them), as (width, series of the first group).  Narrow groups reach
+def _width(h, B, C, L, mask, backward):
+    """How many series of a batch lie interleaved in the copy that a pass leaves in its workspace (1: no groups)."""
+    import torch
+    x = torch.randn((B, C, L), device="cuda")
+    x[-1, 0, 0], x[-1, 0, 1] = 123.25, 321.5        # neighbours in the series
+    ws = torch.zeros(rocket.rocket_workspace_bytes(h, B, mask, backward), dtype=torch.uint8, device="cuda")
+    if backward:
+        gout = torch.zeros((B, rocket.rocket_num_features(mask) * h.K), device="cuda")
+        rocket.rocket_soft_ppv_backward(h, x, mask, gout, 10.0, -3.0, bool(mask & 1), workspace=ws)
+    else:
+        rocket.rocket_transform(h, x, mask, workspace=ws)
+    words = ws.view(torch.float32)
+    at = [(words == v).nonzero().flatten().tolist() for v in (123.25, 321.5)]
+    assert len(at[0]) == 1 and len(at[1]) == 1
+    return at[1][0] - at[0][0]
+
+
+# Widths that the rule gives (_width looks at what a call does), as (width, series of the first group).  Narrow groups reach
 # the staged small dilations (width x dilation below 16) and bands of 32 rows, wide ones of short series the few-rows strips only; first
 # groups of one series (and an empty place), as wide as the others and narrower, with all their series and with idle ones (3 of 4, 13 of 16).
 CASES = [
     (9, 2, 2000, 4000, (2, 1)), (13, 3, 700, 3000, (4, 1)), (27, 2, 400, 2500, (8, 3)), (13, 2, 128, 6000, (16, 13)), (70, 1, 100, 4000, (32, 6)),
     (200, 1, 40, 6000, (64, 8)), (130, 1, 25, 4000, (64, 2)), (3, 1, 61, 9000, (4, 3)), (200, 9, 90, 700, (16, 8)), (6, 1, 11, 3000, (8, 6)),
     (60, 1, 12000, 1000, (2, 2)),      # beyond the one-wavefront kernels' series
+    (149, 18, 1263, 600, (4, 1)),      # 38 groups: the first six one after the other, each on all XCDs
+    (200, 20, 1200, 400, (4, 4)),      # 50: two by kernels, then 40 side by side and eight more
 ]
 
 
@@ -48,6 +67,7 @@ def test_groups_against_the_oracle(B, C, L, K, groups, u8):
     g = rng.standard_normal((B, 2 * K)).astype(np.float32)
     sel = np.arange(0, K, max(1, K // 150), dtype=np.int32)
     print("groups", B, C, L, K, groups, "u8" if u8 else "f32", flush=True)
+    assert _width(h, B, C, L, 5, True) == groups[0] and (B - 1) % groups[0] + 1 == groups[1]
     gw, gb = entry(h, xd, 4, _gpu(g[:, K:]), 4.0, -3.0, False)
     check_backward(x, kr, gw.cpu().numpy(), gb.cpu().numpy(), g[:, K:], None, 4.0, -3.0, sel=sel)
     gw, gb = entry(h, xd, 5, _gpu(g), 4.0, -3.0, True)
@@ -67,6 +87,7 @@ def test_groups_equal_single_series(B, C, L, K, groups):
     gout = torch.randn((B, 2 * K), generator=gen, device="cuda")
     h = rocket.rocket_make_kernels(L + 1, K, C, L)
     print("groups and single series", B, C, L, K, groups, flush=True)
+    assert _width(h, B, C, L, 5, True) == groups[0] and _width(h, 1, C, L, 5, True) == 1
     ws = torch.full((rocket.rocket_workspace_bytes(h, B, 5, True),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing writes
     whole = rocket.rocket_soft_ppv_backward(h, x, 5, gout, 10.0, -3.0, True, workspace=ws)
     parts = [rocket.rocket_soft_ppv_backward(h, x[b:b + 1].contiguous(), 5, gout[b:b + 1].contiguous(), 10.0, -3.0, True) for b in range(B)]
@@ -103,6 +124,7 @@ def test_exact_ties_in_groups(B, L):
     g = np.zeros((B, 2 * K), np.float32)
     g[:, :K] = rng.integers(1, 4, size=(B, K)).astype(np.float32)
     print("ties in groups", B, L, flush=True)
+    assert _width(h, B, C, L, 5, True) > 1
     gw, gb = rocket.rocket_soft_ppv_backward(h, _gpu(x), 5, _gpu(g), 10.0, -3.0, True)
     torch.cuda.synchronize()
     gw_ref, gb_ref = oracle.backward(x, kr, g[:, K:].astype(np.float64), g[:, :K].astype(np.float64), lam=10.0, shift=-3.0)
@@ -112,7 +134,7 @@ def test_exact_ties_in_groups(B, L):
 
 # (width, series of the first group) of a transform without softPPV; one series alone is never a group
 AHEAD = [(28, 15, 134, 2351, (8, 4)), (149, 3, 166, 3236, (32, 21)), (3, 2, 200, 9000, (4, 3)), (20, 18, 1263, 4822, (4, 4)), (9, 4, 600, 6000, (4, 1)),
-         (130, 2, 60, 4000, (64, 2)), (100, 4, 600, 200, (2, 2))]
+         (130, 2, 60, 4000, (64, 2)), (100, 4, 600, 200, (2, 2)), (149, 18, 1263, 600, (4, 1)), (200, 20, 1200, 400, (4, 4))]
 
 
 @pytest.mark.parametrize("B,C,L,K,groups", AHEAD)
@@ -129,6 +151,8 @@ def test_features_of_groups(B, C, L, K, groups, u8):
         entry, xd = rocket.rocket_transform, _gpu(x)
     h = rocket.rocket_make_kernels(L, K, C, L)
     print("features of groups", B, C, L, K, groups, "u8" if u8 else "f32", flush=True)
+    assert all(_width(h, B, C, L, mask, False) == groups[0] for mask in (1, 2, 3)) and (B - 1) % groups[0] + 1 == groups[1]
+    assert _width(h, 1, C, L, 3, False) == 1 and _width(h, B, C, L, 7, False) == 1
     alone = torch.cat([entry(h, xd[b:b + 1].contiguous(), 3) for b in range(B)])
     ws = torch.full((rocket.rocket_workspace_bytes(h, B, 3, False),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing writes
     both = entry(h, xd, 3, workspace=ws)
@@ -144,9 +168,9 @@ def test_features_of_groups(B, C, L, K, groups, u8):
         assert rc == rocket.ROCKET_OK and torch.equal(out, both)
 
 
-@pytest.mark.parametrize("C,L,K,B", [(14, 2857, 1724, 24), (2, 3000, 2000, 9), (5, 8192, 700, 40), (1, 1500, 300, 120), (3, 1030, 1100, 3)])
+@pytest.mark.parametrize("C,L,K,B", [(14, 2857, 1724, 24), (2, 3000, 2000, 9), (5, 8192, 700, 40), (1, 1500, 300, 120), (3, 1030, 1100, 40)])
 def test_four_wavefronts_give_the_same_bits(C, L, K, B):
-    """one series alone takes four wavefronts to a kernel (tests/sanitize/groups_driver.cpp), a batch one or groups: all their features"""
+    """one series alone takes four wavefronts to a kernel, a batch one or groups (tests/sanitize/groups_driver.cpp has the routes): all their features"""
     import torch
     x = np.random.default_rng(K).standard_normal((B, C, L)).astype(np.float32)
     h = rocket.rocket_make_kernels(K, K, C, L)
@@ -171,6 +195,7 @@ def test_groups_keep_their_series_apart():
     x[12, 0] = 3e38
     h = rocket.rocket_make_kernels(6, K, C, L)
     print("groups keep their series apart", flush=True)
+    assert _width(h, B, C, L, 3, False) > 1
     both = rocket.rocket_transform(h, x, 3)
     alone = torch.cat([rocket.rocket_transform(h, x[b:b + 1].contiguous(), 3) for b in range(B)])
     assert torch.equal(torch.nan_to_num(both, nan=-7.0), torch.nan_to_num(alone, nan=-7.0))
@@ -195,6 +220,7 @@ def test_groups_in_a_graph():
         rocket.rocket_soft_ppv_backward(h, x, 5, gout, 10.0, -3.0, True, grad_w=gw, grad_b=gb, workspace=ws)
 
     print("groups in a graph", flush=True)
+    assert _width(h, B, C, L, 3, False) > 1 and _width(h, B, C, L, 5, True) > 1
     step()
     torch.cuda.synchronize()
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
