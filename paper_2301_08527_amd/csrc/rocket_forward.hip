@@ -60,9 +60,7 @@ int rk_launch_forward(const rocket_kernels *h, const float *xpad, int32_t B, uin
 {
     const int spread = rk_spread(h, B);
     if (mask & ROCKET_F_SOFTPPV) return rk_launch_forward_soft(h, xpad, B, mask, nl, ns, partials, spread, stream);
-    if (mask == ROCKET_F_MAX) return rk_forward_launch<kThreads, ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
-    if (mask == ROCKET_F_PPV) return rk_forward_launch<kThreads, ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
-    return rk_forward_launch<kThreads, ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
+    return rk_forward_launch_mask<kThreads, 0>(h, xpad, B, mask, nl, ns, partials, spread, stream);
 }
 
 // One thread per (series, kernel): combines the kernel's job partials in job order and

@@ -212,8 +212,8 @@ __device__ __forceinline__ void rk_forward_body(const KernelCtx &k, int nout, co
         const int nrows = left + (own_tail > 0 ? 1 : 0);
         if (nrows == 0) return;
         if (nrows <= 8) { rk_few_rows<LEN, 8, NT>(k, row0, left, own_tail, st); return; }
-        if (nrows <= 16) { rk_few_rows<LEN, 16, NT>(k, row0, left, own_tail, st); return; }
-        rk_few_rows<LEN, few, NT>(k, row0, left, own_tail, st);
+        if (few == 16 || nrows <= 16) { rk_few_rows<LEN, 16, NT>(k, row0, left, own_tail, st); return; }
+        if constexpr (few > 16) rk_few_rows<LEN, few, NT>(k, row0, left, own_tail, st);
         return;
     }
     // smaller dilations: bands of 16, 8, 4, 2 rows, tallest first; rows that are left go to the next
@@ -297,6 +297,20 @@ inline int rk_forward_launch(const rocket_kernels *h, const float *xpad, int32_t
                        static_cast<hipStream_t>(stream), xpad, static_cast<int>(h->row_len), h->lead, h->L, h->C, J, h->d_rec, h->d_jobs,
                        h->d_channels, h->d_weights, nl, ns, partials, B, spread);
     return hipGetLastError() == hipSuccess ? ROCKET_OK : ROCKET_EHIP;
+}
+
+// The kernel of a mask with softPPV (SOFT = ROCKET_F_SOFTPPV) or without (0).
+template <int NT, uint32_t SOFT>
+inline int rk_forward_launch_mask(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns, float *partials, int spread,
+                                  void *stream)
+{
+    const uint32_t hard = mask & (ROCKET_F_MAX | ROCKET_F_PPV);
+    if (hard == ROCKET_F_MAX) return rk_forward_launch<NT, SOFT | ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
+    if (hard == ROCKET_F_PPV) return rk_forward_launch<NT, SOFT | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
+    if constexpr (SOFT != 0) {
+        if (hard == 0) return rk_forward_launch<NT, SOFT>(h, xpad, B, nl, ns, partials, spread, stream);
+    }
+    return rk_forward_launch<NT, SOFT | ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
 }
 
 // The kernels of the masks with softPPV are translation units of their own (rocket_forward_soft.hip, rocket_forward_short_soft.hip).

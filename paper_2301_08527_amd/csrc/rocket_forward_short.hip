@@ -9,7 +9,5 @@ int rk_launch_forward_short(const rocket_kernels *h, const float *xpad, int32_t 
 {
     const int spread = 0;   // measured: the per-XCD series mapping makes the short-series launch 2 % slower
     if (mask & ROCKET_F_SOFTPPV) return rk_launch_forward_short_soft(h, xpad, B, mask, nl, ns, partials, spread, stream);
-    if (mask == ROCKET_F_MAX) return rk_forward_launch<64, ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
-    if (mask == ROCKET_F_PPV) return rk_forward_launch<64, ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
-    return rk_forward_launch<64, ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
+    return rk_forward_launch_mask<64, 0>(h, xpad, B, mask, nl, ns, partials, spread, stream);
 }

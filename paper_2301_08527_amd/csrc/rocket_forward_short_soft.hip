@@ -4,11 +4,5 @@
 int rk_launch_forward_short_soft(const rocket_kernels *h, const float *xpad, int32_t B, uint32_t mask, float nl, float ns, float *partials, int spread,
                                  void *stream)
 {
-    constexpr uint32_t soft = ROCKET_F_SOFTPPV;
-    switch (mask) {
-    case soft: return rk_forward_launch<64, soft>(h, xpad, B, nl, ns, partials, spread, stream);
-    case soft | ROCKET_F_MAX: return rk_forward_launch<64, soft | ROCKET_F_MAX>(h, xpad, B, nl, ns, partials, spread, stream);
-    case soft | ROCKET_F_PPV: return rk_forward_launch<64, soft | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
-    default: return rk_forward_launch<64, soft | ROCKET_F_MAX | ROCKET_F_PPV>(h, xpad, B, nl, ns, partials, spread, stream);
-    }
+    return rk_forward_launch_mask<64, ROCKET_F_SOFTPPV>(h, xpad, B, mask, nl, ns, partials, spread, stream);
 }
