@@ -128,20 +128,21 @@ def _fp64_error_bounds(X, y, alpha, w, a):
     return dw, db
 
 
-@pytest.mark.parametrize("n,p", [(5, 40), (16, 70), (33, 300), (64, 500), (137, 1000)])
-def test_well_conditioned_systems_keep_fp64_accuracy(n, p):
-    """against 80-bit sums, within what fp64 arithmetic explains (1e-13 to 6e-11 of the coefficients): a step of the
-    factorisation that loses a few digits would stay below the 1e-8 of the other tests.  The centred rows add up to zero, so
-    alpha is the smallest eigenvalue of the system; with alpha = p its condition is a small number."""
-    alpha = float(p)
-    print("ridge accuracy", n, p, flush=True)
+@pytest.mark.parametrize("n,p,share", [(5, 40, 1.0), (16, 70, 1.0), (33, 300, 1.0), (64, 500, 1.0), (137, 1000, 1.0), (260, 1300, 1.0), (520, 900, 1.0),
+                                       (137, 1000, 0.01), (300, 1100, 0.01)])
+def test_well_conditioned_systems_keep_fp64_accuracy(n, p, share):
+    """against 80-bit sums, within what fp64 arithmetic explains (1e-13 to 6e-10 of the coefficients, a hundred times as much with a
+    hundredth of alpha): a step of the factorisation that loses a few digits would stay below the 1e-8 of the other tests.  The centred
+    rows add up to zero, so alpha is the smallest eigenvalue of the system; with alpha = p its condition is a small number.  One to seventeen panels."""
+    alpha = float(p) * share
+    print("ridge accuracy", n, p, alpha, flush=True)
     rng = np.random.default_rng(n + p)
     X = (rng.standard_normal((n, p)) + rng.uniform(-1, 1, p)).astype(np.float32)
     y = (X[:, :4].sum(axis=1) * 0.25 + 1.0 + 0.05 * rng.standard_normal(n)).astype(np.float32)
     w_ref, b_ref, a_ref = _fit_in_80_bits(X, y, alpha)
     dw, db = _fp64_error_bounds(X, y, alpha, w_ref, a_ref)
     norm = float(np.sqrt((w_ref ** 2).sum()))
-    assert dw < 1e-10 * norm                 # the bound says something
+    assert dw < 1e-9 / share * norm          # the bound says something
     w, b, _ = _fit(X, y, alpha)
     err = float(np.sqrt(((w - w_ref) ** 2).sum()))
     print("error", err / norm, "bound", dw / norm, flush=True)
