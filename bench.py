@@ -32,14 +32,14 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3   # MI355X datasheet, packed FP32 on the vector 
 # side of that interface and is not told apart from HBM by any counter of the compute dies.
 # (workload, batch, feature mask) -> figures; other shapes report null.
 MEASURED_TRAFFIC = {
-    # 9,547,000 KiB x 1.968 fetched + 56,700 KiB written; 1.527e8 read requests x 128 B + 1.05e6 write requests x 64 B
+    # 9,898,000 KiB x 1.968 fetched + 60,210 KiB written; 1.584e8 read requests x 128 B + 1.125e6 write requests x 64 B
     ("multivariate-20x50k", 64, 3): {
-        "l2_fill_bytes": 19298000000, "dram_bytes": 19613000000,
-        "source": "profiles/rk_forward_multivariate-20x50k.md", "commit": "e304e0a"},
-    # 16,320,000 KiB x 1.968 fetched + 153,600 KiB written; 2.61e8 read requests x 128 B + 2.94e6 write requests x 64 B
+        "l2_fill_bytes": 20008000000, "dram_bytes": 20347000000,
+        "source": "profiles/rk_forward_multivariate-20x50k.md", "commit": "248fbe1"},
+    # 17,380,000 KiB x 1.968 fetched + 159,400 KiB written; 2.788e8 read requests x 128 B + 2.745e6 write requests x 64 B
     ("multivariate-20x50k-grad", 60, 5): {
-        "l2_fill_bytes": 33046000000, "dram_bytes": 33596000000,
-        "source": "profiles/rk_backward_multivariate-20x50k-grad.md", "commit": "e304e0a"},
+        "l2_fill_bytes": 35188000000, "dram_bytes": 35862000000,
+        "source": "profiles/rk_backward_multivariate-20x50k-grad.md", "commit": "248fbe1"},
 }
 
 WORKLOADS = {

@@ -113,11 +113,13 @@ int32_t rocket_num_features(uint32_t feature_mask);
  * Bytes of device workspace that rocket_transform (backward = 0) or
  * rocket_soft_ppv_backward (backward = 1) needs for a batch of B series.
  * Returns 0 on invalid arguments.  The workspace holds a zero-padded copy of
- * the batch (so that dilated reads never leave a row) and partial results: for
- * the transform the pooled values of every (series, time tile of a kernel), for
- * the backward pass the partial gradients of every (series, time tile of a
- * kernel); and 16 bytes per (series, channel) row for the statistics of the
- * 8-bit entry points.  Its contents are scratch.
+ * the batch (so that dilated reads never leave a row; where short series are
+ * worked on in groups, the series of a group lie interleaved in it) and partial
+ * results: for the transform the pooled values of every (series, time tile of a
+ * kernel), none in groups; for the backward pass the partial gradients of every
+ * (series, time tile of a kernel), or of every (group, kernel); and 16 bytes per
+ * (series, channel) row for the statistics of the 8-bit entry points.  The size
+ * is the same either way.  Its contents are scratch.
  */
 size_t rocket_workspace_bytes(const rocket_kernels *kernels, int32_t B, uint32_t feature_mask, int backward);
 
@@ -205,7 +207,8 @@ int rocket_soft_ppv_backward_u8(rocket_kernels *kernels, const uint8_t *x_u8_dev
 /*
  * The work decomposition, for inspection and tests.  The outputs of kernel k are viewed as
  * rows of d consecutive positions (position t = row*d + column); its n / d full rows are cut
- * into jobs (time tiles), one workgroup per (series, job) in both passes.  Job j covers rows
+ * into jobs (time tiles), one workgroup per (series, job) in both passes, or, for short series whose
+ * kernels are one job each, per (group of series, kernel).  Job j covers rows
  * [row0[j], row1[j]) of kernel kernel[j]; bit 0 of flags[j] says that it also owns the partial
  * last row (the n mod d positions after the full rows), bit 1 that it is the only job of its
  * kernel.  Jobs are listed in launch order.  The pointers are borrowed from the handle

@@ -753,8 +753,8 @@ static int transform_impl(const char *fn, rocket_kernels *h, const void *x_dev, 
     float *xpad = static_cast<float *>(ws);
     const float nl = -lambda * kLog2e, ns = -shift * kLog2e;
     // Short univariate series: sets of kernels of one dilation, straight from the samples (raw bytes are normalised into
-    // the padded copy); the sets' edges rest on lambda > 0.  Which path a call takes follows from the handle and from lambda, never
-    // from the batch.
+    // the padded copy); the sets' edges rest on lambda > 0.  Whether a call goes over sets follows from the handle and from lambda, never from the
+    // batch, and so does the path of a mask with softPPV; max and PPV alone go the way that is fastest for the batch, with the same bits.
     const bool series = !h->sets.empty() && (!(mask & ROCKET_F_SOFTPPV) || -nl > 1e-30f);
     const ForwardWay way = series ? ForwardWay{rk_groups(B, 1, 1), false} : forward_way(h, B, mask);
     const RkGroups &groups = way.groups;

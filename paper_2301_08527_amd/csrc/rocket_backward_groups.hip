@@ -11,8 +11,9 @@
 // instead of one for each series.  The largest output stays a matter of each series: its position is found over the
 // lanes of equal tid % width, and the max plane's sub-gradient is added here, since a job is a whole kernel.
 // Bound: vector-instruction issue; few rows to a strip (L / d) and bands that do not fill the lanes are what is left.  Which
-// width: the rule at backward_groups in rocket_api.hip.  64 x 1 x 1,000 samples, 1,000 kernels: 184 -> 92 us with the padded copy and
-// the sums; 28 x 18 x 158, 15,408 kernels 1,820 -> 307 us; 167 x 9 x 1,205, 1,737 kernels 1,870 -> 1,057 us.
+// width: the rule at backward_groups in rocket_api.hip.  Whole calls, one series at a time and in groups, the padded copy and the sums
+// included: 64 x 1 x 1,000 samples, 1,000 kernels 170 -> 89 us (the kernel alone 80); 28 x 18 x 158, 15,408 kernels 1,695 -> 302 us; 167 x 9 x 1,205,
+// 1,737 kernels 1,782 -> 912 us.
 #include "rocket_backward_impl.hpp"
 
 namespace {

@@ -50,7 +50,7 @@ __device__ __forceinline__ void rk_track_max(float z, int t, BwdState &st)
 
 // The same for the outputs t0, t0 + d, ... of a strip: their maximum first, half an instruction an output, and its first position only if
 // some lane of the wavefront needs it, two.  (Output by output the rule takes five and two scalar ones:
-// 15 x 20 x 50,000, 10,000 kernels 16.85 -> 16.40 ms, 64 x 1 x 1,000, 1,000 kernels 95 -> 88 us, 30 x 1 x 20,000, 2,000 kernels 1,230 -> 1,104.
+// whole calls: 15 x 20 x 50,000, 10,000 kernels 16.85 -> 16.40 ms, 64 x 1 x 1,000, 1,000 kernels 95 -> 88 us, 30 x 1 x 20,000, 2,000 kernels 1,230 -> 1,104.
 // The few-rows strips, whose last row only some lanes have, keep it: there this form cost a wavefront per SIMD.)
 template <int R>
 __device__ __forceinline__ void rk_track_strip(const float (&z)[R], int t0, int d, BwdState &st)

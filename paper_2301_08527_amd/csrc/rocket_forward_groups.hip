@@ -6,8 +6,8 @@
 // its reductions over the lanes of a series and writes the features: no partial results.  A largest output and a count of
 // positive ones are the same numbers in whatever order positions come, so features depend on neither the width nor the batch;
 // a sum of sigmoids would, which is why masks with softPPV go one series at a time.
-// Bound: vector-instruction issue; what a pass costs whose strips do not fill the lanes.  Which width: the rule at forward_groups in
-// rocket_api.hip.  Max and PPV, one series at a time and in groups: 28 x 15 x 134 samples, 2,351 kernels 94 -> 37 us; 149 x 3 x 166, 3,236
+// Bound: vector-instruction issue; what a pass costs whose strips do not fill the lanes.  Which width: the rules at best_groups and
+// forward_way in rocket_api.hip.  Max and PPV, one series at a time and in groups: 28 x 15 x 134 samples, 2,351 kernels 94 -> 37 us; 149 x 3 x 166, 3,236
 // kernels 402 -> 88 us; 149 x 18 x 1,263, 4,822 kernels 1,640 -> 1,076 us.
 #include "rocket_forward_impl.hpp"
 

@@ -27,8 +27,9 @@
 // The samples come straight from the batch with bounds checks, so no padded copy is made.  Counts are
 // integers and added with atomics: the result does not depend on the order.  Where every group is one tile (short
 // series) the workgroup writes the features itself.
-// Bound by vector-instruction issue (a matrix instruction takes about ten of a SIMD's clocks from the others, 84 v_alignbit per
-// 64 positions and lane group, the staging).  Measured at 64 x 20 x 50,000 with 119 groups: 2.57 ms for the call with additions
+// Bound by vector-instruction issue: a matrix instruction keeps its unit busy for 16 of a SIMD's clocks and takes some nine of them from
+// the others (four wavefronts, 0, 2, 4, 8 and 12 independent multiply-adds to each: 18.5, 19.5, 26.6, 44.0 and 60.5 clk, the multiply-adds
+// alone 18.4 for 4, 34.8 for 8, 50.8 for 12), and there are six to seven others to each (84 v_alignbit per 64 positions and lane group, the staging).  Measured at 64 x 20 x 50,000 with 119 groups: 2.57 ms for the call with additions
 // and comparisons, 1.97 with the matrix cores, 1.99 with the limits of the split looked after; at 256 x 1 x 1,000
 // (rk_mr_forward_series) 258, 175 and 176 us.
 // The split carries sums and biases that are zero or in [2^-96, 2^60] in magnitude.  Staging notes others, and such a group of a

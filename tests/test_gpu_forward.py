@@ -98,7 +98,7 @@ def test_small_and_ragged_shapes(B, C, L, K):
     """shortest legal series, lengths that are not multiples of any tile, one series;
     lengths on both sides of the switch between the one-wavefront kernel (L <= 8192)
     and the four-wavefront kernel; batches of 8 and more series that are not multiples of
-    the number of XCDs (the per-XCD series mapping leaves workgroups without a series)"""
+    the number of XCDs (the per-XCD series mapping takes the series left over first, each on all XCDs)"""
     rng = np.random.default_rng(L)
     x = rng.standard_normal((B, C, L)).astype(np.float32)
     h = rocket.rocket_make_kernels(7, K, C, L)
