@@ -681,8 +681,10 @@ static RkGroups best_groups(const rocket_kernels *h, int32_t B, double passes, d
 // Four wavefronts need a tenth's lead over one by the estimates, groups a twentieth more (4 x 20 x 1,200 and 10,000 kernels: ahead by 12 %
 // there, 106 us against 99).  Up to 512 samples one wavefront has the strips of a kernel in a pass or two and four only wait for one
 // another (5 x 19 x 417 and 870 kernels 22 us on one and 27 on four, 4 x 19 x 269 and 1,122 22/26, 5 x 11 x 375 and 775 22/25; 13 x 19 x 1,018 and 170
-// 36/21, 8 x 13 x 533 and 387 22/19).  Max and PPV, in us.  Groups, of 21 shapes measured at every width the fastest or one
-// within 8 % of it, against one wavefront: 28 x 15 x 134 samples and 2,351 kernels 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236
+// 36/21, 8 x 13 x 533 and 387 22/19).  Over 840 shapes drawn at
+// random (2 to 256 series of 2 to 20 channels and 60 to 8,192 samples, 100 to 20,000 kernels) and timed every way the choice takes 3.6 % longer
+// than the fastest on average; for 24 it is more than 2 % slower than one wavefront, at most 12 % (14 x 2 x 1,858 and 305 18/20).  Max and PPV, in
+// us.  Groups against one wavefront: 28 x 15 x 134 samples and 2,351 kernels 37/94 (8 series; 4: 40, 16: 46), 149 x 3 x 166 and 3,236
 // 88/402 (32 series; 16: 91, 64: 103), 4 x 5 x 300 and 10,000 33/49 (4), 149 x 18 x 1,263 and 4,822 1,076/1,640 (8; 2: 1,315, 32: 1,415),
 // 227 x 16 x 930 and 5,723 1,386/2,210 (16; 4: 1,575).  Series of thousands of samples gain little or nothing (23 x 6 x 4,099 and 1,537
 // 185/181, 16 x 3 x 2,000 and 300 30/24).  Four wavefronts against one: 1 x 14 x 2,857 and 1,724 26/54, 1 x 20 x 8,000 and 1,000
