@@ -43,7 +43,7 @@ def too_early(asm):
         operands = [o.strip() for o in rest.split(",")]
         writes = set()
         if name.startswith("v_"):
-            carries = "_co_" in name or name.startswith("v_div_scale")
+            carries = "_co_" in name or name.startswith(("v_div_scale", "v_mad_u64", "v_mad_i64"))     # the second operand is written
             reads = set().union(*[scalars(o) for o in operands[2 if carries else 1:]]) if len(operands) > 1 else set()
             bad += [line for r in reads if age.get(r, NEEDED) < NEEDED]
             if carries:
@@ -60,6 +60,7 @@ def test_scanner():
     assert too_early("v_cmp_lt_f32 vcc, s4, v1\nv_addc_co_u32 v0, vcc, 0, v0, vcc")
     assert too_early("v_cmp_lt_f32 vcc, s4, v1\ns_nop 0\nv_addc_co_u32 v0, vcc, 0, v0, vcc")
     assert too_early("v_cmp_lt_f32 s[6:7], s4, v1\nv_mov_b32 v2, v3\nv_cndmask_b32 v0, 0, v1, s[6:7]")
+    assert not too_early("v_mad_u64_u32 v[0:1], s[6:7], v2, s4, 0\nv_mad_u64_u32 v[0:1], s[6:7], v3, s4, 0")
     assert not too_early("v_cmp_lt_f32 vcc, s4, v1\ns_nop 1\nv_addc_co_u32 v0, vcc, 0, v0, vcc\nv_addc_co_u32 v5, vcc, v1, v2, s[6:7]")
 
 
